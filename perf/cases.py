@@ -34,7 +34,7 @@ def _conv(name, model, batch, image, op="train", reach=1.0, pick=1.0):
 def listed():
     """`reach`: the part of the tensor chain, counted from the output, that the mask reaches into; `pick`: the share of
     the tensors in that part that it selects.  Selecting for half of the full step's time leaves masks of the kind
-    (0.38, 0.4) on a transformer and somewhat deeper ones on the convolutional models; 1, 1 is full training."""
+    (0.38, 0.4) on a transformer and somewhat deeper ones on the ResNet; 1, 1 is full training."""
     return [
         # The smallest model, float32, batch 32, full training: a step of a dozen tiny launches, all latency.
         dict(name="mlp_b32_full", model="mlp", op="train", batch=32, d_in=256, hidden=256, layers=4, classes=10, reach=1.0, pick=1.0),
@@ -57,8 +57,8 @@ def listed():
         _conv("resnet50_b32_half", "resnet50", 32, 224, reach=0.6, pick=0.4),
         # ResNet-50 on few images of another size, full training: odd feature maps (50, 25, 13, 7) and ragged row counts.
         _conv("resnet50_b6_i200_full", "resnet50", 6, 200),
-        # VGG16, batch 32, half of the time.
-        _conv("vgg16_b32_half", "vgg16", 32, 224, reach=0.6, pick=0.4),
+        # VGG16, batch 32, fine-tuning its last stage and its linear layers (123 of 135 million weights).
+        _conv("vgg16_b32_top", "vgg16", 32, 224, reach=0.37, pick=0.6),
         # MobileNetV2, batch 32, full training: some five hundred short launches.
         _conv("mobilenetv2_b32_full", "mobilenetv2", 32, 224),
     ]
@@ -84,8 +84,9 @@ def draw(rng):
         elif u < 0.64:
             case = _conv("", "resnet50", _log_int(rng, 1, 40), rng.choice((224, rng.randint(96, 256))), op=op, **mask)
         elif u < 0.76:
-            # the input side of this plain stack is reached by short masks only (see tolerance)
-            case = _conv("", "vgg16", _log_int(rng, 1, 36), 32 * rng.randint(3, 8), reach=rng.uniform(0.1, 0.6), pick=rng.uniform(0.1, 0.9))
+            # masks that end in the last stage: in front of its pooling, near-ties in bf16 let two correct evaluations pick other
+            # taps, and their gradients are 5 per cent apart
+            case = _conv("", "vgg16", _log_int(rng, 1, 36), 32 * rng.randint(3, 8), reach=rng.uniform(0.1, 0.37), pick=rng.uniform(0.1, 0.9))
         elif u < 0.88:
             case = _conv("", "mobilenetv2", _log_int(rng, 1, 48), rng.choice((224, rng.randint(96, 256))), op=op, **mask)
         else:
@@ -138,8 +139,9 @@ def _chain(case):
     if case["model"] == "vgg16":
         cin = 3
         for s, (w, n) in enumerate(zip(VGG16["widths"], VGG16["convs"])):
-            for _ in range(n):
-                out += [("s%d.W" % s if cin != 3 else "first.W", (w, 3, 3, cin), "matrix", B * side * side), ("s%d.b" % s, (w,), "vector", 0)]
+            for k in range(n):
+                name = "first" if cin == 3 else "pool%d" % s if k + 1 == n else "s%d" % s   # pool: the one in front of the stage's pooling
+                out += [(name + ".W", (w, 3, 3, cin), "matrix", B * side * side), (name + ".b", (w,), "vector", 0)]
                 cin = w
             side //= 2
         fin = side * side * cin
@@ -201,7 +203,9 @@ def _initial(case, role, shape, gen):
     In the convolutional models three channels of four are mostly on and every fourth is mostly off: shifts of about three standard
     deviations, weights that cancel the mean of their inputs.  Channels balanced on the edge of their ReLU, which is what zero
     shifts give, make two correct bf16 evaluations of a deep stack disagree by several per cent in the gradients (each
-    stored value rounds differently, and a fraction of the masks follows), so that no results could be compared."""
+    stored value rounds differently, and a fraction of the masks follows), so that no results could be compared.
+    In front of a max pooling, where only the largest of four values passes a gradient, the shift is smaller: the finer bf16 grid
+    leaves fewer near-ties for the choice."""
     leaf = role.split(".")[-1]
     normal = lambda std: torch.randn(shape, generator=gen, device="cuda") * std  # noqa: E731
     if case["model"] == "vit":
@@ -216,7 +220,7 @@ def _initial(case, role, shape, gen):
         return {"c3.g": 0.25, "join.g": 0.25, "stem.g": 0.7}.get(role, 1.0) * (1.0 + normal(0.02))
     if leaf == "b":
         mean_on, mean_off = {"c3.b": (0.0, -1.0), "join.b": (0.0, 0.0), "proj.b": (0.0, 0.0), "head.b": (0.0, 0.0), "fc%d.b" % len(VGG16["fc"]): (0.0, 0.0)}.get(
-            role, (3.0, -3.0))
+            role, (0.7, -3.0) if role.startswith("pool") else (2.2, -2.2) if case["model"] == "vgg16" and not role.startswith("fc") else (3.0, -3.0))
         return torch.where(on(shape[0]), mean_on, mean_off) + normal(0.02)
     if role == "dw.W":
         w = normal(0.2)
@@ -266,7 +270,8 @@ class _Model:
         self.y = torch.randint(0, case.get("classes", CLASSES), (B,), generator=gen, device="cuda", dtype=torch.int32)
         self.opt = et.et_opt()
         self.opt.kind = et.ET_ADAM if case["model"] == "vit" else et.ET_SGDW
-        self.opt.lr, self.opt.beta1, self.opt.beta2, self.opt.eps = 1e-4, 0.9, 0.999, 1e-8
+        # fine-tuning rates between 1e-5 and 1e-4 (a plain stack of convolutions oscillates from step to step at 1e-4)
+        self.opt.lr, self.opt.beta1, self.opt.beta2, self.opt.eps = 1e-4 if case["model"] == "vit" else 1e-5, 0.9, 0.999, 1e-8
         self.opt.momentum, self.opt.wd, self.opt.step = 0.9, 5e-4, 0
         if case["op"] == "importance":
             self.snapshot = (self.w.float() + 1e-3 * torch.randn(total, generator=gen, device="cuda")).to(self.dtype)
@@ -276,7 +281,7 @@ class _Model:
         return {role: arena[part] for role, part in self.roles.items()}
 
     def __del__(self):
-        if self.ctx is not None:
+        if self.ctx is not None and torch is not None:
             torch.cuda.synchronize()
             et.et_destroy(self.ctx)
 
@@ -329,7 +334,7 @@ def tolerance(case):
     """Measured by evaluating every listed case and some drawn ones twice, the second time with the features of the first product in
     another order (the inputs of a perceptron or a transformer, the image channels, the stem's output channels), results put back
     in place: float32 sums 7e-7 at most (largest single difference 1e-5 of the root mean square); bf16 gradients and moments
-    0.005 to 0.013 on the transformers (0.6 at most for a single value), 0.008 to 0.012 on ResNet-50, 0.004 to 0.017 on VGG16,
+    0.005 to 0.013 on the transformers (0.6 at most for a single value), 0.008 to 0.012 on ResNet-50, 0.003 to 0.019 on VGG16 (the latter over six steps),
     0.01 on MobileNetV2; importances 0.01."""
     if case["model"] == "mlp":
         return {"rel": 3e-6, "max": 1e-4}
