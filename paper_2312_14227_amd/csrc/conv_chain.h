@@ -70,8 +70,8 @@ inline bool needs_cols(const ConvUnit& u) { return u.k > 1 || u.stride > 1; }
 inline bool gathered_kind(const ConvUnit& u) { return (u.k == 3 && (u.stride == 1 || u.stride == 2)) || (u.k == 1 && u.stride == 2); }
 inline bool implicit_fwd(const ConvUnit& u) { return gathered_kind(u) && (u.Cin % 64) == 0; }
 inline bool implicit_dy(const ConvUnit& u) { return u.k == 3 && u.stride == 1 && (u.Cout % 64) == 0 && (u.Cin % 8) == 0; }
-inline bool implicit_dw(const et_ctx* c, const ConvUnit& u) {
-  return gathered_kind(u) && (u.Cin % 8) == 0 && ((size_t)c->desc.batch * u.Ho * u.Wo) % 64 == 0 && u.H < 4096 && u.W < 4096;
+inline bool implicit_dw(const et_ctx*, const ConvUnit& u) {
+  return gathered_kind(u) && (u.Cin % 8) == 0 && u.H < 4096 && u.W < 4096;
 }
 // tile and split of a unit's implicit forward (or, with the channel roles exchanged, gradient-passing) product
 inline void plan_implicit(et_ctx* c, et::GemmDesc& g) {
@@ -140,12 +140,6 @@ inline int conv_dw(et_ctx* c, const ConvUnit& u, const bf16* in, const bf16* d, 
     g.partials = c->gemm_partials;
     if (et::gemm_bf16_partial_elems(g.M, g.N, g.split_k) > c->gemm_partial_elems) g.split_k = 1;
     ET_G(g);
-    return ET_OK;
-  }
-  if (implicit_fwd(u)) {     // the im2col matrix exists only here, in the shared column buffer
-    ET_KB(1, 2.0 * ((double)c->desc.batch * u.H * u.W * u.Cin + (double)rows_of(c, u) * u.Kc),
-          et::im2col(in, c->rdcols, geom(c, u), c->stream));
-    ET_G(linear_dw(c, d, u.Cout, c->rdcols, u.Kc, dW, (int)rows_of(c, u), u.Cout, u.Kc));
     return ET_OK;
   }
   const bf16* A = needs_cols(u) ? u.cols : in;

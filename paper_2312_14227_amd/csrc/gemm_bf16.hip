@@ -2,6 +2,7 @@
 #include <algorithm>
 
 #include "gemm_bf16_kernels.h"
+#include "gemm_bf16_ring.h"
 
 namespace et {
 namespace {
@@ -94,7 +95,7 @@ __global__ __launch_bounds__(256) void splitk_reduce_epilogue_kernel(ReduceEpi e
 }
 
 enum TileId : int { T_AUTO = 0, T_128x128 = 1, T_128x64 = 3, T_DMA_256x256 = 5, T_DMA_256x128 = 7, T_PP_256x256 = 11, T_PP_256x192 = 13,
-              T_PP_256x128 = 15, T_PP_512x64 = 17, T_PP_128x256 = 19, T_PP_64x512 = 21 };
+              T_PP_256x128 = 15, T_PP_512x64 = 17, T_PP_128x256 = 19, T_PP_64x512 = 21, T_RING_64x64 = 23 };
 
 // number of compute units of the current device (256 on an MI355X), looked up once per device; a multiple of 8
 // (one share per XCD) as the resident kernels' unit order assumes whenever a workgroup takes a second unit
@@ -157,10 +158,57 @@ Plan plan_conv_dw(int M, int N, int K) {
 // CU sustains on the VGG16 layer shapes (the shifted rows of the nine taps hit in the L2, so the wide tiles
 // run faster here than on a stored matrix)
 int choose_conv_tile(const GemmDesc& d) {
-  if (d.tile == T_PP_256x256 || d.tile == T_PP_256x192 || d.tile == T_PP_256x128 || d.tile == T_PP_512x64) return d.tile;
+  if (d.tile == T_PP_256x256 || d.tile == T_PP_256x192 || d.tile == T_PP_256x128 || d.tile == T_PP_512x64 || d.tile == T_RING_64x64) return d.tile;
   static const TileRate cand[4] = {{T_PP_256x256, 256, 256, 4.5e12}, {T_PP_256x192, 256, 192, 4.0e12},
                                    {T_PP_256x128, 256, 128, 3.3e12}, {T_PP_512x64, 512, 64, 2.6e12}};
   return plan_tiles(d.M, d.N, d.K, false, cand, 4).tile;
+}
+
+// Small and medium products: the tile with the least estimated time (seconds) for `count` batch entries or chunks.  Fixed
+// cost apart, a CU works through its share of the tiles one slice after the other, whether one or three workgroups
+// share it (us per slice of 64 and per tile, measured on [788 .. 6304 rows] x [64 .. 4096] x [16 .. 4096]):
+//   ring 64x64     0.175 (0.205 with one tile per CU) + 0.5: any K; 1.6 - 3.6 x faster than the register-staged tiles on
+//                  long K ([788 x 768 x 3072] 36.2 -> 13.9 us, [1568 x 512 x 2048] 25.3 -> 10.0, [1024 x 1024] over 6304
+//                  rows 69.8 -> 26.6, all unsplit), equal at 3 - 5 slices;
+//   staged 128x64  0.33 + 0.75, but a memory round trip of 0.75 per slice when a CU has one tile only;
+//   staged 128x128 0.66 + 1.2, the same: ahead where tiles are many and short, by halving or quartering the operand
+//                  re-reads and the per-tile cost ([100352 x 256 x 64] 17.6 us against 23.3, [25088 x 512 x 128] 12.5
+//                  against 15.1).
+Plan plan_small(int M, int N, int K, int count) {
+  struct Cand { int tile, bm, bn; double slice, solo, fixed; };
+  static const Cand cand[3] = {{T_RING_64x64, 64, 64, 0.175e-6, 0.205e-6, 0.5e-6},
+                               {T_128x64, 128, 64, 0.33e-6, 0.75e-6, 0.75e-6},
+                               {T_128x128, 128, 128, 0.66e-6, 0.85e-6, 1.2e-6}};
+  Plan best = {T_128x64, 1, 1e30};
+  const int slices = (K + gemm::SBK - 1) / gemm::SBK;
+  for (const Cand& c : cand) {
+    const long long tiles = (long long)((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn) * count;
+    const long long per_cu = (tiles + 255) / 256;
+    const double t = std::max(per_cu * (slices * c.slice + c.fixed), slices * c.solo + c.fixed);
+    if (t < best.cost) best = {c.tile, 1, t};
+  }
+  return best;
+}
+
+// The ring tile with its reduction split so that the estimated time is least: a CU's share of the units, one after the
+// other (`solo` / `loaded` seconds per slice of 64 with one / several workgroups per CU), at least the time the operands
+// take to stream in with as many CUs as there are units; a split adds the partials' traffic and a second launch (3 us).
+Plan plan_ring(int M, int N, int K, bool may_split, double solo, double loaded) {
+  const int slices = (K + gemm::PBK - 1) / gemm::PBK;
+  const double stream = 2.0 * ((double)M + N) * K / 4e12;
+  const int max_split = may_split && (N & 3) == 0 ? std::max(1, std::min(256, slices / 4)) : 1;
+  Plan best = {T_RING_64x64, 1, 1e30};
+  for (int s = 1; s <= max_split; s++) {
+    const int per = (slices + s - 1) / s;
+    if ((slices + per - 1) / per != s) continue;   // this split leaves empty chunks
+    const long long units = (long long)((M + 63) / 64) * ((N + 63) / 64) * s;
+    const double load = stream * 256.0 / (double)std::min<long long>(units, 256);
+    const double ring = units <= 256 ? per * solo + 0.5e-6 : (double)((units + 255) / 256) * (per * loaded + 0.5e-6);
+    double t = std::max(load, ring);
+    if (s > 1) t += (2.0 * s + 1.0) * M * N * 4.0 / 3.5e12 + 3e-6;
+    if (t < best.cost * 0.999) best = {T_RING_64x64, s, t};
+  }
+  return best;
 }
 
 int choose_tile(const GemmDesc& d, int k_per_block) {
@@ -170,43 +218,44 @@ int choose_tile(const GemmDesc& d, int k_per_block) {
   if (d.tile == T_PP_256x128 || d.tile == T_PP_512x64 || d.tile == T_PP_128x256 || d.tile == T_PP_64x512) return pp_ok ? d.tile : T_128x128;
   if (d.tile == T_DMA_256x256 || d.tile == T_DMA_256x128) return dma_ok ? d.tile : T_128x128;
   if (d.tile != T_AUTO) return d.tile;
-  if (d.N <= 64 || d.K <= 64) return T_128x64;   // one K slice: a stream over the rows, more workgroups in flight win
-  // large problems: a two-group tile where K comes in slices of 64 (4-20 % faster than either
-  // direct-to-LDS tile on every forward, passing and gradient product of the ViT shapes), else
-  // the direct-to-LDS tile with slices of 32
-  // too few 256x256 tiles to fill the 256 CUs: products of more than 8 GFLOP (a ViT-L layer at batch 32) take the
-  // 256x128 two-group tile (13 % faster there than 256x192), smaller ones (late ResNet / MobileNet stages: a few
-  // thousand rows) the register-staged tiles, several workgroups per CU, which are up to twice as fast there
-  const long long big_tiles = (long long)((d.M + 255) / 256) * ((d.N + 255) / 256) * d.z_outer * d.z_inner;
-  if (d.M >= 512 && d.N >= 256 && big_tiles < 128 && d.mode != EPI_GELU_FWD && d.mode != EPI_GELU_BWD && d.mode != EPI_GELU_ONLY) {
-    if (pp_ok && k_per_block >= 4 * gemm::PBK && 2.0 * d.M * d.N * (double)k_per_block >= 8e9 && d.z_outer * d.z_inner == 1)
-      return T_PP_256x128;
-    return (long long)((d.M + 127) / 128) * ((d.N + 127) / 128) >= 256 ? T_128x128 : T_128x64;
+  // large problems (8 GFLOP and more, a ViT-L layer at batch 32 has 13): a two-group tile where K comes in slices of 64
+  // (4-20 % faster than either direct-to-LDS tile on every forward, passing and gradient product of the ViT shapes),
+  // else the direct-to-LDS tile with slices of 32.  Too few 256x256 tiles to fill the 256 CUs: the 256x128 tile
+  // (13 % faster there than 256x192).  The GELU forward epilogues cost a 256x256 tile as much as half its main loop;
+  // two 256x128 direct-to-LDS workgroups per CU that overlap one's epilogue with the other's MFMAs run no faster than
+  // the resident two-group tile (101.7 against 101.3 us for the ViT-B fc1 product).
+  const int batch = d.z_outer * d.z_inner;
+  if (d.M >= 512 && d.N >= 256 && 2.0 * d.M * d.N * (double)k_per_block * batch >= 8e9) {
+    const long long big_tiles = (long long)((d.M + 255) / 256) * ((d.N + 255) / 256) * batch;
+    const bool gelu = d.mode == EPI_GELU_FWD || d.mode == EPI_GELU_BWD || d.mode == EPI_GELU_ONLY;
+    if (pp_ok && k_per_block >= 4 * gemm::PBK)
+      return big_tiles < 128 && !gelu && batch == 1 ? (int)T_PP_256x128 : plan_large(d.M, d.N, k_per_block, false).tile;
+    if (dma_ok && k_per_block >= 4 * gemm::DBK && big_tiles >= 128) return d.N >= 2560 ? T_DMA_256x128 : T_DMA_256x256;
   }
-  if (d.M >= 512 && d.N >= 256) {
-    // (the GELU forward epilogues, 20 instructions per element, cost a 256x256 tile as much as half its main loop;
-    // two 256x128 direct-to-LDS workgroups per CU that overlap one's epilogue with the other's MFMAs run no
-    // faster than the resident two-group tile: 101.7 against 101.3 us for the ViT-B fc1 product)
-    if (pp_ok && k_per_block >= 4 * gemm::PBK) return plan_large(d.M, d.N, k_per_block, false).tile;
-    if (dma_ok && k_per_block >= 4 * gemm::DBK) return d.N >= 2560 ? T_DMA_256x128 : T_DMA_256x256;
-  }
-  return T_128x128;
+  return plan_small(d.M, d.N, k_per_block, batch * std::max(1, d.split_k)).tile;
 }
 
 }  // namespace
 
 size_t gemm_bf16_partial_elems(int M, int N, int split_k) { return split_k > 1 ? (size_t)M * N * split_k : 0; }
 
+// Implicit convolutions: the ring tile up to 14 GFLOP and for at most 64 output channels, the two-group tiles beyond.
+// Measured at batch 32, forward (two-group plan / ring): 7x7x512 27.9 / 22, 14x14x256 27.6 / 17.8, 56x56x64 24.5 / 21.8,
+// 224x224x64 285 / 254 us, but 14x14x512 51 / 59, 112x112x128 176 / 189; weight gradients: 14x14x256 32.0 / 23.7, 56x56x64
+// 43.5 / 24.6, 224x224x64 390 / 240, but 56x56 128 -> 256 81 / 110.
+static bool conv_on_ring(int rows, int channels, int K) { return channels <= 64 || 2.0 * rows * channels * (double)K < 1.4e10; }
+
 void gemm_bf16_plan_conv(int M, int N, int K, int* tile, int* split_k) {
   static const TileRate cand[4] = {{T_PP_256x256, 256, 256, 4.5e12}, {T_PP_256x192, 256, 192, 4.0e12},
                                    {T_PP_256x128, 256, 128, 3.3e12}, {T_PP_512x64, 512, 64, 2.6e12}};
-  const Plan pl = plan_tiles(M, N, K, (N & 3) == 0, cand, 4);
+  const Plan pl = conv_on_ring(M, N, K) ? plan_ring(M, N, K, true, 0.26e-6, 0.19e-6) : plan_tiles(M, N, K, (N & 3) == 0, cand, 4);
   *tile = pl.tile;
   *split_k = pl.split;
 }
 
 void gemm_bf16_plan_conv_dw(int M, int N, int K, int* tile, int* split_k) {
-  const Plan pl = plan_conv_dw(M, N, K);
+  // (a pixel count that is not a multiple of 64 runs on the ring tile whatever its size)
+  const Plan pl = (K % gemm::PBK) || conv_on_ring(K, M, N) ? plan_ring(M, N, K, true, 0.26e-6, 0.19e-6) : plan_conv_dw(M, N, K);
   *tile = pl.tile;
   *split_k = pl.split;
 }
@@ -214,11 +263,15 @@ void gemm_bf16_plan_conv_dw(int M, int N, int K, int* tile, int* split_k) {
 void gemm_bf16_plan_split(int M, int N, int K, int* tile, int* split_k) {
   *tile = T_AUTO;
   *split_k = 1;
-  if (M >= 256 && N >= 256 && (K % gemm::PBK) == 0 && K >= 4 * gemm::PBK) {
+  // up to 16 GFLOP the ring tile wins ([1024 x 256] over 6272 rows 11.9 us against 25.1 for the best two-group plan,
+  // [768 x 768] over 12 608 29.9 / 33.0, [3072 x 768] over 3136 32.7 / 34.5), beyond it the two-group tiles do ([2304 x 768]
+  // over 6272 42.5 / 40.3, [768 x 3072] over 12 608 96 / 72)
+  const bool large = 2.0 * M * N * (double)K >= 1.6e10;
+  if (large && M >= 256 && N >= 256 && (K % gemm::PBK) == 0 && K >= 4 * gemm::PBK) {
     const Plan pl = plan_large(M, N, K, true);
     *tile = pl.tile;
     *split_k = pl.split;
-  } else if (M >= 256 && N >= 256 && (K % gemm::DBK) == 0 && K >= 128 * gemm::DBK) {
+  } else if (large && M >= 256 && N >= 256 && (K % gemm::DBK) == 0 && K >= 128 * gemm::DBK) {
     // a long reduction whose length is a multiple of 32 but not of 64 (ViT-L at batch 32: 6 304 rows) takes the
     // direct-to-LDS tiles; unsplit, its 16-64 tiles of 256x256 would leave most CUs idle.  Measured on those shapes:
     // about 256 units in all, at most 8 chunks (4096x1024: 98 -> 71 us with 4 chunks; 1024x1024: 70 -> 31 us with 8).
@@ -226,10 +279,10 @@ void gemm_bf16_plan_split(int M, int N, int K, int* tile, int* split_k) {
     const int tiles = ((M + 255) / 256) * ((N + 255) / 256);
     *split_k = std::max(1, std::min(8, 256 / tiles));
     *tile = tiles >= 32 ? T_DMA_256x256 : T_DMA_256x128;
-  } else {   // small outputs: as many chunks as keep the CUs busy, each at least 4 slices
-    const int tiles = ((M + 127) / 128) * ((N + 127) / 128);
-    const int slices = (K + gemm::SBK - 1) / gemm::SBK;
-    *split_k = std::max(1, std::min(std::min(256 / std::max(tiles, 1), std::max(1, slices / 4)), 256));
+  } else {   // everything else runs on the ring tile, any K
+    const Plan pl = plan_ring(M, N, K, true, 0.205e-6, 0.175e-6);
+    *split_k = pl.split;
+    if (pl.split > 1) *tile = pl.tile;   // (unsplit: whichever tile choose_tile prefers)
   }
 }
 
@@ -271,8 +324,7 @@ hipError_t gemm_bf16(const GemmDesc& d, hipStream_t s, int* launches) {
   }
   if (stem) {
   } else if (conv_dw) {   // B is the activation; the reduction runs over the output pixels
-    if ((d.conv_c & 7) || d.N != taps2 * d.conv_c || (d.K % (conv_ho * conv_wo)) || (d.K % gemm::PBK) || d.z_outer != 1 ||
-        d.z_inner != 1 || !d.c_f32)
+    if ((d.conv_c & 7) || d.N != taps2 * d.conv_c || (d.K % (conv_ho * conv_wo)) || d.z_outer != 1 || d.z_inner != 1 || !d.c_f32)
       return hipErrorInvalidValue;
   } else if (conv) {
     if ((d.conv_c % gemm::PBK) || d.K != taps2 * d.conv_c || (d.M % (conv_ho * conv_wo)) || d.a_t || d.b_t || d.z_outer != 1 ||
@@ -354,7 +406,10 @@ hipError_t gemm_bf16(const GemmDesc& d, hipStream_t s, int* launches) {
   gemm::LaunchFn fn;
   const bool conv_general = conv && !(d.conv_taps == 3 && d.conv_stride == 1);   // geometry as launch arguments
   bool resident = true;   // the two-group kernels keep one workgroup per CU that walks over the tiles
-  if (conv_dw) {
+  if (conv_dw && d.tile == T_RING_64x64 && !stem) {
+    BM = 64; BN = 64; fn = gemm::ring_convdw_64x64(epi); resident = false;
+  } else if (conv_dw) {
+    if (d.K % gemm::PBK) return hipErrorInvalidValue;
     int tile = d.tile;
     if (tile != T_PP_256x256 && tile != T_PP_256x192 && tile != T_PP_128x256 && tile != T_PP_64x512)
       tile = plan_conv_dw(d.M, d.N, k_per_block).tile;
@@ -368,6 +423,7 @@ hipError_t gemm_bf16(const GemmDesc& d, hipStream_t s, int* launches) {
     BM = 512; BN = 64; fn = gemm::pp_conv_512x64(epi, conv_general);
   } else if (conv) {
     switch (choose_conv_tile(d)) {
+      case T_RING_64x64: BM = 64; BN = 64; fn = gemm::ring_conv_64x64(epi); resident = false; break;
       case T_PP_512x64: BM = 512; BN = 64; fn = gemm::pp_conv_512x64(epi, conv_general); break;
       case T_PP_256x128: BM = 256; BN = 128; fn = gemm::pp_conv_256x128(epi, conv_general); break;
       case T_PP_256x192: BM = 256; BN = 192; fn = gemm::pp_conv_256x192(epi, conv_general); break;
@@ -380,6 +436,7 @@ hipError_t gemm_bf16(const GemmDesc& d, hipStream_t s, int* launches) {
     case T_PP_512x64: BM = 512; BN = 64; fn = gemm::pp_512x64(d.a_t, d.b_t, epi); break;
     case T_PP_256x128: BM = 256; BN = 128; fn = gemm::pp_256x128(d.a_t, d.b_t, epi); break;
     case T_128x64: BM = 128; BN = 64; fn = gemm::staged_128x64(d.a_t, d.b_t, epi); resident = false; break;
+    case T_RING_64x64: BM = 64; BN = 64; fn = gemm::ring_64x64(d.a_t, d.b_t, epi); resident = false; break;
     case T_DMA_256x256: BM = 256; BN = 256; fn = gemm::dma_256x256(d.a_t, d.b_t, epi); resident = false; break;
     case T_DMA_256x128: BM = 256; BN = 128; fn = gemm::dma_256x128(d.a_t, d.b_t, epi); resident = false; break;
     case T_PP_256x192: BM = 256; BN = 192; fn = gemm::pp_256x192(d.a_t, d.b_t, epi); break;

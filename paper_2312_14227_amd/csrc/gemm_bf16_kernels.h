@@ -17,9 +17,9 @@
 //     [k-rows][tile rows] and the lanes fetch their 2 x 4 k values with ds_read_b64_tr_b16, the
 //     LDS transpose read of gfx950: in every group of 16 lanes, lane 4c+a supplies the address of
 //     4 consecutive elements of k-row c, and lane i receives element i of k-rows 0..3.
-// Three main loops share this:
+// Four main loops share this (the fourth, the ring of small tiles, is in gemm_bf16_ring.h):
 //   gemm_staged_kernel: K slices of 64 through two LDS buffers, the global loads of slice t+1 are
-//     issued into registers before the MFMAs of slice t (small tiles, several workgroups per CU;
+//     issued into registers before the MFMAs of slice t (many short tiles, several workgroups per CU;
 //     any K, with a predicated last slice);
 //   gemm_dma_kernel: K slices of 32 loaded with global_load_lds_dwordx4 straight into a ring of
 //     LDS stages, several slices in flight (large tiles; K a multiple of 32);

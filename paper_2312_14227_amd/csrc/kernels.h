@@ -66,7 +66,7 @@ struct GemmDesc {
   // multiple of 64; row-major operands, no batching; split_k > 1 (with `partials`, ldc == N, bf16 outputs, not with
   // the ADD / GELU modes) reduces in a second kernel that also applies the epilogue.
   // With a_t and b_t (weight gradient): B is the activation standing for [K = batch Ho Wo output pixels]
-  // [N = taps^2 conv_c]; conv_c % 8 == 0, K a multiple of 64, fp32 output, split allowed
+  // [N = taps^2 conv_c]; conv_c % 8 == 0, K a multiple of 64 (any K on the ring tile), fp32 output, split allowed
   int conv_h = 0, conv_w = 0, conv_c = 0, conv_taps = 3, conv_stride = 1;
   int tile = 0;                    // 0 = choose by shape; else a TileId (tuning/tests)
 };
