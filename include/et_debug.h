@@ -94,6 +94,9 @@ int et_debug_depthwise3x3(int op, const void* a, const void* b, const void* gain
  * Device pointers, 16-byte aligned.  Returns 0, -1 (T > 224, bad sizes or pointers), -3 as above. */
 int et_debug_attention(int op, const void* qkv, void* out, float* lse, const void* dout, void* dqkv, int B, int T, int H,
                        void* stream);
+/* The same through the streaming kernels, for any number of tokens (the training step uses them beyond 224). */
+int et_debug_attention_long(int op, const void* qkv, void* out, float* lse, const void* dout, void* dqkv, int B, int T, int H,
+                            void* stream);
 
 /* Device address and element count (bf16) of an activation the last forward pass of a bound context stored,
  * so that a test can check one layer at a time against the layer's definition applied to the stored input.

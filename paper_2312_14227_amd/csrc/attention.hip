@@ -1,4 +1,4 @@
-// Fused attention core for short sequences (tokens <= 224, head size 64): forward
+// Fused attention core (head size 64); sequences of at most 224 tokens here, longer ones in attention_long.hip: forward
 // O = softmax(Q K^T / sqrt(d)) V and its backward (dQ, dK, dV), one workgroup per (batch, head).
 // These are the "attention operations" the paper counts among the non-trainable layers (Section
 // 5.4): they hold no weights, their backward time is charged to the tensor whose passing needs it.
@@ -16,35 +16,16 @@
 // V stored [key][d].  No shuffle or LDS round trip between the two matrix products.
 // The backward pass uses the mirrored trick (S = Q K^T, a lane holds one key) for dK and dV, and takes
 // rowsum(P * dP) of a query from the stored forward output: it equals dO . O.
-#include "kernels.h"
+#include "attention_tiles.h"
 
 #include <type_traits>
 
 namespace et {
 namespace {
 
-typedef bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef bf16 bf16x4 __attribute__((ext_vector_type(4)));
-typedef short s16x4 __attribute__((ext_vector_type(4)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
+using namespace attn;
 
-constexpr int DH = 64;
 constexpr int NWAVES = 8, NTHREADS = NWAVES * 64;
-// LDS rows are the 128 bytes of 64 bf16 without padding; the 16-byte chunk c of row r sits at chunk position
-// c ^ swz(r).  Every tile is read two ways and both must spread over the 64 banks:
-//   - row-major fragments (ds_read_b128, 16 consecutive rows x one chunk per 16 lanes): rows alternate between the
-//     two 128-byte halves of the 256-byte bank span, so the 8 even rows of a group need 8 different positions;
-//   - transposing fragments (ds_read_b64_tr_b16, 4 consecutive rows x 64 contiguous bytes per 32 lanes): rows
-//     r and r + 2 share a half, so their 64-byte pieces must land in different quarters.
-// swz(r) = bit 1 of r as the high bit, bits 2..3 of r as the low bits, does both (a plain (r >> 1) & 7 leaves the
-// transposing reads two-way conflicted, as did padded rows of 160 bytes: 41-45 % conflict cycles measured).
-constexpr int PITCH = 128;
-__device__ __forceinline__ int swz(int row) { return (((row >> 1) & 1) << 2) | ((row >> 2) & 3); }
-
-__device__ __forceinline__ bf16x4 lds_read_tr(const unsigned char* p) {
-  s16x4 v = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3)))*)(p));
-  return __builtin_bit_cast(bf16x4, v);
-}
 
 // rows [0, T) of NM [T][64] bf16 matrices (row stride ld[m] elements) into LDS rows of PITCH bytes; rows
 // [T, TP) are zero-filled.  All loads are issued before the first store, so the matrices arrive
@@ -71,60 +52,6 @@ __device__ __forceinline__ void stage_rows(unsigned char* const (&dst)[NM], cons
     }
 }
 
-// A- or B-operand fragment of rows [row0, row0+32) for reduction slice ks (16 of the 64 columns):
-// lane l gets row row0 + l%32, columns ks*16 + (l/32)*8 .. +7
-__device__ __forceinline__ bf16x8 frag_direct(const unsigned char* m, int row0, int ks, int lane) {
-  const int row = row0 + (lane & 31);
-  return *(const bf16x8*)(m + row * PITCH + (((ks * 2 + (lane >> 5)) ^ swz(row)) << 4));
-}
-
-// B-operand fragment for a reduction over ROWS of a matrix stored [row][64]: lane l gets column
-// col0 + l%32 and the 8 rows  row0 + (e/4)*8 + (l/32)*4 + e%4  (e = 0..7)
-__device__ __forceinline__ bf16x8 frag_rows_tr(const unsigned char* m, int row0, int col0, int lane) {
-  const int g = lane >> 4, r16 = lane & 15;
-  // (rows r and r + 8 differ in bit 3, which is bit 1 of swz: the second address is computed on its own)
-  const int row = row0 + (g >> 1) * 4 + (r16 >> 2);
-  const int byte = (col0 + (g & 1) * 16 + 4 * (r16 & 3)) * 2;      // 8-byte piece inside the logical row
-  const int chunk = byte >> 4, half = byte & 8;
-  const unsigned char* p = m + row * PITCH + ((chunk ^ swz(row)) << 4) + half;
-  const unsigned char* p8 = m + (row + 8) * PITCH + ((chunk ^ swz(row + 8)) << 4) + half;
-  const bf16x4 lo = lds_read_tr(p), hi = lds_read_tr(p8);
-  return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-}
-
-// element r of an MFMA result tile: row offset inside the 32x32 tile
-__device__ __forceinline__ int tile_row(int r, int lane) { return (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3); }
-
-// Store a 32 x 64 result tile (lane = row l%32, registers t[dt][a*4 + e] = column dt*32 + a*8 + (l/32)*4 + e), times
-// `mul`, as bf16 rows of `ld` elements starting at `base` (row 0 of the tile), rows >= `rows` left out.  Straight
-// from the registers a store instruction would put 16 bytes into each of 32 rows (8-byte pieces of two lanes);
-// written that way the 19 MB of a ViT-B forward output cost 6 us.  The tile goes through a wave-private 4 KiB LDS
-// area instead (16-byte chunks XORed with (row >> 1) & 7: even and odd rows lie in different halves of the 256-byte
-// bank span, so 16 consecutive rows of one column are spread over all 64 banks) and
-// leaves as whole 128-byte rows, 8 lanes x 16 bytes each.  LDS instructions of one wave execute in order, so no
-// barrier is needed between the writes and the reads, nor between two tiles through the same area.
-constexpr int STORE_AREA = 32 * 128;
-__device__ __forceinline__ void store_tile(unsigned char* area, const f32x16 (&t)[2], float mul, bf16* base, long long ld,
-                                           int rows, int lane) {
-  asm volatile("" : "+v"(lane));   // (addresses below are computed here, not kept live through the caller's main loop)
-  const int l32 = lane & 31, khalf = lane >> 5;
-#pragma unroll
-  for (int dt = 0; dt < 2; dt++)
-#pragma unroll
-    for (int a = 0; a < 4; a++) {
-      bf16x4 v;
-#pragma unroll
-      for (int e = 0; e < 4; e++) v[e] = (bf16)(t[dt][a * 4 + e] * mul);
-      *(bf16x4*)(area + l32 * 128 + (((dt * 4 + a) ^ ((l32 >> 1) & 7)) << 4) + khalf * 8) = v;
-    }
-#pragma unroll
-  for (int i = 0; i < 4; i++) {
-    const int row = i * 8 + (lane >> 3), chunk = lane & 7;
-    const bf16x8 v = *(const bf16x8*)(area + row * 128 + ((chunk ^ ((row >> 1) & 7)) << 4));
-    if (row < rows) *(bf16x8*)(base + row * ld + chunk * 8) = v;
-  }
-}
-
 // -------------------------------------------------------------------------------------------------
 // forward
 // -------------------------------------------------------------------------------------------------
@@ -134,10 +61,6 @@ __device__ __forceinline__ void store_tile(unsigned char* area, const f32x16 (&t
 // (base in M0) + 16 * lane: the bank swizzle is therefore applied on the global side (the lane at chunk position p
 // of row r fetches chunk p ^ swz(r)).  Rows beyond the sequence repeat the last row: their keys are masked with
 // -inf, and a probability of zero times a finite V row adds nothing.
-__device__ __forceinline__ void dma16(const void* gptr, unsigned lds_base) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds_base), "v"(gptr) : "memory");
-}
-
 template <int KT>
 __global__ __launch_bounds__(NTHREADS) void attention_fwd_kernel(const bf16* __restrict__ qkv, bf16* __restrict__ out,
                                                                  float* __restrict__ lse, int T, int H, float scale, int items) {
@@ -427,11 +350,12 @@ hipError_t launch_bwd(const bf16* qkv, const bf16* out, const bf16* dout, const 
 
 }  // namespace
 
-bool attention_fused_supported(int T, int head_dim) { return head_dim == DH && T >= 1 && T <= 224; }
+bool attention_fused_supported(int T, int head_dim) { return head_dim == DH && T >= 1 && T < (1 << 20); }
 
 hipError_t attention_fwd(const bf16* qkv, bf16* out, float* lse, int B, int T, int H, int head_dim, float scale,
                          hipStream_t s) {
   if (!attention_fused_supported(T, head_dim) || B < 1 || H < 1) return hipErrorInvalidValue;
+  if (T > 224) return attention_long_fwd(qkv, out, lse, B, T, H, scale, s);
   switch ((T + 31) / 32) {
     case 1: return launch_fwd<1>(qkv, out, lse, B, T, H, scale, s);
     case 2: return launch_fwd<2>(qkv, out, lse, B, T, H, scale, s);
@@ -446,6 +370,7 @@ hipError_t attention_fwd(const bf16* qkv, bf16* out, float* lse, int B, int T, i
 hipError_t attention_bwd(const bf16* qkv, const bf16* out, const bf16* dout, const float* lse, bf16* dqkv, int B, int T, int H,
                          int head_dim, float scale, hipStream_t s) {
   if (!attention_fused_supported(T, head_dim) || B < 1 || H < 1 || !out) return hipErrorInvalidValue;
+  if (T > 224) return attention_long_bwd(qkv, out, dout, lse, dqkv, B, T, H, scale, s);
   switch ((T + 31) / 32) {
     case 1: return launch_bwd<1>(qkv, out, dout, lse, dqkv, B, T, H, scale, s);
     case 2: return launch_bwd<2>(qkv, out, dout, lse, dqkv, B, T, H, scale, s);

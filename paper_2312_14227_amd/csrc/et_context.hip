@@ -57,6 +57,7 @@ int build_vit(et_ctx* c) {
 
   const size_t B = d.batch, M = B * T, H = d.heads, ldT = round8(d.tokens), C8 = round8(d.classes);
   const size_t f32 = sizeof(float), b16 = sizeof(bf16);
+  const bool fused = et::attention_fused_supported(d.tokens, d.width / d.heads);   // no score is ever stored
   reserve(c, &c->e, f32 * B * (T - 1) * D);
   c->blk.assign(d.blocks, VitBlockBufs());
   for (int l = 0; l < d.blocks; l++) {
@@ -67,7 +68,7 @@ int build_vit(et_ctx* c) {
     reserve(c, &b.mean2, f32 * M); reserve(c, &b.rstd2, f32 * M);
     reserve(c, &b.a1, b16 * M * D);
     reserve(c, &b.qkv, b16 * M * 3 * D);
-    reserve(c, &b.p, b16 * B * H * T * ldT);
+    if (!fused) reserve(c, &b.p, b16 * B * H * T * ldT);
     reserve(c, &b.lse, f32 * B * H * T);
     reserve(c, &b.o, b16 * M * D);
     reserve(c, &b.a2, b16 * M * D);
@@ -75,7 +76,7 @@ int build_vit(et_ctx* c) {
     reserve(c, &b.ga, b16 * M * F);
   }
   reserve(c, &c->h_out, f32 * M * D);
-  reserve(c, &c->s_f32, f32 * B * H * T * ldT);
+  if (!fused) reserve(c, &c->s_f32, f32 * B * H * T * ldT);
   reserve(c, &c->meanf, f32 * B); reserve(c, &c->rstdf, f32 * B);
   reserve(c, &c->zc, b16 * B * D);
   reserve(c, &c->logits, f32 * B * C);
@@ -89,7 +90,7 @@ int build_vit(et_ctx* c) {
   reserve(c, &c->du, b16 * M * F);
   reserve(c, &c->dattn, b16 * M * D);
   reserve(c, &c->dqkv, b16 * M * 3 * D);
-  reserve(c, &c->ds, b16 * B * H * T * ldT);
+  if (!fused) reserve(c, &c->ds, b16 * B * H * T * ldT);
   reserve(c, &c->de, b16 * B * (T - 1) * D);
   // split-K partials: the largest weight gradient
   size_t pe = 0;

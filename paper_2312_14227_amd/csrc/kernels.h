@@ -126,7 +126,8 @@ hipError_t softmax_rows(const float* s, bf16* p, int rows, int cols, int ld, hip
 hipError_t softmax_bwd_rows(const float* dp, const bf16* p, bf16* ds, float scale, int rows, int cols, int ld,
                             hipStream_t stream);
 
-// fused attention core (tokens <= 224, head size 64), one workgroup per (batch, head):
+// fused attention core (head size 64): up to 224 tokens one workgroup per (batch, head), beyond that one per 128 queries
+// (or keys) of a (batch, head):
 //   forward: out[b][t][h*64+d] = softmax(Q K^T * scale) V, lse[b][h][t] = log-sum-exp of the scaled scores
 //   backward: dqkv (same layout as qkv) from dout, recomputing the probabilities from lse; `out` is the stored
 //   forward output (rowsum(P * dP) = dout . out)
@@ -135,6 +136,10 @@ hipError_t attention_fwd(const bf16* qkv, bf16* out, float* lse, int B, int T, i
                          hipStream_t s);
 hipError_t attention_bwd(const bf16* qkv, const bf16* out, const bf16* dout, const float* lse, bf16* dqkv, int B, int T, int H,
                          int head_dim, float scale, hipStream_t s);
+// the same for sequences of any length, streamed (attention_fwd / _bwd choose)
+hipError_t attention_long_fwd(const bf16* qkv, bf16* out, float* lse, int B, int T, int H, float scale, hipStream_t s);
+hipError_t attention_long_bwd(const bf16* qkv, const bf16* out, const bf16* dout, const float* lse, bf16* dqkv, int B, int T, int H,
+                              float scale, hipStream_t s);
 
 // mean softmax cross-entropy: dlogits fp32 and (if not null) a bf16 copy [B][ld16], zero padded; `loss` points to
 // 64 + B floats: the loss in element 0, the per-row terms from element 64 on (two launches)
