@@ -331,6 +331,74 @@ __global__ __launch_bounds__(NTHREADS) void attention_bwd_kernel(const bf16* __r
   }
 }
 
+// -------------------------------------------------------------------------------------------------
+// backward of a single query per (batch, head), token 0, over all keys: with p_t = exp(scale q.k_t - lse) and
+// ds_t = p_t (dO.v_t - dO.O) scale:  dV_t = p_t dO,  dK_t = ds_t q,  dQ_0 = sum_t ds_t k_t, dQ of the other tokens zero.
+// Vector work bound by memory (K and V read, dQ, dK, dV written: 97 MB for 64 x 12 heads of 197 tokens); one workgroup per
+// (batch, head), eight lanes per token with 16 bytes each.
+// -------------------------------------------------------------------------------------------------
+__global__ __launch_bounds__(256) void attention_bwd_cls_kernel(const bf16* __restrict__ qkv, const bf16* __restrict__ out,
+                                                                const bf16* __restrict__ dout, const float* __restrict__ lse,
+                                                                bf16* __restrict__ dqkv, int T, int H, float scale) {
+  __shared__ float red[32][DH + 4];
+  const int tid = threadIdx.x, part = tid & 7, grp = tid >> 3;
+  const int b = blockIdx.x / H, h = blockIdx.x % H, D = H * DH;
+  const long long ld = 3LL * D, base = (long long)b * T * ld + h * DH + part * 8;
+  const bf16x8 q8 = *(const bf16x8*)(qkv + base);
+  const bf16x8 do8 = *(const bf16x8*)(dout + (long long)b * T * D + h * DH + part * 8);
+  const bf16x8 o8 = *(const bf16x8*)(out + (long long)b * T * D + h * DH + part * 8);
+  float q[8], g[8], dot = 0.f;
+#pragma unroll
+  for (int e = 0; e < 8; e++) {
+    q[e] = (float)q8[e];
+    g[e] = (float)do8[e];
+    dot += g[e] * (float)o8[e];
+  }
+#pragma unroll
+  for (int m = 1; m < 8; m <<= 1) dot += __shfl_xor(dot, m, 64);
+  const float c = scale * 1.44269504088896341f, l = lse[((long long)b * H + h) * T] * 1.44269504088896341f;
+  float dq[8];
+#pragma unroll
+  for (int e = 0; e < 8; e++) dq[e] = 0.f;
+  const bf16x8 zero = {};
+#pragma unroll 2
+  for (int t = grp; t < T; t += 32) {
+    const long long at = base + (long long)t * ld;
+    const bf16x8 k8 = *(const bf16x8*)(qkv + at + D), v8 = *(const bf16x8*)(qkv + at + 2 * D);
+    float sc = 0.f, dp = 0.f;
+#pragma unroll
+    for (int e = 0; e < 8; e++) {
+      sc += q[e] * (float)k8[e];
+      dp += g[e] * (float)v8[e];
+    }
+#pragma unroll
+    for (int m = 1; m < 8; m <<= 1) {
+      sc += __shfl_xor(sc, m, 64);
+      dp += __shfl_xor(dp, m, 64);
+    }
+    const float p = __builtin_amdgcn_exp2f(fmaf(sc, c, -l)), ds = p * (dp - dot) * scale;
+    bf16x8 dk8, dv8;
+#pragma unroll
+    for (int e = 0; e < 8; e++) {
+      dk8[e] = (bf16)(ds * q[e]);
+      dv8[e] = (bf16)(p * g[e]);
+      dq[e] += ds * (float)k8[e];
+    }
+    if (t > 0) *(bf16x8*)(dqkv + at) = zero;
+    *(bf16x8*)(dqkv + at + D) = dk8;
+    *(bf16x8*)(dqkv + at + 2 * D) = dv8;
+  }
+#pragma unroll
+  for (int e = 0; e < 8; e++) red[grp][part * 8 + e] = dq[e];
+  __syncthreads();
+  if (tid < DH) {
+    float s = red[0][tid];
+#pragma unroll
+    for (int k = 1; k < 32; k++) s += red[k][tid];
+    dqkv[(long long)b * T * ld + h * DH + tid] = (bf16)s;
+  }
+}
+
 template <int KT>
 hipError_t launch_fwd(const bf16* qkv, bf16* out, float* lse, int B, int T, int H, float scale, hipStream_t s) {
   // one resident workgroup per CU (two LDS buffers of K and V each); fewer when there are fewer items
@@ -349,6 +417,13 @@ hipError_t launch_bwd(const bf16* qkv, const bf16* out, const bf16* dout, const 
 }
 
 }  // namespace
+
+hipError_t attention_bwd_cls(const bf16* qkv, const bf16* out, const bf16* dout, const float* lse, bf16* dqkv, int B, int T, int H,
+                             int head_dim, float scale, hipStream_t s) {
+  if (!attention_fused_supported(T, head_dim) || B < 1 || H < 1) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(attention_bwd_cls_kernel, dim3(B * H), dim3(256), 0, s, qkv, out, dout, lse, dqkv, T, H, scale);
+  return hipGetLastError();
+}
 
 bool attention_fused_supported(int T, int head_dim) { return head_dim == DH && T >= 1 && T < (1 << 20); }
 

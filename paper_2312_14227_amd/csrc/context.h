@@ -21,14 +21,19 @@ constexpr uint32_t SEG_ELEMS = 16384;  // elements per chunk of the importance /
 
 enum Phase { PH_FWD = 0, PH_DW = 1, PH_DY = 2, PH_UPD = 3 };
 
+struct Share {  // part of a timed region's time that belongs to a piece (phase, tensor) of the time model
+  int phase, tensor;
+  double weight;
+};
+
 struct TensorInfo {
   std::string name;
   size_t numel;
   int32_t dtype;
 };
 
-struct Scope {  // one timed region of the profile (tensor2 >= 0: its time is shared evenly by two tensors)
-  int phase, tensor, tensor2;
+struct Scope {  // one timed region of the profile; its time is divided among the shares in proportion to their weights
+  std::vector<Share> shares;
   hipEvent_t e0, e1;
 };
 
@@ -101,8 +106,15 @@ struct et_ctx {
   float *e = nullptr, *h_out = nullptr, *s_f32 = nullptr, *meanf = nullptr, *rstdf = nullptr, *dh = nullptr;
   bf16 *zc = nullptr, *dl16 = nullptr, *dz = nullptr, *dh16 = nullptr, *da = nullptr, *du = nullptr, *dattn = nullptr,
        *dqkv = nullptr, *ds = nullptr, *de = nullptr;
-  float *gemm_partials = nullptr, *colsum_partials = nullptr;
+  float* gemm_partials = nullptr;
   size_t gemm_partial_elems = 0;
+
+  // column sums of the backward pass that wait for their second step: partial rows in sum_arena (bump allocated), finished
+  // together by one launch at the end of the pass, or earlier when the arena is full
+  float* sum_arena = nullptr;
+  size_t sum_arena_elems = 0, sum_used = 0;
+  std::vector<et::SumJob> sum_jobs;
+  std::vector<int> sum_tensors;
 
   // ResNet buffers
   ConvUnit stem;
@@ -128,7 +140,6 @@ struct et_ctx {
   // inverted-residual network: blocks; the stem and the last convolution are ConvUnits (`stem`, `mlast`)
   std::vector<MbBlockBufs> mblk;
   ConvUnit mlast;
-  float* dw_part = nullptr;         // partial sums of a depthwise weight gradient
 
   // tables for importance / update
   std::vector<uint32_t> seg_begin;  // [N+1]
@@ -207,13 +218,17 @@ struct Region {
   et_ctx* c;
   bool on;
   size_t idx = 0;
-  Region(et_ctx* ctx, int phase, int tensor, int tensor2 = -1) : c(ctx), on(ctx->profiling) {
+  Region(et_ctx* ctx, int phase, int tensor) : c(ctx), on(ctx->profiling) {
+    const Share one = {phase, tensor, 1.0};
+    begin(phase, &one, 1);
+  }
+  // `phase`: what the launches are counted as
+  Region(et_ctx* ctx, int phase, const Share* shares, size_t n) : c(ctx), on(ctx->profiling) { begin(phase, shares, n); }
+  void begin(int phase, const Share* shares, size_t n) {
     c->cur_phase = phase;
     if (!on) return;
     Scope s;
-    s.phase = phase;
-    s.tensor = tensor;
-    s.tensor2 = tensor2;
+    s.shares.assign(shares, shares + n);
     if (get_event(c, &s.e0) != hipSuccess || get_event(c, &s.e1) != hipSuccess) {
       on = false;
       c->hip_err = hipErrorOutOfMemory;
@@ -227,6 +242,52 @@ struct Region {
     if (on) (void)hipEventRecord(c->scopes[idx].e1, c->stream);
   }
 };
+
+// ---- column sums (see et_ctx::sum_arena)
+// workspace for the partial sums of a backward pass: `total` floats hold every sum at once, `largest` the largest group that is
+// allocated together; beyond 64 MB the pass finishes what it has and starts over
+inline void reserve_sums(et_ctx* c, size_t total, size_t largest) {
+  c->sum_arena_elems = std::max(std::max(largest, (size_t)64), std::min(total, (size_t)16 << 20));
+  reserve(c, &c->sum_arena, sizeof(float) * c->sum_arena_elems);
+}
+inline size_t sum_elems(size_t rows, size_t cols) { return (rows * cols + 63) / 64 * 64; }
+
+inline int sums_finish(et_ctx* c) {
+  if (c->sum_jobs.empty()) return ET_OK;
+  std::vector<Share> shares;
+  if (c->profiling)
+    for (int t : c->sum_tensors) shares.push_back({PH_DW, t, 1.0});
+  Region r(c, PH_DW, shares.data(), shares.size());
+  int n = 0;
+  const hipError_t e = et::sum_finish(c->sum_jobs.data(), (int)c->sum_jobs.size(), c->stream, &n);
+  c->launches[PH_DW] += n;
+  c->sum_jobs.clear();
+  c->sum_tensors.clear();
+  c->sum_used = 0;
+  if (e != hipSuccess) { c->hip_err = e; return ET_EHIP; }
+  return ET_OK;
+}
+// makes room for a group of sums that one kernel produces
+inline int sums_room(et_ctx* c, size_t elems) { return c->sum_used + elems > c->sum_arena_elems ? sums_finish(c) : ET_OK; }
+// partial rows of one sum, to be finished into the gradient of `tensor`
+inline float* sum_job(et_ctx* c, int tensor, int rows, int cols) {
+  float* p = c->sum_arena + c->sum_used;
+  c->sum_used += sum_elems(rows, cols);
+  c->sum_jobs.push_back({p, c->grad[tensor], rows, cols, 0});
+  c->sum_tensors.push_back(tensor);
+  return p;
+}
+// gradient of `tensor` = column sum of a [rows][cols] matrix (times the normalised h)
+inline int colsum_dw(et_ctx* c, int tensor, const bf16* d, const float* d32, long long d_stride, int rows, int cols, const float* h = nullptr,
+                     long long h_stride = 0, const float* mean = nullptr, const float* rstd = nullptr, long long stat_stride = 1) {
+  const int parts = et::colsum_parts(rows, cols);
+  const int rc = sums_room(c, sum_elems(parts, cols));
+  if (rc != ET_OK) return rc;
+  Region r(c, PH_DW, tensor);
+  float* part = sum_job(c, tensor, parts, cols);
+  ET_K(1, et::colsum_part(d, d32, d_stride, h, h_stride, mean, rstd, stat_stride, part, rows, cols, c->stream));
+  return ET_OK;
+}
 
 // split of the reduction dimension for a weight gradient [Mo][No] reduced over K rows
 inline int split_for(int Mo, int No, int K) {

@@ -169,19 +169,6 @@ __global__ __launch_bounds__(256) void affine_kernel(const bf16* __restrict__ z1
   }
 }
 
-// out = d * gain[c]
-__global__ __launch_bounds__(256) void scale_cols_kernel(const bf16* __restrict__ d, const bf16* __restrict__ gain,
-                                                         bf16* __restrict__ out, long long n8, int C) {
-  const int c8n = C >> 3;
-  for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n8; i += (long long)gridDim.x * blockDim.x) {
-    const bf16x8 a = *(const bf16x8*)(d + i * 8), g = *(const bf16x8*)(gain + (int)(i % c8n) * 8);
-    bf16x8 r;
-#pragma unroll
-    for (int j = 0; j < 8; j++) r[j] = (bf16)((float)a[j] * (float)g[j]);
-    *(bf16x8*)(out + i * 8) = r;
-  }
-}
-
 // out = (a + b) * (0 < mask < hi); b may be null; mask may be null (plain sum)
 __global__ __launch_bounds__(256) void add_mask_kernel(const bf16* __restrict__ a, const bf16* __restrict__ b,
                                                        const bf16* __restrict__ mask, bf16* __restrict__ out,
@@ -637,13 +624,6 @@ hipError_t affine_act(const bf16* z1, const float* z1_f32, const bf16* g1, const
   else
     hipLaunchKernelGGL((affine_kernel<false>), dim3(grid_for(n8)), dim3(256), 0, s, z1, z1_f32, g1, b1, z2, g2, b2,
                        relu ? 1 : 0, out, n8, C);
-  return hipGetLastError();
-}
-
-hipError_t scale_cols(const bf16* d, const bf16* gain, bf16* out, long long rows, int C, hipStream_t s) {
-  if (rows < 1 || C < 8 || (C & 7) || !al16(d) || !al16(gain) || !al16(out)) return hipErrorInvalidValue;
-  const long long n8 = rows * (C >> 3);
-  hipLaunchKernelGGL(scale_cols_kernel, dim3(grid_for(n8)), dim3(256), 0, s, d, gain, out, n8, C);
   return hipGetLastError();
 }
 

@@ -20,30 +20,28 @@ namespace et_exec {
 
 // The per-channel pieces of a folded-BN affine y = z * gain + shift (tensors tg = gain, tg + 1 = shift) on the
 // gradient d [M][C] of y: dw(shift) = column sum of d, dw(gain) = column sum of d * z (z bf16, or float32 z32),
-// dy(gain): dout = d * gain.  With gain and shift both selected one kernel reads d once for both sums (same
-// summation order as the separate kernels, so a tensor's gradient does not depend on its neighbour's selection);
-// the profile shares that kernel's time evenly between the two tensors.  dy_used = false skips dy(gain) although
+// dy(gain): dout = d * gain.  One kernel reads d once for whichever of the three are wanted (the order of a sum does not
+// depend on the others); the profile divides its time by the bytes each of them adds.  dy_used = false skips dy(gain) although
 // the chain passes the tensor: a projection shortcut's scaled gradient has no reader when its weight is not selected
 // and nothing in front of the block is (the time model then charges a few microseconds that are not spent).
 inline int affine_back(et_ctx* c, const uint8_t* mask, int jstar, int tg, const bf16* d, const bf16* z, const float* z32,
                        bf16* dout, long long M, int C, bool dy_used = true) {
-  float* cp = c->colsum_partials;
-  hipStream_t s = c->stream;
   const double zb = z32 ? 4.0 : 2.0;
-  if (mask[tg] && mask[tg + 1]) {
-    Region r(c, PH_DW, tg + 1, tg);
-    ET_KB(2, (2.0 + zb) * M * C, et::colsum_pair(d, z, z32, c->grad[tg + 1], c->grad[tg], cp, (int)M, C, s));
-  } else if (mask[tg + 1]) {
-    Region r(c, PH_DW, tg + 1);
-    ET_KB(2, 2.0 * M * C, et::colsum(d, nullptr, C, nullptr, 0, nullptr, nullptr, c->grad[tg + 1], cp, (int)M, C, s));
-  } else if (mask[tg]) {
-    Region r(c, PH_DW, tg);
-    ET_KB(2, (2.0 + zb) * M * C, et::colsum_mul(d, z, z32, c->grad[tg], cp, (int)M, C, s));
-  }
-  if (tg > jstar && dy_used) {
-    Region r(c, PH_DY, tg);
-    ET_KB(1, 4.0 * M * C, et::scale_cols(d, (const bf16*)c->w[tg], dout, M, C, s));
-  }
+  const bool scaled = tg > jstar && dy_used;
+  if (!mask[tg] && !mask[tg + 1] && !scaled) return ET_OK;
+  const int parts = et::colsum_parts((int)M, C);
+  const int rc = sums_room(c, 2 * sum_elems(parts, C));
+  if (rc != ET_OK) return rc;
+  Share shares[3];
+  size_t n = 0;
+  double bytes = 2.0;
+  if (scaled) { shares[n++] = {PH_DY, tg, 4.0}; bytes += 2.0; }
+  if (mask[tg + 1]) shares[n++] = {PH_DW, tg + 1, 0.5};
+  if (mask[tg]) { shares[n++] = {PH_DW, tg, zb}; bytes += zb; }
+  float* part_sum = mask[tg + 1] ? sum_job(c, tg + 1, parts, C) : nullptr;
+  float* part_mul = mask[tg] ? sum_job(c, tg, parts, C) : nullptr;
+  Region r(c, scaled && n == 1 ? PH_DY : PH_DW, shares, n);
+  ET_KB(1, bytes * M * C, et::colsum_pair_part(d, z, z32, (const bf16*)c->w[tg], scaled ? dout : nullptr, part_sum, part_mul, (int)M, C, c->stream));
   return ET_OK;
 }
 

@@ -100,7 +100,13 @@ int build_vit(et_ctx* c) {
   wg(3 * D, D, M); wg(D, D, M); wg(F, D, M); wg(D, F, M); wg(D, P, B * (T - 1)); wg(C, D, B);
   c->gemm_partial_elems = pe;
   reserve(c, &c->gemm_partials, f32 * std::max<size_t>(pe, 64));
-  reserve(c, &c->colsum_partials, f32 * et::colsum_partial_elems((int)M, (int)std::max(3 * D, F)));
+  {
+    // per block: gain, shift and bias sums of both LayerNorms, the fc1 and qkv biases; largest group: three sums of one LayerNorm
+    const size_t ln = std::max(sum_elems(et::layernorm_bwd_parts((int)M), D), sum_elems(et::colsum_parts((int)M, (int)D), D));
+    const size_t f1 = sum_elems(et::colsum_parts((int)M, (int)F), F), q = sum_elems(et::colsum_parts((int)M, (int)(3 * D)), 3 * D);
+    reserve_sums(c, (size_t)d.blocks * (6 * ln + f1 + q) + 4 * ln + sum_elems(et::colsum_parts((int)B, (int)C), C),
+                 std::max(std::max(3 * ln, f1), std::max(q, sum_elems(et::colsum_parts((int)B, (int)C), C))));
+  }
   return ET_OK;
 }
 
@@ -320,6 +326,43 @@ int vit_attention_backward(et_ctx* c, const VitDims& v, VitBlockBufs& b) {
   return ET_OK;
 }
 
+// One LayerNorm of the chain (gain tg, shift tg + 1; gradient d of its output): dw(shift), dw(gain) and dy(gain), and behind
+// dy(gain) the gradient of the bias tb (-1: none) that was added in front of the LayerNorm's input, the column sum of the
+// resulting stream.  Where the gradient is passed on, one kernel produces whatever of these is selected from the same
+// reads; its time in the profile is divided by what each output adds to it (measured on [12608 x 768]: the input gradient
+// alone 22.7 us, each sum 0.7 us).  `a` comes filled in except for the partial sums.
+int layernorm_back(et_ctx* c, const uint8_t* mask, int jstar, int tg, int tb, et::LayerNormBwd a) {
+  const int ts = tg + 1;
+  const bool pass = tg > jstar, fused = pass && a.D <= et::LAYERNORM_SUMS_MAX_D;
+  int rc;
+  if (!fused) {
+    if (mask[ts] && (rc = colsum_dw(c, ts, a.d, nullptr, a.d_stride, a.rows, a.D)) != ET_OK) return rc;
+    if (mask[tg] && (rc = colsum_dw(c, tg, a.d, nullptr, a.d_stride, a.rows, a.D, a.h, a.h_stride, a.mean, a.rstd, a.stat_stride)) != ET_OK)
+      return rc;
+    if (!pass) return ET_OK;
+    {
+      Region r(c, PH_DY, tg);
+      ET_K(1, et::layernorm_bwd(a, c->stream));
+    }
+    return tb >= 0 && mask[tb] ? colsum_dw(c, tb, nullptr, a.dh, a.out_stride, a.rows, a.D) : ET_OK;
+  }
+  const int parts = et::layernorm_bwd_parts(a.rows);
+  if ((rc = sums_room(c, 3 * sum_elems(parts, a.D))) != ET_OK) return rc;
+  Share shares[4] = {{PH_DY, tg, 22.7}};
+  size_t n = 1;
+  auto sum = [&](int t) -> float* {
+    if (t < 0 || !mask[t]) return nullptr;
+    shares[n++] = {PH_DW, t, 0.7};
+    return sum_job(c, t, parts, a.D);
+  };
+  a.part_gain = sum(tg);
+  a.part_shift = sum(ts);
+  a.part_bias = sum(tb);
+  Region r(c, PH_DY, shares, n);
+  ET_K(1, et::layernorm_bwd(a, c->stream));
+  return ET_OK;
+}
+
 int vit_backward(et_ctx* c, const void* x, const uint8_t* mask) {
   const VitDims v = vit_dims(c->desc);
   const int N = (int)c->tensors.size();
@@ -331,13 +374,16 @@ int vit_backward(et_ctx* c, const void* x, const uint8_t* mask) {
   auto sel = [&](int j) { return mask[j] != 0; };
   auto pass = [&](int j) { return j > jstar; };
   hipStream_t s = c->stream;
-  float* cp = c->colsum_partials;
+  int rc;
+
+  // Behind the last block only the CLS row of a sequence is read, so the gradient that enters it is zero everywhere else:
+  // down to the attention core its MLP, LayerNorm and projection work on B rows, T rows apart in the same buffers.  The
+  // attention core spreads the gradient over all tokens.  (Head sizes without a fused kernel carry the zero rows.)
+  const bool cls = et::attention_fused_supported(v.T, v.dh);
+  const long long sD = (long long)v.T * v.D;
 
   // ---- head and final LayerNorm (CLS rows)
-  if (sel(N - 1)) {
-    Region r(c, PH_DW, N - 1);
-    ET_K(2, et::colsum(nullptr, c->dlogits, v.C, nullptr, 0, nullptr, nullptr, c->grad[N - 1], cp, v.B, v.C, s));
-  }
+  if (sel(N - 1) && (rc = colsum_dw(c, N - 1, nullptr, c->dlogits, v.C, v.B, v.C)) != ET_OK) return rc;
   if (sel(N - 2)) {
     Region r(c, PH_DW, N - 2);
     ET_G(linear_dw(c, c->dl16, v.C8, c->zc, v.D, c->grad[N - 2], v.B, v.C, v.D));
@@ -348,21 +394,16 @@ int vit_backward(et_ctx* c, const void* x, const uint8_t* mask) {
     g.lda = v.C8; g.C = c->dz;
     ET_G(g);
   }
-  if (sel(N - 3)) {
-    Region r(c, PH_DW, N - 3);
-    ET_K(2, et::colsum(c->dz, nullptr, v.D, nullptr, 0, nullptr, nullptr, c->grad[N - 3], cp, v.B, v.D, s));
-  }
-  if (sel(N - 4)) {
-    Region r(c, PH_DW, N - 4);
-    ET_K(2, et::colsum(c->dz, nullptr, v.D, c->h_out, (long long)v.T * v.D, c->meanf, c->rstdf, c->grad[N - 4], cp,
-                       v.B, v.D, s));
-  }
-  if (pass(N - 4)) {
+  if (pass(N - 4) && !cls) {
     Region r(c, PH_DY, N - 4);
     ET_K(1, et::fill_zero(c->dh, sizeof(float) * (size_t)v.M * v.D, s));
     ET_K(1, et::fill_zero(c->dh16, sizeof(bf16) * (size_t)v.M * v.D, s));
-    ET_K(1, et::layernorm_bwd_dx(c->dz, c->h_out, (long long)v.T * v.D, c->meanf, c->rstdf, W(N - 4), nullptr, c->dh,
-                                 c->dh16, (long long)v.T * v.D, v.B, v.D, s));
+  }
+  {
+    et::LayerNormBwd a;
+    a.d = c->dz; a.d_stride = v.D; a.h = c->h_out; a.h_stride = sD; a.mean = c->meanf; a.rstd = c->rstdf; a.gain = W(N - 4);
+    a.dh = c->dh; a.dh16 = c->dh16; a.out_stride = sD; a.rows = v.B; a.D = v.D;
+    if ((rc = layernorm_back(c, mask, jstar, N - 4, N - 5, a)) != ET_OK) return rc;
   }
 
   // ---- blocks, output side first
@@ -370,67 +411,57 @@ int vit_backward(et_ctx* c, const void* x, const uint8_t* mask) {
     VitBlockBufs& b = c->blk[l];
     const int t0 = 4 + 12 * l;
     if (jstar > t0 + 11) break;
-    if (sel(t0 + 11)) {
-      Region r(c, PH_DW, t0 + 11);
-      ET_K(2, et::colsum(nullptr, c->dh, v.D, nullptr, 0, nullptr, nullptr, c->grad[t0 + 11], cp, v.M, v.D, s));
-    }
+    // rows of the stream with a gradient, and the strides between them
+    const bool few = cls && l + 1 == v.L;
+    const int R = few ? v.B : v.M, step = few ? v.T : 1;
+    const int ldD = step * v.D, ldF = step * v.F;
     if (sel(t0 + 10)) {
       Region r(c, PH_DW, t0 + 10);
-      ET_G(linear_dw(c, c->dh16, v.D, b.ga, v.F, c->grad[t0 + 10], v.M, v.D, v.F));
+      ET_G(linear_dw(c, c->dh16, ldD, b.ga, ldF, c->grad[t0 + 10], R, v.D, v.F));
     }
     if (pass(t0 + 10)) {  // through fc2.W, then through the GELU (b.u holds gelu'(pre-activation))
       Region r(c, PH_DY, t0 + 10);
-      et::GemmDesc g = linear_dx(c->dh16, W(t0 + 10), v.M, v.D, v.F);
+      et::GemmDesc g = linear_dx(c->dh16, W(t0 + 10), R, v.D, v.F);
+      g.lda = ldD; g.ldc = ldF;
       g.mode = et::EPI_GELU_BWD; g.U = b.u; g.C = c->du;
       ET_G(g);
     }
-    if (sel(t0 + 9)) {
-      Region r(c, PH_DW, t0 + 9);
-      ET_K(2, et::colsum(c->du, nullptr, v.F, nullptr, 0, nullptr, nullptr, c->grad[t0 + 9], cp, v.M, v.F, s));
-    }
+    if (sel(t0 + 9) && (rc = colsum_dw(c, t0 + 9, c->du, nullptr, ldF, R, v.F)) != ET_OK) return rc;
     if (sel(t0 + 8)) {
       Region r(c, PH_DW, t0 + 8);
-      ET_G(linear_dw(c, c->du, v.F, b.a2, v.D, c->grad[t0 + 8], v.M, v.F, v.D));
+      ET_G(linear_dw(c, c->du, ldF, b.a2, ldD, c->grad[t0 + 8], R, v.F, v.D));
     }
     if (pass(t0 + 8)) {
       Region r(c, PH_DY, t0 + 8);
-      et::GemmDesc g = linear_dx(c->du, W(t0 + 8), v.M, v.F, v.D);
+      et::GemmDesc g = linear_dx(c->du, W(t0 + 8), R, v.F, v.D);
+      g.lda = ldF; g.ldc = ldD;
       g.C = c->da;
       ET_G(g);
     }
-    if (sel(t0 + 7)) {
-      Region r(c, PH_DW, t0 + 7);
-      ET_K(2, et::colsum(c->da, nullptr, v.D, nullptr, 0, nullptr, nullptr, c->grad[t0 + 7], cp, v.M, v.D, s));
-    }
-    if (sel(t0 + 6)) {
-      Region r(c, PH_DW, t0 + 6);
-      ET_K(2, et::colsum(c->da, nullptr, v.D, b.h_mid, v.D, b.mean2, b.rstd2, c->grad[t0 + 6], cp, v.M, v.D, s));
-    }
-    if (pass(t0 + 6)) {  // LayerNorm input gradient joined by the residual branch
-      Region r(c, PH_DY, t0 + 6);
-      ET_K(1, et::layernorm_bwd_dx(c->da, b.h_mid, v.D, b.mean2, b.rstd2, W(t0 + 6), c->dh, c->dh, c->dh16, v.D, v.M,
-                                   v.D, s));
-    }
-    if (sel(t0 + 5)) {
-      Region r(c, PH_DW, t0 + 5);
-      ET_K(2, et::colsum(nullptr, c->dh, v.D, nullptr, 0, nullptr, nullptr, c->grad[t0 + 5], cp, v.M, v.D, s));
+    {  // LayerNorm input gradient joined by the residual branch
+      et::LayerNormBwd a;
+      a.d = c->da; a.d_stride = ldD; a.h = b.h_mid; a.h_stride = ldD; a.mean = b.mean2; a.rstd = b.rstd2; a.stat_stride = step;
+      a.gain = W(t0 + 6); a.skip = c->dh; a.dh = c->dh; a.dh16 = c->dh16; a.out_stride = ldD; a.rows = R; a.D = v.D;
+      if ((rc = layernorm_back(c, mask, jstar, t0 + 6, t0 + 5, a)) != ET_OK) return rc;
     }
     if (sel(t0 + 4)) {
       Region r(c, PH_DW, t0 + 4);
-      ET_G(linear_dw(c, c->dh16, v.D, b.o, v.D, c->grad[t0 + 4], v.M, v.D, v.D));
+      ET_G(linear_dw(c, c->dh16, ldD, b.o, ldD, c->grad[t0 + 4], R, v.D, v.D));
     }
     if (pass(t0 + 4)) {  // through proj.W, then through the attention core
       Region r(c, PH_DY, t0 + 4);
-      et::GemmDesc g = linear_dx(c->dh16, W(t0 + 4), v.M, v.D, v.D);
+      et::GemmDesc g = linear_dx(c->dh16, W(t0 + 4), R, v.D, v.D);
+      g.lda = ldD; g.ldc = ldD;
       g.C = c->dattn;
       ET_G(g);
-      int rc = vit_attention_backward(c, v, b);
-      if (rc != ET_OK) return rc;
+      if (few) {
+        KernelTimer kt(c, 6, 8.0 * v.B * v.H * (double)v.T * v.dh);
+        ET_K(1, et::attention_bwd_cls(b.qkv, b.o, c->dattn, b.lse, c->dqkv, v.B, v.T, v.H, v.dh, v.scale, s));
+      } else if ((rc = vit_attention_backward(c, v, b)) != ET_OK) {
+        return rc;
+      }
     }
-    if (sel(t0 + 3)) {
-      Region r(c, PH_DW, t0 + 3);
-      ET_K(2, et::colsum(c->dqkv, nullptr, 3 * v.D, nullptr, 0, nullptr, nullptr, c->grad[t0 + 3], cp, v.M, 3 * v.D, s));
-    }
+    if (sel(t0 + 3) && (rc = colsum_dw(c, t0 + 3, c->dqkv, nullptr, 3 * v.D, v.M, 3 * v.D)) != ET_OK) return rc;
     if (sel(t0 + 2)) {
       Region r(c, PH_DW, t0 + 2);
       ET_G(linear_dw(c, c->dqkv, 3 * v.D, b.a1, v.D, c->grad[t0 + 2], v.M, 3 * v.D, v.D));
@@ -441,18 +472,11 @@ int vit_backward(et_ctx* c, const void* x, const uint8_t* mask) {
       g.C = c->da;
       ET_G(g);
     }
-    if (sel(t0 + 1)) {
-      Region r(c, PH_DW, t0 + 1);
-      ET_K(2, et::colsum(c->da, nullptr, v.D, nullptr, 0, nullptr, nullptr, c->grad[t0 + 1], cp, v.M, v.D, s));
-    }
-    if (sel(t0 + 0)) {
-      Region r(c, PH_DW, t0 + 0);
-      ET_K(2, et::colsum(c->da, nullptr, v.D, b.h_in, v.D, b.mean1, b.rstd1, c->grad[t0 + 0], cp, v.M, v.D, s));
-    }
-    if (pass(t0 + 0)) {
-      Region r(c, PH_DY, t0 + 0);
-      ET_K(1, et::layernorm_bwd_dx(c->da, b.h_in, v.D, b.mean1, b.rstd1, W(t0 + 0), c->dh, c->dh, c->dh16, v.D, v.M,
-                                   v.D, s));
+    {
+      et::LayerNormBwd a;
+      a.d = c->da; a.d_stride = v.D; a.h = b.h_in; a.h_stride = v.D; a.mean = b.mean1; a.rstd = b.rstd1; a.gain = W(t0 + 0);
+      a.skip = c->dh; a.skip_period = step; a.dh = c->dh; a.dh16 = c->dh16; a.out_stride = v.D; a.rows = v.M; a.D = v.D;
+      if ((rc = layernorm_back(c, mask, jstar, t0 + 0, l > 0 ? t0 - 1 : -1, a)) != ET_OK) return rc;   // (fc2.b of the block before)
     }
   }
 
@@ -470,10 +494,7 @@ int vit_backward(et_ctx* c, const void* x, const uint8_t* mask) {
       Region r(c, PH_DY, 2);
       ET_K(1, et::gather_patch_rows(c->dh, c->de, v.B, v.T, v.D, s));
     }
-    if (sel(1)) {
-      Region r(c, PH_DW, 1);
-      ET_K(2, et::colsum(c->de, nullptr, v.D, nullptr, 0, nullptr, nullptr, c->grad[1], cp, v.B * (v.T - 1), v.D, s));
-    }
+    if (sel(1) && (rc = colsum_dw(c, 1, c->de, nullptr, v.D, v.B * (v.T - 1), v.D)) != ET_OK) return rc;
     if (sel(0)) {
       Region r(c, PH_DW, 0);
       ET_G(linear_dw(c, c->de, v.D, (const bf16*)x, v.P, c->grad[0], v.B * (v.T - 1), v.D, v.P));
@@ -493,10 +514,15 @@ int run_forward(et_ctx* c, const void* x, const int32_t* y, const uint8_t* mask 
 }
 int run_backward(et_ctx* c, const void* x, const uint8_t* mask) {
   c->cur_phase = PH_DW;
-  if (c->desc.kind == ET_RESNET) return resnet_backward(c, x, mask);
-  if (c->desc.kind == ET_VGG) return vgg_backward(c, x, mask);
-  if (c->desc.kind == ET_MOBILENET) return mobilenet_backward(c, x, mask);
-  return c->desc.kind == ET_MLP ? mlp_backward(c, x, mask) : vit_backward(c, x, mask);
+  c->sum_jobs.clear();      // (a pass that ended early leaves nothing behind)
+  c->sum_tensors.clear();
+  c->sum_used = 0;
+  int rc;
+  if (c->desc.kind == ET_RESNET) rc = resnet_backward(c, x, mask);
+  else if (c->desc.kind == ET_VGG) rc = vgg_backward(c, x, mask);
+  else if (c->desc.kind == ET_MOBILENET) rc = mobilenet_backward(c, x, mask);
+  else rc = c->desc.kind == ET_MLP ? mlp_backward(c, x, mask) : vit_backward(c, x, mask);
+  return rc == ET_OK ? sums_finish(c) : rc;
 }
 
 int run_update(et_ctx* c, const uint8_t* mask, const et_opt* opt, bool dry) {
@@ -942,11 +968,15 @@ int et_profile(et_ctx* c, const void* x_dev, const int32_t* y_dev, int32_t warmu
       ET_HIP(hipEventElapsedTime(&ms, sc.e0, sc.e1));
       double ns = (double)ms * 1e6;
       ns -= std::min(overhead, 0.5 * ns);
-      if (sc.phase == PH_FWD) sf += ns;
-      else if (sc.phase == PH_UPD) su += ns;
-      else if (sc.phase == PH_DW && sc.tensor2 >= 0) { sdw[sc.tensor] += 0.5 * ns; sdw[sc.tensor2] += 0.5 * ns; }
-      else if (sc.phase == PH_DW) sdw[sc.tensor] += ns;
-      else sdy[sc.tensor] += ns;
+      double weights = 0.0;
+      for (const Share& h : sc.shares) weights += h.weight;
+      for (const Share& h : sc.shares) {
+        const double part = ns * h.weight / weights;
+        if (h.phase == PH_FWD) sf += part;
+        else if (h.phase == PH_UPD) su += part;
+        else if (h.phase == PH_DW) sdw[h.tensor] += part;
+        else sdy[h.tensor] += part;
+      }
     }
     fwd[0].push_back(sf);
     upd[0].push_back(su);

@@ -156,7 +156,7 @@ extern "C" int et_debug_stem(int op, const void* x, const void* w_or_d, float* o
 extern "C" size_t et_debug_depthwise3x3_ws_floats(int batch, int H, int W, int C, int stride) {
   if (batch < 1 || H < 1 || W < 1 || C < 8 || (C & 7) || (stride != 1 && stride != 2)) return 0;
   const int R = et::depthwise3x3_dw_rows(batch, H, W, C, stride);
-  return (size_t)R * C * 9 + et::colsum_partial_elems(R, C * 9) + 64;
+  return (size_t)R * C * 9 + 64;
 }
 
 extern "C" int et_debug_depthwise3x3(int op, const void* a, const void* b, const void* gain, const void* shift, void* out0,
@@ -172,8 +172,9 @@ extern "C" int et_debug_depthwise3x3(int op, const void* a, const void* b, const
     if (!ws || et_debug_depthwise3x3_ws_floats(batch, H, W, C, stride) == 0) return ET_EINVAL;
     const int R = et::depthwise3x3_dw_rows(batch, H, W, C, stride);
     e = et::depthwise3x3_dw((P)a, (P)b, ws, batch, H, W, C, stride, s);
-    if (e == hipSuccess)
-      e = et::colsum(nullptr, ws, C * 9, nullptr, 0, nullptr, nullptr, (float*)out0, ws + (size_t)R * C * 9, R, C * 9, s);
+    et::SumJob job = {ws, (float*)out0, R, C * 9, 0};
+    int launches;
+    if (e == hipSuccess) e = et::sum_finish(&job, 1, s, &launches);
   } else {
     return ET_EINVAL;
   }

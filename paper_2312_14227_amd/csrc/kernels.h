@@ -106,16 +106,44 @@ hipError_t gemm_f32(const GemmF32Desc& d, hipStream_t s);
 // LayerNorm forward over rows of an fp32 matrix; in_stride = elements between consecutive rows
 hipError_t layernorm_fwd(const float* h, long long in_stride, const bf16* gain, const bf16* shift, float eps,
                          bf16* out, float* mean, float* rstd, int rows, int D, hipStream_t s);
-// LayerNorm input gradient: dh = skip + LN'(d); writes fp32 and a bf16 copy.  skip may be null.
-// out_stride lets the result be scattered (final LayerNorm on CLS rows); skip uses out_stride too.
-hipError_t layernorm_bwd_dx(const bf16* d, const float* h, long long in_stride, const float* mean, const float* rstd,
-                            const bf16* gain, const float* skip, float* dh, bf16* dh_bf16, long long out_stride,
-                            int rows, int D, hipStream_t s);
-// column sums over rows: out[c] = sum_r d[r][c] * (h ? (h[r][c]-mean[r])*rstd[r] : 1)
-//   d is bf16 (d_f32 == nullptr) or fp32; two deterministic stages through `partials`
-hipError_t colsum(const bf16* d, const float* d_f32, long long d_stride, const float* h, long long h_stride,
-                  const float* mean, const float* rstd, float* out, float* partials, int rows, int cols,
-                  hipStream_t s);
+// LayerNorm backward over `rows` rows of D elements: dh = skip + LN'(d), in fp32 and bf16; and, where a part_* pointer is given
+// (D <= LAYERNORM_SUMS_MAX_D), layernorm_bwd_parts(rows) rows of D partial column sums of
+//   d * xhat (gain gradient), d (shift gradient), dh (gradient of the bias added in front of the LayerNorm's input).
+// Strides in elements between consecutive rows: d, h, the statistics, and dh / dh16 / skip; skip may be null, and is
+// added only to every skip_period-th row if that is above 1.
+struct LayerNormBwd {
+  const bf16* d = nullptr;
+  const float *h = nullptr, *mean = nullptr, *rstd = nullptr;
+  const bf16* gain = nullptr;
+  const float* skip = nullptr;
+  float* dh = nullptr;
+  bf16* dh16 = nullptr;
+  float *part_gain = nullptr, *part_shift = nullptr, *part_bias = nullptr;
+  long long d_stride = 0, h_stride = 0, stat_stride = 1, out_stride = 0;
+  int rows = 0, D = 0, skip_period = 1;
+};
+constexpr int LAYERNORM_SUMS_MAX_D = 2048;
+int layernorm_bwd_parts(int rows);
+hipError_t layernorm_bwd(const LayerNormBwd& a, hipStream_t s);
+
+// Column sums over rows come in two steps.  A first kernel leaves partial sums, colsum_parts(rows, cols) rows of `cols`
+// floats (colsum_partial_elems in all); sum_finish adds the partial rows of any number of such jobs in one launch, in a
+// fixed order.
+//   colsum_part: sum_r d[r][c] * (h ? (h[r][c]-mean[r])*rstd[r] : 1);  d is bf16 (d_f32 == nullptr) or fp32
+//   colsum_pair_part: sum_r d[r][c] (part_sum) and sum_r d[r][c] * z[r][c] (part_mul), either may be null; z bf16, or fp32
+//   when z_f32 is given; with gain also dout[r][c] = d[r][c] * gain[c], all from one read of d
+struct SumJob {
+  const float* part;   // [rows][cols], 16-byte aligned
+  float* out;          // [cols]
+  int rows, cols;      // cols a multiple of 4
+  int block0;          // filled in by sum_finish
+};
+hipError_t colsum_part(const bf16* d, const float* d_f32, long long d_stride, const float* h, long long h_stride, const float* mean,
+                       const float* rstd, long long stat_stride, float* part, int rows, int cols, hipStream_t s);
+hipError_t colsum_pair_part(const bf16* d, const bf16* z, const float* z_f32, const bf16* gain, bf16* dout, float* part_sum, float* part_mul,
+                            int rows, int cols, hipStream_t s);
+hipError_t sum_finish(SumJob* jobs, int n, hipStream_t s, int* launches);
+int colsum_parts(int rows, int cols);
 size_t colsum_partial_elems(int rows, int cols);
 // sum over the batch: out[t][c] = sum_b d[b][t][c]   (t < T_out; fp32 in/out)
 hipError_t batchsum(const float* d, float* out, int B, long long batch_stride, int n, hipStream_t s);
@@ -136,6 +164,9 @@ hipError_t attention_fwd(const bf16* qkv, bf16* out, float* lse, int B, int T, i
                          hipStream_t s);
 hipError_t attention_bwd(const bf16* qkv, const bf16* out, const bf16* dout, const float* lse, bf16* dqkv, int B, int T, int H,
                          int head_dim, float scale, hipStream_t s);
+// backward when only the first token's row of dout is read (the others are zeros that need not be stored): dqkv complete
+hipError_t attention_bwd_cls(const bf16* qkv, const bf16* out, const bf16* dout, const float* lse, bf16* dqkv, int B, int T, int H,
+                             int head_dim, float scale, hipStream_t s);
 // the same for sequences of any length, streamed (attention_fwd / _bwd choose)
 hipError_t attention_long_fwd(const bf16* qkv, bf16* out, float* lse, int B, int T, int H, float scale, hipStream_t s);
 hipError_t attention_long_bwd(const bf16* qkv, const bf16* out, const bf16* dout, const float* lse, bf16* dqkv, int B, int T, int H,
@@ -174,8 +205,6 @@ hipError_t col2im(const void* dcols, bool dcols_f32, const bf16* add, const bf16
 // z1 is bf16, or fp32 when z1_f32 is given; rows x C, C % 8 == 0
 hipError_t affine_act(const bf16* z1, const float* z1_f32, const bf16* g1, const bf16* b1, const bf16* z2,
                       const bf16* g2, const bf16* b2, bool relu, bf16* out, long long rows, int C, hipStream_t s);
-// out[r][c] = d[r][c] * gain[c]
-hipError_t scale_cols(const bf16* d, const bf16* gain, bf16* out, long long rows, int C, hipStream_t s);
 // out = (a + b) * (mask > 0), n elements (n % 8 == 0); b nullable; out may alias a or b
 hipError_t add_mask(const bf16* a, const bf16* b, const bf16* mask, bf16* out, long long n, hipStream_t s,
                     float mask_hi = __builtin_inff());
@@ -220,13 +249,6 @@ hipError_t strip_rows(const float* in, float* out, int rows, int K, int Kc, hipS
 hipError_t stem_pad_image(const bf16* x, bf16* out, int B, int H, int W, int C, int Hp, int Wp, hipStream_t s);
 hipError_t stem_pack_weight(const bf16* w, bf16* out, int O, int C, hipStream_t s);
 hipError_t stem_unpack_dw(const float* in, float* out, int O, int C, hipStream_t s);
-// out[c] = sum_r d[r][c] * z[r][c]   (z bf16, or fp32 when z_f32 is given); same two stages as colsum
-hipError_t colsum_mul(const bf16* d, const bf16* z, const float* z_f32, float* out, float* partials, int rows, int cols,
-                      hipStream_t s);
-// both sums from one read of d: out_sum[c] = sum_r d[r][c], out_mul[c] = sum_r d[r][c] * z[r][c], each identical to
-// what colsum / colsum_mul give; partials must hold 2 * colsum_partial_elems(rows, cols) floats
-hipError_t colsum_pair(const bf16* d, const bf16* z, const float* z_f32, float* out_sum, float* out_mul, float* partials,
-                       int rows, int cols, hipStream_t s);
 
 // ------------------------------------------------------------------------------------------
 // importance (Eq. 2) and masked optimizer update over a table of tensors

@@ -72,10 +72,12 @@ int build_mobilenet(et_ctx* c) {
   add("head.W", (size_t)C * d.last); add("head.b", C);
 
   // ---- workspace
-  size_t max_act = 0, max_cs = 0, pe = 0, max_dwp = 64;
+  size_t max_act = 0, max_cs = 0, all_cs = 0, pe = 0, max_dwp = 64;
   auto act = [&](size_t rows, size_t ch) {
     max_act = std::max(max_act, rows * ch);
-    max_cs = std::max(max_cs, 2 * et::colsum_partial_elems((int)rows, (int)ch));   // (gain and shift sums in one launch)
+    const size_t pair = 2 * sum_elems(et::colsum_parts((int)rows, (int)ch), ch);   // gain and shift sums from one kernel
+    max_cs = std::max(max_cs, pair);
+    all_cs += pair;
   };
   auto wgrad = [&](int out, int in, size_t rows) {
     pe = std::max(pe, et::gemm_bf16_partial_elems(out, in, split_for(out, in, (int)rows)));
@@ -109,7 +111,8 @@ int build_mobilenet(et_ctx* c) {
     wgrad(b.Cout, b.hid, Mo);
     const int R = et::depthwise3x3_dw_rows(d.batch, b.H, b.W, b.hid, b.stride);
     max_dwp = std::max(max_dwp, (size_t)R * b.hid * 9);
-    max_cs = std::max(max_cs, et::colsum_partial_elems(R, b.hid * 9));
+    max_cs = std::max(max_cs, sum_elems(R, (size_t)b.hid * 9));
+    all_cs += sum_elems(R, (size_t)b.hid * 9);
   }
   {
     ConvUnit& u = c->mlast;
@@ -125,14 +128,13 @@ int build_mobilenet(et_ctx* c) {
   reserve(c, &c->dl16, b16 * B * C);
   reserve(c, &c->loss, 256 + sizeof(float) * (size_t)d.batch);
   reserve(c, &c->dz, b16 * B * d.last);
-  max_cs = std::max(max_cs, et::colsum_partial_elems((int)B, C));
+  const size_t hb = sum_elems(et::colsum_parts((int)B, C), C);
   wgrad(C, d.last, B);
   for (int i = 0; i < 3; i++) reserve(c, &c->rd[i], b16 * max_act);
   reserve(c, &c->rdsum, b16 * max_act);
-  reserve(c, &c->dw_part, f32 * max_dwp);
   c->gemm_partial_elems = pe;
   reserve(c, &c->gemm_partials, f32 * std::max<size_t>(pe, 64));
-  reserve(c, &c->colsum_partials, f32 * std::max<size_t>(max_cs, 64));
+  reserve_sums(c, all_cs + hb, std::max(max_cs, hb));
   // every matrix dimension and element count below is handled as int by the GEMM
   if (max_act > 0x7fffffffull || rows_of(c, c->stem) * c->stem.Kc > 0x7fffffffull || max_dwp > 0x7fffffffull) return ET_EINVAL;
   return ET_OK;
@@ -199,7 +201,6 @@ int mobilenet_backward(et_ctx* c, const void* x, const uint8_t* mask) {
   auto sel = [&](int j) { return mask[j] != 0; };
   auto pass = [&](int j) { return j > jstar; };
   hipStream_t s = c->stream;
-  float* cp = c->colsum_partials;
 
   auto affine_back = [&](int tg, const bf16* dsrc, const bf16* z, bf16* dout, long long M, int C) -> int {
     return et_exec::affine_back(c, mask, jstar, tg, dsrc, z, nullptr, dout, M, C);
@@ -210,10 +211,7 @@ int mobilenet_backward(et_ctx* c, const void* x, const uint8_t* mask) {
   const ConvUnit& ul = c->mlast;
   const int tl = ul.t, Cl = ul.Cout, C = md.classes, HWl = ul.Ho * ul.Wo;
   const long long Ml = (long long)rows_of(c, ul);
-  if (sel(tl + 4)) {
-    Region r(c, PH_DW, tl + 4);
-    ET_K(2, et::colsum(nullptr, c->dlogits, C, nullptr, 0, nullptr, nullptr, c->grad[tl + 4], cp, B, C, s));
-  }
+  if (sel(tl + 4) && (rc = colsum_dw(c, tl + 4, nullptr, c->dlogits, C, B, C)) != ET_OK) return rc;
   if (sel(tl + 3)) {
     Region r(c, PH_DW, tl + 3);
     ET_G(linear_dw(c, c->dl16, C, c->zc, Cl, c->grad[tl + 3], B, C, Cl));
@@ -268,10 +266,11 @@ int mobilenet_backward(et_ctx* c, const void* x, const uint8_t* mask) {
     if (jstar > td) return ET_OK;
     const bf16* dw_in = b.expand ? b.y_exp : b.x;
     if (sel(td)) {
-      Region r(c, PH_DW, td);
       const int R = et::depthwise3x3_dw_rows(B, b.H, b.W, b.hid, b.stride);
-      ET_KB(1, 2.0 * (Mo + Mi) * b.hid + 4.0 * R * b.hid * 9, et::depthwise3x3_dw(c->rd[0], dw_in, c->dw_part, B, b.H, b.W, b.hid, b.stride, s));
-      ET_KB(2, 4.0 * R * b.hid * 9, et::colsum(nullptr, c->dw_part, b.hid * 9, nullptr, 0, nullptr, nullptr, c->grad[td], cp, R, b.hid * 9, s));
+      if ((rc = sums_room(c, sum_elems(R, (size_t)b.hid * 9))) != ET_OK) return rc;
+      Region r(c, PH_DW, td);
+      float* part = sum_job(c, td, R, b.hid * 9);
+      ET_KB(1, 2.0 * (Mo + Mi) * b.hid + 4.0 * R * b.hid * 9, et::depthwise3x3_dw(c->rd[0], dw_in, part, B, b.H, b.W, b.hid, b.stride, s));
     }
     if (!pass(td)) return ET_OK;
     if (!b.expand) {

@@ -73,10 +73,12 @@ int build_resnet(et_ctx* c) {
   add("head.W", (size_t)C * Cf); add("head.b", C);
 
   // ---- workspace
-  size_t max_act = 0, max_cols = 0, max_cs = 0, pe = 0, max_flip = 8, dcols_b = 16;
+  size_t max_act = 0, max_cols = 0, max_cs = 0, all_cs = 0, pe = 0, max_flip = 8, dcols_b = 16;
   auto act = [&](size_t rows, size_t ch) {
     max_act = std::max(max_act, rows * ch);
-    max_cs = std::max(max_cs, 2 * et::colsum_partial_elems((int)rows, (int)ch));   // (gain and shift sums in one launch)
+    const size_t pair = 2 * sum_elems(et::colsum_parts((int)rows, (int)ch), ch);   // gain and shift sums from one kernel
+    max_cs = std::max(max_cs, pair);
+    all_cs += pair;
   };
   auto wg = [&](const ConvUnit& u) {
     const int M = (int)rows_of(c, u);
@@ -134,7 +136,6 @@ int build_resnet(et_ctx* c) {
   reserve(c, &c->dl16, b16 * B * C8);
   reserve(c, &c->loss, 256 + sizeof(float) * (size_t)d.batch);
   reserve(c, &c->dz, b16 * B * Cf);
-  max_cs = std::max(max_cs, et::colsum_partial_elems((int)B, C));
   pe = std::max(pe, et::gemm_bf16_partial_elems(C, Cf, split_for(C, Cf, (int)B)));
   for (int i = 0; i < 2; i++) reserve(c, &c->rd[i], b16 * max_act);
   reserve(c, &c->rdsum, b16 * max_act);
@@ -143,7 +144,8 @@ int build_resnet(et_ctx* c) {
   reserve(c, &c->wflip, b16 * max_flip);
   c->gemm_partial_elems = pe;
   reserve(c, &c->gemm_partials, f32 * std::max<size_t>(pe, 64));
-  reserve(c, &c->colsum_partials, f32 * std::max<size_t>(max_cs, 64));
+  const size_t hb = sum_elems(et::colsum_parts((int)B, C), C);
+  reserve_sums(c, all_cs + hb, std::max(max_cs, hb));
   // every matrix dimension and element count below is handled as int by the GEMM
   if (max_act > 0x7fffffffull || max_cols > 0x7fffffffull || rows_of(c, c->stem) * c->stem.Kc > 0x7fffffffull)
     return ET_EINVAL;
@@ -223,16 +225,12 @@ int resnet_backward(et_ctx* c, const void* x, const uint8_t* mask) {
   auto sel = [&](int j) { return mask[j] != 0; };
   auto pass = [&](int j) { return j > jstar; };
   hipStream_t s = c->stream;
-  float* cp = c->colsum_partials;
   int rc;
 
   // ---- head
   const ResBlockBufs& last = c->rblk.back();
   const int Cf = last.c3.Cout, C = md.classes, C8 = round8(md.classes), HWf = last.c3.Ho * last.c3.Wo;
-  if (sel(N - 1)) {
-    Region r(c, PH_DW, N - 1);
-    ET_K(2, et::colsum(nullptr, c->dlogits, C, nullptr, 0, nullptr, nullptr, c->grad[N - 1], cp, B, C, s));
-  }
+  if (sel(N - 1) && (rc = colsum_dw(c, N - 1, nullptr, c->dlogits, C, B, C)) != ET_OK) return rc;
   if (sel(N - 2)) {
     Region r(c, PH_DW, N - 2);
     ET_G(linear_dw(c, c->dl16, C8, c->zc, Cf, c->grad[N - 2], B, C, Cf));

@@ -74,7 +74,12 @@ int build_vgg(et_ctx* c) {
   }
 
   // ---- workspace
-  size_t max_act = 0, max_cols = 0, max_cs = 0, pe = 0, max_flip = 8, dcols_b = 16;
+  size_t max_act = 0, max_cols = 0, max_cs = 0, all_cs = 0, pe = 0, max_flip = 8, dcols_b = 16;
+  auto bias_sum = [&](size_t rows, int cols) {
+    const size_t n = sum_elems(et::colsum_parts((int)rows, cols), cols);
+    max_cs = std::max(max_cs, n);
+    all_cs += n;
+  };
   c->vpool.assign(d.n_stages, nullptr);
   c->varg.assign(d.n_stages, nullptr);
   for (size_t i = 0; i < c->vconv.size(); i++) {
@@ -86,7 +91,7 @@ int build_vgg(et_ctx* c) {
     max_act = std::max(max_act, std::max(M * u.Cout, M * round8(u.Cin)));
     if (!implicit_dw(c, u) || !implicit_dy(u)) max_cols = std::max(max_cols, M * u.Kc);
     if (i > 0 && !implicit_dy(u)) dcols_b = std::max(dcols_b, dcols_bytes(c, u));   // conv0 passes nothing on
-    max_cs = std::max(max_cs, et::colsum_partial_elems((int)M, u.Cout));
+    bias_sum(M, u.Cout);
     pe = std::max(pe, std::max(conv_dw_partials(c, u), conv_split_partials(c, u)));
     const bool last_of_stage = i + 1 == c->vconv.size() || c->vstage[i + 1] != c->vstage[i];
     if (last_of_stage) {
@@ -112,7 +117,7 @@ int build_vgg(et_ctx* c) {
   reserve(c, &c->fc_z32, f32 * max_fc);
   for (int j = 0; j < n_fc; j++) {
     max_act = std::max(max_act, B * (size_t)std::max(c->vdims[j], c->vdims[j + 1]));
-    max_cs = std::max(max_cs, et::colsum_partial_elems((int)B, c->vdims[j + 1]));
+    bias_sum(B, c->vdims[j + 1]);
     pe = std::max(pe, et::gemm_bf16_partial_elems(c->vdims[j + 1], c->vdims[j], split_for(c->vdims[j + 1], c->vdims[j], (int)B)));
   }
   const int C = d.classes;
@@ -125,7 +130,7 @@ int build_vgg(et_ctx* c) {
   reserve(c, &c->wflip, b16 * max_flip);
   c->gemm_partial_elems = pe;
   reserve(c, &c->gemm_partials, f32 * std::max<size_t>(pe, 64));
-  reserve(c, &c->colsum_partials, f32 * std::max<size_t>(max_cs, 64));
+  reserve_sums(c, all_cs, max_cs);
   // every matrix dimension and element count below is handled as int by the GEMM
   if (max_act > 0x7fffffffull || max_cols > 0x7fffffffull) return ET_EINVAL;
   return ET_OK;
@@ -192,7 +197,6 @@ int vgg_backward(et_ctx* c, const void* x, const uint8_t* mask) {
   auto sel = [&](int j) { return mask[j] != 0; };
   auto pass = [&](int j) { return j > jstar; };
   hipStream_t s = c->stream;
-  float* cp = c->colsum_partials;
   const int n_fc = (int)c->vdims.size() - 1, n_conv = (int)c->vconv.size(), t_fc = 2 * n_conv;
   int rc;
 
@@ -207,11 +211,7 @@ int vgg_backward(et_ctx* c, const void* x, const uint8_t* mask) {
     const bool last = j == n_fc - 1;
     const bf16* dmat = last ? c->dl16 : dcur;   // the matrix products read the bf16 copy of the logit gradient
     if (jstar > tw + 1) return ET_OK;
-    if (sel(tw + 1)) {
-      Region r(c, PH_DW, tw + 1);
-      if (last) ET_K(2, et::colsum(nullptr, c->dlogits, out, nullptr, 0, nullptr, nullptr, c->grad[tw + 1], cp, B, out, s));
-      else ET_K(2, et::colsum(dcur, nullptr, out, nullptr, 0, nullptr, nullptr, c->grad[tw + 1], cp, B, out, s));
-    }
+    if (sel(tw + 1) && (rc = colsum_dw(c, tw + 1, last ? nullptr : dcur, last ? c->dlogits : nullptr, out, B, out)) != ET_OK) return rc;
     if (sel(tw)) {
       Region r(c, PH_DW, tw);
       ET_G(linear_dw(c, dmat, out, c->vact[j], in, c->grad[tw], B, out, in));
@@ -240,8 +240,8 @@ int vgg_backward(et_ctx* c, const void* x, const uint8_t* mask) {
     if (jstar > t + 1) return ET_OK;
     const long long M = (long long)rows_of(c, u);
     if (sel(t + 1)) {
-      Region r(c, PH_DW, t + 1);
-      ET_KB(2, 2.0 * M * u.Cout, et::colsum(dcur, nullptr, u.Cout, nullptr, 0, nullptr, nullptr, c->grad[t + 1], cp, (int)M, u.Cout, s));
+      KernelTimer kt(c, 7, 2.0 * M * u.Cout);
+      if ((rc = colsum_dw(c, t + 1, dcur, nullptr, u.Cout, (int)M, u.Cout)) != ET_OK) return rc;
     }
     if (sel(t)) {
       Region r(c, PH_DW, t);
