@@ -228,8 +228,8 @@ hipError_t maxpool2x2_bwd(const bf16* d, const uint8_t* arg, const bf16* y, bf16
 // 3x3 depthwise convolution, zero padding 1, stride 1 or 2, NHWC, C % 8 == 0, weights [C][9] (bf16):
 //   fwd: z (nullable: not kept) = the convolution, rounded; y = clamp(z * gain + shift, 0, 6)
 //   dx:  out[B][H][W][C] = (adjoint applied to d [B][Ho][Wo][C] + add) * (0 < relu6_y < 6); add, relu6_y nullable
-//   dw:  part[R][C * 9] fp32 partial sums over R = depthwise3x3_dw_rows(..) interleaved pixel subsets; their
-//        column sum (colsum over R rows) is the gradient [C][9]
+//   dw:  part[R][C * 9] fp32 partial sums of R = depthwise3x3_dw_rows(..) workgroups; their column sum (sum_finish) is the
+//        gradient [C][9]
 hipError_t depthwise3x3_fwd(const bf16* x, const bf16* w, const bf16* gain, const bf16* shift, bf16* z, bf16* y, int B, int H,
                             int W, int C, int stride, hipStream_t s);
 hipError_t depthwise3x3_dx(const bf16* d, const bf16* w, const bf16* add, const bf16* relu6_y, bf16* out, int B, int H, int W,
