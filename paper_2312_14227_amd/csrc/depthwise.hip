@@ -147,15 +147,14 @@ __global__ __launch_bounds__(256) void depthwise_strip_kernel(const bf16* __rest
       if (MODE == 1 && p0) na = *(const bf16x4*)(p0 + at + step_at);
       if (MODE == 1 && p1) nk = *(const bf16x4*)(p1 + at + step_at);
     }
-    F4 acc = {};
+    F4 acc = {};   // taps of w in ascending order in either direction
 #pragma unroll
-    for (int k = 0; k < 3; k++)
+    for (int t = 0; t < 9; t++) {
+      const int at_w = MODE == 1 ? 8 - t : t, ky = at_w / 3, k = at_w % 3;
+      const F4& px = win[ky == 0 ? top : ky == 1 ? mid : bot][k];
 #pragma unroll
-      for (int j = 0; j < 4; j++) {
-        acc.v[j] = fmaf(win[top][k].v[j], wt[k].v[j], acc.v[j]);
-        acc.v[j] = fmaf(win[mid][k].v[j], wt[3 + k].v[j], acc.v[j]);
-        acc.v[j] = fmaf(win[bot][k].v[j], wt[6 + k].v[j], acc.v[j]);
-      }
+      for (int j = 0; j < 4; j++) acc.v[j] = fmaf(px.v[j], wt[at_w].v[j], acc.v[j]);
+    }
     if (MODE == 0) {
       bf16x4 z4, r;
 #pragma unroll
@@ -203,9 +202,9 @@ __global__ __launch_bounds__(256) void depthwise_dx2_kernel(const bf16* __restri
 #pragma unroll
     for (int j = 0; j < 4; j++) {
       acc[0].v[j] = t0.v[j] * wt[4].v[j];
-      acc[1].v[j] = t0.v[j] * wt[5].v[j] + t1.v[j] * wt[3].v[j];
-      acc[2].v[j] = t0.v[j] * wt[7].v[j] + b0.v[j] * wt[1].v[j];
-      acc[3].v[j] = (t0.v[j] * wt[8].v[j] + t1.v[j] * wt[6].v[j]) + (b0.v[j] * wt[2].v[j] + b1.v[j] * wt[0].v[j]);
+      acc[1].v[j] = fmaf(t0.v[j], wt[5].v[j], t1.v[j] * wt[3].v[j]);
+      acc[2].v[j] = fmaf(t0.v[j], wt[7].v[j], b0.v[j] * wt[1].v[j]);
+      acc[3].v[j] = fmaf(t0.v[j], wt[8].v[j], fmaf(t1.v[j], wt[6].v[j], fmaf(b0.v[j], wt[2].v[j], b1.v[j] * wt[0].v[j])));
     }
 #pragma unroll
     for (int q = 0; q < 4; q++)
