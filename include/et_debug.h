@@ -84,6 +84,21 @@ size_t et_debug_depthwise3x3_ws_floats(int batch, int H, int W, int C, int strid
 int et_debug_depthwise3x3(int op, const void* a, const void* b, const void* gain, const void* shift, void* out0, void* out1,
                           float* ws, int batch, int H, int W, int C, int stride, void* stream);
 
+/* Mirrored weights out[c][8 - tap][o] = w[o][tap][c] of n convolutions in one launch: w[i] bf16 [O[i]][9][C[i]], out[i] bf16
+ * [C[i]][9][O[i]], O and C multiples of 8; host arrays of device pointers, 16-byte aligned.  Returns 0, -1, -3 as above. */
+int et_debug_flip3x3(const void* const* w, void* const* out, const int* O, const int* C, int n, void* stream);
+
+/* Backward of a per-channel affine with its activation's mask, one pass over the gradient (every folded BatchNorm of a
+ * convolutional chain): m = (d + add) where open, else 0, rounded to bf16; dmid = m, dout = m * gain, sum[c] = column sums of m,
+ * mul[c] = column sums of m * z.  Open: everywhere; where 0 < y < hi (y given); where 0 < clamp(z * gain + shift, 0, hi) < hi
+ * as rounded to bf16 (mask_from_z).  All [rows][cols] bf16, cols a multiple of 8; z32 = z in fp32 instead (then no add, y, mask);
+ * add, y, z, dmid, dout, sum, mul nullable; ws = device scratch of et_debug_affine_back_ws_floats(..) floats.  Device
+ * pointers, 16-byte aligned.  Returns 0, -1, -3 as above. */
+size_t et_debug_affine_back_ws_floats(int rows, int cols);
+int et_debug_affine_back(const void* d, const void* add, const void* y, const void* z, const float* z32, const void* gain,
+                         const void* shift, void* dmid, void* dout, float* sum, float* mul, float* ws, float hi, int mask_from_z,
+                         int rows, int cols, void* stream);
+
 /* Fused attention core of one layer for sequences of at most 224 tokens and head size 64 (Section 5.4 counts the
  * attention operations among the layers without weights; their backward time is charged to the tensor whose
  * gradient passing needs them).  qkv bf16 [B][T][3 D], D = 64 H, holding Q | K | V of every token; scale = 1/sqrt(64).

@@ -56,6 +56,7 @@ struct ConvUnit {
   bf16* cols;                 // im2col matrix [B*Ho*Wo][Kc] (null: the input itself is the matrix)
   bf16* z;                    // convolution output [B*Ho*Wo][Cout]
   bf16* y;                    // after affine (+ReLU); for the last unit of a block: the block output
+  bf16* wflip;                // mirrored weight [Cin][3][3][Cout] of a unit whose dy() is an implicit convolution
 };
 struct ResBlockBufs {
   int t;
@@ -134,7 +135,6 @@ struct et_ctx {
   std::vector<uint8_t*> varg;
   std::vector<bf16*> vact;
   std::vector<int> vdims;           // vdims[j] -> vdims[j+1]: linear layer j
-  bf16* wflip = nullptr;            // mirrored weight of the convolution whose dy() is running
   float* fc_z32 = nullptr;          // reduced sum of a linear layer's split forward product
 
   // inverted-residual network: blocks; the stem and the last convolution are ConvUnits (`stem`, `mlast`)

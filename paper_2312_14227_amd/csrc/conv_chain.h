@@ -18,30 +18,54 @@ namespace et_exec {
     ET_K(n, expr);                         \
   } while (0)
 
+// Gradient that reaches an affine, before the activation's mask and the shortcut's share have been applied: ((d + add) where
+// 0 < y < hi); `tensor` is the one whose dy() handed it over.  Whoever else reads the finished gradient finds it in `dmid`.
+// from_z: the activation is the affine's own, its openness follows from z where z is stored.
+struct Incoming {
+  const bf16 *d = nullptr, *add = nullptr, *y = nullptr;
+  bf16* dmid = nullptr;
+  float hi = __builtin_inff();
+  int tensor = -1;
+  bool from_z = false;
+};
+
 // The per-channel pieces of a folded-BN affine y = z * gain + shift (tensors tg = gain, tg + 1 = shift) on the
 // gradient d [M][C] of y: dw(shift) = column sum of d, dw(gain) = column sum of d * z (z bf16, or float32 z32),
 // dy(gain): dout = d * gain.  One kernel reads d once for whichever of the three are wanted (the order of a sum does not
-// depend on the others); the profile divides its time by the bytes each of them adds.  dy_used = false skips dy(gain) although
-// the chain passes the tensor: a projection shortcut's scaled gradient has no reader when its weight is not selected
-// and nothing in front of the block is (the time model then charges a few microseconds that are not spent).
-inline int affine_back(et_ctx* c, const uint8_t* mask, int jstar, int tg, const bf16* d, const bf16* z, const float* z32,
-                       bf16* dout, long long M, int C, bool dy_used = true) {
+// depend on the others), and finishes d first; the profile divides its time by the bytes each of them adds.  dy_used = false
+// skips dy(gain) although the chain passes the tensor: a projection shortcut's scaled gradient has no reader when its weight
+// is not selected and nothing in front of the block is (the time model then charges a few microseconds that are not spent).
+// *done (if given) tells whether the kernel ran, i.e. whether in.dmid is written.
+inline int affine_back(et_ctx* c, const uint8_t* mask, int jstar, int tg, const Incoming& in, const bf16* z, const float* z32,
+                       bf16* dout, long long M, int C, bool dy_used = true, bool* done = nullptr) {
+  if (done) *done = false;
   const double zb = z32 ? 4.0 : 2.0;
   const bool scaled = tg > jstar && dy_used;
   if (!mask[tg] && !mask[tg + 1] && !scaled) return ET_OK;
-  const int parts = et::colsum_parts((int)M, C);
+  const int parts = et::affine_back_parts((int)M, C);
   const int rc = sums_room(c, 2 * sum_elems(parts, C));
   if (rc != ET_OK) return rc;
-  Share shares[3];
+  et::AffineBack a;
+  a.d = in.d; a.add = in.add; a.dmid = in.dmid; a.hi = in.hi; a.rows = (int)M; a.cols = C;
+  a.mask_from_z = in.y && in.from_z && mask[tg];
+  a.y = a.mask_from_z ? nullptr : in.y;
+  a.z = mask[tg] ? z : nullptr; a.z32 = mask[tg] ? z32 : nullptr;
+  a.gain = (const bf16*)c->w[tg]; a.shift = (const bf16*)c->w[tg + 1];
+  Share shares[4];
   size_t n = 0;
   double bytes = 2.0;
   if (scaled) { shares[n++] = {PH_DY, tg, 4.0}; bytes += 2.0; }
   if (mask[tg + 1]) shares[n++] = {PH_DW, tg + 1, 0.5};
   if (mask[tg]) { shares[n++] = {PH_DW, tg, zb}; bytes += zb; }
-  float* part_sum = mask[tg + 1] ? sum_job(c, tg + 1, parts, C) : nullptr;
-  float* part_mul = mask[tg] ? sum_job(c, tg, parts, C) : nullptr;
-  Region r(c, scaled && n == 1 ? PH_DY : PH_DW, shares, n);
-  ET_KB(1, bytes * M * C, et::colsum_pair_part(d, z, z32, (const bf16*)c->w[tg], scaled ? dout : nullptr, part_sum, part_mul, (int)M, C, c->stream));
+  const double extra = (a.add ? 2.0 : 0.0) + (a.y ? 2.0 : 0.0) + (a.dmid ? 2.0 : 0.0);
+  const bool alone = scaled && n == 1;
+  if (extra > 0.0) shares[n++] = {PH_DY, in.tensor, extra};
+  a.dout = scaled ? dout : nullptr;
+  a.part_sum = mask[tg + 1] ? sum_job(c, tg + 1, parts, C) : nullptr;
+  a.part_mul = mask[tg] ? sum_job(c, tg, parts, C) : nullptr;
+  Region r(c, alone ? PH_DY : PH_DW, shares, n);
+  ET_KB(1, (bytes + extra) * M * C, et::affine_back_part(a, c->stream));
+  if (done) *done = true;
   return ET_OK;
 }
 
@@ -58,7 +82,7 @@ inline void init_unit(ConvUnit& u, int t, int H, int W, int Cin, int Cout, int k
   u.Ho = (H + 2 * pad - k) / stride + 1;
   u.Wo = (W + 2 * pad - k) / stride + 1;
   u.Kc = round8(k * k * Cin);
-  u.in = nullptr; u.cols = nullptr; u.z = nullptr; u.y = nullptr;
+  u.in = nullptr; u.cols = nullptr; u.z = nullptr; u.y = nullptr; u.wflip = nullptr;
 }
 
 inline size_t rows_of(const et_ctx* c, const ConvUnit& u) { return (size_t)c->desc.batch * u.Ho * u.Wo; }
@@ -160,11 +184,32 @@ inline int conv_dcols(et_ctx* c, const ConvUnit& u, const bf16* d, const bf16* W
 }
 
 
+// room for the mirrored weight of a unit
+inline void reserve_flip(et_ctx* c, ConvUnit& u) {
+  if (implicit_dy(u)) reserve(c, &u.wflip, sizeof(bf16) * (size_t)u.Cout * 9 * u.Cin);
+}
+// the mirrored weights of all units that this backward pass takes dy() of (the weights stand until its update)
+inline int mirror_weights(et_ctx* c, const std::vector<const ConvUnit*>& units, int jstar) {
+  std::vector<et::FlipJob> jobs;
+  std::vector<Share> shares;
+  for (const ConvUnit* u : units)
+    if (implicit_dy(*u) && u->t > jstar) {
+      jobs.push_back({(const bf16*)c->w[u->t], u->wflip, u->Cout, u->Cin, 0});
+      shares.push_back({PH_DY, u->t, (double)u->Cout * u->Cin});
+    }
+  if (jobs.empty()) return ET_OK;
+  Region r(c, PH_DY, shares.data(), shares.size());
+  int n = 0;
+  const hipError_t e = et::flip3x3(jobs.data(), (int)jobs.size(), c->stream, &n);
+  c->launches[PH_DY] += n;
+  if (e != hipSuccess) { c->hip_err = e; return ET_EHIP; }
+  return ET_OK;
+}
+
 // dy() of a 3x3 / stride 1 unit as an implicit GEMM: out = (convolution of d with the mirrored weight), times
-// the ReLU mask (relu_y > 0) if given; c->wflip receives the mirrored weight [Cin][3][3][Cout]
-inline int conv_dy_implicit(et_ctx* c, const ConvUnit& u, const bf16* d, const bf16* W, const bf16* relu_y, bf16* out) {
-  ET_K(1, et::flip3x3(W, c->wflip, u.Cout, u.Cin, c->stream));
-  et::GemmDesc g = linear_fwd(d, c->wflip, nullptr, (int)rows_of(c, u), u.Cin, 9 * u.Cout);
+// the ReLU mask (relu_y > 0) if given
+inline int conv_dy_implicit(et_ctx* c, const ConvUnit& u, const bf16* d, const bf16* relu_y, bf16* out) {
+  et::GemmDesc g = linear_fwd(d, u.wflip, nullptr, (int)rows_of(c, u), u.Cin, 9 * u.Cout);
   g.conv_h = u.H; g.conv_w = u.W; g.conv_c = u.Cout;
   g.C = out;
   if (relu_y) { g.mode = et::EPI_RELU_MASK; g.U = relu_y; }

@@ -182,6 +182,42 @@ extern "C" int et_debug_depthwise3x3(int op, const void* a, const void* b, const
   return e == hipSuccess ? ET_OK : ET_EHIP;
 }
 
+extern "C" int et_debug_flip3x3(const void* const* w, void* const* out, const int* O, const int* C, int n, void* stream) {
+  if (!w || !out || !O || !C || n < 1) return ET_EINVAL;
+  std::vector<et::FlipJob> jobs;
+  for (int i = 0; i < n; i++) jobs.push_back({(const et::bf16*)w[i], (et::bf16*)out[i], O[i], C[i], 0});
+  int launches;
+  const hipError_t e = et::flip3x3(jobs.data(), n, (hipStream_t)stream, &launches);
+  if (e == hipErrorInvalidValue) return ET_EINVAL;
+  return e == hipSuccess ? ET_OK : ET_EHIP;
+}
+
+extern "C" size_t et_debug_affine_back_ws_floats(int rows, int cols) {
+  if (rows < 1 || cols < 8 || (cols & 7)) return 0;
+  return 2 * (((size_t)et::affine_back_parts(rows, cols) * cols + 63) / 64 * 64);
+}
+
+extern "C" int et_debug_affine_back(const void* d, const void* add, const void* y, const void* z, const float* z32, const void* gain,
+                                    const void* shift, void* dmid, void* dout, float* sum, float* mul, float* ws, float hi,
+                                    int mask_from_z, int rows, int cols, void* stream) {
+  if (!et_debug_affine_back_ws_floats(rows, cols) || !ws) return ET_EINVAL;
+  typedef const et::bf16* P;
+  et::AffineBack a;
+  a.d = (P)d; a.add = (P)add; a.y = (P)y; a.z = (P)z; a.z32 = z32; a.gain = (P)gain; a.shift = (P)shift;
+  a.dmid = (et::bf16*)dmid; a.dout = (et::bf16*)dout; a.hi = hi; a.mask_from_z = mask_from_z != 0; a.rows = rows; a.cols = cols;
+  a.part_sum = sum ? ws : nullptr;
+  a.part_mul = mul ? ws + et_debug_affine_back_ws_floats(rows, cols) / 2 : nullptr;
+  hipError_t e = et::affine_back_part(a, (hipStream_t)stream);
+  et::SumJob jobs[2];
+  int n = 0, launches;
+  const int parts = et::affine_back_parts(rows, cols);
+  if (sum) jobs[n++] = {a.part_sum, sum, parts, cols, 0};
+  if (mul) jobs[n++] = {a.part_mul, mul, parts, cols, 0};
+  if (e == hipSuccess && n) e = et::sum_finish(jobs, n, (hipStream_t)stream, &launches);
+  if (e == hipErrorInvalidValue) return ET_EINVAL;
+  return e == hipSuccess ? ET_OK : ET_EHIP;
+}
+
 extern "C" int et_debug_attention(int op, const void* qkv, void* out, float* lse, const void* dout, void* dqkv, int B, int T,
                                   int H, void* stream) {
   if (!qkv || !out || !lse || B < 1 || H < 1 || T < 1 || T > 224) return ET_EINVAL;

@@ -130,8 +130,6 @@ hipError_t layernorm_bwd(const LayerNormBwd& a, hipStream_t s);
 // floats (colsum_partial_elems in all); sum_finish adds the partial rows of any number of such jobs in one launch, in a
 // fixed order.
 //   colsum_part: sum_r d[r][c] * (h ? (h[r][c]-mean[r])*rstd[r] : 1);  d is bf16 (d_f32 == nullptr) or fp32
-//   colsum_pair_part: sum_r d[r][c] (part_sum) and sum_r d[r][c] * z[r][c] (part_mul), either may be null; z bf16, or fp32
-//   when z_f32 is given; with gain also dout[r][c] = d[r][c] * gain[c], all from one read of d
 struct SumJob {
   const float* part;   // [rows][cols], 16-byte aligned
   float* out;          // [cols]
@@ -140,11 +138,24 @@ struct SumJob {
 };
 hipError_t colsum_part(const bf16* d, const float* d_f32, long long d_stride, const float* h, long long h_stride, const float* mean,
                        const float* rstd, long long stat_stride, float* part, int rows, int cols, hipStream_t s);
-hipError_t colsum_pair_part(const bf16* d, const bf16* z, const float* z_f32, const bf16* gain, bf16* dout, float* part_sum, float* part_mul,
-                            int rows, int cols, hipStream_t s);
 hipError_t sum_finish(SumJob* jobs, int n, hipStream_t s, int* launches);
 int colsum_parts(int rows, int cols);
 size_t colsum_partial_elems(int rows, int cols);
+// Backward of a per-channel affine, rows x cols, cols a multiple of 8.  With m = (d + add) where the activation is open, else 0 (as
+// rounded to bf16): dmid = m; dout = m * gain; part_sum, part_mul: affine_back_parts(rows, cols) rows of partial sums of m and of
+// m * z.  Every output is nullable, dmid may alias d or add.  Open: everywhere; or where 0 < y < hi; or (mask_from_z) where
+// 0 < clamp(z * gain + shift, 0, hi) < hi, rounded as the forward pass stores it.  z is bf16, or z32 fp32 (then no add, no y).
+struct AffineBack {
+  const bf16 *d = nullptr, *add = nullptr, *y = nullptr, *z = nullptr, *gain = nullptr, *shift = nullptr;
+  const float* z32 = nullptr;
+  bf16 *dmid = nullptr, *dout = nullptr;
+  float *part_sum = nullptr, *part_mul = nullptr;
+  float hi = __builtin_inff();
+  bool mask_from_z = false;
+  int rows = 0, cols = 0;
+};
+int affine_back_parts(int rows, int cols);
+hipError_t affine_back_part(const AffineBack& a, hipStream_t s);
 // sum over the batch: out[t][c] = sum_b d[b][t][c]   (t < T_out; fp32 in/out)
 hipError_t batchsum(const float* d, float* out, int B, long long batch_stride, int n, hipStream_t s);
 
@@ -239,8 +250,14 @@ hipError_t depthwise3x3_dw(const bf16* d, const bf16* x, float* part, int B, int
 // out[rows][N] (bf16) = max(z[rows][N] + bias[N], 0), z fp32; N % 4 == 0
 hipError_t bias_relu_rows(const float* z, const bf16* bias, bf16* out, int rows, int N, hipStream_t s);
 // out[C][3][3][O] = w[O][3][3][C] with mirrored taps: the weight of the 3x3 convolution that maps an output
-// gradient to the input gradient
-hipError_t flip3x3(const bf16* w, bf16* out, int O, int C, hipStream_t s);
+// gradient to the input gradient; any number of weights in one launch.  O, C multiples of 8, 16-byte aligned.
+struct FlipJob {
+  const bf16* w;
+  bf16* out;
+  int O, C;
+  int block0;          // filled in by flip3x3
+};
+hipError_t flip3x3(FlipJob* jobs, int n, hipStream_t s, int* launches);
 hipError_t pad_rows(const bf16* in, bf16* out, int rows, int K, int Kc, hipStream_t s);
 hipError_t strip_rows(const float* in, float* out, int rows, int K, int Kc, hipStream_t s);
 // operands of the stem convolution (7x7 / stride 2 / zero padding 3, C <= 4 input channels) for its gathered GEMM:

@@ -75,7 +75,7 @@ int build_mobilenet(et_ctx* c) {
   size_t max_act = 0, max_cs = 0, all_cs = 0, pe = 0, max_dwp = 64;
   auto act = [&](size_t rows, size_t ch) {
     max_act = std::max(max_act, rows * ch);
-    const size_t pair = 2 * sum_elems(et::colsum_parts((int)rows, (int)ch), ch);   // gain and shift sums from one kernel
+    const size_t pair = 2 * sum_elems(et::affine_back_parts((int)rows, (int)ch), ch);   // gain and shift sums from one kernel
     max_cs = std::max(max_cs, pair);
     all_cs += pair;
   };
@@ -202,9 +202,16 @@ int mobilenet_backward(et_ctx* c, const void* x, const uint8_t* mask) {
   auto pass = [&](int j) { return j > jstar; };
   hipStream_t s = c->stream;
 
-  auto affine_back = [&](int tg, const bf16* dsrc, const bf16* z, bf16* dout, long long M, int C) -> int {
-    return et_exec::affine_back(c, mask, jstar, tg, dsrc, z, nullptr, dout, M, C);
+  auto affine_back = [&](int tg, const Incoming& in, const bf16* z, bf16* dout, long long M, int C) -> int {
+    return et_exec::affine_back(c, mask, jstar, tg, in, z, nullptr, dout, M, C);
   };
+  // the gradient behind a unit's own ReLU6, whose mask is yet to be applied
+  auto behind = [](const bf16* d, const bf16* y, int tensor) {
+    Incoming in;
+    in.d = d; in.y = y; in.hi = 6.f; in.tensor = tensor; in.from_z = true;
+    return in;
+  };
+  auto plain = [](const bf16* d) { Incoming in; in.d = d; return in; };
   int rc;
 
   // ---- head and the last convolution
@@ -224,7 +231,7 @@ int mobilenet_backward(et_ctx* c, const void* x, const uint8_t* mask) {
     ET_G(g);
     ET_KB(1, 4.0 * Ml * Cl, et::avgpool_bwd_relu(c->dz, ul.y, c->rd[1], B, HWl, Cl, s, 6.f));
   }
-  if ((rc = affine_back(tl + 1, c->rd[1], ul.z, c->rd[0], Ml, Cl)) != ET_OK) return rc;
+  if ((rc = affine_back(tl + 1, plain(c->rd[1]), ul.z, c->rd[0], Ml, Cl)) != ET_OK) return rc;
   if (jstar > tl) return ET_OK;
   const bf16* last_in = c->mblk.back().y;
   if (sel(tl)) {
@@ -239,15 +246,18 @@ int mobilenet_backward(et_ctx* c, const void* x, const uint8_t* mask) {
     ET_G(g);
   }
 
-  // ---- blocks, output side first; on entry rdsum holds the gradient of the block output
+  // ---- blocks, output side first; on entry `out` is the gradient of the block output (rdsum, or rd[2] still without the share
+  // of the shortcut, which is in rdsum)
+  Incoming out = plain(c->rdsum);
   for (int bi = (int)c->mblk.size() - 1; bi >= 0; bi--) {
     const MbBlockBufs& b = c->mblk[bi];
     const int t = b.t, td = b.t_dw;
     if (jstar > td + 5) return ET_OK;
     const long long Mi = (long long)rows_in(c, b), Mo = (long long)rows_out(c, b);
     const bf16* stem_y = bi == 0 ? c->stem.y : nullptr;   // ReLU6 of the stem sits in front of the first block
-    // projection
-    if ((rc = affine_back(td + 4, c->rdsum, b.z_proj, c->rd[0], Mo, b.Cout)) != ET_OK) return rc;
+    // projection (a shortcut hands the block output's gradient on: it is kept in rdsum)
+    if (b.shortcut && out.d != c->rdsum) out.dmid = c->rdsum;
+    if ((rc = affine_back(td + 4, out, b.z_proj, c->rd[0], Mo, b.Cout)) != ET_OK) return rc;
     if (jstar > td + 3) return ET_OK;
     if (sel(td + 3)) {
       Region r(c, PH_DW, td + 3);
@@ -259,10 +269,9 @@ int mobilenet_backward(et_ctx* c, const void* x, const uint8_t* mask) {
       et::GemmDesc g = linear_dx(c->rd[0], Wt(td + 3), (int)Mo, b.Cout, b.hid);
       g.C = c->rd[1];
       ET_G(g);
-      ET_KB(1, 6.0 * Mo * b.hid, et::add_mask(c->rd[1], nullptr, b.y_dw, c->rd[1], Mo * b.hid, s, 6.f));
     }
     // depthwise convolution
-    if ((rc = affine_back(td + 1, c->rd[1], b.z_dw, c->rd[0], Mo, b.hid)) != ET_OK) return rc;
+    if ((rc = affine_back(td + 1, behind(c->rd[1], b.y_dw, td + 3), b.z_dw, c->rd[0], Mo, b.hid)) != ET_OK) return rc;
     if (jstar > td) return ET_OK;
     const bf16* dw_in = b.expand ? b.y_exp : b.x;
     if (sel(td)) {
@@ -278,37 +287,38 @@ int mobilenet_backward(et_ctx* c, const void* x, const uint8_t* mask) {
       Region r(c, PH_DY, td);
       ET_KB(1, 2.0 * (Mo + Mi * (b.shortcut ? 3.0 : 2.0)) * b.hid,
             et::depthwise3x3_dx(c->rd[0], Wt(td), b.shortcut ? c->rdsum : nullptr, stem_y, c->rdsum, B, b.H, b.W, b.hid, b.stride, s));
+      out = plain(c->rdsum);
       continue;
     }
-    {  // through the depthwise convolution and the ReLU6 after the expansion
+    {  // through the depthwise convolution
       Region r(c, PH_DY, td);
-      ET_KB(1, 2.0 * (Mo + 2.0 * Mi) * b.hid, et::depthwise3x3_dx(c->rd[0], Wt(td), nullptr, b.y_exp, c->rd[1], B, b.H, b.W, b.hid, b.stride, s));
+      ET_KB(1, 2.0 * (Mo + Mi) * b.hid, et::depthwise3x3_dx(c->rd[0], Wt(td), nullptr, nullptr, c->rd[1], B, b.H, b.W, b.hid, b.stride, s));
     }
     // expansion
-    if ((rc = affine_back(t + 1, c->rd[1], b.z_exp, c->rd[0], Mi, b.hid)) != ET_OK) return rc;
+    if ((rc = affine_back(t + 1, behind(c->rd[1], b.y_exp, td), b.z_exp, c->rd[0], Mi, b.hid)) != ET_OK) return rc;
     if (jstar > t) return ET_OK;
     if (sel(t)) {
       Region r(c, PH_DW, t);
       ET_G(linear_dw(c, c->rd[0], b.hid, b.x, b.Cin, c->grad[t], (int)Mi, b.hid, b.Cin));
     }
     if (!pass(t)) return ET_OK;
-    {  // through the expansion matrix to the block input, where the shortcut's gradient joins
+    {  // through the expansion matrix to the block input, where the shortcut's gradient joins (in front of the first block, the stem's ReLU6)
       Region r(c, PH_DY, t);
       et::GemmDesc g = linear_dx(c->rd[0], Wt(t), (int)Mi, b.hid, b.Cin);
-      const bool fix = b.shortcut || stem_y;
-      g.C = fix ? c->rd[2] : c->rdsum;
+      out = stem_y ? behind(c->rd[2], stem_y, t) : plain(c->rd[2]);
+      out.tensor = t;
+      if (b.shortcut) out.add = c->rdsum;
+      else if (!stem_y) out.d = c->rdsum;
+      g.C = const_cast<bf16*>(out.d);
       ET_G(g);
-      if (fix)
-        ET_KB(1, (b.shortcut ? 8.0 : 6.0) * Mi * b.Cin,
-              et::add_mask(c->rd[2], b.shortcut ? c->rdsum : nullptr, stem_y, c->rdsum, Mi * b.Cin, s, 6.f));
     }
   }
 
-  // ---- stem: rdsum holds the gradient of its activation's input side (after the ReLU6 mask)
+  // ---- stem
   {
     const ConvUnit& u = c->stem;
     const long long M = (long long)rows_of(c, u);
-    if ((rc = affine_back(1, c->rdsum, u.z, c->rd[0], M, u.Cout)) != ET_OK) return rc;
+    if ((rc = affine_back(1, out, u.z, c->rd[0], M, u.Cout)) != ET_OK) return rc;
     if (sel(0)) {
       Region r(c, PH_DW, 0);
       ET_G(linear_dw(c, c->rd[0], u.Cout, u.cols, u.Kc, c->stem_dw8, (int)M, u.Cout, u.Kc));

@@ -73,10 +73,10 @@ int build_resnet(et_ctx* c) {
   add("head.W", (size_t)C * Cf); add("head.b", C);
 
   // ---- workspace
-  size_t max_act = 0, max_cols = 0, max_cs = 0, all_cs = 0, pe = 0, max_flip = 8, dcols_b = 16;
+  size_t max_act = 0, max_cols = 0, max_cs = 0, all_cs = 0, pe = 0, dcols_b = 16;
   auto act = [&](size_t rows, size_t ch) {
     max_act = std::max(max_act, rows * ch);
-    const size_t pair = 2 * sum_elems(et::colsum_parts((int)rows, (int)ch), ch);   // gain and shift sums from one kernel
+    const size_t pair = 2 * sum_elems(et::affine_back_parts((int)rows, (int)ch), ch);   // gain and shift sums from one kernel
     max_cs = std::max(max_cs, pair);
     all_cs += pair;
   };
@@ -85,7 +85,6 @@ int build_resnet(et_ctx* c) {
     pe = std::max(pe, std::max(conv_dw_partials(c, u), conv_split_partials(c, u)));
     max_cols = std::max(max_cols, (size_t)M * u.Kc);   // the column matrix of any unit fits rdcols,
     dcols_b = std::max(dcols_b, dcols_bytes(c, u));     // and so does its column gradient
-    if (implicit_dy(u)) max_flip = std::max(max_flip, (size_t)u.Cout * 9 * u.Cin);
   };
   auto unit = [&](ConvUnit& u, bool with_y) {
     const size_t M = rows_of(c, u);
@@ -94,6 +93,7 @@ int build_resnet(et_ctx* c) {
     if (with_y) reserve(c, &u.y, b16 * M * u.Cout);
     act(M, u.Cout);
     wg(u);
+    reserve_flip(c, u);
   };
   {
     ConvUnit& u = c->stem;
@@ -141,7 +141,6 @@ int build_resnet(et_ctx* c) {
   reserve(c, &c->rdsum, b16 * max_act);
   reserve(c, &c->rdsc, b16 * max_act);
   reserve(c, &c->rdcols, std::max(b16 * std::max<size_t>(max_cols, 8), dcols_b));
-  reserve(c, &c->wflip, b16 * max_flip);
   c->gemm_partial_elems = pe;
   reserve(c, &c->gemm_partials, f32 * std::max<size_t>(pe, 64));
   const size_t hb = sum_elems(et::colsum_parts((int)B, C), C);
@@ -243,48 +242,65 @@ int resnet_backward(et_ctx* c, const void* x, const uint8_t* mask) {
     ET_KB(1, 4.0 * B * HWf * Cf, et::avgpool_bwd_relu(c->dz, last.y, c->rdsum, B, HWf, Cf, s));
   }
 
-  // ---- blocks, output side first.  On entry rdsum holds the gradient of the block's pre-ReLU sum.
+  std::vector<const ConvUnit*> c2s;
+  for (const ResBlockBufs& b : c->rblk) c2s.push_back(&b.c2);
+  if ((rc = mirror_weights(c, c2s, jstar)) != ET_OK) return rc;
+
+  // the gradient behind a unit's own ReLU, whose mask is yet to be applied
+  auto behind = [](const bf16* d, const bf16* y, int tensor) {
+    Incoming in;
+    in.d = d; in.y = y; in.tensor = tensor; in.from_z = true;
+    return in;
+  };
+  auto plain = [](const bf16* d) { Incoming in; in.d = d; return in; };
+
+  // ---- blocks, output side first.  On entry `out` is the gradient of the block's pre-ReLU sum: rdsum, or the main branch's rd[1]
+  // still without the share of the shortcut, which is in rdsum, and without the ReLU's mask (finished by the block's first affine).
+  Incoming out = plain(c->rdsum);
   for (int bi = (int)c->rblk.size() - 1; bi >= 0; bi--) {
     const ResBlockBufs& b = c->rblk[bi];
     const int t = b.t;
     if (jstar > t + (b.proj ? 11 : 8)) break;
     const long long M3 = (long long)rows_of(c, b.c3), M2 = (long long)rows_of(c, b.c2), M1 = (long long)rows_of(c, b.c1);
     if (b.proj) {
-      if ((rc = affine_back(c, mask, jstar, t + 10, c->rdsum, b.sc.z, nullptr, c->rdsc, M3, b.sc.Cout, sel(t + 9) || pass(t))) != ET_OK)
+      bool done;
+      if ((rc = affine_back(c, mask, jstar, t + 10, out, b.sc.z, nullptr, c->rdsc, M3, b.sc.Cout, sel(t + 9) || pass(t), &done)) != ET_OK)
         return rc;
+      if (done) out = plain(c->rdsum);
       if (sel(t + 9)) {
         Region r(c, PH_DW, t + 9);
         if ((rc = conv_dw(c, b.sc, b.x, c->rdsc, c->grad[t + 9])) != ET_OK) return rc;
       }
     }
     // main branch: c3
-    if ((rc = affine_back(c, mask, jstar, t + 7, c->rdsum, b.c3.z, nullptr, c->rd[0], M3, b.c3.Cout)) != ET_OK) return rc;
+    if ((rc = affine_back(c, mask, jstar, t + 7, out, b.c3.z, nullptr, c->rd[0], M3, b.c3.Cout)) != ET_OK) return rc;
     if (sel(t + 6)) {
       Region r(c, PH_DW, t + 6);
       if ((rc = conv_dw(c, b.c3, b.c2.y, c->rd[0], c->grad[t + 6])) != ET_OK) return rc;
     }
-    if (pass(t + 6)) {  // through the 1x1 convolution and the ReLU after c2
+    if (pass(t + 6)) {  // through the 1x1 convolution (the ReLU after c2 with c2's affine)
       Region r(c, PH_DY, t + 6);
       if ((rc = conv_dcols(c, b.c3, c->rd[0], Wt(t + 6), c->rd[1])) != ET_OK) return rc;
-      ET_KB(1, 6.0 * M2 * b.c2.Cout, et::add_mask(c->rd[1], nullptr, b.c2.y, c->rd[1], M2 * b.c2.Cout, s));
     }
     // c2
-    if ((rc = affine_back(c, mask, jstar, t + 4, c->rd[1], b.c2.z, nullptr, c->rd[0], M2, b.c2.Cout)) != ET_OK) return rc;
+    if ((rc = affine_back(c, mask, jstar, t + 4, behind(c->rd[1], b.c2.y, t + 6), b.c2.z, nullptr, c->rd[0], M2, b.c2.Cout)) != ET_OK) return rc;
     if (sel(t + 3)) {
       Region r(c, PH_DW, t + 3);
       if ((rc = conv_dw(c, b.c2, b.c1.y, c->rd[0], c->grad[t + 3])) != ET_OK) return rc;
     }
-    if (pass(t + 3)) {  // through the 3x3 convolution and the ReLU after c1
+    // through the 3x3 convolution and the ReLU after c1; where c1's z is stored, c1's affine applies the mask without reading y
+    const bool late = implicit_dy(b.c2) && sel(t + 1);
+    if (pass(t + 3)) {
       Region r(c, PH_DY, t + 3);
       if (implicit_dy(b.c2)) {
-        if ((rc = conv_dy_implicit(c, b.c2, c->rd[0], Wt(t + 3), b.c1.y, c->rd[1])) != ET_OK) return rc;
+        if ((rc = conv_dy_implicit(c, b.c2, c->rd[0], late ? nullptr : b.c1.y, c->rd[1])) != ET_OK) return rc;
       } else {
         if ((rc = conv_dcols(c, b.c2, c->rd[0], Wt(t + 3), c->rdcols)) != ET_OK) return rc;
         ET_KB(1, (dcols_f32(b.c2) ? 4.0 : 2.0) * M2 * b.c2.Kc + 4.0 * M1 * b.c1.Cout, et::col2im(c->rdcols, dcols_f32(b.c2), nullptr, b.c1.y, c->rd[1], geom(c, b.c2), s));
       }
     }
     // c1
-    if ((rc = affine_back(c, mask, jstar, t + 1, c->rd[1], b.c1.z, nullptr, c->rd[0], M1, b.c1.Cout)) != ET_OK) return rc;
+    if ((rc = affine_back(c, mask, jstar, t + 1, late ? behind(c->rd[1], b.c1.y, t + 3) : plain(c->rd[1]), b.c1.z, nullptr, c->rd[0], M1, b.c1.Cout)) != ET_OK) return rc;
     if (sel(t)) {
       Region r(c, PH_DW, t);
       if ((rc = conv_dw(c, b.c1, b.x, c->rd[0], c->grad[t])) != ET_OK) return rc;
@@ -300,8 +316,9 @@ int resnet_backward(et_ctx* c, const void* x, const uint8_t* mask) {
         if ((rc = conv_dcols(c, b.sc, c->rdsc, Wt(t + 9), c->rdcols)) != ET_OK) return rc;
         ET_KB(1, 2.0 * M3 * b.sc.Kc + (prev_y ? 6.0 : 4.0) * M1 * b.c1.Cin,
               et::col2im(c->rdcols, dcols_f32(b.sc), c->rd[1], prev_y, prev_y ? c->rdsum : c->rd[0], geom(c, b.sc), s));
-      } else {
-        ET_KB(1, 8.0 * M1 * b.c1.Cin, et::add_mask(c->rd[1], c->rdsum, prev_y, c->rdsum, M1 * b.c1.Cin, s));
+        out = plain(c->rdsum);
+      } else {   // (never the first block, which has a projection)
+        out.d = c->rd[1]; out.add = c->rdsum; out.y = prev_y; out.dmid = c->rdsum; out.tensor = t; out.from_z = false;
       }
       if (!prev_y) {
         const ConvUnit& u = c->stem;
@@ -315,7 +332,7 @@ int resnet_backward(et_ctx* c, const void* x, const uint8_t* mask) {
   if (jstar <= 2) {
     const ConvUnit& u = c->stem;
     const long long M = (long long)rows_of(c, u);
-    if ((rc = affine_back(c, mask, jstar, 1, c->rdsum, nullptr, c->stem_z32, c->rd[0], M, u.Cout)) != ET_OK) return rc;
+    if ((rc = affine_back(c, mask, jstar, 1, plain(c->rdsum), nullptr, c->stem_z32, c->rd[0], M, u.Cout)) != ET_OK) return rc;
     if (sel(0)) {
       Region r(c, PH_DW, 0);
       if (stem_gathered(c)) {   // B operand: the padded image standing for [pixel][8 x 8 x 4]

@@ -92,71 +92,6 @@ __global__ __launch_bounds__(256) void colsum_stage1(const bf16* __restrict__ d1
   }
 }
 
-// one read of d for everything the backward of a per-channel affine needs: column sums of d and of d * z, and d * gain; the sums'
-// chunking and order are those of colsum_stage1, whichever of the outputs are wanted
-template <int CT, bool Z32>
-__global__ __launch_bounds__(256) void colsum_pair_stage1(const bf16* __restrict__ d, const bf16* __restrict__ z16, const float* __restrict__ z32,
-                                                          const bf16* __restrict__ gain, bf16* __restrict__ dout, float* __restrict__ part_sum,
-                                                          float* __restrict__ part_mul, int rows, int cols) {
-  constexpr int CS_COLS = CT * 8, RT = 256 / CT;
-  __shared__ float red[2][RT][CS_COLS + 1];
-  const int cx = threadIdx.x % CT, ry = threadIdx.x / CT;
-  const int c0 = blockIdx.x * CS_COLS + cx * 8;
-  const int chunk_rows = cs_rows(rows, cols);
-  const int r_begin = blockIdx.y * chunk_rows, r_end = min(rows, r_begin + chunk_rows);
-  float acc[8], accz[8], gn[8];
-#pragma unroll
-  for (int j = 0; j < 8; j++) acc[j] = accz[j] = gn[j] = 0.f;
-  if (c0 < cols) {
-    if (dout) {
-      const bf16x8 g8 = *(const bf16x8*)(gain + c0);
-#pragma unroll
-      for (int j = 0; j < 8; j++) gn[j] = (float)g8[j];
-    }
-    for (int r = r_begin + ry; r < r_end; r += RT) {
-      const long long at = (long long)r * cols + c0;
-      const bf16x8 a = *(const bf16x8*)(d + at);
-      float zz[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-      if (part_mul) {
-        if (Z32) {
-          const float4 p = *(const float4*)(z32 + at), q = *(const float4*)(z32 + at + 4);
-          zz[0] = p.x; zz[1] = p.y; zz[2] = p.z; zz[3] = p.w; zz[4] = q.x; zz[5] = q.y; zz[6] = q.z; zz[7] = q.w;
-        } else {
-          const bf16x8 b = *(const bf16x8*)(z16 + at);
-#pragma unroll
-          for (int j = 0; j < 8; j++) zz[j] = (float)b[j];
-        }
-      }
-      bf16x8 o;
-#pragma unroll
-      for (int j = 0; j < 8; j++) {
-        acc[j] += (float)a[j];
-        accz[j] += (float)a[j] * zz[j];
-        o[j] = (bf16)((float)a[j] * gn[j]);
-      }
-      if (dout) *(bf16x8*)(dout + at) = o;
-    }
-  }
-  if (!part_sum && !part_mul) return;
-#pragma unroll
-  for (int j = 0; j < 8; j++) {
-    red[0][ry][cx * 8 + j] = acc[j];
-    red[1][ry][cx * 8 + j] = accz[j];
-  }
-  __syncthreads();
-  if (threadIdx.x < 2 * CS_COLS) {
-    const int which = threadIdx.x / CS_COLS, cl = threadIdx.x % CS_COLS;
-    const int c = blockIdx.x * CS_COLS + cl;
-    float* part = which ? part_mul : part_sum;
-    if (c < cols && part) {
-      float s = red[which][0][cl];
-#pragma unroll
-      for (int k = 1; k < RT; k++) s += red[which][k][cl];
-      part[(long long)blockIdx.y * cols + c] = s;
-    }
-  }
-}
-
 // Second step of many column sums at once: a workgroup adds the partial rows of 16 columns of one job, 64 threads per
 // four columns taking every 64th row, then in a fixed tree.  One launch for a whole backward pass: as a launch per sum this
 // step was 4.7 us each, 100 of them in a full ViT-B step.
@@ -358,29 +293,6 @@ hipError_t colsum_part(const bf16* d, const float* d_f32, long long d_stride, co
     else ET_CS(false, false);
   }
 #undef ET_CS
-#undef ET_CT
-  return hipGetLastError();
-}
-
-hipError_t colsum_pair_part(const bf16* d, const bf16* z, const float* z_f32, const bf16* gain, bf16* dout, float* part_sum, float* part_mul,
-                            int rows, int cols, hipStream_t s) {
-  if (rows <= 0 || cols <= 0 || (cols & 7) || !d || (part_mul && !z && !z_f32) || (dout && !gain) || (!part_sum && !part_mul && !dout))
-    return hipErrorInvalidValue;
-  if (!al16(d) || (z && !al16(z)) || (z_f32 && !al16(z_f32)) || (dout && (!al16(gain) || !al16(dout))) || !al16(part_sum) || !al16(part_mul))
-    return hipErrorInvalidValue;
-  const int ct = cs_threads(cols);
-  const dim3 grid((cols + ct * 8 - 1) / (ct * 8), colsum_parts(rows, cols)), block(256);
-#define ET_CT(CT, Z32) \
-  hipLaunchKernelGGL((colsum_pair_stage1<CT, Z32>), grid, block, 0, s, d, z, z_f32, gain, dout, part_sum, part_mul, rows, cols)
-  if (z_f32) {
-    if (ct == 2) ET_CT(2, true);
-    else if (ct == 4) ET_CT(4, true);
-    else ET_CT(8, true);
-  } else {
-    if (ct == 2) ET_CT(2, false);
-    else if (ct == 4) ET_CT(4, false);
-    else ET_CT(8, false);
-  }
 #undef ET_CT
   return hipGetLastError();
 }

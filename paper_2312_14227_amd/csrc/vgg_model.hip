@@ -74,7 +74,7 @@ int build_vgg(et_ctx* c) {
   }
 
   // ---- workspace
-  size_t max_act = 0, max_cols = 0, max_cs = 0, all_cs = 0, pe = 0, max_flip = 8, dcols_b = 16;
+  size_t max_act = 0, max_cols = 0, max_cs = 0, all_cs = 0, pe = 0, dcols_b = 16;
   auto bias_sum = [&](size_t rows, int cols) {
     const size_t n = sum_elems(et::colsum_parts((int)rows, cols), cols);
     max_cs = std::max(max_cs, n);
@@ -86,7 +86,7 @@ int build_vgg(et_ctx* c) {
     ConvUnit& u = c->vconv[i];
     const size_t M = rows_of(c, u);
     if (!implicit_fwd(u)) reserve(c, &u.cols, b16 * M * u.Kc);
-    if (implicit_dy(u)) max_flip = std::max(max_flip, (size_t)u.Cout * 9 * u.Cin);
+    if (i > 0) reserve_flip(c, u);   // conv0 passes nothing on
     reserve(c, &u.y, b16 * M * u.Cout);
     max_act = std::max(max_act, std::max(M * u.Cout, M * round8(u.Cin)));
     if (!implicit_dw(c, u) || !implicit_dy(u)) max_cols = std::max(max_cols, M * u.Kc);
@@ -127,7 +127,6 @@ int build_vgg(et_ctx* c) {
   reserve(c, &c->loss, 256 + sizeof(float) * (size_t)d.batch);
   for (int i = 0; i < 3; i++) reserve(c, &c->rd[i], b16 * max_act);
   reserve(c, &c->rdcols, std::max(b16 * std::max<size_t>(max_cols, 8), dcols_b));
-  reserve(c, &c->wflip, b16 * max_flip);
   c->gemm_partial_elems = pe;
   reserve(c, &c->gemm_partials, f32 * std::max<size_t>(pe, 64));
   reserve_sums(c, all_cs, max_cs);
@@ -234,6 +233,9 @@ int vgg_backward(et_ctx* c, const void* x, const uint8_t* mask) {
   }
 
   // ---- convolutions
+  std::vector<const ConvUnit*> units;
+  for (int i = 1; i < n_conv; i++) units.push_back(&c->vconv[i]);
+  if ((rc = mirror_weights(c, units, jstar)) != ET_OK) return rc;
   for (int i = n_conv - 1; i >= 0; i--) {
     const ConvUnit& u = c->vconv[i];
     const int t = u.t;
@@ -260,7 +262,7 @@ int vgg_backward(et_ctx* c, const void* x, const uint8_t* mask) {
       const bool same_stage = c->vstage[i - 1] == c->vstage[i];
       if (implicit_dy(u)) {
         // input gradient = 3x3 convolution of d with the mirrored weight [Cin][3][3][Cout]
-        if ((rc = conv_dy_implicit(c, u, dcur, Wt(t), same_stage ? p.y : nullptr, same_stage ? dn : c->rd[2])) != ET_OK) return rc;
+        if ((rc = conv_dy_implicit(c, u, dcur, same_stage ? p.y : nullptr, same_stage ? dn : c->rd[2])) != ET_OK) return rc;
         if (!same_stage)
           ET_KB(1, 3.0 * nin + 16.0 * nin, et::maxpool2x2_bwd(c->rd[2], c->varg[c->vstage[i - 1]], p.y, dn, B, p.Ho, p.Wo, p.Cout, s));
         dcur = dn;
