@@ -95,7 +95,7 @@ __global__ __launch_bounds__(256) void splitk_reduce_epilogue_kernel(ReduceEpi e
 }
 
 enum TileId : int { T_AUTO = 0, T_128x128 = 1, T_128x64 = 3, T_DMA_256x256 = 5, T_DMA_256x128 = 7, T_PP_256x256 = 11, T_PP_256x192 = 13,
-              T_PP_256x128 = 15, T_PP_512x64 = 17, T_PP_128x256 = 19, T_PP_64x512 = 21, T_RING_64x64 = 23 };
+              T_PP_256x128 = 15, T_PP_512x64 = 17, T_PP_128x256 = 19, T_PP_64x512 = 21, T_RING_64x64 = 23, T_RING_64x128 = 25, T_RING_128x64 = 27, T_RING_128x128 = 29 };
 
 // number of compute units of the current device (256 on an MI355X), looked up once per device; a multiple of 8
 // (one share per XCD) as the resident kernels' unit order assumes whenever a workgroup takes a second unit
@@ -158,7 +158,9 @@ Plan plan_conv_dw(int M, int N, int K) {
 // CU sustains on the VGG16 layer shapes (the shifted rows of the nine taps hit in the L2, so the wide tiles
 // run faster here than on a stored matrix)
 int choose_conv_tile(const GemmDesc& d) {
-  if (d.tile == T_PP_256x256 || d.tile == T_PP_256x192 || d.tile == T_PP_256x128 || d.tile == T_PP_512x64 || d.tile == T_RING_64x64) return d.tile;
+  if (d.tile == T_PP_256x256 || d.tile == T_PP_256x192 || d.tile == T_PP_256x128 || d.tile == T_PP_512x64 || d.tile == T_RING_64x64 ||
+      d.tile == T_RING_64x128 || d.tile == T_RING_128x64 || d.tile == T_RING_128x128)
+    return d.tile;
   static const TileRate cand[4] = {{T_PP_256x256, 256, 256, 4.5e12}, {T_PP_256x192, 256, 192, 4.0e12},
                                    {T_PP_256x128, 256, 128, 3.3e12}, {T_PP_512x64, 512, 64, 2.6e12}};
   return plan_tiles(d.M, d.N, d.K, false, cand, 4).tile;
@@ -170,13 +172,17 @@ int choose_conv_tile(const GemmDesc& d) {
 //   ring 64x64     0.175 (0.205 with one tile per CU) + 0.5: any K; 1.6 - 3.6 x faster than the register-staged tiles on
 //                  long K ([788 x 768 x 3072] 36.2 -> 13.9 us, [1568 x 512 x 2048] 25.3 -> 10.0, [1024 x 1024] over 6304
 //                  rows 69.8 -> 26.6, all unsplit), equal at 3 - 5 slices;
+//   ring 64x128    0.30 (0.33) + 1.0: [4616 x 384 x 1536] 12.5 us against 13.3, [6272 x 256 x 1024] 8.9 against 9.3;
+//   ring 128x128   0.55 + 2.3, one workgroup per CU: [25088 x 128 x 512] 11.1 us against 12.9, [1568 x 2048 x 512] 9.1 against 10.6;
 //   staged 128x64  0.33 + 0.75, but a memory round trip of 0.75 per slice when a CU has one tile only;
 //   staged 128x128 0.66 + 1.2, the same: ahead where tiles are many and short, by halving or quartering the operand
 //                  re-reads and the per-tile cost ([100352 x 256 x 64] 17.6 us against 23.3, [25088 x 512 x 128] 12.5
 //                  against 15.1).
 Plan plan_small(int M, int N, int K, int count) {
   struct Cand { int tile, bm, bn; double slice, solo, fixed; };
-  static const Cand cand[3] = {{T_RING_64x64, 64, 64, 0.175e-6, 0.205e-6, 0.5e-6},
+  static const Cand cand[5] = {{T_RING_64x64, 64, 64, 0.175e-6, 0.205e-6, 0.5e-6},
+                               {T_RING_64x128, 64, 128, 0.30e-6, 0.33e-6, 1.0e-6},
+                               {T_RING_128x128, 128, 128, 0.55e-6, 0.55e-6, 2.3e-6},
                                {T_128x64, 128, 64, 0.33e-6, 0.75e-6, 0.75e-6},
                                {T_128x128, 128, 128, 0.66e-6, 0.85e-6, 1.2e-6}};
   Plan best = {T_128x64, 1, 1e30};
@@ -190,26 +196,41 @@ Plan plan_small(int M, int N, int K, int count) {
   return best;
 }
 
-// The ring tile with its reduction split so that the estimated time is least: a CU's share of the units, one after the
-// other (`solo` / `loaded` seconds per slice of 64 with one / several workgroups per CU), at least the time the operands
-// take to stream in with as many CUs as there are units; a split adds the partials' traffic and a second launch (3 us).
-Plan plan_ring(int M, int N, int K, bool may_split, double solo, double loaded) {
+// A ring tile with its reduction split so that the estimated time is least: a CU's share of the units, one after the
+// other (`solo` / `loaded` seconds per slice of 64 with one / several workgroups per CU, `fixed` per unit), at least the time the
+// operands take to stream in with as many CUs as there are units (an activation read by nine taps counts once); a split adds the partials' traffic and a second launch (3 us).
+struct RingTile { int tile, bm, bn; double solo, loaded, fixed; };
+
+template <int N_TILES>
+Plan plan_ring(int M, int N, int K, bool may_split, double operand_elems, const RingTile (&tiles)[N_TILES]) {
   const int slices = (K + gemm::PBK - 1) / gemm::PBK;
-  const double stream = 2.0 * ((double)M + N) * K / 4e12;
+  const double stream = 2.0 * operand_elems / 4e12;
   const int max_split = may_split && (N & 3) == 0 ? std::max(1, std::min(256, slices / 4)) : 1;
   Plan best = {T_RING_64x64, 1, 1e30};
-  for (int s = 1; s <= max_split; s++) {
-    const int per = (slices + s - 1) / s;
-    if ((slices + per - 1) / per != s) continue;   // this split leaves empty chunks
-    const long long units = (long long)((M + 63) / 64) * ((N + 63) / 64) * s;
-    const double load = stream * 256.0 / (double)std::min<long long>(units, 256);
-    const double ring = units <= 256 ? per * solo + 0.5e-6 : (double)((units + 255) / 256) * (per * loaded + 0.5e-6);
-    double t = std::max(load, ring);
-    if (s > 1) t += (2.0 * s + 1.0) * M * N * 4.0 / 3.5e12 + 3e-6;
-    if (t < best.cost * 0.999) best = {T_RING_64x64, s, t};
-  }
+  for (const RingTile& r : tiles)
+    for (int s = 1; s <= max_split; s++) {
+      const int per = (slices + s - 1) / s;
+      if ((slices + per - 1) / per != s) continue;   // this split leaves empty chunks
+      const long long units = (long long)((M + r.bm - 1) / r.bm) * ((N + r.bn - 1) / r.bn) * s;
+      const double load = stream * 256.0 / (double)std::min<long long>(units, 256);
+      const double ring = units <= 256 ? per * r.solo + r.fixed : (double)((units + 255) / 256) * (per * r.loaded + r.fixed);
+      double t = std::max(load, ring);
+      if (s > 1) t += (2.0 * s + 1.0) * M * N * 4.0 / 3.5e12 + 3e-6;
+      if (t < best.cost * 0.999) best = {r.tile, s, t};
+    }
   return best;
 }
+
+// Rates measured per tile.  Weight gradients [rows of A^T][B^T], any layout of a split reduction (plan_small has the 64x64 rates):
+// [1152 x 384] over 4616 rows in 4 chunks 9.8 us on 64x128, 10.5 on 64x64.
+const RingTile kRingDw[2] = {{T_RING_64x64, 64, 64, 0.25e-6, 0.175e-6, 0.5e-6}, {T_RING_64x128, 64, 128, 0.36e-6, 0.33e-6, 1.0e-6}};
+// Implicit convolutions, 32 images, best 64x64 plan / chosen: 28x28x128 18.7 / 14.9 us (128x128), 14x14x256 17.7 / 15.8 (64x128),
+// 224x224x64 257 / 220 (128x64).
+const RingTile kRingConv[4] = {{T_RING_64x64, 64, 64, 0.28e-6, 0.19e-6, 0.5e-6}, {T_RING_64x128, 64, 128, 0.38e-6, 0.33e-6, 1.0e-6},
+                               {T_RING_128x64, 128, 64, 0.45e-6, 0.33e-6, 1.0e-6}, {T_RING_128x128, 128, 128, 0.56e-6, 0.56e-6, 2.5e-6}};
+// Their weight gradients: 28x28x128 20.2 / 17.8 us, 14x14x256 20.6 / 18.2 (128x64), 224x224x64 219 / 185 (64x128).
+const RingTile kRingConvDw[3] = {{T_RING_64x64, 64, 64, 0.365e-6, 0.24e-6, 0.5e-6}, {T_RING_64x128, 64, 128, 0.46e-6, 0.36e-6, 1.0e-6},
+                                 {T_RING_128x64, 128, 64, 0.36e-6, 0.34e-6, 1.0e-6}};
 
 int choose_tile(const GemmDesc& d, int k_per_block) {
   const bool dma_ok = (d.K % gemm::DBK) == 0 && (k_per_block % gemm::DBK) == 0;
@@ -239,23 +260,23 @@ int choose_tile(const GemmDesc& d, int k_per_block) {
 
 size_t gemm_bf16_partial_elems(int M, int N, int split_k) { return split_k > 1 ? (size_t)M * N * split_k : 0; }
 
-// Implicit convolutions: the ring tile up to 14 GFLOP and for at most 64 output channels, the two-group tiles beyond.
-// Measured at batch 32, forward (two-group plan / ring): 7x7x512 27.9 / 22, 14x14x256 27.6 / 17.8, 56x56x64 24.5 / 21.8,
-// 224x224x64 285 / 254 us, but 14x14x512 51 / 59, 112x112x128 176 / 189; weight gradients: 14x14x256 32.0 / 23.7, 56x56x64
-// 43.5 / 24.6, 224x224x64 390 / 240, but 56x56 128 -> 256 81 / 110.
-static bool conv_on_ring(int rows, int channels, int K) { return channels <= 64 || 2.0 * rows * channels * (double)K < 1.4e10; }
+// Implicit convolutions: the ring tiles up to 32 GFLOP (weight gradients: 14) and for at most 64 output channels, the two-group
+// tiles beyond.  Measured at batch 32, forward (two-group plan / ring): 7x7x512 27.9 / 20, 14x14x256 27.6 / 15.8, 56x56x64
+// 24.5 / 20, 224x224x64 285 / 220 us, 14x14x512 45.8 / 42, but 112x112x128 155 / 170; weight gradients: 14x14x256 32.0 / 20,
+// 56x56x64 43.5 / 23, 224x224x64 390 / 195, but 14x14x512 52 / 54, 56x56 128 -> 256 81 / 110.
+static bool conv_on_ring(int rows, int channels, int K, double most) { return channels <= 64 || 2.0 * rows * channels * (double)K < most; }
 
 void gemm_bf16_plan_conv(int M, int N, int K, int* tile, int* split_k) {
   static const TileRate cand[4] = {{T_PP_256x256, 256, 256, 4.5e12}, {T_PP_256x192, 256, 192, 4.0e12},
                                    {T_PP_256x128, 256, 128, 3.3e12}, {T_PP_512x64, 512, 64, 2.6e12}};
-  const Plan pl = conv_on_ring(M, N, K) ? plan_ring(M, N, K, true, 0.26e-6, 0.19e-6) : plan_tiles(M, N, K, (N & 3) == 0, cand, 4);
+  const Plan pl = conv_on_ring(M, N, K, 3.2e10) ? plan_ring(M, N, K, true, K / 9.0 * M + (double)N * K, kRingConv) : plan_tiles(M, N, K, (N & 3) == 0, cand, 4);
   *tile = pl.tile;
   *split_k = pl.split;
 }
 
 void gemm_bf16_plan_conv_dw(int M, int N, int K, int* tile, int* split_k) {
   // (a pixel count that is not a multiple of 64 runs on the ring tile whatever its size)
-  const Plan pl = (K % gemm::PBK) || conv_on_ring(K, M, N) ? plan_ring(M, N, K, true, 0.26e-6, 0.19e-6) : plan_conv_dw(M, N, K);
+  const Plan pl = (K % gemm::PBK) || conv_on_ring(K, M, N, 1.4e10) ? plan_ring(M, N, K, true, (M + N / 9.0) * K, kRingConvDw) : plan_conv_dw(M, N, K);
   *tile = pl.tile;
   *split_k = pl.split;
 }
@@ -280,7 +301,7 @@ void gemm_bf16_plan_split(int M, int N, int K, int* tile, int* split_k) {
     *split_k = std::max(1, std::min(8, 256 / tiles));
     *tile = tiles >= 32 ? T_DMA_256x256 : T_DMA_256x128;
   } else {   // everything else runs on the ring tile, any K
-    const Plan pl = plan_ring(M, N, K, true, 0.205e-6, 0.175e-6);
+    const Plan pl = plan_ring(M, N, K, true, ((double)M + N) * K, kRingDw);
     *split_k = pl.split;
     if (pl.split > 1) *tile = pl.tile;   // (unsplit: whichever tile choose_tile prefers)
   }
@@ -406,8 +427,9 @@ hipError_t gemm_bf16(const GemmDesc& d, hipStream_t s, int* launches) {
   gemm::LaunchFn fn;
   const bool conv_general = conv && !(d.conv_taps == 3 && d.conv_stride == 1);   // geometry as launch arguments
   bool resident = true;   // the two-group kernels keep one workgroup per CU that walks over the tiles
-  if (conv_dw && d.tile == T_RING_64x64 && !stem) {
-    BM = 64; BN = 64; fn = gemm::ring_convdw_64x64(epi); resident = false;
+  if (conv_dw && !stem && (d.tile == T_RING_64x64 || d.tile == T_RING_64x128 || d.tile == T_RING_128x64)) {
+    BM = d.tile == T_RING_128x64 ? 128 : 64; BN = d.tile == T_RING_64x128 ? 128 : 64; resident = false;
+    fn = d.tile == T_RING_64x64 ? gemm::ring_convdw_64x64(epi) : d.tile == T_RING_64x128 ? gemm::ring_convdw_64x128(epi) : gemm::ring_convdw_128x64(epi);
   } else if (conv_dw) {
     if (d.K % gemm::PBK) return hipErrorInvalidValue;
     int tile = d.tile;
@@ -424,6 +446,9 @@ hipError_t gemm_bf16(const GemmDesc& d, hipStream_t s, int* launches) {
   } else if (conv) {
     switch (choose_conv_tile(d)) {
       case T_RING_64x64: BM = 64; BN = 64; fn = gemm::ring_conv_64x64(epi); resident = false; break;
+      case T_RING_64x128: BM = 64; BN = 128; fn = gemm::ring_conv_64x128(epi); resident = false; break;
+      case T_RING_128x64: BM = 128; BN = 64; fn = gemm::ring_conv_128x64(epi); resident = false; break;
+      case T_RING_128x128: BM = 128; BN = 128; fn = gemm::ring_conv_128x128(epi); resident = false; break;
       case T_PP_512x64: BM = 512; BN = 64; fn = gemm::pp_conv_512x64(epi, conv_general); break;
       case T_PP_256x128: BM = 256; BN = 128; fn = gemm::pp_conv_256x128(epi, conv_general); break;
       case T_PP_256x192: BM = 256; BN = 192; fn = gemm::pp_conv_256x192(epi, conv_general); break;
@@ -437,6 +462,8 @@ hipError_t gemm_bf16(const GemmDesc& d, hipStream_t s, int* launches) {
     case T_PP_256x128: BM = 256; BN = 128; fn = gemm::pp_256x128(d.a_t, d.b_t, epi); break;
     case T_128x64: BM = 128; BN = 64; fn = gemm::staged_128x64(d.a_t, d.b_t, epi); resident = false; break;
     case T_RING_64x64: BM = 64; BN = 64; fn = gemm::ring_64x64(d.a_t, d.b_t, epi); resident = false; break;
+    case T_RING_64x128: BM = 64; BN = 128; fn = gemm::ring_64x128(d.a_t, d.b_t, epi); resident = false; break;
+    case T_RING_128x128: BM = 128; BN = 128; fn = gemm::ring_128x128(d.a_t, d.b_t, epi); resident = false; break;
     case T_DMA_256x256: BM = 256; BN = 256; fn = gemm::dma_256x256(d.a_t, d.b_t, epi); resident = false; break;
     case T_DMA_256x128: BM = 256; BN = 128; fn = gemm::dma_256x128(d.a_t, d.b_t, epi); resident = false; break;
     case T_PP_256x192: BM = 256; BN = 192; fn = gemm::pp_256x192(d.a_t, d.b_t, epi); break;

@@ -7,7 +7,9 @@
 // in flight per workgroup, without holding registers, and the tiles are small enough that the launch has a
 // workgroup for every CU.
 //
-// One workgroup of four waves (2 x 2 over the tile) computes BM x BN.  Per slice t: wait for the loads of slice t + 1
+// One workgroup computes BM x BN: four waves (2 x 2) a tile of 64 x 64, eight waves one of 64 x 128, 128 x 64 or 128 x 128, which
+// read a half and a quarter less of the operands (a CU takes in about 100 bytes per ns from the L2 while all do, 0.16 us for
+// the 16 KB of a 64 x 64 slice) where they still leave a workgroup for most CUs.  Per slice t: wait for the loads of slice t + 1
 // (s_waitcnt vmcnt counts loads in order, younger slices stay in flight), one barrier, request slice t + RING into the
 // stage of slice t, whose fragments every wave holds in registers by then, read the fragments of slice t + 1, multiply
 // slice t.  LDS layouts, bank swizzles and the exchanged MFMA
@@ -316,8 +318,15 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_ring_kernel(Params g) {
 }
 
 LaunchFn ring_64x64(bool a_t, bool b_t, int epi);
+LaunchFn ring_64x128(bool a_t, bool b_t, int epi);
+LaunchFn ring_128x128(bool a_t, bool b_t, int epi);
 LaunchFn ring_conv_64x64(int epi);
+LaunchFn ring_conv_64x128(int epi);
+LaunchFn ring_conv_128x64(int epi);
+LaunchFn ring_conv_128x128(int epi);
 LaunchFn ring_convdw_64x64(int epi);
+LaunchFn ring_convdw_64x128(int epi);
+LaunchFn ring_convdw_128x64(int epi);
 
 }  // namespace gemm
 }  // namespace et

@@ -48,3 +48,29 @@ def test_planned_convolution_over_odd_maps(batch, H, W, C, N):
     """Tile and split from the planner, pixel counts that are not multiples of 64."""
     _case_split(batch, H, W, C, N, 3, 0, 0, seed=C)
     _case_dw(batch, H, W, C, N, 0, 0, seed=C + 1)
+
+
+@pytest.mark.parametrize("tile", [25, 29])
+@pytest.mark.parametrize("a_t,b_t", [(0, 0), (0, 1), (1, 1)])
+@pytest.mark.parametrize("M,N,K", [(64, 128, 64), (3, 8, 8), (129, 136, 191), (130, 260, 193), (72, 104, 509), (260, 130, 1000)])
+def test_eight_wave_ring_tiles(M, N, K, a_t, b_t, tile):
+    _run(M, N, K, a_t, b_t, 1, True, a_t == 0 and b_t == 0, 1, tile, seed=M + N + K)
+    _run(M, N, K, a_t, b_t, 0, True, False, 1, tile, seed=M + K)
+    if a_t and N % 4 == 0 and K > 500:
+        _run(M, N, K, 1, 1, 1, False, False, 3, tile, seed=K)
+
+
+@pytest.mark.parametrize("tile", [25, 27, 29])
+@pytest.mark.parametrize("batch,H,W,C,N", [(1, 1, 1, 64, 64), (1, 5, 7, 64, 72), (2, 9, 8, 128, 64), (3, 13, 13, 192, 200)])
+def test_eight_wave_ring_convolution(batch, H, W, C, N, tile):
+    for mode in (0, 1, 2):
+        _case(batch, H, W, C, N, mode, tile, seed=H + C + mode)
+    _case_split(batch, H, W, C, N, 3, 2, tile, seed=H)
+    if tile != 29:
+        _case_dw(batch, H, W, C, N, 2 if H > 10 else 1, tile, seed=H + N)
+
+
+@pytest.mark.parametrize("tile", [25, 27])
+def test_eight_wave_ring_convolution_with_stride(tile):
+    for taps, stride in ((3, 2), (1, 2)):
+        _case_gathered(3, 15, 17, 64, 72, taps, stride, tile, seed=taps + stride)
