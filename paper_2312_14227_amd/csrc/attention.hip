@@ -188,8 +188,10 @@ __global__ __launch_bounds__(NTHREADS) void attention_fwd_kernel(const bf16* __r
 template <int KT>
 __global__ __launch_bounds__(NTHREADS) void attention_bwd_kernel(const bf16* __restrict__ qkv, const bf16* __restrict__ out,
                                                             const bf16* __restrict__ dout, const float* __restrict__ lse,
-                                                            bf16* __restrict__ dqkv, int T, int H, float scale) {
+                                                            bf16* __restrict__ dqkv, float* __restrict__ part, int T, int H, float scale) {
   constexpr int TP = KT * 32;
+  static_assert(KT <= NWAVES, "a wave owns at most one tile");
+  __shared__ float s_sum[3][KT][DH];   // column sums of dQ, dK, dV per wave
   __shared__ __attribute__((aligned(16))) unsigned char sq[TP * PITCH];
   __shared__ __attribute__((aligned(16))) unsigned char sk[TP * PITCH];
   __shared__ __attribute__((aligned(16))) unsigned char sv[TP * PITCH];
@@ -271,6 +273,7 @@ __global__ __launch_bounds__(NTHREADS) void attention_bwd_kernel(const bf16* __r
       }
     }
     store_tile(s_store + wave * STORE_AREA, dq, scale, dqkv + ((long long)b * T + qt * 32) * ld + h * DH, ld, T - qt * 32, lane);
+    if (part) s_sum[0][qt][lane] = tile_colsum(s_store + wave * STORE_AREA, T - qt * 32, lane);
   }
   __syncthreads();
 
@@ -327,7 +330,18 @@ __global__ __launch_bounds__(NTHREADS) void attention_bwd_kernel(const bf16* __r
     }
     bf16* drow0 = dqkv + ((long long)b * T + kt * 32) * ld + h * DH;
     store_tile(s_store + wave * STORE_AREA, dk, scale, drow0 + D, ld, T - kt * 32, lane);
+    if (part) s_sum[1][kt][lane] = tile_colsum(s_store + wave * STORE_AREA, T - kt * 32, lane);
     store_tile(s_store + wave * STORE_AREA, dv, 1.f, drow0 + 2 * D, ld, T - kt * 32, lane);
+    if (part) s_sum[2][kt][lane] = tile_colsum(s_store + wave * STORE_AREA, T - kt * 32, lane);
+  }
+  if (!part) return;
+  __syncthreads();
+  if (tid < 3 * DH) {   // row b of the partial sums [B][3 D]
+    const int which = tid / DH, col = tid % DH;
+    float s = s_sum[which][0][col];
+#pragma unroll
+    for (int k = 1; k < KT; k++) s += s_sum[which][k][col];
+    part[b * ld + which * D + h * DH + col] = s;
   }
 }
 
@@ -339,8 +353,8 @@ __global__ __launch_bounds__(NTHREADS) void attention_bwd_kernel(const bf16* __r
 // -------------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void attention_bwd_cls_kernel(const bf16* __restrict__ qkv, const bf16* __restrict__ out,
                                                                 const bf16* __restrict__ dout, const float* __restrict__ lse,
-                                                                bf16* __restrict__ dqkv, int T, int H, float scale) {
-  __shared__ float red[32][DH + 4];
+                                                                bf16* __restrict__ dqkv, float* __restrict__ part_out, int T, int H, float scale) {
+  __shared__ float red[3][32][DH + 4];   // dQ, and the column sums of dK and dV
   const int tid = threadIdx.x, part = tid & 7, grp = tid >> 3;
   const int b = blockIdx.x / H, h = blockIdx.x % H, D = H * DH;
   const long long ld = 3LL * D, base = (long long)b * T * ld + h * DH + part * 8;
@@ -357,9 +371,9 @@ __global__ __launch_bounds__(256) void attention_bwd_cls_kernel(const bf16* __re
 #pragma unroll
   for (int m = 1; m < 8; m <<= 1) dot += __shfl_xor(dot, m, 64);
   const float c = scale * 1.44269504088896341f, l = lse[((long long)b * H + h) * T] * 1.44269504088896341f;
-  float dq[8];
+  float dq[8], ks[8], vs[8];
 #pragma unroll
-  for (int e = 0; e < 8; e++) dq[e] = 0.f;
+  for (int e = 0; e < 8; e++) dq[e] = ks[e] = vs[e] = 0.f;
   const bf16x8 zero = {};
 #pragma unroll 2
   for (int t = grp; t < T; t += 32) {
@@ -383,19 +397,31 @@ __global__ __launch_bounds__(256) void attention_bwd_cls_kernel(const bf16* __re
       dk8[e] = (bf16)(ds * q[e]);
       dv8[e] = (bf16)(p * g[e]);
       dq[e] += ds * (float)k8[e];
+      ks[e] += (float)dk8[e];
+      vs[e] += (float)dv8[e];
     }
     if (t > 0) *(bf16x8*)(dqkv + at) = zero;
     *(bf16x8*)(dqkv + at + D) = dk8;
     *(bf16x8*)(dqkv + at + 2 * D) = dv8;
   }
 #pragma unroll
-  for (int e = 0; e < 8; e++) red[grp][part * 8 + e] = dq[e];
+  for (int e = 0; e < 8; e++) {
+    red[0][grp][part * 8 + e] = dq[e];
+    red[1][grp][part * 8 + e] = ks[e];
+    red[2][grp][part * 8 + e] = vs[e];
+  }
   __syncthreads();
-  if (tid < DH) {
-    float s = red[0][tid];
+  if (tid < 3 * DH) {
+    const int which = tid / DH, col = tid % DH;
+    float s = red[which][0][col];
 #pragma unroll
-    for (int k = 1; k < 32; k++) s += red[k][tid];
-    dqkv[(long long)b * T * ld + h * DH + tid] = (bf16)s;
+    for (int k = 1; k < 32; k++) s += red[which][k][col];
+    if (which == 0) {
+      const bf16 v = (bf16)s;
+      dqkv[(long long)b * T * ld + h * DH + col] = v;
+      s = (float)v;
+    }
+    if (part_out) part_out[b * ld + which * D + h * DH + col] = s;
   }
 }
 
@@ -411,19 +437,21 @@ hipError_t launch_fwd(const bf16* qkv, bf16* out, float* lse, int B, int T, int 
 }
 template <int KT>
 hipError_t launch_bwd(const bf16* qkv, const bf16* out, const bf16* dout, const float* lse, bf16* dqkv, int B, int T, int H,
-                      float scale, hipStream_t s) {
-  hipLaunchKernelGGL((attention_bwd_kernel<KT>), dim3(B * H), dim3(NTHREADS), 0, s, qkv, out, dout, lse, dqkv, T, H, scale);
+                      float scale, hipStream_t s, float* part) {
+  hipLaunchKernelGGL((attention_bwd_kernel<KT>), dim3(B * H), dim3(NTHREADS), 0, s, qkv, out, dout, lse, dqkv, part, T, H, scale);
   return hipGetLastError();
 }
 
 }  // namespace
 
 hipError_t attention_bwd_cls(const bf16* qkv, const bf16* out, const bf16* dout, const float* lse, bf16* dqkv, int B, int T, int H,
-                             int head_dim, float scale, hipStream_t s) {
+                             int head_dim, float scale, hipStream_t s, float* part) {
   if (!attention_fused_supported(T, head_dim) || B < 1 || H < 1) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(attention_bwd_cls_kernel, dim3(B * H), dim3(256), 0, s, qkv, out, dout, lse, dqkv, T, H, scale);
+  hipLaunchKernelGGL(attention_bwd_cls_kernel, dim3(B * H), dim3(256), 0, s, qkv, out, dout, lse, dqkv, part, T, H, scale);
   return hipGetLastError();
 }
+
+int attention_bwd_parts(int B, int T) { return T > 224 ? attention_long_bwd_parts(B, T) : B; }
 
 bool attention_fused_supported(int T, int head_dim) { return head_dim == DH && T >= 1 && T < (1 << 20); }
 
@@ -443,17 +471,17 @@ hipError_t attention_fwd(const bf16* qkv, bf16* out, float* lse, int B, int T, i
 }
 
 hipError_t attention_bwd(const bf16* qkv, const bf16* out, const bf16* dout, const float* lse, bf16* dqkv, int B, int T, int H,
-                         int head_dim, float scale, hipStream_t s) {
+                         int head_dim, float scale, hipStream_t s, float* part) {
   if (!attention_fused_supported(T, head_dim) || B < 1 || H < 1 || !out) return hipErrorInvalidValue;
-  if (T > 224) return attention_long_bwd(qkv, out, dout, lse, dqkv, B, T, H, scale, s);
+  if (T > 224) return attention_long_bwd(qkv, out, dout, lse, dqkv, B, T, H, scale, s, part);
   switch ((T + 31) / 32) {
-    case 1: return launch_bwd<1>(qkv, out, dout, lse, dqkv, B, T, H, scale, s);
-    case 2: return launch_bwd<2>(qkv, out, dout, lse, dqkv, B, T, H, scale, s);
-    case 3: return launch_bwd<3>(qkv, out, dout, lse, dqkv, B, T, H, scale, s);
-    case 4: return launch_bwd<4>(qkv, out, dout, lse, dqkv, B, T, H, scale, s);
-    case 5: return launch_bwd<5>(qkv, out, dout, lse, dqkv, B, T, H, scale, s);
-    case 6: return launch_bwd<6>(qkv, out, dout, lse, dqkv, B, T, H, scale, s);
-    default: return launch_bwd<7>(qkv, out, dout, lse, dqkv, B, T, H, scale, s);
+    case 1: return launch_bwd<1>(qkv, out, dout, lse, dqkv, B, T, H, scale, s, part);
+    case 2: return launch_bwd<2>(qkv, out, dout, lse, dqkv, B, T, H, scale, s, part);
+    case 3: return launch_bwd<3>(qkv, out, dout, lse, dqkv, B, T, H, scale, s, part);
+    case 4: return launch_bwd<4>(qkv, out, dout, lse, dqkv, B, T, H, scale, s, part);
+    case 5: return launch_bwd<5>(qkv, out, dout, lse, dqkv, B, T, H, scale, s, part);
+    case 6: return launch_bwd<6>(qkv, out, dout, lse, dqkv, B, T, H, scale, s, part);
+    default: return launch_bwd<7>(qkv, out, dout, lse, dqkv, B, T, H, scale, s, part);
   }
 }
 

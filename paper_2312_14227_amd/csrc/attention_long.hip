@@ -137,9 +137,10 @@ __global__ __launch_bounds__(LTHREADS) void attention_long_fwd_kernel(const bf16
 
 __global__ __launch_bounds__(LTHREADS) void attention_long_bwd_kernel(const bf16* __restrict__ qkv, const bf16* __restrict__ out,
                                                                       const bf16* __restrict__ dout, const float* __restrict__ lse,
-                                                                      bf16* __restrict__ dqkv, int T, int H, float scale, int items, int blocks) {
+                                                                      bf16* __restrict__ dqkv, float* __restrict__ part, int T, int H, float scale, int items, int blocks) {
   __shared__ __attribute__((aligned(1024))) unsigned char smem[2 * 2 * MAT + LW * STORE_AREA];
   __shared__ __attribute__((aligned(16))) float s_lse[2][CH], s_dot[2][CH];
+  __shared__ float s_sum[2][LW][DH];   // column sums of dQ, or of dK and dV, per wave
   int item, blk;
   if (!locate(2 * blocks, items, item, blk)) return;
   const bool keys = blk >= blocks;       // own keys (dK, dV); the first `blocks` workgroups own queries (dQ)
@@ -211,6 +212,15 @@ __global__ __launch_bounds__(LTHREADS) void attention_long_bwd_kernel(const bf16
       }
     }
     store_tile(area, dq, scale, dqkv + ((long long)b * T + own0) * ld + h * DH, ld, T - own0, lane);
+    if (!part) return;
+    s_sum[0][wave][lane] = tile_colsum(area, T - own0, lane);
+    __syncthreads();
+    if (tid < DH) {   // row (b, blk) of the partial sums [B * blocks][3 D]
+      float s = s_sum[0][0][tid];
+#pragma unroll
+      for (int k = 1; k < LW; k++) s += s_sum[0][k][tid];
+      part[(b * blocks + blk) * ld + h * DH + tid] = s;
+    }
     return;
   }
 
@@ -287,7 +297,18 @@ __global__ __launch_bounds__(LTHREADS) void attention_long_bwd_kernel(const bf16
   }
   bf16* drow0 = dqkv + ((long long)b * T + own0) * ld + h * DH;
   store_tile(area, dk, scale, drow0 + D, ld, T - own0, lane);
+  if (part) s_sum[0][wave][lane] = tile_colsum(area, T - own0, lane);
   store_tile(area, dv, 1.f, drow0 + 2 * D, ld, T - own0, lane);
+  if (!part) return;
+  s_sum[1][wave][lane] = tile_colsum(area, T - own0, lane);
+  __syncthreads();
+  if (tid < 2 * DH) {
+    const int which = tid / DH, col = tid % DH;
+    float s = s_sum[which][0][col];
+#pragma unroll
+    for (int k = 1; k < LW; k++) s += s_sum[which][k][col];
+    part[(b * blocks + blk) * ld + (1 + which) * D + h * DH + col] = s;
+  }
 }
 
 // grid: items rounded up to a multiple of 8 (one share per XCD) times the blocks of an item
@@ -310,12 +331,14 @@ hipError_t attention_long_fwd(const bf16* qkv, bf16* out, float* lse, int B, int
 }
 
 hipError_t attention_long_bwd(const bf16* qkv, const bf16* out, const bf16* dout, const float* lse, bf16* dqkv, int B, int T, int H,
-                              float scale, hipStream_t s) {
+                              float scale, hipStream_t s, float* part) {
   const int blocks = (T + OWN - 1) / OWN;
   unsigned grid;
   if (B < 1 || H < 1 || T < 1 || !out || !grid_of(B, T, H, 2 * blocks, &grid)) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(attention_long_bwd_kernel, dim3(grid), dim3(LTHREADS), 0, s, qkv, out, dout, lse, dqkv, T, H, scale, B * H, blocks);
+  hipLaunchKernelGGL(attention_long_bwd_kernel, dim3(grid), dim3(LTHREADS), 0, s, qkv, out, dout, lse, dqkv, part, T, H, scale, B * H, blocks);
   return hipGetLastError();
 }
+
+int attention_long_bwd_parts(int B, int T) { return B * ((T + OWN - 1) / OWN); }
 
 }  // namespace et

@@ -82,6 +82,19 @@ __device__ __forceinline__ void store_tile(unsigned char* area, const f32x16 (&t
   }
 }
 
+// Column sum of the tile that store_tile has just left in `area` (rows below `rows`): lane l returns that of column l.  The
+// rounded values are added, those that a sum over the stored matrix would read; 32 two-byte LDS reads per tile instead of
+// another pass over dQ, dK and dV (8.5 us per layer for 12 608 x 2304).
+__device__ __forceinline__ float tile_colsum(const unsigned char* area, int rows, int lane) {
+  float s = 0.f;
+#pragma unroll
+  for (int r = 0; r < 32; r++) {
+    const bf16 v = *(const bf16*)(area + r * 128 + (((lane >> 3) ^ ((r >> 1) & 7)) << 4) + (lane & 7) * 2);
+    s += r < rows ? (float)v : 0.f;
+  }
+  return s;
+}
+
 // 16 bytes per lane from global memory straight into LDS at (base in M0) + 16 * lane
 __device__ __forceinline__ void dma16(const void* gptr, unsigned lds_base) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds_base), "v"(gptr) : "memory");

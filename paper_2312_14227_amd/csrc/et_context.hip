@@ -103,7 +103,8 @@ int build_vit(et_ctx* c) {
   {
     // per block: gain, shift and bias sums of both LayerNorms, the fc1 and qkv biases; largest group: three sums of one LayerNorm
     const size_t ln = std::max(sum_elems(et::layernorm_bwd_parts((int)M), D), sum_elems(et::colsum_parts((int)M, (int)D), D));
-    const size_t f1 = sum_elems(et::colsum_parts((int)M, (int)F), F), q = sum_elems(et::colsum_parts((int)M, (int)(3 * D)), 3 * D);
+    const size_t f1 = sum_elems((M + 31) / 32, F);
+    const size_t q = std::max(sum_elems(et::colsum_parts((int)M, (int)(3 * D)), 3 * D), sum_elems(et::attention_bwd_parts((int)B, (int)T), 3 * D));
     reserve_sums(c, (size_t)d.blocks * (6 * ln + f1 + q) + 4 * ln + sum_elems(et::colsum_parts((int)B, (int)C), C),
                  std::max(std::max(3 * ln, f1), std::max(q, sum_elems(et::colsum_parts((int)B, (int)C), C))));
   }
@@ -281,10 +282,11 @@ int vit_forward(et_ctx* c, const void* x, const int32_t* y, const uint8_t* mask)
   return ET_OK;
 }
 
-int vit_attention_backward(et_ctx* c, const VitDims& v, VitBlockBufs& b) {
+// part: where the fused core leaves the partial column sums of dqkv (the bias of the product in front of it), or null
+int vit_attention_backward(et_ctx* c, const VitDims& v, VitBlockBufs& b, float* part) {
   if (et::attention_fused_supported(v.T, v.dh)) {
     KernelTimer kt(c, 6, 8.0 * v.B * v.H * (double)v.T * v.T * v.dh);
-    ET_K(1, et::attention_bwd(b.qkv, b.o, c->dattn, b.lse, c->dqkv, v.B, v.T, v.H, v.dh, v.scale, c->stream));
+    ET_K(1, et::attention_bwd(b.qkv, b.o, c->dattn, b.lse, c->dqkv, v.B, v.T, v.H, v.dh, v.scale, c->stream, part));
     return ET_OK;
   }
   const long long sQo = (long long)v.T * 3 * v.D, sPo = (long long)v.H * v.T * v.ldT, sPi = (long long)v.T * v.ldT;
@@ -419,14 +421,18 @@ int vit_backward(et_ctx* c, const void* x, const uint8_t* mask) {
       Region r(c, PH_DW, t0 + 10);
       ET_G(linear_dw(c, c->dh16, ldD, b.ga, ldF, c->grad[t0 + 10], R, v.D, v.F));
     }
-    if (pass(t0 + 10)) {  // through fc2.W, then through the GELU (b.u holds gelu'(pre-activation))
-      Region r(c, PH_DY, t0 + 10);
+    if (pass(t0 + 10)) {  // through fc2.W, then through the GELU (b.u holds gelu'(pre-activation)); fc1.b's column sums on the way
       et::GemmDesc g = linear_dx(c->dh16, W(t0 + 10), R, v.D, v.F);
       g.lda = ldD; g.ldc = ldF;
       g.mode = et::EPI_GELU_BWD; g.U = b.u; g.C = c->du;
+      if (sel(t0 + 9)) {
+        const int parts = (R + 31) / 32;
+        if ((rc = sums_room(c, sum_elems(parts, v.F))) != ET_OK) return rc;
+        g.colsum = sum_job(c, t0 + 9, parts, v.F);
+      }
+      Region r(c, PH_DY, t0 + 10);
       ET_G(g);
     }
-    if (sel(t0 + 9) && (rc = colsum_dw(c, t0 + 9, c->du, nullptr, ldF, R, v.F)) != ET_OK) return rc;
     if (sel(t0 + 8)) {
       Region r(c, PH_DW, t0 + 8);
       ET_G(linear_dw(c, c->du, ldF, b.a2, ldD, c->grad[t0 + 8], R, v.F, v.D));
@@ -448,7 +454,13 @@ int vit_backward(et_ctx* c, const void* x, const uint8_t* mask) {
       Region r(c, PH_DW, t0 + 4);
       ET_G(linear_dw(c, c->dh16, ldD, b.o, ldD, c->grad[t0 + 4], R, v.D, v.D));
     }
-    if (pass(t0 + 4)) {  // through proj.W, then through the attention core
+    if (pass(t0 + 4)) {  // through proj.W, then through the attention core, which leaves the column sums of qkv.b
+      float* part = nullptr;
+      if (sel(t0 + 3) && cls) {
+        const int parts = few ? v.B : et::attention_bwd_parts(v.B, v.T);
+        if ((rc = sums_room(c, sum_elems(parts, 3 * v.D))) != ET_OK) return rc;
+        part = sum_job(c, t0 + 3, parts, 3 * v.D);
+      }
       Region r(c, PH_DY, t0 + 4);
       et::GemmDesc g = linear_dx(c->dh16, W(t0 + 4), R, v.D, v.D);
       g.lda = ldD; g.ldc = ldD;
@@ -456,12 +468,12 @@ int vit_backward(et_ctx* c, const void* x, const uint8_t* mask) {
       ET_G(g);
       if (few) {
         KernelTimer kt(c, 6, 8.0 * v.B * v.H * (double)v.T * v.dh);
-        ET_K(1, et::attention_bwd_cls(b.qkv, b.o, c->dattn, b.lse, c->dqkv, v.B, v.T, v.H, v.dh, v.scale, s));
-      } else if ((rc = vit_attention_backward(c, v, b)) != ET_OK) {
+        ET_K(1, et::attention_bwd_cls(b.qkv, b.o, c->dattn, b.lse, c->dqkv, v.B, v.T, v.H, v.dh, v.scale, s, part));
+      } else if ((rc = vit_attention_backward(c, v, b, part)) != ET_OK) {
         return rc;
       }
     }
-    if (sel(t0 + 3) && (rc = colsum_dw(c, t0 + 3, c->dqkv, nullptr, 3 * v.D, v.M, 3 * v.D)) != ET_OK) return rc;
+    if (sel(t0 + 3) && !cls && (rc = colsum_dw(c, t0 + 3, c->dqkv, nullptr, 3 * v.D, v.M, 3 * v.D)) != ET_OK) return rc;
     if (sel(t0 + 2)) {
       Region r(c, PH_DW, t0 + 2);
       ET_G(linear_dw(c, c->dqkv, 3 * v.D, b.a1, v.D, c->grad[t0 + 2], v.M, 3 * v.D, v.D));

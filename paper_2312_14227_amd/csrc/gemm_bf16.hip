@@ -373,6 +373,7 @@ hipError_t gemm_bf16(const GemmDesc& d, hipStream_t s, int* launches) {
   p.cH = d.conv_h; p.cW = d.conv_w; p.cC = d.conv_c;
   p.cT = stem ? 8 : d.conv_taps; p.cS = d.conv_stride; p.cHo = conv_ho; p.cWo = conv_wo;
   p.act_lo = d.act_lo; p.act_hi = d.act_hi; p.mask_hi = d.mask_hi;
+  p.colsum = d.colsum;
   int zdim = d.z_outer * d.z_inner;
   int epi;
   int k_per_block = d.K;
@@ -414,7 +415,7 @@ hipError_t gemm_bf16(const GemmDesc& d, hipStream_t s, int* launches) {
       if (!d.U || d.c_f32 || d.residual || d.bias || !aligned(d.U, 8)) return hipErrorInvalidValue;
       epi = gemm::E_RELU_MASK;
     } else if (d.mode == EPI_GELU_BWD) {
-      if (!d.U || d.c_f32 || d.residual || d.bias || !aligned(d.U, 8)) return hipErrorInvalidValue;
+      if (!d.U || d.c_f32 || d.residual || d.bias || !aligned(d.U, 8) || (d.colsum && zdim != 1)) return hipErrorInvalidValue;
       epi = gemm::E_GELU_BWD;
     } else if (d.c_f32) {
       epi = d.residual ? gemm::E_F32_RES : gemm::E_F32;

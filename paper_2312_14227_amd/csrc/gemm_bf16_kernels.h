@@ -84,6 +84,7 @@ struct Params {
   const bf16* U;
   float act_lo, act_hi;  // E_AFFINE, E_AFFINE_ADD: the activation is a clamp to [act_lo, act_hi] (0, +inf: ReLU; 0, 6: ReLU6; -inf, +inf: none)
   float mask_hi;         // E_RELU_MASK passes where 0 < U < mask_hi
+  float* colsum;         // E_GELU_BWD (nullable): column sums of the stored C over every 32 rows, [(M + 31) / 32][N]
   int cH, cW, cC;        // implicit convolution (gemm_pp_kernel<.., CONV>): input height, width, channels;
   int cT, cS, cHo, cWo;  // taps per side (3, or 1 for a strided 1x1), stride, output height and width
 };
@@ -404,6 +405,7 @@ __device__ __forceinline__ void wave_epilogue_impl(const Params& g, f32x16 (&acc
       float4 rd[ITERS];
 #pragma unroll
       for (int it = 0; it < ITERS; it++) rd[it] = *(const float4*)(stf + min(it * RPI + rsub, 31) * PITCH + c4);
+      float csum[EPI == E_GELU_BWD ? 4 : 1] = {};   // this lane's columns of the stored result, summed over its rows of the block
       if (col_any) {
         long long ci = ci0;
 #pragma unroll
@@ -449,7 +451,10 @@ __device__ __forceinline__ void wave_epilogue_impl(const Params& g, f32x16 (&acc
             } else {
               bf16x4 o;
 #pragma unroll
-              for (int j = 0; j < 4; j++) o[j] = (bf16)v[j];
+              for (int j = 0; j < 4; j++) {
+                o[j] = (bf16)v[j];
+                if (EPI == E_GELU_BWD) csum[EPI == E_GELU_BWD ? j : 0] += (float)o[j];
+              }
               *(bf16x4*)((bf16*)g.C + ci) = o;
             }
           } else {  // ragged right edge: element by element
@@ -467,8 +472,27 @@ __device__ __forceinline__ void wave_epilogue_impl(const Params& g, f32x16 (&acc
                 g.C2[ci + j] = (bf16)fminf(fmaxf(((float)z * gain[j] + bias[j]) + ((float)g.U[ci + j] * gain2[j] + bias2[j]), g.act_lo), g.act_hi);
               } else {
                 ((bf16*)g.C)[ci + j] = (bf16)x;
+                if (EPI == E_GELU_BWD) csum[EPI == E_GELU_BWD ? j : 0] += (float)(bf16)x;
               }
             }
+          }
+        }
+      }
+      if constexpr (EPI == E_GELU_BWD) {
+        if (g.colsum && row0 + mi * 32 < g.M) {   // the lanes of one column quadruple, added in row order
+          if (rsub < RPI) *(float4*)(stf + rsub * PITCH + c4) = make_float4(csum[0], csum[1], csum[2], csum[3]);
+          float4 s = *(const float4*)(stf + c4);
+#pragma unroll
+          for (int k = 1; k < RPI; k++) {
+            const float4 t = *(const float4*)(stf + k * PITCH + c4);
+            s.x += t.x; s.y += t.y; s.z += t.z; s.w += t.w;
+          }
+          if (rsub == 0 && col_any) {
+            float* out = g.colsum + (long long)((row0 + mi * 32) >> 5) * g.N + col;
+            const float v[4] = {s.x, s.y, s.z, s.w};
+#pragma unroll
+            for (int j = 0; j < 4; j++)
+              if (FULL || col + j < g.N) out[j] = v[j];
           }
         }
       }

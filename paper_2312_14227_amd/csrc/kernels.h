@@ -59,6 +59,7 @@ struct GemmDesc {
   int ldc = 0;
   bool c_f32 = false;
   bf16* C2 = nullptr;              // EPI_GELU_FWD
+  float* colsum = nullptr;         // EPI_GELU_BWD (nullable): (M + 31) / 32 rows of N partial column sums of C as rounded, over 32 rows each
   const bf16* U = nullptr;         // EPI_GELU_BWD, EPI_AFFINE_ADD_RELU, EPI_RELU_MASK: same leading dimension as C
   // implicit convolution (conv_c > 0), 3x3 with zero padding 1 (conv_taps = 3) or 1x1 (conv_taps = 1), stride
   // conv_stride (1 or 2): A is the NHWC activation [batch, conv_h, conv_w, conv_c] itself, standing for its im2col
@@ -173,15 +174,19 @@ hipError_t softmax_bwd_rows(const float* dp, const bf16* p, bf16* ds, float scal
 bool attention_fused_supported(int T, int head_dim);
 hipError_t attention_fwd(const bf16* qkv, bf16* out, float* lse, int B, int T, int H, int head_dim, float scale,
                          hipStream_t s);
+// part (nullable): attention_bwd_parts(B, T) rows of partial sums over the rows of dqkv, 3 * 64 H columns each
 hipError_t attention_bwd(const bf16* qkv, const bf16* out, const bf16* dout, const float* lse, bf16* dqkv, int B, int T, int H,
-                         int head_dim, float scale, hipStream_t s);
-// backward when only the first token's row of dout is read (the others are zeros that need not be stored): dqkv complete
+                         int head_dim, float scale, hipStream_t s, float* part = nullptr);
+int attention_bwd_parts(int B, int T);
+// backward when only the first token's row of dout is read (the others are zeros that need not be stored): dqkv complete; part
+// (nullable): B rows of partial sums
 hipError_t attention_bwd_cls(const bf16* qkv, const bf16* out, const bf16* dout, const float* lse, bf16* dqkv, int B, int T, int H,
-                             int head_dim, float scale, hipStream_t s);
+                             int head_dim, float scale, hipStream_t s, float* part = nullptr);
 // the same for sequences of any length, streamed (attention_fwd / _bwd choose)
 hipError_t attention_long_fwd(const bf16* qkv, bf16* out, float* lse, int B, int T, int H, float scale, hipStream_t s);
 hipError_t attention_long_bwd(const bf16* qkv, const bf16* out, const bf16* dout, const float* lse, bf16* dqkv, int B, int T, int H,
-                              float scale, hipStream_t s);
+                              float scale, hipStream_t s, float* part = nullptr);
+int attention_long_bwd_parts(int B, int T);
 
 // mean softmax cross-entropy: dlogits fp32 and (if not null) a bf16 copy [B][ld16], zero padded; `loss` points to
 // 64 + B floats: the loss in element 0, the per-row terms from element 64 on (two launches)
