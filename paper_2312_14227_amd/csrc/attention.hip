@@ -272,8 +272,8 @@ __global__ __launch_bounds__(NTHREADS) void attention_bwd_kernel(const bf16* __r
           dq[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_rows_tr(sk, kt * 32 + j * 16, dt * 32, lane), dsf, dq[dt], 0, 0, 0);
       }
     }
-    store_tile(s_store + wave * STORE_AREA, dq, scale, dqkv + ((long long)b * T + qt * 32) * ld + h * DH, ld, T - qt * 32, lane);
-    if (part) s_sum[0][qt][lane] = tile_colsum(s_store + wave * STORE_AREA, T - qt * 32, lane);
+    store_tile(s_store + wave * STORE_AREA, dq, scale, dqkv + ((long long)b * T + qt * 32) * ld + h * DH, ld, T - qt * 32, lane,
+               part ? s_sum[0][qt] : nullptr);
   }
   __syncthreads();
 
@@ -329,10 +329,8 @@ __global__ __launch_bounds__(NTHREADS) void attention_bwd_kernel(const bf16* __r
       }
     }
     bf16* drow0 = dqkv + ((long long)b * T + kt * 32) * ld + h * DH;
-    store_tile(s_store + wave * STORE_AREA, dk, scale, drow0 + D, ld, T - kt * 32, lane);
-    if (part) s_sum[1][kt][lane] = tile_colsum(s_store + wave * STORE_AREA, T - kt * 32, lane);
-    store_tile(s_store + wave * STORE_AREA, dv, 1.f, drow0 + 2 * D, ld, T - kt * 32, lane);
-    if (part) s_sum[2][kt][lane] = tile_colsum(s_store + wave * STORE_AREA, T - kt * 32, lane);
+    store_tile(s_store + wave * STORE_AREA, dk, scale, drow0 + D, ld, T - kt * 32, lane, part ? s_sum[1][kt] : nullptr);
+    store_tile(s_store + wave * STORE_AREA, dv, 1.f, drow0 + 2 * D, ld, T - kt * 32, lane, part ? s_sum[2][kt] : nullptr);
   }
   if (!part) return;
   __syncthreads();

@@ -211,9 +211,9 @@ __global__ __launch_bounds__(LTHREADS) void attention_long_bwd_kernel(const bf16
         }
       }
     }
-    store_tile(area, dq, scale, dqkv + ((long long)b * T + own0) * ld + h * DH, ld, T - own0, lane);
+    store_tile(area, dq, scale, dqkv + ((long long)b * T + own0) * ld + h * DH, ld, T - own0, lane,
+               part ? s_sum[0][wave] : nullptr);
     if (!part) return;
-    s_sum[0][wave][lane] = tile_colsum(area, T - own0, lane);
     __syncthreads();
     if (tid < DH) {   // row (b, blk) of the partial sums [B * blocks][3 D]
       float s = s_sum[0][0][tid];
@@ -296,11 +296,9 @@ __global__ __launch_bounds__(LTHREADS) void attention_long_bwd_kernel(const bf16
     }
   }
   bf16* drow0 = dqkv + ((long long)b * T + own0) * ld + h * DH;
-  store_tile(area, dk, scale, drow0 + D, ld, T - own0, lane);
-  if (part) s_sum[0][wave][lane] = tile_colsum(area, T - own0, lane);
-  store_tile(area, dv, 1.f, drow0 + 2 * D, ld, T - own0, lane);
+  store_tile(area, dk, scale, drow0 + D, ld, T - own0, lane, part ? s_sum[0][wave] : nullptr);
+  store_tile(area, dv, 1.f, drow0 + 2 * D, ld, T - own0, lane, part ? s_sum[1][wave] : nullptr);
   if (!part) return;
-  s_sum[1][wave][lane] = tile_colsum(area, T - own0, lane);
   __syncthreads();
   if (tid < 2 * DH) {
     const int which = tid / DH, col = tid % DH;

@@ -61,8 +61,11 @@ __device__ __forceinline__ int tile_row(int r, int lane) { return (r >> 2) * 8 +
 // leaves as whole 128-byte rows, 8 lanes x 16 bytes each.  LDS instructions of one wave execute in order, so no
 // barrier is needed between the writes and the reads, nor between two tiles through the same area.
 constexpr int STORE_AREA = 32 * 128;
+// `sums` (nullable, wave-private, in LDS): receives the column sums of the stored rows, 64 floats, as rounded.  Each lane adds the
+// pieces it stores, then the eight lanes of a column share out the adding (7 shuffles): 2 us of a launch of 64 x 12 heads
+// where another pass over dQ, dK and dV took 8.5, and 32 two-byte reads per column 6.5.
 __device__ __forceinline__ void store_tile(unsigned char* area, const f32x16 (&t)[2], float mul, bf16* base, long long ld,
-                                           int rows, int lane) {
+                                           int rows, int lane, float* sums = nullptr) {
   asm volatile("" : "+v"(lane));   // (addresses below are computed here, not kept live through the caller's main loop)
   const int l32 = lane & 31, khalf = lane >> 5;
 #pragma unroll
@@ -74,25 +77,25 @@ __device__ __forceinline__ void store_tile(unsigned char* area, const f32x16 (&t
       for (int e = 0; e < 4; e++) v[e] = (bf16)(t[dt][a * 4 + e] * mul);
       *(bf16x4*)(area + l32 * 128 + (((dt * 4 + a) ^ ((l32 >> 1) & 7)) << 4) + khalf * 8) = v;
     }
+  float s8[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
   for (int i = 0; i < 4; i++) {
     const int row = i * 8 + (lane >> 3), chunk = lane & 7;
     const bf16x8 v = *(const bf16x8*)(area + row * 128 + ((chunk ^ ((row >> 1) & 7)) << 4));
     if (row < rows) *(bf16x8*)(base + row * ld + chunk * 8) = v;
-  }
-}
-
-// Column sum of the tile that store_tile has just left in `area` (rows below `rows`): lane l returns that of column l.  The
-// rounded values are added, those that a sum over the stored matrix would read; 32 two-byte LDS reads per tile instead of
-// another pass over dQ, dK and dV (8.5 us per layer for 12 608 x 2304).
-__device__ __forceinline__ float tile_colsum(const unsigned char* area, int rows, int lane) {
-  float s = 0.f;
+    if (sums && row < rows)
 #pragma unroll
-  for (int r = 0; r < 32; r++) {
-    const bf16 v = *(const bf16*)(area + r * 128 + (((lane >> 3) ^ ((r >> 1) & 7)) << 4) + (lane & 7) * 2);
-    s += r < rows ? (float)v : 0.f;
+      for (int e = 0; e < 8; e++) s8[e] += (float)v[e];
   }
-  return s;
+  if (!sums) return;
+  const bool b5 = lane & 32, b4 = lane & 16, b3 = lane & 8;
+  float s4[4], s2[2];
+#pragma unroll
+  for (int e = 0; e < 4; e++) s4[e] = (b5 ? s8[e + 4] : s8[e]) + __shfl_xor(b5 ? s8[e] : s8[e + 4], 32, 64);
+#pragma unroll
+  for (int e = 0; e < 2; e++) s2[e] = (b4 ? s4[e + 2] : s4[e]) + __shfl_xor(b4 ? s4[e] : s4[e + 2], 16, 64);
+  const float s1 = (b3 ? s2[1] : s2[0]) + __shfl_xor(b3 ? s2[0] : s2[1], 8, 64);
+  sums[(lane & 7) * 8 + (b5 ? 4 : 0) + (b4 ? 2 : 0) + (b3 ? 1 : 0)] = s1;
 }
 
 // 16 bytes per lane from global memory straight into LDS at (base in M0) + 16 * lane
