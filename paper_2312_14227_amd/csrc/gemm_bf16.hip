@@ -1,5 +1,6 @@
 // Host side of the bf16 MFMA GEMM: argument checks, tile choice, split-K reduction.
 #include <algorithm>
+#include <cmath>
 
 #include "gemm_bf16_kernels.h"
 #include "gemm_bf16_ring.h"
@@ -232,6 +233,35 @@ const RingTile kRingConv[4] = {{T_RING_64x64, 64, 64, 0.28e-6, 0.19e-6, 0.5e-6},
 const RingTile kRingConvDw[3] = {{T_RING_64x64, 64, 64, 0.365e-6, 0.24e-6, 0.5e-6}, {T_RING_64x128, 64, 128, 0.46e-6, 0.36e-6, 1.0e-6},
                                  {T_RING_128x64, 128, 64, 0.36e-6, 0.34e-6, 1.0e-6}};
 
+// Large products with K in slices of 64, one batch entry: rounds of workgroups x (slices x time per slice + fixed part), us, in a
+// launch of its own but for 2 us that all share.  A slice of a two-group tile takes longer the more CUs are at work (the clock
+// follows the load), one of a 64x128 ring tile the more rounds there are (its operand re-reads); with an fp32
+// residual and result beside them the operands come from further away, which costs a two-group tile, one slice ahead, some per
+// slice and a ring tile little.  Against the rule
+// before (two-group tiles only), 138 shapes of [3152 .. 12608 rows] x [512 .. 4096] x [512 .. 4096] took 5351 us and take 5020, the
+// best of five tiles each 5006; [3152 x 768 x 3072] 47.3 -> 29.1 us, [6304 x 512 x 2048] 34.4 -> 22.1, [4616 x 768 x 3072] with
+// residual 54.9 -> 36.1, [6304 x 1024 x 4096] with residual 91.7 -> 84.5.
+int choose_large_tile(const GemmDesc& d, int K) {
+  struct Cand { int tile, bm, bn; double slice, per_cu, per_round, solo, fixed; };
+  static const Cand cand[5] = {{T_PP_256x256, 256, 256, 0.65, 0.0045, 0.0, 0.0, 6.4}, {T_PP_256x192, 256, 192, 0.72, 0.0023, 0.0, 0.0, 7.5},
+                               {T_PP_256x128, 256, 128, 0.75, 0.0008, 0.0, 0.0, 7.0},
+                               {T_RING_64x128, 64, 128, 0.30, 0.0, 0.01, 0.36, 1.2}, {T_RING_128x128, 128, 128, 0.56, 0.0, 0.0, 0.53, 2.8}};
+  const bool gelu = d.mode == EPI_GELU_FWD || d.mode == EPI_GELU_BWD || d.mode == EPI_GELU_ONLY;
+  const int slices = K / gemm::PBK;
+  int best = T_PP_256x256;
+  double least = 1e30;
+  for (const Cand& c : cand) {
+    const bool ring = c.solo > 0.0;
+    if (c.tile == T_PP_256x128 && gelu) continue;   // (not built)
+    const double tiles = (double)((d.M + c.bm - 1) / c.bm) * ((d.N + c.bn - 1) / c.bn), rounds = std::ceil(tiles / 256.0);
+    const double slice = ring && rounds == 1.0 ? c.solo : c.slice + c.per_cu * tiles / rounds + c.per_round * rounds;
+    double t = rounds * (slices * slice + c.fixed);
+    if (d.residual) t += ring ? 8.0 * d.M * d.N / 9e6 : 0.33 * slices;
+    if (t < least) { least = t; best = c.tile; }
+  }
+  return best;
+}
+
 int choose_tile(const GemmDesc& d, int k_per_block) {
   const bool dma_ok = (d.K % gemm::DBK) == 0 && (k_per_block % gemm::DBK) == 0;
   const bool pp_ok = (d.K % gemm::PBK) == 0 && (k_per_block % gemm::PBK) == 0;
@@ -239,18 +269,15 @@ int choose_tile(const GemmDesc& d, int k_per_block) {
   if (d.tile == T_PP_256x128 || d.tile == T_PP_512x64 || d.tile == T_PP_128x256 || d.tile == T_PP_64x512) return pp_ok ? d.tile : T_128x128;
   if (d.tile == T_DMA_256x256 || d.tile == T_DMA_256x128) return dma_ok ? d.tile : T_128x128;
   if (d.tile != T_AUTO) return d.tile;
-  // large problems (8 GFLOP and more, a ViT-L layer at batch 32 has 13): a two-group tile where K comes in slices of 64
-  // (4-20 % faster than either direct-to-LDS tile on every forward, passing and gradient product of the ViT shapes),
-  // else the direct-to-LDS tile with slices of 32.  Too few 256x256 tiles to fill the 256 CUs: the 256x128 tile
-  // (13 % faster there than 256x192).  The GELU forward epilogues cost a 256x256 tile as much as half its main loop;
-  // two 256x128 direct-to-LDS workgroups per CU that overlap one's epilogue with the other's MFMAs run no faster than
-  // the resident two-group tile (101.7 against 101.3 us for the ViT-B fc1 product).
+  // large problems (8 GFLOP and more, a ViT-L layer at batch 32 has 13): the tile with the least estimated time where K comes
+  // in slices of 64, else the direct-to-LDS tile with slices of 32.  The GELU forward epilogues cost a 256x256 tile as much
+  // as half its main loop; two 256x128 direct-to-LDS workgroups per CU that overlap one's epilogue with the other's MFMAs run no
+  // faster than the resident two-group tile (101.7 against 101.3 us for the ViT-B fc1 product).
   const int batch = d.z_outer * d.z_inner;
   if (d.M >= 512 && d.N >= 256 && 2.0 * d.M * d.N * (double)k_per_block * batch >= 8e9) {
     const long long big_tiles = (long long)((d.M + 255) / 256) * ((d.N + 255) / 256) * batch;
-    const bool gelu = d.mode == EPI_GELU_FWD || d.mode == EPI_GELU_BWD || d.mode == EPI_GELU_ONLY;
     if (pp_ok && k_per_block >= 4 * gemm::PBK)
-      return big_tiles < 128 && !gelu && batch == 1 ? (int)T_PP_256x128 : plan_large(d.M, d.N, k_per_block, false).tile;
+      return batch == 1 ? choose_large_tile(d, k_per_block) : plan_large(d.M, d.N, k_per_block, false).tile;
     if (dma_ok && k_per_block >= 4 * gemm::DBK && big_tiles >= 128) return d.N >= 2560 ? T_DMA_256x128 : T_DMA_256x256;
   }
   return plan_small(d.M, d.N, k_per_block, batch * std::max(1, d.split_k)).tile;
