@@ -96,17 +96,20 @@ inline bool implicit_dw(const et_ctx*, const ConvUnit& u) {
   return gathered_kind(u) && (u.Cin % 8) == 0 && u.H < 4096 && u.W < 4096;
 }
 // tile and split of a unit's implicit forward (or, with the channel roles exchanged, gradient-passing) product
-inline void plan_implicit(et_ctx* c, et::GemmDesc& g) {
-  et::gemm_bf16_plan_conv(g.M, g.N, g.K, &g.tile, &g.split_k);
+// (a plain stack's forward pass has `fixed_sums`: in front of a max pooling, near-ties of bf16 values are decided by the last bit,
+// and with another order of the sums another tap wins here and there, which moves gradients by some per cent; so the order
+// stays that of one plan while the tile is free)
+inline void plan_implicit(et_ctx* c, et::GemmDesc& g, bool fixed_sums = false) {
+  et::gemm_bf16_plan_conv(g.M, g.N, g.K, &g.tile, &g.split_k, fixed_sums);
   g.partials = c->gemm_partials;
   if (et::gemm_bf16_partial_elems(g.M, g.N, g.split_k) > c->gemm_partial_elems) g.split_k = 1;
 }
-inline size_t conv_split_partials(const et_ctx* c, const ConvUnit& u) {
+inline size_t conv_split_partials(const et_ctx* c, const ConvUnit& u, bool fixed_sums = false) {
   size_t n = 0;
   int tile, split;
   const int M = (int)rows_of(c, u);
   if (implicit_fwd(u)) {
-    et::gemm_bf16_plan_conv(M, u.Cout, u.k * u.k * u.Cin, &tile, &split);
+    et::gemm_bf16_plan_conv(M, u.Cout, u.k * u.k * u.Cin, &tile, &split, fixed_sums);
     n = std::max(n, et::gemm_bf16_partial_elems(M, u.Cout, split));
   }
   if (implicit_dy(u)) {

@@ -203,13 +203,14 @@ Plan plan_small(int M, int N, int K, int count) {
 struct RingTile { int tile, bm, bn; double solo, loaded, fixed; };
 
 template <int N_TILES>
-Plan plan_ring(int M, int N, int K, bool may_split, double operand_elems, const RingTile (&tiles)[N_TILES]) {
+Plan plan_ring(int M, int N, int K, bool may_split, double operand_elems, const RingTile (&tiles)[N_TILES], int only_split = 0) {
   const int slices = (K + gemm::PBK - 1) / gemm::PBK;
   const double stream = 2.0 * operand_elems / 4e12;
   const int max_split = may_split && (N & 3) == 0 ? std::max(1, std::min(256, slices / 4)) : 1;
   Plan best = {T_RING_64x64, 1, 1e30};
   for (const RingTile& r : tiles)
     for (int s = 1; s <= max_split; s++) {
+      if (only_split && s != only_split) continue;
       const int per = (slices + s - 1) / s;
       if ((slices + per - 1) / per != s) continue;   // this split leaves empty chunks
       const long long units = (long long)((M + r.bm - 1) / r.bm) * ((N + r.bn - 1) / r.bn) * s;
@@ -293,10 +294,12 @@ size_t gemm_bf16_partial_elems(int M, int N, int split_k) { return split_k > 1 ?
 // 56x56x64 43.5 / 23, 224x224x64 390 / 195, but 14x14x512 52 / 54, 56x56 128 -> 256 81 / 110.
 static bool conv_on_ring(int rows, int channels, int K, double most) { return channels <= 64 || 2.0 * rows * channels * (double)K < most; }
 
-void gemm_bf16_plan_conv(int M, int N, int K, int* tile, int* split_k) {
+void gemm_bf16_plan_conv(int M, int N, int K, int* tile, int* split_k, bool fixed_sums) {
   static const TileRate cand[4] = {{T_PP_256x256, 256, 256, 4.5e12}, {T_PP_256x192, 256, 192, 4.0e12},
                                    {T_PP_256x128, 256, 128, 3.3e12}, {T_PP_512x64, 512, 64, 2.6e12}};
-  const Plan pl = conv_on_ring(M, N, K, 3.2e10) ? plan_ring(M, N, K, true, K / 9.0 * M + (double)N * K, kRingConv) : plan_tiles(M, N, K, (N & 3) == 0, cand, 4);
+  const bool ring = conv_on_ring(M, N, K, 3.2e10);
+  const Plan wide = !ring || fixed_sums ? plan_tiles(M, N, K, (N & 3) == 0, cand, 4) : Plan{T_AUTO, 0, 0.0};
+  const Plan pl = ring ? plan_ring(M, N, K, true, K / 9.0 * M + (double)N * K, kRingConv, wide.split) : wide;
   *tile = pl.tile;
   *split_k = pl.split;
 }

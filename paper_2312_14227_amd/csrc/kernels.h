@@ -82,7 +82,8 @@ size_t gemm_bf16_partial_elems(int M, int N, int split_k);
 void gemm_bf16_plan_split(int M, int N, int K, int* tile, int* split_k);
 // the same for the implicit forward / gradient-passing 3x3 convolution [M pixels][N channels], K = 9 input channels:
 // layers with few pixels split the reduction, and a second kernel sums the parts and applies the epilogue
-void gemm_bf16_plan_conv(int M, int N, int K, int* tile, int* split_k);
+// fixed_sums: the split, and with it the order of every sum, is that of the plan for the wide tiles whichever tile is chosen
+void gemm_bf16_plan_conv(int M, int N, int K, int* tile, int* split_k, bool fixed_sums = false);
 // the same for the implicit weight gradient of a 3x3 convolution (M output channels, N = 9 input channels, K pixels)
 void gemm_bf16_plan_conv_dw(int M, int N, int K, int* tile, int* split_k);
 

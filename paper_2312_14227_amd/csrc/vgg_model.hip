@@ -92,7 +92,7 @@ int build_vgg(et_ctx* c) {
     if (!implicit_dw(c, u) || !implicit_dy(u)) max_cols = std::max(max_cols, M * u.Kc);
     if (i > 0 && !implicit_dy(u)) dcols_b = std::max(dcols_b, dcols_bytes(c, u));   // conv0 passes nothing on
     bias_sum(M, u.Cout);
-    pe = std::max(pe, std::max(conv_dw_partials(c, u), conv_split_partials(c, u)));
+    pe = std::max(pe, std::max(conv_dw_partials(c, u), conv_split_partials(c, u, true)));
     const bool last_of_stage = i + 1 == c->vconv.size() || c->vstage[i + 1] != c->vstage[i];
     if (last_of_stage) {
       reserve(c, &c->vpool[c->vstage[i]], b16 * (M / 4) * u.Cout);
@@ -151,7 +151,7 @@ int vgg_forward(et_ctx* c, const void* x, const int32_t* y) {
     g.mode = et::EPI_BIAS_RELU; g.C = u.y;
     if (implicit_fwd(u)) {
       g.A = h; g.conv_h = u.H; g.conv_w = u.W; g.conv_c = u.Cin;
-      plan_implicit(c, g);
+      plan_implicit(c, g, true);
     } else {
       ET_KB(1, 2.0 * ((double)M * u.Cin + (double)M * u.Kc), et::im2col(h, u.cols, geom(c, u), s));
     }
