@@ -84,6 +84,12 @@ size_t et_debug_depthwise3x3_ws_floats(int batch, int H, int W, int C, int strid
 int et_debug_depthwise3x3(int op, const void* a, const void* b, const void* gain, const void* shift, void* out0, void* out1,
                           float* ws, int batch, int H, int W, int C, int stride, void* stream);
 
+/* First 3x3 convolution of a chain (zero padding 1, stride 1 or 2, C <= 3): x bf16 [batch][H][W][C], w bf16 [N][3][3][C], N a multiple
+ * of 8.  With gain: z (nullable) = the convolution as rounded, y = min(max(z * gain + shift, lo), hi); without: y =
+ * max(convolution + shift, 0); both bf16 [batch][Ho][Wo][N].  Device pointers, 16-byte aligned.  Returns 0, -1, -3 as above. */
+int et_debug_conv_first(const void* x, const void* w, const void* gain, const void* shift, void* z, void* y, int batch, int H, int W,
+                        int C, int N, int stride, float lo, float hi, void* stream);
+
 /* Mirrored weights out[c][8 - tap][o] = w[o][tap][c] of n convolutions in one launch: w[i] bf16 [O[i]][9][C[i]], out[i] bf16
  * [C[i]][9][O[i]], O and C multiples of 8; host arrays of device pointers, 16-byte aligned.  Returns 0, -1, -3 as above. */
 int et_debug_flip3x3(const void* const* w, void* const* out, const int* O, const int* C, int n, void* stream);

@@ -182,6 +182,18 @@ extern "C" int et_debug_depthwise3x3(int op, const void* a, const void* b, const
   return e == hipSuccess ? ET_OK : ET_EHIP;
 }
 
+extern "C" int et_debug_conv_first(const void* x, const void* w, const void* gain, const void* shift, void* z, void* y, int batch, int H,
+                                   int W, int C, int N, int stride, float lo, float hi, void* stream) {
+  if (stride != 1 && stride != 2) return ET_EINVAL;
+  typedef const et::bf16* P;
+  et::ConvGeom g = {};
+  g.B = batch; g.H = H; g.W = W; g.C = C; g.k = 3; g.stride = stride; g.pad = 1;
+  g.Ho = (H - 1) / stride + 1; g.Wo = (W - 1) / stride + 1;
+  const hipError_t e = et::conv_first((P)x, (P)w, g, N, (P)gain, (P)shift, (et::bf16*)z, (et::bf16*)y, lo, hi, (hipStream_t)stream);
+  if (e == hipErrorInvalidValue) return ET_EINVAL;
+  return e == hipSuccess ? ET_OK : ET_EHIP;
+}
+
 extern "C" int et_debug_flip3x3(const void* const* w, void* const* out, const int* O, const int* C, int n, void* stream) {
   if (!w || !out || !O || !C || n < 1) return ET_EINVAL;
   std::vector<et::FlipJob> jobs;

@@ -214,6 +214,11 @@ struct ConvGeom {
 };
 // cols[B*Ho*Wo][Kc], column order (ky, kx, c); out-of-image taps and the row tail are zero
 hipError_t im2col(const bf16* x, bf16* cols, const ConvGeom& g, hipStream_t s);
+// first convolution of a chain (3x3, at most three input channels), no column matrix.  w [N][3][3][C].  With gain: z (nullable) =
+// the convolution as rounded, y = clamp(z * gain + shift, lo, hi); without: y = max(convolution + shift, 0)
+bool conv_first_supported(int k, int C);
+hipError_t conv_first(const bf16* x, const bf16* w, const ConvGeom& g, int N, const bf16* gain, const bf16* shift, bf16* z, bf16* y, float lo,
+                      float hi, hipStream_t s);
 // out[B][H][W][C] = (adjoint of im2col applied to dcols  + add) * (mask > 0); add, mask nullable; C % 8 == 0;
 // dcols is float32 [B*Ho*Wo][Kc] (dcols_f32) or bf16; the taps are added in float32, the result is rounded once
 hipError_t col2im(const void* dcols, bool dcols_f32, const bf16* add, const bf16* mask, bf16* out, const ConvGeom& g,

@@ -149,7 +149,11 @@ int mobilenet_forward(et_ctx* c, const void* x, const int32_t* y, const uint8_t*
   auto keep = [&](bf16* z, int gain_index) -> bf16* { return (!mask || mask[gain_index]) ? z : nullptr; };
   const int B = d.batch;
   int rc;
-  {  // stem: 3x3 / stride 2 convolution over the im2col matrix (rows padded to 16 bytes), affine, ReLU6
+  if (et::conv_first_supported(c->stem.k, c->stem.Cin)) {   // stem: 3x3 / stride 2, affine, ReLU6
+    ConvUnit& u = c->stem;
+    ET_KB(1, 2.0 * ((double)B * u.H * u.W * u.Cin + (double)rows_of(c, u) * u.Cout),
+          et::conv_first((const bf16*)x, Wt(0), geom(c, u), u.Cout, Wt(1), Wt(2), keep(u.z, 1), u.y, 0.f, 6.f, s));
+  } else {   // more input channels: over the im2col matrix (rows padded to 16 bytes)
     ConvUnit& u = c->stem;
     const size_t M = rows_of(c, u);
     ET_K(1, et::pad_rows(Wt(0), c->stem_w8, u.Cout, 9 * u.Cin, u.Kc, s));
@@ -321,10 +325,11 @@ int mobilenet_backward(et_ctx* c, const void* x, const uint8_t* mask) {
     if ((rc = affine_back(1, out, u.z, c->rd[0], M, u.Cout)) != ET_OK) return rc;
     if (sel(0)) {
       Region r(c, PH_DW, 0);
+      if (et::conv_first_supported(u.k, u.Cin))   // (the forward pass has written no column matrix)
+        ET_KB(1, 2.0 * ((double)B * u.H * u.W * u.Cin + (double)M * u.Kc), et::im2col((const bf16*)x, u.cols, geom(c, u), s));
       ET_G(linear_dw(c, c->rd[0], u.Cout, u.cols, u.Kc, c->stem_dw8, (int)M, u.Cout, u.Kc));
       ET_K(1, et::strip_rows(c->stem_dw8, c->grad[0], u.Cout, 9 * u.Cin, u.Kc, s));
     }
   }
-  (void)x;
   return ET_OK;
 }

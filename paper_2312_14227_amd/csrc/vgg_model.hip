@@ -146,16 +146,20 @@ int vgg_forward(et_ctx* c, const void* x, const int32_t* y) {
     ConvUnit& u = c->vconv[i];
     const size_t M = rows_of(c, u);
     u.in = h;
-    if (u.Kc != 9 * u.Cin) ET_K(1, et::pad_rows(Wt(u.t), c->stem_w8, u.Cout, 9 * u.Cin, u.Kc, s));
+    const bool first = et::conv_first_supported(u.k, u.Cin);   // (the column matrix is then written by dw(), if that runs)
+    if (u.Kc != 9 * u.Cin && !first) ET_K(1, et::pad_rows(Wt(u.t), c->stem_w8, u.Cout, 9 * u.Cin, u.Kc, s));
     et::GemmDesc g = linear_fwd(u.cols, conv_matrix(c, i), Wt(u.t + 1), (int)M, u.Cout, u.Kc);
     g.mode = et::EPI_BIAS_RELU; g.C = u.y;
     if (implicit_fwd(u)) {
       g.A = h; g.conv_h = u.H; g.conv_w = u.W; g.conv_c = u.Cin;
       plan_implicit(c, g, true);
-    } else {
+    } else if (!first) {
       ET_KB(1, 2.0 * ((double)M * u.Cin + (double)M * u.Kc), et::im2col(h, u.cols, geom(c, u), s));
     }
-    ET_G(g);
+    if (first)
+      ET_KB(1, 2.0 * (double)M * (u.Cin + u.Cout), et::conv_first(h, Wt(u.t), geom(c, u), u.Cout, nullptr, Wt(u.t + 1), nullptr, u.y, 0.f, 0.f, s));
+    else
+      ET_G(g);
     h = u.y;
     if (i + 1 == c->vconv.size() || c->vstage[i + 1] != c->vstage[i]) {
       const int st = c->vstage[i];
@@ -247,6 +251,8 @@ int vgg_backward(et_ctx* c, const void* x, const uint8_t* mask) {
     }
     if (sel(t)) {
       Region r(c, PH_DW, t);
+      if (et::conv_first_supported(u.k, u.Cin))
+        ET_KB(1, 2.0 * ((double)M * u.Cin + (double)M * u.Kc), et::im2col((const bf16*)x, u.cols, geom(c, u), s));
       if (u.Kc == 9 * u.Cin) {
         if ((rc = conv_dw(c, u, u.in, dcur, c->grad[t])) != ET_OK) return rc;
       } else {
@@ -278,6 +284,5 @@ int vgg_backward(et_ctx* c, const void* x, const uint8_t* mask) {
       dcur = dn;
     }
   }
-  (void)x;
   return ET_OK;
 }
