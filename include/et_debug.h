@@ -118,6 +118,10 @@ int et_debug_attention(int op, const void* qkv, void* out, float* lse, const voi
 /* The same through the streaming kernels, for any number of tokens (the training step uses them beyond 224). */
 int et_debug_attention_long(int op, const void* qkv, void* out, float* lse, const void* dout, void* dqkv, int B, int T, int H,
                             void* stream);
+/* The same as the training step calls them: rest, bf16 [B][T][D] (nullable), receives what rounding left out of `out` in op 0 and is added to it in op 1.  op 2: the
+ * backward pass of the first query alone (dout read in token 0 only, as if zero elsewhere). */
+int et_debug_attention_long_rest(int op, const void* qkv, void* out, void* rest, float* lse, const void* dout, void* dqkv, int B, int T, int H,
+                                 void* stream);
 
 /* Device address and element count (bf16) of an activation the last forward pass of a bound context stored,
  * so that a test can check one layer at a time against the layer's definition applied to the stored input.

@@ -79,6 +79,7 @@ def _load():
         "et_debug_affine_back": (C.c_int, [vp] * 12 + [C.c_float] + [C.c_int] * 3 + [vp]),
         "et_debug_attention": (C.c_int, [C.c_int] + [vp] * 5 + [C.c_int] * 3 + [vp]),
         "et_debug_attention_long": (C.c_int, [C.c_int] + [vp] * 5 + [C.c_int] * 3 + [vp]),
+        "et_debug_attention_long_rest": (C.c_int, [C.c_int] + [vp] * 6 + [C.c_int] * 3 + [vp]),
         "et_debug_conv3x3_split": (C.c_int, [vp, vp, vp, vp] + [C.c_int] * 5 + [vp, vp, vp, C.c_int, C.c_int, vp, C.c_int, vp]),
         "et_debug_conv3x3_dw": (C.c_int, [vp, vp, vp] + [C.c_int] * 6 + [vp, C.c_int, vp]),
         "et_debug_conv_gathered": (C.c_int, [C.c_int, vp, vp, vp] + [C.c_int] * 8 + [vp, C.c_int, vp]),
@@ -98,7 +99,7 @@ EXPORTS = ["et_create", "et_destroy", "et_num_tensors", "et_tensor_info", "et_wo
            "et_bind", "et_profile", "et_importance", "et_importance_master", "et_importance_reduce_static", "et_select", "et_select_stats", "et_tensor_metric", "et_train_step", "et_last_launch_counts",
            "et_kernel_timing", "et_kernel_timing_read", "et_kernel_timing_overhead", "et_last_hip_error", "et_strerror", "et_debug_gemm_bf16", "et_debug_copy", "et_debug_mfma_peak", "et_debug_conv3x3",
            "et_debug_conv3x3_dw", "et_debug_depthwise3x3", "et_debug_depthwise3x3_ws_floats", "et_debug_affine_back", "et_debug_affine_back_ws_floats", "et_debug_flip3x3", "et_debug_conv_first",
-           "et_debug_activation", "et_debug_conv3x3_split", "et_debug_attention", "et_debug_attention_long",
+           "et_debug_activation", "et_debug_conv3x3_split", "et_debug_attention", "et_debug_attention_long", "et_debug_attention_long_rest",
            "et_debug_conv_gathered", "et_debug_stem", "et_debug_stem_ws_bytes"]
 
 
@@ -376,6 +377,11 @@ def et_debug_attention(op, qkv, out, lse, dout, dqkv, B, T, H, stream=0):
 def et_debug_attention_long(op, qkv, out, lse, dout, dqkv, B, T, H, stream=0):
     return _lib.et_debug_attention_long(op, C.c_void_p(qkv), C.c_void_p(out), C.c_void_p(lse), C.c_void_p(dout), C.c_void_p(dqkv),
                                         B, T, H, C.c_void_p(stream))
+
+
+def et_debug_attention_long_rest(op, qkv, out, rest, lse, dout, dqkv, B, T, H, stream=0):
+    return _lib.et_debug_attention_long_rest(op, C.c_void_p(qkv), C.c_void_p(out), C.c_void_p(rest), C.c_void_p(lse), C.c_void_p(dout),
+                                             C.c_void_p(dqkv), B, T, H, C.c_void_p(stream))
 
 
 def et_debug_mfma_peak(out, workgroups, iters, stream=0):

@@ -349,7 +349,7 @@ __global__ __launch_bounds__(NTHREADS) void attention_bwd_kernel(const bf16* __r
 // Vector work bound by memory (K and V read, dQ, dK, dV written: 97 MB for 64 x 12 heads of 197 tokens); one workgroup per
 // (batch, head), eight lanes per token with 16 bytes each.
 // -------------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void attention_bwd_cls_kernel(const bf16* __restrict__ qkv, const bf16* __restrict__ out,
+__global__ __launch_bounds__(256) void attention_bwd_cls_kernel(const bf16* __restrict__ qkv, const bf16* __restrict__ out, const bf16* __restrict__ rest,
                                                                 const bf16* __restrict__ dout, const float* __restrict__ lse,
                                                                 bf16* __restrict__ dqkv, float* __restrict__ part_out, int T, int H, float scale) {
   __shared__ float red[3][32][DH + 4];   // dQ, and the column sums of dK and dV
@@ -359,12 +359,14 @@ __global__ __launch_bounds__(256) void attention_bwd_cls_kernel(const bf16* __re
   const bf16x8 q8 = *(const bf16x8*)(qkv + base);
   const bf16x8 do8 = *(const bf16x8*)(dout + (long long)b * T * D + h * DH + part * 8);
   const bf16x8 o8 = *(const bf16x8*)(out + (long long)b * T * D + h * DH + part * 8);
+  bf16x8 r8 = {};   // what the rounding of `out` left out
+  if (rest) r8 = *(const bf16x8*)(rest + (long long)b * T * D + h * DH + part * 8);
   float q[8], g[8], dot = 0.f;
 #pragma unroll
   for (int e = 0; e < 8; e++) {
     q[e] = (float)q8[e];
     g[e] = (float)do8[e];
-    dot += g[e] * (float)o8[e];
+    dot += g[e] * ((float)o8[e] + (float)r8[e]);
   }
 #pragma unroll
   for (int m = 1; m < 8; m <<= 1) dot += __shfl_xor(dot, m, 64);
@@ -442,21 +444,23 @@ hipError_t launch_bwd(const bf16* qkv, const bf16* out, const bf16* dout, const 
 
 }  // namespace
 
-hipError_t attention_bwd_cls(const bf16* qkv, const bf16* out, const bf16* dout, const float* lse, bf16* dqkv, int B, int T, int H,
+hipError_t attention_bwd_cls(const bf16* qkv, const bf16* out, const bf16* rest, const bf16* dout, const float* lse, bf16* dqkv, int B, int T, int H,
                              int head_dim, float scale, hipStream_t s, float* part) {
   if (!attention_fused_supported(T, head_dim) || B < 1 || H < 1) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(attention_bwd_cls_kernel, dim3(B * H), dim3(256), 0, s, qkv, out, dout, lse, dqkv, part, T, H, scale);
+  hipLaunchKernelGGL(attention_bwd_cls_kernel, dim3(B * H), dim3(256), 0, s, qkv, out, rest, dout, lse, dqkv, part, T, H, scale);
   return hipGetLastError();
 }
+
+bool attention_wants_rest(int T) { return T > 224; }
 
 int attention_bwd_parts(int B, int T) { return T > 224 ? attention_long_bwd_parts(B, T) : B; }
 
 bool attention_fused_supported(int T, int head_dim) { return head_dim == DH && T >= 1 && T < (1 << 20); }
 
-hipError_t attention_fwd(const bf16* qkv, bf16* out, float* lse, int B, int T, int H, int head_dim, float scale,
+hipError_t attention_fwd(const bf16* qkv, bf16* out, bf16* rest, float* lse, int B, int T, int H, int head_dim, float scale,
                          hipStream_t s) {
   if (!attention_fused_supported(T, head_dim) || B < 1 || H < 1) return hipErrorInvalidValue;
-  if (T > 224) return attention_long_fwd(qkv, out, lse, B, T, H, scale, s);
+  if (T > 224) return attention_long_fwd(qkv, out, rest, lse, B, T, H, scale, s);
   switch ((T + 31) / 32) {
     case 1: return launch_fwd<1>(qkv, out, lse, B, T, H, scale, s);
     case 2: return launch_fwd<2>(qkv, out, lse, B, T, H, scale, s);
@@ -468,10 +472,10 @@ hipError_t attention_fwd(const bf16* qkv, bf16* out, float* lse, int B, int T, i
   }
 }
 
-hipError_t attention_bwd(const bf16* qkv, const bf16* out, const bf16* dout, const float* lse, bf16* dqkv, int B, int T, int H,
+hipError_t attention_bwd(const bf16* qkv, const bf16* out, const bf16* rest, const bf16* dout, const float* lse, bf16* dqkv, int B, int T, int H,
                          int head_dim, float scale, hipStream_t s, float* part) {
   if (!attention_fused_supported(T, head_dim) || B < 1 || H < 1 || !out) return hipErrorInvalidValue;
-  if (T > 224) return attention_long_bwd(qkv, out, dout, lse, dqkv, B, T, H, scale, s, part);
+  if (T > 224) return attention_long_bwd(qkv, out, rest, dout, lse, dqkv, B, T, H, scale, s, part);
   switch ((T + 31) / 32) {
     case 1: return launch_bwd<1>(qkv, out, dout, lse, dqkv, B, T, H, scale, s, part);
     case 2: return launch_bwd<2>(qkv, out, dout, lse, dqkv, B, T, H, scale, s, part);

@@ -5,11 +5,16 @@
 //   forward   own queries, stream K and V: running maximum and sum per query (a lane holds one query), the result is
 //             rescaled when the maximum of a chunk exceeds what was seen before;
 //   backward  one launch, two kinds of workgroups: own queries, stream K and V -> dQ; own keys, stream Q and dO -> dK, dV.
-//             Both recompute the probabilities from the stored log-sum-exp; rowsum(P * dP) of a query is dO . O.
+//             Both recompute the probabilities from the stored log-sum-exp; rowsum(P * dP) of a query is dO . O, with O as the
+//             stored bf16 value plus a second one, `rest`, that the forward pass leaves.  From the stored output alone,
+//             dP - rowsum(P * dP) keeps the rounding error of O wherever values share a mean across tokens (relative error of dQ at 577
+//             tokens, values of mean 3: 1.0e-2, against 3.0e-3 from materialised bf16 probabilities and 2.4e-3 with the rest).
+//             out + rest is the result divided by the sum of the probabilities as rounded, so that what all keys share is exact.
+//             It costs 2.0 us of the forward pass and 1.0 of the backward (times below).
 // The register layout (transposed scores, no LDS round trip between the two products) is that of attention.hip.
 // No score ever goes to memory: at 577 tokens, 8 x 6 heads, the former path (scores, softmax, batched products: eight launches
 // for a layer's forward and backward, 64 MB of fp32 scores written and read several times) took about 170 us per layer, these
-// two take 15.8 and 34.9 us; the full step of 12 such layers went from 5357 to 3929 us.  Up to 224 tokens the kernels that
+// two take 19.8 and 40.7 us; the full step of 12 such layers went from 5357 to 3929 us.  Up to 224 tokens the kernels that
 // hold a head on chip stay ahead (64 x 12 heads of 197 tokens: 24.5 / 63.8 us against 28.7 / 88.5 here).
 // Workgroups of one (batch, head) are dealt to the same XCD, whose L2 then holds the streamed rows.
 #include "attention_tiles.h"
@@ -54,7 +59,7 @@ __device__ __forceinline__ void load_own(const bf16* m, long long ld, int row, b
   for (int ks = 0; ks < 4; ks++) f[ks] = *(const bf16x8*)(m + (long long)row * ld + ks * 16 + khalf * 8);
 }
 
-__global__ __launch_bounds__(LTHREADS) void attention_long_fwd_kernel(const bf16* __restrict__ qkv, bf16* __restrict__ out,
+__global__ __launch_bounds__(LTHREADS) void attention_long_fwd_kernel(const bf16* __restrict__ qkv, bf16* __restrict__ out, bf16* __restrict__ rest,
                                                                       float* __restrict__ lse, int T, int H, float scale, int items, int blocks) {
   __shared__ __attribute__((aligned(1024))) unsigned char smem[2 * 2 * MAT + LW * STORE_AREA];
   int item, blk;
@@ -71,7 +76,12 @@ __global__ __launch_bounds__(LTHREADS) void attention_long_fwd_kernel(const bf16
   load_own(q, ld, min(own0 + l32, T - 1), qf, khalf);
   issue_chunk(q + D, ld, q + 2 * D, ld, 0, T, lds0, tid);
   float m = -INFINITY, sum = 0.f;
-  f32x16 o[2];
+  f32x16 o[2], sum16;   // sum16: of the rounded probabilities, a product with ones (the same sum in every register)
+  bf16x8 ones;
+#pragma unroll
+  for (int e = 0; e < 8; e++) ones[e] = (bf16)1.f;
+#pragma unroll
+  for (int r = 0; r < 16; r++) sum16[r] = 0.f;
 #pragma unroll
   for (int dt = 0; dt < 2; dt++)
 #pragma unroll
@@ -107,6 +117,8 @@ __global__ __launch_bounds__(LTHREADS) void attention_long_fwd_kernel(const bf16
       const float f = __builtin_amdgcn_exp2f((m - mx) * c);   // (0 for the first chunk)
       sum *= f;
 #pragma unroll
+      for (int r = 0; r < 16; r++) sum16[r] *= f;
+#pragma unroll
       for (int dt = 0; dt < 2; dt++)
 #pragma unroll
         for (int r = 0; r < 16; r++) o[dt][r] *= f;
@@ -124,18 +136,36 @@ __global__ __launch_bounds__(LTHREADS) void attention_long_fwd_kernel(const bf16
           sum += p;
           pf[e] = (bf16)p;
         }
+        sum16 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ones, pf, sum16, 0, 0, 0);
 #pragma unroll
         for (int dt = 0; dt < 2; dt++)
           o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_rows_tr(sv, kt * 32 + j * 16, dt * 32, lane), pf, o[dt], 0, 0, 0);
       }
   }
-  const float S = sum + __shfl_xor(sum, 32, 64);
+  const float S = sum + __shfl_xor(sum, 32, 64), inv = 1.f / S, inv16 = 1.f / sum16[0];
   const int row = own0 + l32;
   if (khalf == 0 && row < T) lse[((long long)b * H + h) * T + row] = m * scale + logf(S);
-  store_tile(smem + 2 * 2 * MAT + wave * STORE_AREA, o, 1.f / S, out + ((long long)b * T + own0) * D + h * DH, D, T - own0, lane);
+  unsigned char* area = smem + 2 * 2 * MAT + wave * STORE_AREA;
+  const long long at = ((long long)b * T + own0) * D + h * DH;
+  store_tile(area, o, inv, out + at, D, T - own0, lane);
+  if (!rest) return;
+#pragma unroll
+  for (int dt = 0; dt < 2; dt++)
+#pragma unroll
+    for (int r = 0; r < 16; r++) o[dt][r] = o[dt][r] * inv16 - (float)(bf16)(o[dt][r] * inv);
+  store_tile(area, o, 1.f, rest + at, D, T - own0, lane);
 }
 
-__global__ __launch_bounds__(LTHREADS) void attention_long_bwd_kernel(const bf16* __restrict__ qkv, const bf16* __restrict__ out,
+// sum += x . (y + r), 8 elements; r nullable
+__device__ __forceinline__ void add_dot(float& sum, const bf16* x, const bf16* y, const bf16* r) {
+  const bf16x8 a = *(const bf16x8*)x, b = *(const bf16x8*)y;
+  bf16x8 c = {};
+  if (r) c = *(const bf16x8*)r;
+#pragma unroll
+  for (int e = 0; e < 8; e++) sum += (float)a[e] * ((float)b[e] + (float)c[e]);
+}
+
+__global__ __launch_bounds__(LTHREADS) void attention_long_bwd_kernel(const bf16* __restrict__ qkv, const bf16* __restrict__ out, const bf16* __restrict__ rest,
                                                                       const bf16* __restrict__ dout, const float* __restrict__ lse,
                                                                       bf16* __restrict__ dqkv, float* __restrict__ part, int T, int H, float scale, int items, int blocks) {
   __shared__ __attribute__((aligned(1024))) unsigned char smem[2 * 2 * MAT + LW * STORE_AREA];
@@ -151,6 +181,7 @@ __global__ __launch_bounds__(LTHREADS) void attention_long_bwd_kernel(const bf16
   const bf16* q = qkv + (long long)b * T * ld + h * DH;
   const bf16* dO = dout + (long long)b * T * D + h * DH;
   const bf16* oo = out + (long long)b * T * D + h * DH;
+  const bf16* orest = rest ? rest + (long long)b * T * D + h * DH : nullptr;
   const float* ls = lse + ((long long)b * H + h) * T;
   const unsigned lds0 = (unsigned)(unsigned long long)(__attribute__((address_space(3))) unsigned char*)smem;
   const float log2e = 1.44269504088896341f, c = scale * log2e;   // exp(scale * s - lse) = 2^(c s - lse log2(e))
@@ -161,15 +192,15 @@ __global__ __launch_bounds__(LTHREADS) void attention_long_bwd_kernel(const bf16
 
   if (!keys) {
     issue_chunk(q + D, ld, q + 2 * D, ld, 0, T, lds0, tid);
-    bf16x8 qf[4], dof[4], of[4];
+    bf16x8 qf[4], dof[4];
     load_own(q, ld, own, qf, khalf);
     load_own(dO, D, own, dof, khalf);
-    load_own(oo, D, own, of, khalf);
     float dot = 0.f;
 #pragma unroll
-    for (int ks = 0; ks < 4; ks++)
-#pragma unroll
-      for (int e = 0; e < 8; e++) dot += (float)of[ks][e] * (float)dof[ks][e];
+    for (int ks = 0; ks < 4; ks++) {
+      const long long at = (long long)own * D + ks * 16 + khalf * 8;
+      add_dot(dot, dO + at, oo + at, orest ? orest + at : nullptr);
+    }
     dot += __shfl_xor(dot, 32, 64);
     const float my_lse = ls[own] * log2e;
     f32x16 dq[2];
@@ -231,11 +262,7 @@ __global__ __launch_bounds__(LTHREADS) void attention_long_bwd_kernel(const bf16
     const long long at = (long long)min(row, T - 1) * D + part * 16;
     float dot = 0.f;
 #pragma unroll
-    for (int i = 0; i < 2; i++) {
-      const bf16x8 x = *(const bf16x8*)(oo + at + i * 8), y = *(const bf16x8*)(dO + at + i * 8);
-#pragma unroll
-      for (int e = 0; e < 8; e++) dot += (float)x[e] * (float)y[e];
-    }
+    for (int i = 0; i < 2; i++) add_dot(dot, dO + at + i * 8, oo + at + i * 8, orest ? orest + at + i * 8 : nullptr);
     dot += __shfl_xor(dot, 1, 64);
     dot += __shfl_xor(dot, 2, 64);
     if (part == 0) {
@@ -320,20 +347,20 @@ bool grid_of(int B, int T, int H, int per_item, unsigned* grid) {
 
 }  // namespace
 
-hipError_t attention_long_fwd(const bf16* qkv, bf16* out, float* lse, int B, int T, int H, float scale, hipStream_t s) {
+hipError_t attention_long_fwd(const bf16* qkv, bf16* out, bf16* rest, float* lse, int B, int T, int H, float scale, hipStream_t s) {
   const int blocks = (T + OWN - 1) / OWN;
   unsigned grid;
   if (B < 1 || H < 1 || T < 1 || !grid_of(B, T, H, blocks, &grid)) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(attention_long_fwd_kernel, dim3(grid), dim3(LTHREADS), 0, s, qkv, out, lse, T, H, scale, B * H, blocks);
+  hipLaunchKernelGGL(attention_long_fwd_kernel, dim3(grid), dim3(LTHREADS), 0, s, qkv, out, rest, lse, T, H, scale, B * H, blocks);
   return hipGetLastError();
 }
 
-hipError_t attention_long_bwd(const bf16* qkv, const bf16* out, const bf16* dout, const float* lse, bf16* dqkv, int B, int T, int H,
-                              float scale, hipStream_t s, float* part) {
+hipError_t attention_long_bwd(const bf16* qkv, const bf16* out, const bf16* rest, const bf16* dout, const float* lse, bf16* dqkv, int B, int T,
+                              int H, float scale, hipStream_t s, float* part) {
   const int blocks = (T + OWN - 1) / OWN;
   unsigned grid;
   if (B < 1 || H < 1 || T < 1 || !out || !grid_of(B, T, H, 2 * blocks, &grid)) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(attention_long_bwd_kernel, dim3(grid), dim3(LTHREADS), 0, s, qkv, out, dout, lse, dqkv, part, T, H, scale, B * H, blocks);
+  hipLaunchKernelGGL(attention_long_bwd_kernel, dim3(grid), dim3(LTHREADS), 0, s, qkv, out, rest, dout, lse, dqkv, part, T, H, scale, B * H, blocks);
   return hipGetLastError();
 }
 

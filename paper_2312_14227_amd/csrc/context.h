@@ -46,6 +46,7 @@ struct KernelRecord {  // one timed kernel launch (measurement support)
 struct VitBlockBufs {
   float *h_in, *h_mid, *mean1, *rstd1, *mean2, *rstd2, *lse;
   bf16 *a1, *qkv, *p, *o, *a2, *u, *ga;
+  bf16* o_rest = nullptr;   // what rounding o to bf16 left out (long sequences only)
 };
 
 // activations kept by one convolution + affine (+ReLU) unit of the ResNet

@@ -71,6 +71,7 @@ int build_vit(et_ctx* c) {
     if (!fused) reserve(c, &b.p, b16 * B * H * T * ldT);
     reserve(c, &b.lse, f32 * B * H * T);
     reserve(c, &b.o, b16 * M * D);
+    if (fused && et::attention_wants_rest(d.tokens)) reserve(c, &b.o_rest, b16 * M * D);
     reserve(c, &b.a2, b16 * M * D);
     reserve(c, &b.u, b16 * M * F);
     reserve(c, &b.ga, b16 * M * F);
@@ -227,7 +228,7 @@ int vit_forward(et_ctx* c, const void* x, const int32_t* y, const uint8_t* mask)
     }
     if (et::attention_fused_supported(v.T, v.dh)) {
       KernelTimer kt(c, 5, 4.0 * v.B * v.H * (double)v.T * v.T * v.dh);
-      ET_K(1, et::attention_fwd(b.qkv, b.o, b.lse, v.B, v.T, v.H, v.dh, v.scale, c->stream));
+      ET_K(1, et::attention_fwd(b.qkv, b.o, t0 + 4 > jstar ? b.o_rest : nullptr, b.lse, v.B, v.T, v.H, v.dh, v.scale, c->stream));
     } else {
       {  // S = scale * Q K^T per (batch, head)
         et::GemmDesc g;
@@ -286,7 +287,7 @@ int vit_forward(et_ctx* c, const void* x, const int32_t* y, const uint8_t* mask)
 int vit_attention_backward(et_ctx* c, const VitDims& v, VitBlockBufs& b, float* part) {
   if (et::attention_fused_supported(v.T, v.dh)) {
     KernelTimer kt(c, 6, 8.0 * v.B * v.H * (double)v.T * v.T * v.dh);
-    ET_K(1, et::attention_bwd(b.qkv, b.o, c->dattn, b.lse, c->dqkv, v.B, v.T, v.H, v.dh, v.scale, c->stream, part));
+    ET_K(1, et::attention_bwd(b.qkv, b.o, b.o_rest, c->dattn, b.lse, c->dqkv, v.B, v.T, v.H, v.dh, v.scale, c->stream, part));
     return ET_OK;
   }
   const long long sQo = (long long)v.T * 3 * v.D, sPo = (long long)v.H * v.T * v.ldT, sPi = (long long)v.T * v.ldT;
@@ -468,7 +469,7 @@ int vit_backward(et_ctx* c, const void* x, const uint8_t* mask) {
       ET_G(g);
       if (few) {
         KernelTimer kt(c, 6, 8.0 * v.B * v.H * (double)v.T * v.dh);
-        ET_K(1, et::attention_bwd_cls(b.qkv, b.o, c->dattn, b.lse, c->dqkv, v.B, v.T, v.H, v.dh, v.scale, s, part));
+        ET_K(1, et::attention_bwd_cls(b.qkv, b.o, b.o_rest, c->dattn, b.lse, c->dqkv, v.B, v.T, v.H, v.dh, v.scale, s, part));
       } else if ((rc = vit_attention_backward(c, v, b, part)) != ET_OK) {
         return rc;
       }

@@ -238,10 +238,10 @@ extern "C" int et_debug_attention(int op, const void* qkv, void* out, float* lse
     return ET_EINVAL;
   hipError_t e;
   if (op == 0) {
-    e = et::attention_fwd((const et::bf16*)qkv, (et::bf16*)out, lse, B, T, H, 64, 0.125f, (hipStream_t)stream);
+    e = et::attention_fwd((const et::bf16*)qkv, (et::bf16*)out, nullptr, lse, B, T, H, 64, 0.125f, (hipStream_t)stream);
   } else if (op == 1) {
     if (!dout || !dqkv) return ET_EINVAL;
-    e = et::attention_bwd((const et::bf16*)qkv, (const et::bf16*)out, (const et::bf16*)dout, lse, (et::bf16*)dqkv, B, T, H, 64,
+    e = et::attention_bwd((const et::bf16*)qkv, (const et::bf16*)out, nullptr, (const et::bf16*)dout, lse, (et::bf16*)dqkv, B, T, H, 64,
                           0.125f, (hipStream_t)stream);
   } else {
     return ET_EINVAL;
@@ -250,23 +250,34 @@ extern "C" int et_debug_attention(int op, const void* qkv, void* out, float* lse
   return e == hipSuccess ? ET_OK : ET_EHIP;
 }
 
-extern "C" int et_debug_attention_long(int op, const void* qkv, void* out, float* lse, const void* dout, void* dqkv, int B, int T,
-                                  int H, void* stream) {
+extern "C" int et_debug_attention_long_rest(int op, const void* qkv, void* out, void* rest, float* lse, const void* dout, void* dqkv, int B,
+                                            int T, int H, void* stream) {
   if (!qkv || !out || !lse || B < 1 || H < 1 || !et::attention_fused_supported(T, 64)) return ET_EINVAL;
-  if ((reinterpret_cast<uintptr_t>(qkv) | reinterpret_cast<uintptr_t>(out) | reinterpret_cast<uintptr_t>(lse) |
+  if ((reinterpret_cast<uintptr_t>(qkv) | reinterpret_cast<uintptr_t>(out) | reinterpret_cast<uintptr_t>(rest) | reinterpret_cast<uintptr_t>(lse) |
        reinterpret_cast<uintptr_t>(dout) | reinterpret_cast<uintptr_t>(dqkv)) & 15)
     return ET_EINVAL;
   hipError_t e;
   if (op == 0) {
-    e = et::attention_long_fwd((const et::bf16*)qkv, (et::bf16*)out, lse, B, T, H, 0.125f, (hipStream_t)stream);
+    e = et::attention_long_fwd((const et::bf16*)qkv, (et::bf16*)out, (et::bf16*)rest, lse, B, T, H, 0.125f, (hipStream_t)stream);
   } else if (op == 1) {
     if (!dout || !dqkv) return ET_EINVAL;
-    e = et::attention_long_bwd((const et::bf16*)qkv, (const et::bf16*)out, (const et::bf16*)dout, lse, (et::bf16*)dqkv, B, T, H, 0.125f, (hipStream_t)stream);
+    e = et::attention_long_bwd((const et::bf16*)qkv, (const et::bf16*)out, (const et::bf16*)rest, (const et::bf16*)dout, lse, (et::bf16*)dqkv, B, T, H,
+                               0.125f, (hipStream_t)stream);
+  } else if (op == 2) {
+    if (!dout || !dqkv) return ET_EINVAL;
+    e = et::attention_bwd_cls((const et::bf16*)qkv, (const et::bf16*)out, (const et::bf16*)rest, (const et::bf16*)dout, lse, (et::bf16*)dqkv, B, T, H, 64,
+                              0.125f, (hipStream_t)stream);
   } else {
     return ET_EINVAL;
   }
   if (e == hipErrorInvalidValue) return ET_EINVAL;
   return e == hipSuccess ? ET_OK : ET_EHIP;
+}
+
+extern "C" int et_debug_attention_long(int op, const void* qkv, void* out, float* lse, const void* dout, void* dqkv, int B, int T,
+                                       int H, void* stream) {
+  if (op != 0 && op != 1) return ET_EINVAL;
+  return et_debug_attention_long_rest(op, qkv, out, nullptr, lse, dout, dqkv, B, T, H, stream);
 }
 
 namespace {

@@ -173,20 +173,23 @@ hipError_t softmax_bwd_rows(const float* dp, const bf16* p, bf16* ds, float scal
 //   backward: dqkv (same layout as qkv) from dout, recomputing the probabilities from lse; `out` is the stored
 //   forward output (rowsum(P * dP) = dout . out)
 bool attention_fused_supported(int T, int head_dim);
-hipError_t attention_fwd(const bf16* qkv, bf16* out, float* lse, int B, int T, int H, int head_dim, float scale,
+//   rest (more than 224 tokens, attention_wants_rest(T); nullable): what rounding left out of `out`, as bf16; the forward pass leaves it and the
+//   backward pass takes rowsum(P * dP) from out + rest (null: from `out` alone)
+hipError_t attention_fwd(const bf16* qkv, bf16* out, bf16* rest, float* lse, int B, int T, int H, int head_dim, float scale,
                          hipStream_t s);
+bool attention_wants_rest(int T);
 // part (nullable): attention_bwd_parts(B, T) rows of partial sums over the rows of dqkv, 3 * 64 H columns each
-hipError_t attention_bwd(const bf16* qkv, const bf16* out, const bf16* dout, const float* lse, bf16* dqkv, int B, int T, int H,
+hipError_t attention_bwd(const bf16* qkv, const bf16* out, const bf16* rest, const bf16* dout, const float* lse, bf16* dqkv, int B, int T, int H,
                          int head_dim, float scale, hipStream_t s, float* part = nullptr);
 int attention_bwd_parts(int B, int T);
 // backward when only the first token's row of dout is read (the others are zeros that need not be stored): dqkv complete; part
 // (nullable): B rows of partial sums
-hipError_t attention_bwd_cls(const bf16* qkv, const bf16* out, const bf16* dout, const float* lse, bf16* dqkv, int B, int T, int H,
+hipError_t attention_bwd_cls(const bf16* qkv, const bf16* out, const bf16* rest, const bf16* dout, const float* lse, bf16* dqkv, int B, int T, int H,
                              int head_dim, float scale, hipStream_t s, float* part = nullptr);
 // the same for sequences of any length, streamed (attention_fwd / _bwd choose)
-hipError_t attention_long_fwd(const bf16* qkv, bf16* out, float* lse, int B, int T, int H, float scale, hipStream_t s);
-hipError_t attention_long_bwd(const bf16* qkv, const bf16* out, const bf16* dout, const float* lse, bf16* dqkv, int B, int T, int H,
-                              float scale, hipStream_t s, float* part = nullptr);
+hipError_t attention_long_fwd(const bf16* qkv, bf16* out, bf16* rest, float* lse, int B, int T, int H, float scale, hipStream_t s);
+hipError_t attention_long_bwd(const bf16* qkv, const bf16* out, const bf16* rest, const bf16* dout, const float* lse, bf16* dqkv, int B, int T,
+                              int H, float scale, hipStream_t s, float* part = nullptr);
 int attention_long_bwd_parts(int B, int T);
 
 // mean softmax cross-entropy: dlogits fp32 and (if not null) a bf16 copy [B][ld16], zero padded; `loss` points to
