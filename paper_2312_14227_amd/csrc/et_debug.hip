@@ -107,7 +107,7 @@ bool stem_plan(int batch, int H, int W, int C, int N, StemPlan* p) {
   p->Hp = 2 * (p->Ho - 1) + 8; p->Wp = 2 * (p->Wo - 1) + 8;
   if (p->Hp > 4095 || p->Wp > 4095 || (long long)batch * p->Ho * p->Wo > 0x7fffffffll) return false;
   int tile;
-  et::gemm_bf16_plan_conv_dw(N, 256, batch * p->Ho * p->Wo, &tile, &p->split);
+  et::gemm_bf16_plan_conv_dw(N, 256, batch * p->Ho * p->Wo, &tile, &p->split, 7);
   auto up = [](size_t v) { return (v + 255) / 256 * 256; };
   p->off_w = up((size_t)batch * p->Hp * p->Wp * 4 * 2);
   p->off_dw = p->off_w + up((size_t)N * 256 * 2);

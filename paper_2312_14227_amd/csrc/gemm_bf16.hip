@@ -304,9 +304,11 @@ void gemm_bf16_plan_conv(int M, int N, int K, int* tile, int* split_k, bool fixe
   *split_k = pl.split;
 }
 
-void gemm_bf16_plan_conv_dw(int M, int N, int K, int* tile, int* split_k) {
-  // (a pixel count that is not a multiple of 64 runs on the ring tile whatever its size)
-  const Plan pl = (K % gemm::PBK) || conv_on_ring(K, M, N, 1.4e10) ? plan_ring(M, N, K, true, (M + N / 9.0) * K, kRingConvDw) : plan_conv_dw(M, N, K);
+void gemm_bf16_plan_conv_dw(int M, int N, int K, int* tile, int* split_k, int taps) {
+  // a pixel count that is not a multiple of 64 runs on the ring tile whatever its size; a 7x7 stem always on the two-group tiles, the only
+  // ones built for its window (64 x 256 over 401 408 pixels: 46 us in 251 chunks of 128 x 256; with the 128 that the ring plan asks for 77)
+  const bool ring = taps != 7 && ((K % gemm::PBK) || conv_on_ring(K, M, N, 1.4e10));
+  const Plan pl = ring ? plan_ring(M, N, K, true, (M + N / 9.0) * K, kRingConvDw) : plan_conv_dw(M, N, K);
   *tile = pl.tile;
   *split_k = pl.split;
 }
@@ -464,8 +466,10 @@ hipError_t gemm_bf16(const GemmDesc& d, hipStream_t s, int* launches) {
   } else if (conv_dw) {
     if (d.K % gemm::PBK) return hipErrorInvalidValue;
     int tile = d.tile;
-    if (tile != T_PP_256x256 && tile != T_PP_256x192 && tile != T_PP_128x256 && tile != T_PP_64x512)
+    if (tile != T_PP_256x256 && tile != T_PP_256x192 && tile != T_PP_128x256 && tile != T_PP_64x512) {
+      if (tile != T_AUTO && d.split_k > 1) return hipErrorInvalidValue;   // (a split belongs to the tile that it was planned with)
       tile = plan_conv_dw(d.M, d.N, k_per_block).tile;
+    }
     switch (tile) {
       case T_PP_64x512: BM = 64; BN = 512; fn = gemm::pp_convdw_64x512(epi, conv_general); break;
       case T_PP_128x256: BM = 128; BN = 256; fn = gemm::pp_convdw_128x256(epi, conv_general); break;

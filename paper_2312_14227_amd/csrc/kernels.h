@@ -84,8 +84,9 @@ void gemm_bf16_plan_split(int M, int N, int K, int* tile, int* split_k);
 // layers with few pixels split the reduction, and a second kernel sums the parts and applies the epilogue
 // fixed_sums: the split, and with it the order of every sum, is that of the plan for the wide tiles whichever tile is chosen
 void gemm_bf16_plan_conv(int M, int N, int K, int* tile, int* split_k, bool fixed_sums = false);
-// the same for the implicit weight gradient of a 3x3 convolution (M output channels, N = 9 input channels, K pixels)
-void gemm_bf16_plan_conv_dw(int M, int N, int K, int* tile, int* split_k);
+// the same for the implicit weight gradient of a 3x3 convolution (M output channels, N = 9 input channels, K pixels); taps = 7: of a
+// 7x7 stem (N = 256)
+void gemm_bf16_plan_conv_dw(int M, int N, int K, int* tile, int* split_k, int taps = 3);
 
 // ------------------------------------------------------------------------------------------
 // fp32 GEMM (true fp32 FMA), same operand convention, for the fp32 MLP workload

@@ -113,7 +113,7 @@ int build_resnet(et_ctx* c) {
     act(M, u.Cout);
     if (gathered) {
       int tile, split;
-      et::gemm_bf16_plan_conv_dw(u.Cout, 256, (int)M, &tile, &split);
+      et::gemm_bf16_plan_conv_dw(u.Cout, 256, (int)M, &tile, &split, 7);
       pe = std::max(pe, et::gemm_bf16_partial_elems(u.Cout, 256, split));
     } else {
       pe = std::max(pe, et::gemm_bf16_partial_elems(u.Cout, u.Kc, split_for(u.Cout, u.Kc, (int)M)));
@@ -341,7 +341,7 @@ int resnet_backward(et_ctx* c, const void* x, const uint8_t* mask) {
         g.M = u.Cout; g.N = 256; g.K = (int)M;
         g.C = c->stem_dw8; g.ldc = 256; g.c_f32 = true;
         g.conv_h = c->stem_hp; g.conv_w = c->stem_wp; g.conv_c = 4; g.conv_taps = 7; g.conv_stride = 2;
-        et::gemm_bf16_plan_conv_dw(g.M, g.N, g.K, &g.tile, &g.split_k);
+        et::gemm_bf16_plan_conv_dw(g.M, g.N, g.K, &g.tile, &g.split_k, g.conv_taps);
         g.partials = c->gemm_partials;
         if (et::gemm_bf16_partial_elems(g.M, g.N, g.split_k) > c->gemm_partial_elems) g.split_k = 1;
         ET_G(g);
