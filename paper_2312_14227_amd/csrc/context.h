@@ -117,6 +117,8 @@ struct et_ctx {
   size_t sum_arena_elems = 0, sum_used = 0;
   std::vector<et::SumJob> sum_jobs;
   std::vector<int> sum_tensors;
+  // transformer: share of a launch's time that the column sums riding on it take, measured by et_profile ([the last block's few rows][kernel])
+  double sum_cost[2][3] = {};
 
   // ResNet buffers
   ConvUnit stem;
@@ -257,7 +259,7 @@ inline int sums_finish(et_ctx* c) {
   if (c->sum_jobs.empty()) return ET_OK;
   std::vector<Share> shares;
   if (c->profiling)
-    for (int t : c->sum_tensors) shares.push_back({PH_DW, t, 1.0});
+    for (size_t i = 0; i < c->sum_jobs.size(); i++) shares.push_back({PH_DW, c->sum_tensors[i], (double)c->sum_jobs[i].rows * c->sum_jobs[i].cols});
   Region r(c, PH_DW, shares.data(), shares.size());
   int n = 0;
   const hipError_t e = et::sum_finish(c->sum_jobs.data(), (int)c->sum_jobs.size(), c->stream, &n);

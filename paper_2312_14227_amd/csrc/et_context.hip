@@ -284,7 +284,13 @@ int vit_forward(et_ctx* c, const void* x, const int32_t* y, const uint8_t* mask)
 }
 
 // part: where the fused core leaves the partial column sums of dqkv (the bias of the product in front of it), or null
-int vit_attention_backward(et_ctx* c, const VitDims& v, VitBlockBufs& b, float* part) {
+// few: the gradient is zero but for the first token of a sequence (fused core only)
+int vit_attention_backward(et_ctx* c, const VitDims& v, VitBlockBufs& b, bool few, float* part) {
+  if (few) {
+    KernelTimer kt(c, 6, 8.0 * v.B * v.H * (double)v.T * v.dh);
+    ET_K(1, et::attention_bwd_cls(b.qkv, b.o, b.o_rest, c->dattn, b.lse, c->dqkv, v.B, v.T, v.H, v.dh, v.scale, c->stream, part));
+    return ET_OK;
+  }
   if (et::attention_fused_supported(v.T, v.dh)) {
     KernelTimer kt(c, 6, 8.0 * v.B * v.H * (double)v.T * v.T * v.dh);
     ET_K(1, et::attention_bwd(b.qkv, b.o, b.o_rest, c->dattn, b.lse, c->dqkv, v.B, v.T, v.H, v.dh, v.scale, c->stream, part));
@@ -329,11 +335,79 @@ int vit_attention_backward(et_ctx* c, const VitDims& v, VitBlockBufs& b, float* 
   return ET_OK;
 }
 
+// rows of the stream that have a gradient, and the strides between them: the last block's few, or all
+struct VitRows { bool few; int R, step, ldD, ldF; };
+VitRows vit_rows(const VitDims& v, bool few) { return {few, few ? v.B : v.M, few ? v.T : 1, (few ? v.T : 1) * v.D, (few ? v.T : 1) * v.F}; }
+
+// through fc2.W, then through the GELU (b.u holds gelu'(pre-activation)); fc1.b's column sums on the way
+et::GemmDesc vit_fc2_dx(et_ctx* c, const VitDims& v, const VitRows& q, const VitBlockBufs& b, int t0, float* colsum) {
+  et::GemmDesc g = linear_dx(c->dh16, (const bf16*)c->w[t0 + 10], q.R, v.D, v.F);
+  g.lda = q.ldD; g.ldc = q.ldF;
+  g.mode = et::EPI_GELU_BWD; g.U = b.u; g.C = c->du; g.colsum = colsum;
+  return g;
+}
+// second LayerNorm of a block: input gradient joined by the residual branch
+et::LayerNormBwd vit_ln2_back(et_ctx* c, const VitDims& v, const VitRows& q, const VitBlockBufs& b, int t0) {
+  et::LayerNormBwd a;
+  a.d = c->da; a.d_stride = q.ldD; a.h = b.h_mid; a.h_stride = q.ldD; a.mean = b.mean2; a.rstd = b.rstd2; a.stat_stride = q.step;
+  a.gain = (const bf16*)c->w[t0 + 6]; a.skip = c->dh; a.dh = c->dh; a.dh16 = c->dh16; a.out_stride = q.ldD; a.rows = q.R; a.D = v.D;
+  return a;
+}
+
+// What the column sums add to the three kinds of launches that they ride on, as a share of the launch: each kind is timed with and
+// without them, on the buffers that a backward pass has left (all scratch of the next one).  What a step saves without
+// such a bias depends on the shape: 7.5 of 71 us of the attention of 64 x 12 heads of 197 tokens, nothing where the launch itself is
+// what takes time.
+enum SumKernel : int { SUM_ATTENTION = 0, SUM_GELU = 1, SUM_LAYERNORM = 2 };
+int vit_time_sums(et_ctx* c) {
+  const VitDims v = vit_dims(c->desc);
+  const bool cls = et::attention_fused_supported(v.T, v.dh);
+  constexpr int LAUNCHES = 8, TURNS = 5;
+  for (int few = 0; few <= (cls ? 1 : 0); few++) {
+    const int l = few ? v.L - 1 : 0, t0 = 4 + 12 * l;
+    const VitRows q = vit_rows(v, few != 0);
+    VitBlockBufs& b = c->blk[l];
+    for (int kernel = 0; kernel < 3; kernel++) {
+      c->sum_cost[few][kernel] = 0.0;
+      if ((kernel == SUM_ATTENTION && !cls) || (kernel == SUM_LAYERNORM && v.D > et::LAYERNORM_SUMS_MAX_D)) continue;
+      auto launch = [&](float* part) -> int {
+        if (kernel == SUM_ATTENTION) return vit_attention_backward(c, v, b, few != 0, part);
+        if (kernel == SUM_GELU) {
+          ET_G(vit_fc2_dx(c, v, q, b, t0, part));
+        } else {
+          et::LayerNormBwd a = vit_ln2_back(c, v, q, b, t0);
+          const size_t one = sum_elems(et::layernorm_bwd_parts(q.R), v.D);
+          if (part) { a.part_gain = part; a.part_shift = part + one; a.part_bias = part + 2 * one; }
+          ET_K(1, et::layernorm_bwd(a, c->stream));
+        }
+        return ET_OK;
+      };
+      double least[2] = {1e30, 1e30};
+      for (int turn = 0; turn < 2 * TURNS; turn++) {
+        hipEvent_t e0, e1;
+        ET_HIP(get_event(c, &e0));
+        ET_HIP(get_event(c, &e1));
+        ET_HIP(hipEventRecord(e0, c->stream));
+        for (int i = 0; i < LAUNCHES; i++) {
+          const int rc = launch(turn & 1 ? c->sum_arena : nullptr);
+          if (rc != ET_OK) return rc;
+        }
+        ET_HIP(hipEventRecord(e1, c->stream));
+        ET_HIP(hipEventSynchronize(e1));
+        float ms = 0.f;
+        ET_HIP(hipEventElapsedTime(&ms, e0, e1));
+        least[turn & 1] = std::min(least[turn & 1], (double)ms);
+      }
+      c->sum_cost[few][kernel] = std::max(0.0, std::min(0.5, 1.0 - least[0] / least[1]));
+    }
+  }
+  return ET_OK;
+}
+
 // One LayerNorm of the chain (gain tg, shift tg + 1; gradient d of its output): dw(shift), dw(gain) and dy(gain), and behind
 // dy(gain) the gradient of the bias tb (-1: none) that was added in front of the LayerNorm's input, the column sum of the
 // resulting stream.  Where the gradient is passed on, one kernel produces whatever of these is selected from the same
-// reads; its time in the profile is divided by what each output adds to it (measured on [12608 x 768]: the input gradient
-// alone 22.7 us, each sum 0.7 us).  `a` comes filled in except for the partial sums.
+// reads; its time in the profile is divided by what the sums add to it.  `a` comes filled in except for the partial sums.
 int layernorm_back(et_ctx* c, const uint8_t* mask, int jstar, int tg, int tb, et::LayerNormBwd a) {
   const int ts = tg + 1;
   const bool pass = tg > jstar, fused = pass && a.D <= et::LAYERNORM_SUMS_MAX_D;
@@ -351,11 +425,12 @@ int layernorm_back(et_ctx* c, const uint8_t* mask, int jstar, int tg, int tb, et
   }
   const int parts = et::layernorm_bwd_parts(a.rows);
   if ((rc = sums_room(c, 3 * sum_elems(parts, a.D))) != ET_OK) return rc;
-  Share shares[4] = {{PH_DY, tg, 22.7}};
+  const double cost = c->sum_cost[a.rows == c->desc.batch][SUM_LAYERNORM];
+  Share shares[4] = {{PH_DY, tg, 1.0 - cost}};
   size_t n = 1;
   auto sum = [&](int t) -> float* {
     if (t < 0 || !mask[t]) return nullptr;
-    shares[n++] = {PH_DW, t, 0.7};
+    shares[n++] = {PH_DW, t, cost / 3.0};
     return sum_job(c, t, parts, a.D);
   };
   a.part_gain = sum(tg);
@@ -414,25 +489,23 @@ int vit_backward(et_ctx* c, const void* x, const uint8_t* mask) {
     VitBlockBufs& b = c->blk[l];
     const int t0 = 4 + 12 * l;
     if (jstar > t0 + 11) break;
-    // rows of the stream with a gradient, and the strides between them
-    const bool few = cls && l + 1 == v.L;
-    const int R = few ? v.B : v.M, step = few ? v.T : 1;
-    const int ldD = step * v.D, ldF = step * v.F;
+    const VitRows q = vit_rows(v, cls && l + 1 == v.L);
+    const int R = q.R, ldD = q.ldD, ldF = q.ldF;
     if (sel(t0 + 10)) {
       Region r(c, PH_DW, t0 + 10);
       ET_G(linear_dw(c, c->dh16, ldD, b.ga, ldF, c->grad[t0 + 10], R, v.D, v.F));
     }
-    if (pass(t0 + 10)) {  // through fc2.W, then through the GELU (b.u holds gelu'(pre-activation)); fc1.b's column sums on the way
-      et::GemmDesc g = linear_dx(c->dh16, W(t0 + 10), R, v.D, v.F);
-      g.lda = ldD; g.ldc = ldF;
-      g.mode = et::EPI_GELU_BWD; g.U = b.u; g.C = c->du;
+    if (pass(t0 + 10)) {
+      float* part = nullptr;
       if (sel(t0 + 9)) {
         const int parts = (R + 31) / 32;
         if ((rc = sums_room(c, sum_elems(parts, v.F))) != ET_OK) return rc;
-        g.colsum = sum_job(c, t0 + 9, parts, v.F);
+        part = sum_job(c, t0 + 9, parts, v.F);
       }
-      Region r(c, PH_DY, t0 + 10);
-      ET_G(g);
+      const double cost = c->sum_cost[q.few][SUM_GELU];
+      const Share shares[2] = {{PH_DY, t0 + 10, 1.0 - cost}, {PH_DW, t0 + 9, cost}};
+      Region r(c, PH_DY, shares, part ? 2 : 1);
+      ET_G(vit_fc2_dx(c, v, q, b, t0, part));
     }
     if (sel(t0 + 8)) {
       Region r(c, PH_DW, t0 + 8);
@@ -445,12 +518,7 @@ int vit_backward(et_ctx* c, const void* x, const uint8_t* mask) {
       g.C = c->da;
       ET_G(g);
     }
-    {  // LayerNorm input gradient joined by the residual branch
-      et::LayerNormBwd a;
-      a.d = c->da; a.d_stride = ldD; a.h = b.h_mid; a.h_stride = ldD; a.mean = b.mean2; a.rstd = b.rstd2; a.stat_stride = step;
-      a.gain = W(t0 + 6); a.skip = c->dh; a.dh = c->dh; a.dh16 = c->dh16; a.out_stride = ldD; a.rows = R; a.D = v.D;
-      if ((rc = layernorm_back(c, mask, jstar, t0 + 6, t0 + 5, a)) != ET_OK) return rc;
-    }
+    if ((rc = layernorm_back(c, mask, jstar, t0 + 6, t0 + 5, vit_ln2_back(c, v, q, b, t0))) != ET_OK) return rc;
     if (sel(t0 + 4)) {
       Region r(c, PH_DW, t0 + 4);
       ET_G(linear_dw(c, c->dh16, ldD, b.o, ldD, c->grad[t0 + 4], R, v.D, v.D));
@@ -458,21 +526,21 @@ int vit_backward(et_ctx* c, const void* x, const uint8_t* mask) {
     if (pass(t0 + 4)) {  // through proj.W, then through the attention core, which leaves the column sums of qkv.b
       float* part = nullptr;
       if (sel(t0 + 3) && cls) {
-        const int parts = few ? v.B : et::attention_bwd_parts(v.B, v.T);
+        const int parts = q.few ? v.B : et::attention_bwd_parts(v.B, v.T);
         if ((rc = sums_room(c, sum_elems(parts, 3 * v.D))) != ET_OK) return rc;
         part = sum_job(c, t0 + 3, parts, 3 * v.D);
       }
-      Region r(c, PH_DY, t0 + 4);
-      et::GemmDesc g = linear_dx(c->dh16, W(t0 + 4), R, v.D, v.D);
-      g.lda = ldD; g.ldc = ldD;
-      g.C = c->dattn;
-      ET_G(g);
-      if (few) {
-        KernelTimer kt(c, 6, 8.0 * v.B * v.H * (double)v.T * v.dh);
-        ET_K(1, et::attention_bwd_cls(b.qkv, b.o, b.o_rest, c->dattn, b.lse, c->dqkv, v.B, v.T, v.H, v.dh, v.scale, s, part));
-      } else if ((rc = vit_attention_backward(c, v, b, part)) != ET_OK) {
-        return rc;
+      {
+        Region r(c, PH_DY, t0 + 4);
+        et::GemmDesc g = linear_dx(c->dh16, W(t0 + 4), R, v.D, v.D);
+        g.lda = ldD; g.ldc = ldD;
+        g.C = c->dattn;
+        ET_G(g);
       }
+      const double cost = c->sum_cost[q.few][SUM_ATTENTION];
+      const Share shares[2] = {{PH_DY, t0 + 4, 1.0 - cost}, {PH_DW, t0 + 3, cost}};
+      Region r(c, PH_DY, shares, part ? 2 : 1);
+      if ((rc = vit_attention_backward(c, v, b, q.few, part)) != ET_OK) return rc;
     }
     if (sel(t0 + 3) && !cls && (rc = colsum_dw(c, t0 + 3, c->dqkv, nullptr, 3 * v.D, v.M, 3 * v.D)) != ET_OK) return rc;
     if (sel(t0 + 2)) {
@@ -488,7 +556,7 @@ int vit_backward(et_ctx* c, const void* x, const uint8_t* mask) {
     {
       et::LayerNormBwd a;
       a.d = c->da; a.d_stride = v.D; a.h = b.h_in; a.h_stride = v.D; a.mean = b.mean1; a.rstd = b.rstd1; a.gain = W(t0 + 0);
-      a.skip = c->dh; a.skip_period = step; a.dh = c->dh; a.dh16 = c->dh16; a.out_stride = v.D; a.rows = v.M; a.D = v.D;
+      a.skip = c->dh; a.skip_period = q.step; a.dh = c->dh; a.dh16 = c->dh16; a.out_stride = v.D; a.rows = v.M; a.D = v.D;
       if ((rc = layernorm_back(c, mask, jstar, t0 + 0, l > 0 ? t0 - 1 : -1, a)) != ET_OK) return rc;   // (fc2.b of the block before)
     }
   }
@@ -938,6 +1006,13 @@ int et_profile(et_ctx* c, const void* x_dev, const int32_t* y_dev, int32_t warmu
   const bool with_update = !c->state.empty();
   // per rep: forward time, per tensor dw / dy, update
   std::vector<std::vector<double>> fwd(1), dw(N), dy(N), upd(1);
+  if (c->desc.kind == ET_VIT) {
+    c->events_used = 0;
+    int rc = run_forward(c, x_dev, y_dev);
+    if (rc == ET_OK) rc = run_backward(c, x_dev, ones.data());
+    if (rc == ET_OK) rc = vit_time_sums(c);
+    if (rc != ET_OK) return rc;
+  }
   for (int it = 0; it < warmup + reps; it++) {
     const bool timed = it >= warmup;
     c->profiling = timed;

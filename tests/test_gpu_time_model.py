@@ -1,0 +1,46 @@
+"""The time model charges a bias whose column sums ride on another tensor's launch with what they add to it: qkv.b on the attention's backward pass,
+fc1.b on the product through fc2.W.  Measured by steps with and without these biases at 64 sequences: 5 us a block of the 91 us
+of dy(proj.W) for qkv.b; the launches on their own give 5 per cent of dy(fc2.W) for fc1.b.  Their share of the finishing launch alone is 0.6
+per cent.  At 4 sequences 7 per cent against 1.6 at most.  Bound: 2.5 per cent of the interior blocks' dy."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("batch", [4, 64])
+def test_riding_column_sums_are_charged_to_their_bias(batch):
+    from paper_2312_14227_amd.session import Session
+    from synth import make_workload
+    from synth.configs import ViTConfig
+    cfg = ViTConfig("vit_b_3", batch, 197, 768, 768, 12, 3072, 3, 200)
+    wl = make_workload(cfg, seed=0)
+    s = Session(cfg, wl.weights)
+    xt, yt = s.put_input(wl.x, wl.y)
+    _, t_dw, t_dy = s.profile(xt, yt, warmup=3, reps=7)
+    at = wl.names.index
+    for block in (0, 1):
+        for bias, carrier in (("qkv.b", "proj.W"), ("fc1.b", "fc2.W")):
+            dw, dy = int(t_dw[at("blk%d.%s" % (block, bias))]), int(t_dy[at("blk%d.%s" % (block, carrier))])
+            assert 0.025 * dy <= dw <= 0.5 * dy, (batch, block, bias, dw, dy)
+    s.close()
+
+
+def test_profile_leaves_the_step_as_it_was():
+    """The launches that the profile times apart from a pass work on scratch of the backward pass only: a step after it gives the bits of
+    a step before it."""
+    from paper_2312_14227_amd.session import Session
+    from synth import CONFIGS, make_workload
+    from synth.configs import ViTConfig
+    for cfg in (CONFIGS["vit_small"], CONFIGS["vit_t230"], CONFIGS["vit_w256"], ViTConfig("vit_dh32", 2, 40, 64, 128, 4, 256, 2, 16),
+                ViTConfig("vit_w2112", 1, 7, 64, 2112, 33, 256, 1, 16)):
+        wl = make_workload(cfg, seed=0, init="random")
+        s = Session(cfg, wl.weights)
+        xt, yt = s.put_input(wl.x, wl.y)
+        ones = np.ones(len(wl.weights), np.uint8)
+        before_loss = s.train_step(xt, yt, ones)
+        before = [g.clone() for g in s.grad]
+        s.profile(xt, yt, warmup=0, reps=1)
+        assert s.train_step(xt, yt, ones) == before_loss
+        assert all(bool((a == b).all()) for a, b in zip(before, s.grad)), cfg.name
+        s.close()
