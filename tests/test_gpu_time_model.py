@@ -44,3 +44,21 @@ def test_profile_leaves_the_step_as_it_was():
         assert s.train_step(xt, yt, ones) == before_loss
         assert all(bool((a == b).all()) for a, b in zip(before, s.grad)), cfg.name
         s.close()
+
+
+@pytest.mark.parametrize("name", ["vit_small", "vit_t40"])
+def test_the_attention_class_holds_one_kind_of_launch(name):
+    """Backward attention launches under timing: those over all queries, with their 8 B H T^2 d operations each, and not the last block's."""
+    from paper_2312_14227_amd import binding as et
+    from paper_2312_14227_amd.session import Session
+    from synth import CONFIGS, make_workload
+    cfg = CONFIGS[name]
+    wl = make_workload(cfg, seed=0)
+    s = Session(cfg, wl.weights)
+    xt, yt = s.put_input(wl.x, wl.y)
+    et.et_kernel_timing(s.ctx, 1)
+    s.train_step(xt, yt, np.ones(len(wl.weights), np.uint8))
+    n, _, flops = et.et_kernel_timing_read(s.ctx, 6)
+    et.et_kernel_timing(s.ctx, 0)
+    assert n == cfg.blocks - 1 and flops == n * 8.0 * cfg.batch * cfg.tokens ** 2 * cfg.width
+    s.close()
