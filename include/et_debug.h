@@ -25,6 +25,10 @@ extern "C" {
 int et_debug_gemm_bf16(const void* A, const void* B, void* C, int M, int N, int K, int lda, int ldb, int ldc,
                        int a_t, int b_t, int c_f32, float alpha, const void* bias, const float* residual,
                        int split_k, float* partials, int tile, int epilogue, void* aux, void* stream);
+/* GELU backward (epilogue 2 above, a_t = 0, b_t = 1, bf16 C) that also leaves column sums of C as rounded: colsum, fp32 [(M + 31) / 32][N], row r over
+ * rows 32 r .. 32 r + 31 of C.  Returns 0, -1, -3 as above. */
+int et_debug_gemm_bf16_colsum(const void* A, const void* B, void* C, const void* aux, float* colsum, int M, int N, int K, int lda, int ldb, int ldc,
+                              int tile, void* stream);
 
 /* 3x3 / stride 1 / zero padding 1 convolution as an implicit GEMM (the im2col matrix of Section 5.1's
  * convolution kernels is never written): out[b][h][w][n] = sum over (ky, kx, c) of

@@ -73,6 +73,7 @@ def _load():
         "et_debug_activation": (C.c_int, [vp, C.c_char_p, C.POINTER(vp), C.POINTER(C.c_size_t)]),
         "et_debug_depthwise3x3_ws_floats": (C.c_size_t, [C.c_int] * 5),
         "et_debug_depthwise3x3": (C.c_int, [C.c_int] + [vp] * 7 + [C.c_int] * 5 + [vp]),
+        "et_debug_gemm_bf16_colsum": (C.c_int, [vp] * 5 + [C.c_int] * 7 + [vp]),
         "et_debug_conv_first": (C.c_int, [vp] * 6 + [C.c_int] * 6 + [C.c_float] * 2 + [vp]),
         "et_debug_flip3x3": (C.c_int, [C.POINTER(vp), C.POINTER(vp), C.POINTER(C.c_int), C.POINTER(C.c_int), C.c_int, vp]),
         "et_debug_affine_back_ws_floats": (C.c_size_t, [C.c_int] * 2),
@@ -99,7 +100,7 @@ EXPORTS = ["et_create", "et_destroy", "et_num_tensors", "et_tensor_info", "et_wo
            "et_bind", "et_profile", "et_importance", "et_importance_master", "et_importance_reduce_static", "et_select", "et_select_stats", "et_tensor_metric", "et_train_step", "et_last_launch_counts",
            "et_kernel_timing", "et_kernel_timing_read", "et_kernel_timing_overhead", "et_last_hip_error", "et_strerror", "et_debug_gemm_bf16", "et_debug_copy", "et_debug_mfma_peak", "et_debug_conv3x3",
            "et_debug_conv3x3_dw", "et_debug_depthwise3x3", "et_debug_depthwise3x3_ws_floats", "et_debug_affine_back", "et_debug_affine_back_ws_floats", "et_debug_flip3x3", "et_debug_conv_first",
-           "et_debug_activation", "et_debug_conv3x3_split", "et_debug_attention", "et_debug_attention_long", "et_debug_attention_long_rest",
+           "et_debug_activation", "et_debug_conv3x3_split", "et_debug_attention", "et_debug_attention_long", "et_debug_attention_long_rest", "et_debug_gemm_bf16_colsum",
            "et_debug_conv_gathered", "et_debug_stem", "et_debug_stem_ws_bytes"]
 
 
@@ -348,6 +349,11 @@ def et_debug_depthwise3x3(op, a, b, gain, shift, out0, out1, ws, batch, H, W, Cc
 
 def et_debug_depthwise3x3_ws_floats(batch, H, W, Cch, stride):
     return _lib.et_debug_depthwise3x3_ws_floats(batch, H, W, Cch, stride)
+
+
+def et_debug_gemm_bf16_colsum(A, B, Cp, aux, colsum, M, N, K, lda, ldb, ldc, tile=0, stream=0):
+    return _lib.et_debug_gemm_bf16_colsum(C.c_void_p(A), C.c_void_p(B), C.c_void_p(Cp), C.c_void_p(aux), C.c_void_p(colsum), M, N, K, lda, ldb, ldc,
+                                          tile, C.c_void_p(stream))
 
 
 def et_debug_conv_first(x, w, gain, shift, z, y, batch, H, W, Cin, N, stride, lo, hi, stream=0):

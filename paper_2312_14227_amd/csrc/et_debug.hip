@@ -22,6 +22,18 @@ extern "C" int et_debug_gemm_bf16(const void* A, const void* B, void* C, int M, 
   return e == hipSuccess ? ET_OK : ET_EHIP;
 }
 
+extern "C" int et_debug_gemm_bf16_colsum(const void* A, const void* B, void* C, const void* aux, float* colsum, int M, int N, int K, int lda, int ldb,
+                                         int ldc, int tile, void* stream) {
+  if (!aux || !colsum) return ET_EINVAL;
+  et::GemmDesc g;
+  g.A = (const et::bf16*)A; g.B = (const et::bf16*)B; g.C = C; g.U = (const et::bf16*)aux; g.colsum = colsum;
+  g.M = M; g.N = N; g.K = K; g.lda = lda; g.ldb = ldb; g.ldc = ldc;
+  g.b_t = true; g.mode = et::EPI_GELU_BWD; g.tile = tile;
+  const hipError_t e = et::gemm_bf16(g, (hipStream_t)stream);
+  if (e == hipErrorInvalidValue) return ET_EINVAL;
+  return e == hipSuccess ? ET_OK : ET_EHIP;
+}
+
 extern "C" int et_debug_conv3x3(const void* x, const void* w, void* out, int batch, int H, int W, int C, int N,
                                 const void* bias, const void* U, int mode, int tile, void* stream) {
   et::GemmDesc g;
