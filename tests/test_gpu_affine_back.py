@@ -54,6 +54,40 @@ def test_affine_back(rows, cols):
                         assert torch.all(err <= rows * 2.0 ** -24 * terms.abs().sum(0) + 1e-30)
 
 
+@pytest.mark.parametrize("producer", ["two-group", "ring", "split two-group", "split ring", "first convolution"])
+def test_mask_from_z_is_that_of_the_stored_activation(producer):
+    """z and y as the product's epilogue, its split reduction and the first convolution store them, values spread around either bound of ReLU6
+    (the first convolution: of ReLU): the mask computed from z has to close exactly where the stored y lies on a bound."""
+    import torch
+    from paper_2312_14227_amd import binding as et
+    gen = torch.Generator().manual_seed(3)
+    st = torch.cuda.current_stream().cuda_stream
+    first = producer == "first convolution"
+    batch, H, W, C, N = (2, 40, 40, 3, 64) if first else (2, 16, 24, 64, 64)
+    rows, hi = batch * H * W, float("inf") if first else 6.0
+    dev = lambda a: a.bfloat16().to("cuda:0")
+    x, w = dev(torch.randn(batch, H, W, C, generator=gen)), dev(torch.randn(N, 3, 3, C, generator=gen) / (9 * C) ** 0.5)
+    # every second channel around 0, the others around 6, steps of y near a rounding unit of the bound
+    shift = dev(torch.where(torch.arange(N) % 2 == 0, 0.0, 0.0 if first else 6.0) + torch.randn(N, generator=gen) / 64)
+    gain = dev((1 + torch.rand(N, generator=gen)) / 32)
+    z, y, d, m = (torch.full((rows, N), float("nan"), device="cuda:0", dtype=torch.bfloat16) for _ in range(4))
+    d.copy_(torch.randn(rows, N, generator=gen))
+    p = lambda a: a.data_ptr()
+    if first:
+        assert et.et_debug_conv_first(p(x), p(w), p(gain), p(shift), p(z), p(y), batch, H, W, C, N, 1, 0.0, hi, st) == 0
+    else:
+        split = 3 if producer.startswith("split") else 1
+        part = torch.empty(rows * N * split, device="cuda:0")
+        assert et.et_debug_conv3x3_split(p(x), p(w), p(y), p(z), batch, H, W, C, N, p(shift), p(gain), 0, 3, split, p(part), 23 if "ring" in producer else 17, st) == 0
+    ws = torch.empty(et.et_debug_affine_back_ws_floats(rows, N), device="cuda:0")
+    assert et.et_debug_affine_back(p(d), 0, 0, p(z), 0, p(gain), p(shift), p(m), 0, 0, 0, p(ws), hi, 1, rows, N, st) == 0
+    torch.cuda.synchronize()
+    yf = y.float()
+    is_open = (yf > 0) & (yf < hi)
+    assert 0.2 < is_open.float().mean().item() < 0.8
+    assert torch.equal(m, torch.where(is_open, d, torch.zeros_like(d)))
+
+
 def test_affine_back_rejects():
     import torch
     from paper_2312_14227_amd import binding as et
