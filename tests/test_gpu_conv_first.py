@@ -37,6 +37,16 @@ def test_first_convolution(batch, H, W, C, N, stride):
     assert torch.all((y3.cpu().double() - want).abs() <= 2.0 ** -8 * want + 2 * sums + 2.0 ** -22)
 
 
+@pytest.mark.parametrize("batch,H,W,C,N,stride", [(1, 5, 70, 3, 64, 1), (2, 4, 140, 3, 40, 2), (1, 6, 100, 1, 8, 1), (1, 4, 140, 2, 32, 2)])
+def test_first_convolution_with_tiles_inside_the_image(batch, H, W, C, N, stride):
+    """Rows of 70 output pixels and more: 32 consecutive ones without a border pixel among them, which are gathered without a test."""
+    Wo = (W - 1) // stride + 1
+    inside = lambda p: 0 < p // Wo % ((H - 1) // stride + 1) * stride < H - 1 and 0 < p % Wo * stride < W - 1
+    pixels = batch * ((H - 1) // stride + 1) * Wo
+    assert any(all(inside(p) for p in range(t, t + 32)) for t in range(0, pixels - 31, 32))
+    test_first_convolution(batch, H, W, C, N, stride)
+
+
 def test_first_convolution_rejects():
     import torch
     from paper_2312_14227_amd import binding as et
