@@ -42,7 +42,8 @@ enum Z : int { NO_Z = 0, Z_BF16 = 1, Z_F32 = 2 };
 
 template <int MASK, int ZK, bool ADD>
 __global__ __launch_bounds__(256) void affine_back_kernel(AffineBack a, Plan pl) {
-  __shared__ float red[2][256 * 8], part[2][256];
+  __shared__ __attribute__((aligned(16))) float red[2][256 * 8];
+  __shared__ float part[2][256];
   const int c = threadIdx.x % pl.cw, p = threadIdx.x / pl.cw;
   const int tile = blockIdx.x % pl.tiles, chunk = blockIdx.x / pl.tiles;
   const int c0 = (tile * pl.cw + c) * 8;

@@ -77,7 +77,7 @@ __device__ __forceinline__ Strip strip_of(long long i, const DwGeom& g, const Dw
 // 36 weights of the thread's 4 channels, through LDS; MIRROR: in reverse order of the taps
 template <bool MIRROR>
 __device__ __forceinline__ void load_weights(const bf16* __restrict__ w, int c0, int n, int c, F4 (&wt)[9]) {
-  __shared__ bf16 lw[48 * 36];
+  __shared__ __attribute__((aligned(16))) bf16 lw[48 * 36];
   for (int i = threadIdx.x; i < n * 9; i += 256) *(bf16x4*)(lw + i * 4) = *(const bf16x4*)(w + (long long)c0 * 9 + i * 4);
   __syncthreads();
   bf16x4 raw[9];
@@ -219,7 +219,8 @@ __global__ __launch_bounds__(256) void depthwise_dx2_kernel(const bf16* __restri
 template <int S>
 __global__ __launch_bounds__(256) void depthwise_dw_kernel(const bf16* __restrict__ d, const bf16* __restrict__ x, float* __restrict__ part, DwGeom g,
                                                            DwPlan pl) {
-  __shared__ float red[256 * 12], red2[256];
+  __shared__ __attribute__((aligned(16))) float red[256 * 12];
+  __shared__ float red2[256];
   const int c = threadIdx.x % pl.cw, p = threadIdx.x / pl.cw, c0 = (int)(blockIdx.x % pl.tiles) * pl.cw * 4, c4 = c0 + c * 4;
   F4 acc[9] = {};
   if (p < pl.pw && c4 < g.C) {

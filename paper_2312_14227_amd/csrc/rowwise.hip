@@ -101,7 +101,8 @@ struct SumJobs {
   SumJob job[MAX_JOBS];
 };
 __global__ __launch_bounds__(256) void sum_finish_kernel(SumJobs jobs) {
-  __shared__ float red[64][20], red2[16][17];
+  __shared__ __attribute__((aligned(16))) float red[64][20];
+  __shared__ float red2[16][17];
   int lo = 0, hi = jobs.n - 1;   // the job this workgroup belongs to: the last with block0 <= blockIdx.x
   while (lo < hi) {
     const int mid = (lo + hi + 1) >> 1;
