@@ -16,7 +16,9 @@
 // operands are those of gemm_bf16_kernels.h; with rows of 64 elements (128 bytes) a transposed operand is swizzled by
 // ((k >> 1) & 1) << 2 instead, two k-rows filling one 256-byte bank span.
 // Ragged K needs no predicate on the data path: in the last slice a lane whose piece lies beyond the end reads a block
-// of zeros instead (both operands do, so nothing beyond the matrix is ever multiplied).  The same block stands in for
+// of zeros instead.  A piece of a row-major operand is 8 k values, so its columns K .. round8(K) - 1 are read and multiplied, by
+// zeros if the other operand is transposed and by that one's own if it is row-major too: such padding has to be finite, and zero
+// in one of two row-major operands (as in every other tile of this family).  The same block stands in for
 // the pixels outside the image of an implicit convolution (CONV = 1: operand A is gathered, CONV = 2: operand B of a weight
 // gradient is, over any number of output pixels; geometry from the launch arguments, see gemm_pp_kernel).
 #pragma once
@@ -39,7 +41,7 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_ring_kernel(Params g) {
   static_assert(CONV != 2 || (AT && BT), "implicit convolution, weight gradient: both operands reduce over rows");
   constexpr int EPI_BYTES = NW * epi_wave_bytes<TN>();
   constexpr int SMEM = RING * STAGE > EPI_BYTES ? RING * STAGE : EPI_BYTES;
-  static_assert(RING >= 2 && RING <= 8 && SMEM <= 160 * 1024, "LDS ring");
+  static_assert((RING == 2 || RING == 3) && SMEM <= 160 * 1024, "LDS ring");
   __shared__ __attribute__((aligned(1024))) unsigned char smem[SMEM];
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -234,14 +236,9 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_ring_kernel(Params g) {
   // wait until slice `sl` has landed: up to `most` younger slices stay in flight
   auto wait_slice = [&](int sl, auto most_tag) {
     constexpr int MOST = decltype(most_tag)::value;
-    static_assert(MOST * LOADS <= 63, "vmcnt");
+    static_assert(MOST <= 2 && MOST * LOADS <= 63, "vmcnt");
     const int younger = min(MOST, nk - 1 - sl);
-    if (younger == MOST) { wait_vmcnt<MOST * LOADS>(); return; }
-    if (MOST > 6 && younger == 6) wait_vmcnt<(MOST > 6 ? 6 : 0) * LOADS>();
-    else if (MOST > 5 && younger == 5) wait_vmcnt<(MOST > 5 ? 5 : 0) * LOADS>();
-    else if (MOST > 4 && younger == 4) wait_vmcnt<(MOST > 4 ? 4 : 0) * LOADS>();
-    else if (MOST > 3 && younger == 3) wait_vmcnt<(MOST > 3 ? 3 : 0) * LOADS>();
-    else if (MOST > 2 && younger == 2) wait_vmcnt<(MOST > 2 ? 2 : 0) * LOADS>();
+    if (younger == MOST) wait_vmcnt<MOST * LOADS>();
     else if (MOST > 1 && younger == 1) wait_vmcnt<LOADS>();
     else wait_vmcnt<0>();
   };

@@ -34,6 +34,7 @@ struct GemmDesc {
   const bf16* A = nullptr;
   const bf16* B = nullptr;
   int M = 0, N = 0, K = 0;
+  // a row-major operand is read up to K rounded up to 8: finite values there, and zeros in one of two row-major operands
   int lda = 0, ldb = 0;
   bool a_t = false, b_t = false;
   // batching: blockIdx.z = outer * z_inner + inner; offsets in elements
@@ -130,8 +131,7 @@ int layernorm_bwd_parts(int rows);
 hipError_t layernorm_bwd(const LayerNormBwd& a, hipStream_t s);
 
 // Column sums over rows come in two steps.  A first kernel leaves partial sums, colsum_parts(rows, cols) rows of `cols`
-// floats (colsum_partial_elems in all); sum_finish adds the partial rows of any number of such jobs in one launch, in a
-// fixed order.
+// floats; sum_finish adds the partial rows of any number of such jobs in one launch, in a fixed order.
 //   colsum_part: sum_r d[r][c] * (h ? (h[r][c]-mean[r])*rstd[r] : 1);  d is bf16 (d_f32 == nullptr) or fp32
 struct SumJob {
   const float* part;   // [rows][cols], 16-byte aligned
@@ -143,7 +143,6 @@ hipError_t colsum_part(const bf16* d, const float* d_f32, long long d_stride, co
                        const float* rstd, long long stat_stride, float* part, int rows, int cols, hipStream_t s);
 hipError_t sum_finish(SumJob* jobs, int n, hipStream_t s, int* launches);
 int colsum_parts(int rows, int cols);
-size_t colsum_partial_elems(int rows, int cols);
 // Backward of a per-channel affine, rows x cols, cols a multiple of 8.  With m = (d + add) where the activation is open, else 0 (as
 // rounded to bf16): dmid = m; dout = m * gain; part_sum, part_mul: affine_back_parts(rows, cols) rows of partial sums of m and of
 // m * z.  Every output is nullable, dmid may alias d or add.  Open: everywhere; or where 0 < y < hi; or (mask_from_z) where
@@ -204,8 +203,6 @@ hipError_t embed_assemble(const float* e, const bf16* cls, const bf16* pos, floa
 hipError_t gather_patch_rows(const float* d, bf16* out, int B, int T, int D, hipStream_t s);
 // fill with zeros (a kernel, so that it may be captured in a graph)
 hipError_t fill_zero(void* p, size_t bytes, hipStream_t s);
-// fp32 -> bf16
-hipError_t cast_bf16(const float* in, bf16* out, size_t n, hipStream_t s);
 
 // ------------------------------------------------------------------------------------------
 // convolutional workload: NHWC bf16 activations, a convolution is a GEMM over an im2col matrix

@@ -213,7 +213,7 @@ __global__ __launch_bounds__(64) void xent_loss_kernel(const float* __restrict__
 }
 
 // ---------------------------------------------------------------------------------------------
-// embedding assembly, CLS-row drop, fill, cast
+// embedding assembly, CLS-row drop, fill
 // ---------------------------------------------------------------------------------------------
 __global__ void embed_assemble_kernel(const float* __restrict__ e, const bf16* __restrict__ cls,
                                       const bf16* __restrict__ pos, float* __restrict__ h0, int B, int T, int D) {
@@ -256,11 +256,6 @@ __global__ void fill_zero_kernel(uint4* __restrict__ p, size_t n16, unsigned cha
   if (blockIdx.x == 0 && threadIdx.x < ntail) tail[threadIdx.x] = 0;
 }
 
-__global__ void cast_bf16_kernel(const float* __restrict__ in, bf16* __restrict__ out, size_t n) {
-  const size_t stride = (size_t)gridDim.x * blockDim.x;
-  for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += stride) out[i] = (bf16)in[i];
-}
-
 inline bool al16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
 inline bool al8(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 7) == 0; }
 
@@ -270,7 +265,6 @@ int colsum_parts(int rows, int cols) {
   const int per = cs_rows(rows, cols);
   return (rows + per - 1) / per;
 }
-size_t colsum_partial_elems(int rows, int cols) { return (size_t)colsum_parts(rows, cols) * cols; }
 
 hipError_t colsum_part(const bf16* d, const float* d_f32, long long d_stride, const float* h, long long h_stride, const float* mean,
                        const float* rstd, long long stat_stride, float* part, int rows, int cols, hipStream_t s) {
@@ -374,14 +368,6 @@ hipError_t fill_zero(void* p, size_t bytes, hipStream_t s) {
   if (blocks == 0) blocks = 1;
   hipLaunchKernelGGL(fill_zero_kernel, dim3((unsigned)blocks), dim3(256), 0, s, (uint4*)p, n16,
                      (unsigned char*)p + n16 * 16, ntail);
-  return hipGetLastError();
-}
-
-hipError_t cast_bf16(const float* in, bf16* out, size_t n, hipStream_t s) {
-  if (n == 0) return hipSuccess;
-  size_t blocks = (n + 255) / 256;
-  if (blocks > 4096) blocks = 4096;
-  hipLaunchKernelGGL(cast_bf16_kernel, dim3((unsigned)blocks), dim3(256), 0, s, in, out, n);
   return hipGetLastError();
 }
 
