@@ -165,6 +165,9 @@ int et_bind(et_ctx* ctx, void* const* w_dev, void* const* opt_state_dev, void* c
  *               operations without weights (ReLU/GELU, attention core, residual additions)
  *               are charged to the tensor that must be passed for them to run (Section 5.3);
  *               a LayerNorm's input-gradient kernel is charged to its gain (Section 5.2);
+ *               a bias, gain or shift whose sum rides on a launch of another tensor is charged with what it adds
+ *               to that launch (ET_VIT: these launches are timed with and without it beforehand, one more
+ *               iteration in all) and its share of the launch that finishes the sums;
  *   t_fwd_ns:   the whole forward pass including the loss and its gradient.
  * Every timed iteration is followed by the same iteration without events, timed as a whole; the
  * excess of the instrumented one is the measurement's own overhead and is taken off the regions

@@ -115,7 +115,7 @@ def _run_chain(chain, mask, state):
 
 
 # ----------------------------------------------------------------------------
-# ReLU MLP without biases (BASELINE configs[0])
+# ReLU MLP without biases
 # ----------------------------------------------------------------------------
 def mlp_forward(cfg, weights, x, y):
     W = [_f64(w) for w in weights]
@@ -150,7 +150,7 @@ def mlp_step(cfg, weights, x, y, mask):
 
 
 # ----------------------------------------------------------------------------
-# pre-LN vision transformer encoder (BASELINE configs[1..3])
+# pre-LN vision transformer encoder
 # ----------------------------------------------------------------------------
 def vit_forward(cfg, weights, x, y):
     W = [_f64(w) for w in weights]

@@ -11,7 +11,7 @@ needed exactly when something before the block is selected, so it is part of dy(
 first main convolution, where the two branches are summed.  Backward work of operations without
 weights (ReLU, pooling) lies in the dy() of the tensor that has to be passed for it to be needed.
 
-BatchNorm is "folded" (BASELINE): a per-channel affine y = gain * z + shift without batch
+BatchNorm is "folded": a per-channel affine y = gain * z + shift without batch
 statistics.  Layout NHWC; convolution weights [out, kh, kw, in]; zero padding (k-1)/2.
 
 Storage precision.  With store=None everything is float64 (the plain definition; this is what the

@@ -121,13 +121,13 @@ def mobilenet_blocks(cfg):
 
 
 CONFIGS = {
-    # BASELINE configs[0]: 4-layer ReLU MLP, fp32, batch 32
+    # 4-layer ReLU MLP, fp32, batch 32
     "mlp": MLPConfig("mlp", (256, 256, 256, 256, 10), 32),
-    # BASELINE configs[1]/[2]: ViT-B/16 shape, batch 64
+    # ViT-B/16 shape, batch 64
     "vit_b": ViTConfig("vit_b", 64, 197, 768, 768, 12, 3072, 12, 200),
-    # BASELINE configs[3]: ViT-L/16 shape, batch 32
+    # ViT-L/16 shape, batch 32
     "vit_l": ViTConfig("vit_l", 32, 197, 768, 1024, 16, 4096, 24, 200),
-    # BASELINE configs[4]: ResNet-50 shape, batch 32
+    # ResNet-50 shape, batch 32
     "resnet50": ResNetConfig("resnet50", 32, 224, 3, 64, (3, 4, 6, 3), (64, 128, 256, 512), 200),
     "resnet_tiny": ResNetConfig("resnet_tiny", 2, 16, 3, 8, (1, 1), (8, 8), 8),
     "resnet_small": ResNetConfig("resnet_small", 3, 64, 3, 16, (2, 1, 2, 1), (8, 16, 24, 32), 24),

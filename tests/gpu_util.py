@@ -9,7 +9,7 @@ def rel_l2(got, ref):
 
 
 def tol_for(cfg):
-    """BASELINE tolerance: relative error 2e-2 with bf16 inputs, 1e-5 for the fp32 workload."""
+    """Relative error 2e-2 with bf16 inputs, 1e-5 for the fp32 workload."""
     return 2e-2 if cfg.dtype == "bf16" else 1e-5
 
 
