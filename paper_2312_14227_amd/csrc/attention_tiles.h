@@ -63,7 +63,7 @@ __device__ __forceinline__ int tile_row(int r, int lane) { return (r >> 2) * 8 +
 constexpr int STORE_AREA = 32 * 128;
 // `sums` (nullable, wave-private, in LDS): receives the column sums of the stored rows, 64 floats, as rounded.  Each lane adds the
 // pieces it stores, then the eight lanes of a column share out the adding (7 shuffles).  With the addition over the waves the sums
-// lengthen a backward launch of 64 x 12 heads from 63.5 to 71 us (as 32 two-byte LDS reads per column did); another
+// lengthen a backward launch of 64 x 12 heads from 64.6 to 68.6 us (as 32 two-byte LDS reads per column to 71); another
 // pass over dQ, dK and dV took 8.5 to 11 and a launch.
 __device__ __forceinline__ void store_tile(unsigned char* area, const f32x16 (&t)[2], float mul, bf16* base, long long ld,
                                            int rows, int lane, float* sums = nullptr) {

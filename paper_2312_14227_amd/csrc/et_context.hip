@@ -356,7 +356,7 @@ et::LayerNormBwd vit_ln2_back(et_ctx* c, const VitDims& v, const VitRows& q, con
 
 // What the column sums add to the three kinds of launches that they ride on, as a share of the launch: each kind is timed with and
 // without them, on the buffers that a backward pass has left (all scratch of the next one).  What a step saves without
-// such a bias depends on the shape: 7.5 of 71 us of the attention of 64 x 12 heads of 197 tokens, nothing where the launch itself is
+// such a bias depends on the shape: 4 of 68.6 us of the attention of 64 x 12 heads of 197 tokens, nothing where the launch itself is
 // what takes time.
 enum SumKernel : int { SUM_ATTENTION = 0, SUM_GELU = 1, SUM_LAYERNORM = 2 };
 int vit_time_sums(et_ctx* c) {
