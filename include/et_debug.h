@@ -17,8 +17,8 @@ extern "C" {
  * C is fp32 if c_f32 else bf16, leading dimension ldc.  split_k > 1 needs c_f32, ldc == N and
  * `partials` with M*N*split_k floats.  A residual needs c_f32 and a_t = b_t = 0.  tile: 0 =
  * automatic, otherwise a tile id of the library (1, 3: register-staged 128x128, 128x64; 5, 7:
- * direct-to-LDS 256x256, 256x128; 11, 13, 15, 17, 19, 21: the two-group tiles 256x256, 256x192, 256x128, 512x64,
- * 128x256, 64x512; 23, 25, 29: the ring tiles 64x64, 64x128, 128x128).  epilogue: 0 the plain one above; 1 GELU forward, with u = the value above: bf16 C = gelu'(u) and
+ * direct-to-LDS 256x256, 256x128; 11, 13, 15: the two-group tiles 256x256, 192x256, 128x256 straight to LDS; 17, 19, 21: those
+ * through registers, 512x64, 128x256, 64x512; 23, 25, 29: the ring tiles 64x64, 64x128, 128x128).  epilogue: 0 the plain one above; 1 GELU forward, with u = the value above: bf16 C = gelu'(u) and
  * a second bf16 output aux [M][ldc] = gelu(u); 2 GELU backward: bf16 C = value * aux, aux bf16 [M][ldc] the stored
  * gelu'(u) (b_t = 1 only); 3 bf16 C = gelu(u), aux unused.  stream: hipStream_t.
  * Returns 0, or -1 for a rejected argument, -3 for a HIP error. */

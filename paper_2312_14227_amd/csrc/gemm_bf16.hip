@@ -95,8 +95,10 @@ __global__ __launch_bounds__(256) void splitk_reduce_epilogue_kernel(ReduceEpi e
   ((bf16x4*)e.out)[i] = o;
 }
 
-enum TileId : int { T_AUTO = 0, T_128x128 = 1, T_128x64 = 3, T_DMA_256x256 = 5, T_DMA_256x128 = 7, T_PP_256x256 = 11, T_PP_256x192 = 13,
-              T_PP_256x128 = 15, T_PP_512x64 = 17, T_PP_128x256 = 19, T_PP_64x512 = 21, T_RING_64x64 = 23, T_RING_64x128 = 25, T_RING_128x64 = 27, T_RING_128x128 = 29 };
+// tiles of the plain products; the implicit convolutions have a kernel of their own for 11, 13 (256x192), 15 (256x128) and 17 .. 21
+enum TileId : int { T_AUTO = 0, T_128x128 = 1, T_128x64 = 3, T_DMA_256x256 = 5, T_DMA_256x128 = 7, T_DIRECT_256x256 = 11, T_DIRECT_192x256 = 13,
+              T_DIRECT_128x256 = 15, T_PP_256x256 = 11, T_PP_256x192 = 13, T_PP_256x128 = 15, T_PP_512x64 = 17, T_PP_128x256 = 19, T_PP_64x512 = 21,
+              T_RING_64x64 = 23, T_RING_64x128 = 25, T_RING_128x64 = 27, T_RING_128x128 = 29 };
 
 // number of compute units of the current device (256 on an MI355X), looked up once per device; a multiple of 8
 // (one share per XCD) as the resident kernels' unit order assumes whenever a workgroup takes a second unit
@@ -140,11 +142,6 @@ Plan plan_tiles(int M, int N, int K, bool may_split, const TileRate* cand, int n
     }
   }
   return best;
-}
-
-Plan plan_large(int M, int N, int K, bool may_split) {
-  static const TileRate cand[2] = {{T_PP_256x256, 256, 256, 3.3e12}, {T_PP_256x192, 256, 192, 3.0e12}};
-  return plan_tiles(M, N, K, may_split, cand, 2);
 }
 
 // weight gradient of a convolution, [M = output channels][N = 9 input channels] reduced over the pixels:
@@ -234,51 +231,86 @@ const RingTile kRingConv[4] = {{T_RING_64x64, 64, 64, 0.28e-6, 0.19e-6, 0.5e-6},
 const RingTile kRingConvDw[3] = {{T_RING_64x64, 64, 64, 0.365e-6, 0.24e-6, 0.5e-6}, {T_RING_64x128, 64, 128, 0.46e-6, 0.36e-6, 1.0e-6},
                                  {T_RING_128x64, 128, 64, 0.36e-6, 0.34e-6, 1.0e-6}};
 
-// Large products with K in slices of 64, one batch entry: rounds of workgroups x (slices x time per slice + fixed part), us, in a
-// launch of its own but for 2 us that all share.  A slice of a two-group tile takes longer the more CUs are at work (the clock
-// follows the load), one of a 64x128 ring tile the more rounds there are (its operand re-reads); with an fp32
-// residual and result beside them the operands come from further away, which costs a two-group tile, one slice ahead, some per
-// slice and a ring tile little.  Against the rule
-// before (two-group tiles only), 138 shapes of [3152 .. 12608 rows] x [512 .. 4096] x [512 .. 4096] took 5351 us and take 5020, the
-// best of five tiles each 5006; [3152 x 768 x 3072] 47.3 -> 29.1 us, [6304 x 512 x 2048] 34.4 -> 22.1, [4616 x 768 x 3072] with
-// residual 54.9 -> 36.1, [6304 x 1024 x 4096] with residual 91.7 -> 84.5.
+// Large products with K in slices of 64: rounds of workgroups over the 256 CUs x (slices x time per slice + fixed part), us.  A slice takes longer the more
+// CUs are at work (`load` more with all of them: the clock follows the load); an epilogue with more arithmetic or with an fp32 residual adds per
+// round, a residual its memory traffic.  Fitted (relative error 3 - 5 %) to 161 products of [1576 .. 17000 rows] x [384 .. 4096] x [512 .. 4096]: those of 8 GFLOP
+// and more take 8656 us with this choice, the best tile of each 8641, and took 9877 with the tiles through registers (256x256, 256x192,
+// 256x128) that the direct ones replace: [12608 x 3072 x 768] 78 -> 68 us, with GELU 106 -> 94, [12608 x 768 x 3072] 73 -> 62, with
+// residual 92 -> 73, [9000 x 4096 x 1024] 92 -> 76.  Between 6 and 8 GFLOP 444 -> 431, below nothing.
 int choose_large_tile(const GemmDesc& d, int K) {
-  struct Cand { int tile, bm, bn; double slice, per_cu, per_round, solo, fixed; };
-  static const Cand cand[5] = {{T_PP_256x256, 256, 256, 0.65, 0.0045, 0.0, 0.0, 6.4}, {T_PP_256x192, 256, 192, 0.72, 0.0023, 0.0, 0.0, 7.5},
-                               {T_PP_256x128, 256, 128, 0.75, 0.0008, 0.0, 0.0, 7.0},
-                               {T_RING_64x128, 64, 128, 0.30, 0.0, 0.01, 0.36, 1.2}, {T_RING_128x128, 128, 128, 0.56, 0.0, 0.0, 0.53, 2.8}};
-  const bool gelu = d.mode == EPI_GELU_FWD || d.mode == EPI_GELU_BWD || d.mode == EPI_GELU_ONLY;
-  const int slices = K / gemm::PBK;
-  int best = T_PP_256x256;
+  struct Cand { int tile, bm, bn; double slice, load, rounds2, fixed, once, gelu, gelu_back, res, res_elem, elem; };
+  static const Cand cand[5] = {{T_DIRECT_256x256, 256, 256, 0.870, 0.525, 0.0, 2.79, 3.68, 8.31, 2.56, 3.39, 0.632e-6, 0.238e-6},
+                               {T_DIRECT_192x256, 192, 256, 0.686, 0.536, 0.0, 3.48, 2.62, 6.68, 2.15, 2.20, 0.679e-6, 0.110e-6},
+                               {T_DIRECT_128x256, 128, 256, 0.644, 0.345, 0.0, 2.92, 2.41, 4.66, 1.74, 1.39, 0.785e-6, 0.041e-6},
+                               {T_RING_64x128, 64, 128, 0.227, 0.092, 0.00065, 1.00, 3.90, 1.38, 0.02, 0.0, 0.640e-6, 0.0},
+                               {T_RING_128x128, 128, 128, 0.431, 0.147, 0.0, 2.11, 2.14, 3.31, 0.0, 0.0, 0.715e-6, 0.317e-6}};
+  const bool gelu = d.mode == EPI_GELU_FWD || d.mode == EPI_GELU_ONLY, gelu_back = d.mode == EPI_GELU_BWD;
+  const double slices = (K + gemm::PBK - 1) / gemm::PBK, batch = (double)d.z_outer * d.z_inner * std::max(1, d.split_k), elems = (double)d.M * d.N * batch;
+  int best = T_DIRECT_128x256;
   double least = 1e30;
   for (const Cand& c : cand) {
-    const bool ring = c.solo > 0.0;
-    if (c.tile == T_PP_256x128 && gelu) continue;   // (not built)
-    const double tiles = (double)((d.M + c.bm - 1) / c.bm) * ((d.N + c.bn - 1) / c.bn), rounds = std::ceil(tiles / 256.0);
-    const double slice = ring && rounds == 1.0 ? c.solo : c.slice + c.per_cu * tiles / rounds + c.per_round * rounds;
-    double t = rounds * (slices * slice + c.fixed);
-    if (d.residual) t += ring ? 8.0 * d.M * d.N / 9e6 : 0.33 * slices;
+    // (the epilogues of a folded BatchNorm need more registers than the tallest tiles leave)
+    if (d.mode == EPI_AFFINE_RELU && c.tile == T_DIRECT_256x256) continue;
+    if (d.mode == EPI_AFFINE_ADD_RELU && (c.tile == T_DIRECT_256x256 || c.tile == T_DIRECT_192x256)) continue;
+    const double tiles = (double)((d.M + c.bm - 1) / c.bm) * ((d.N + c.bn - 1) / c.bn) * batch, rounds = std::ceil(tiles / 256.0);
+    double t = rounds * (slices * (c.slice + c.load * tiles / rounds / 256.0 + c.rounds2 * rounds) + c.fixed) + c.once + c.elem * elems;
+    if (d.residual) t += rounds * c.res + c.res_elem * elems;
+    if (gelu || gelu_back) t += rounds * (gelu ? c.gelu : c.gelu_back);
     if (t < least) { least = t; best = c.tile; }
+  }
+  return best;
+}
+
+// Weight gradients [M][N] over K rows of 4 GFLOP and more: tile and split with the least estimated time (us).  As above, with the partials' traffic and
+// the second launch of a split; the time per slice of a ring tile grows with the length of its chunk (its operand re-reads).  Fitted to
+// 85 shapes of [384 .. 4096] x [384 .. 1024] over 1576 .. 17000 rows with up to a dozen plans each: the chosen plans take 3053 us in sum, the best 3007.
+// [3072 x 768] over 12608 rows 77 -> 70 us, [2304 x 768] 63 -> 58, [768 x 768] 38 -> 28, [4096 x 1024] over 6304 71 -> 65.
+Plan plan_dw(int M, int N, int K) {
+  struct Cand { int tile, bm, bn; double slice, slice2, load, solo, fixed, once, part, elem, split, rounds2; };
+  static const Cand cand[5] = {{T_DIRECT_256x256, 256, 256, 0.833, 0.0, 0.696, 0.0, 5.38, 5.92, 0.880e-6, 0.0, 0.0, 0.0},
+                               {T_DIRECT_192x256, 192, 256, 0.841, 0.0, 0.419, 0.0, 3.84, 4.65, 0.890e-6, 0.0, 1.80, 0.0},
+                               {T_DIRECT_128x256, 128, 256, 0.765, 0.0, 0.304, 0.0, 2.35, 5.45, 0.744e-6, 0.0, 2.41, 0.0},
+                               {T_RING_64x128, 64, 128, 0.179, 0.00069, 0.0, 0.0, 0.0, 5.61, 1.377e-6, 0.750e-6, 2.53, 0.0228},
+                               {T_RING_64x64, 64, 64, 0.116, 0.00047, 0.0, 0.0179, 0.0, 5.95, 1.581e-6, 0.189e-6, 1.00, 0.0122}};
+  const int slices = (K + gemm::PBK - 1) / gemm::PBK;
+  const int max_split = (N & 3) == 0 ? std::max(1, std::min(256, slices / 4)) : 1;
+  Plan best = {T_RING_64x128, 1, 1e30};
+  for (const Cand& c : cand) {
+    const double tiles = (double)((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn), elems = (double)M * N;
+    for (int s = 1; s <= max_split; s++) {
+      if (s > 1 && tiles * s > 1280) break;
+      const int per = (slices + s - 1) / s;
+      if ((slices + per - 1) / per != s) continue;   // this split leaves empty chunks
+      const double rounds = std::ceil(tiles * s / 256.0);
+      double t = rounds * (per * (c.slice + c.slice2 * per + c.load * tiles * s / rounds / 256.0 + c.rounds2 * rounds) + c.fixed) + c.once + c.elem * elems;
+      if (rounds == 1.0) t += c.solo * per;
+      if (s > 1) t += c.part * s * elems + c.split;
+      if (t < best.cost) best = {c.tile, s, t};
+    }
   }
   return best;
 }
 
 int choose_tile(const GemmDesc& d, int k_per_block) {
   const bool dma_ok = (d.K % gemm::DBK) == 0 && (k_per_block % gemm::DBK) == 0;
-  const bool pp_ok = (d.K % gemm::PBK) == 0 && (k_per_block % gemm::PBK) == 0;
-  if (d.tile == T_PP_256x256 || d.tile == T_PP_256x192) return pp_ok ? d.tile : (dma_ok ? T_DMA_256x256 : T_128x128);
-  if (d.tile == T_PP_256x128 || d.tile == T_PP_512x64 || d.tile == T_PP_128x256 || d.tile == T_PP_64x512) return pp_ok ? d.tile : T_128x128;
+  const bool slices_ok = (d.K % gemm::PBK) == 0 && (k_per_block % gemm::PBK) == 0;
+  // the direct tiles take any number of rows of a weight gradient; their lanes' offsets within a slice are 32 bits wide
+  const bool direct_ok = (slices_ok || (d.a_t && d.b_t)) && d.lda < (1 << 22) && d.ldb < (1 << 22);
+  if (d.tile == T_DIRECT_256x256 || d.tile == T_DIRECT_192x256 || d.tile == T_DIRECT_128x256) {
+    if (!direct_ok) return dma_ok ? T_DMA_256x256 : T_128x128;
+    if (d.mode == EPI_AFFINE_ADD_RELU) return T_DIRECT_128x256;
+    return d.mode == EPI_AFFINE_RELU && d.tile == T_DIRECT_256x256 ? T_DIRECT_192x256 : d.tile;
+  }
+  if (d.tile == T_PP_512x64 || d.tile == T_PP_128x256 || d.tile == T_PP_64x512) return slices_ok ? d.tile : T_128x128;
   if (d.tile == T_DMA_256x256 || d.tile == T_DMA_256x128) return dma_ok ? d.tile : T_128x128;
   if (d.tile != T_AUTO) return d.tile;
-  // large problems (8 GFLOP and more, a ViT-L layer at batch 32 has 13): the tile with the least estimated time where K comes
-  // in slices of 64, else the direct-to-LDS tile with slices of 32.  The GELU forward epilogues cost a 256x256 tile as much
-  // as half its main loop; two 256x128 direct-to-LDS workgroups per CU that overlap one's epilogue with the other's MFMAs run no
-  // faster than the resident two-group tile (101.7 against 101.3 us for the ViT-B fc1 product).
+  // large problems (6 GFLOP and more, with the epilogues of a folded BatchNorm 8; a ViT-L layer at batch 32 has 13): the tile with the least
+  // estimated time where K comes in slices of 64, else the direct-to-LDS tile with slices of 32.
   const int batch = d.z_outer * d.z_inner;
-  if (d.M >= 512 && d.N >= 256 && 2.0 * d.M * d.N * (double)k_per_block * batch >= 8e9) {
+  const bool affine = d.mode == EPI_AFFINE_RELU || d.mode == EPI_AFFINE_ADD_RELU;
+  if (d.M >= 512 && d.N >= 256 && 2.0 * d.M * d.N * (double)k_per_block * batch >= (affine ? 8e9 : 6e9)) {
     const long long big_tiles = (long long)((d.M + 255) / 256) * ((d.N + 255) / 256) * batch;
-    if (pp_ok && k_per_block >= 4 * gemm::PBK)
-      return batch == 1 ? choose_large_tile(d, k_per_block) : plan_large(d.M, d.N, k_per_block, false).tile;
+    if (direct_ok && k_per_block >= 4 * gemm::PBK) return choose_large_tile(d, k_per_block);
     if (dma_ok && k_per_block >= 4 * gemm::DBK && big_tiles >= 128) return d.N >= 2560 ? T_DMA_256x128 : T_DMA_256x256;
   }
   return plan_small(d.M, d.N, k_per_block, batch * std::max(1, d.split_k)).tile;
@@ -316,22 +348,10 @@ void gemm_bf16_plan_conv_dw(int M, int N, int K, int* tile, int* split_k, int ta
 void gemm_bf16_plan_split(int M, int N, int K, int* tile, int* split_k) {
   *tile = T_AUTO;
   *split_k = 1;
-  // up to 16 GFLOP the ring tile wins ([1024 x 256] over 6272 rows 11.9 us against 25.1 for the best two-group plan,
-  // [768 x 768] over 12 608 29.9 / 33.0, [3072 x 768] over 3136 32.7 / 34.5), beyond it the two-group tiles do ([2304 x 768]
-  // over 6272 42.5 / 40.3, [768 x 3072] over 12 608 96 / 72)
-  const bool large = 2.0 * M * N * (double)K >= 1.6e10;
-  if (large && M >= 256 && N >= 256 && (K % gemm::PBK) == 0 && K >= 4 * gemm::PBK) {
-    const Plan pl = plan_large(M, N, K, true);
+  if (2.0 * M * N * (double)K >= 4e9 && M >= 256 && N >= 256 && K >= 4 * gemm::PBK) {
+    const Plan pl = plan_dw(M, N, K);
     *tile = pl.tile;
     *split_k = pl.split;
-  } else if (large && M >= 256 && N >= 256 && (K % gemm::DBK) == 0 && K >= 128 * gemm::DBK) {
-    // a long reduction whose length is a multiple of 32 but not of 64 (ViT-L at batch 32: 6 304 rows) takes the
-    // direct-to-LDS tiles; unsplit, its 16-64 tiles of 256x256 would leave most CUs idle.  Measured on those shapes:
-    // about 256 units in all, at most 8 chunks (4096x1024: 98 -> 71 us with 4 chunks; 1024x1024: 70 -> 31 us with 8).
-    // Shorter reductions (1 568 rows: the last ResNet-50 stage) are better off with the rule below.
-    const int tiles = ((M + 255) / 256) * ((N + 255) / 256);
-    *split_k = std::max(1, std::min(8, 256 / tiles));
-    *tile = tiles >= 32 ? T_DMA_256x256 : T_DMA_256x128;
   } else {   // everything else runs on the ring tile, any K
     const Plan pl = plan_ring(M, N, K, true, ((double)M + N) * K, kRingDw);
     *split_k = pl.split;
@@ -494,15 +514,15 @@ hipError_t gemm_bf16(const GemmDesc& d, hipStream_t s, int* launches) {
     case T_PP_64x512: BM = 64; BN = 512; fn = gemm::pp_64x512(d.a_t, d.b_t, epi); break;
     case T_PP_128x256: BM = 128; BN = 256; fn = gemm::pp_128x256(d.a_t, d.b_t, epi); break;
     case T_PP_512x64: BM = 512; BN = 64; fn = gemm::pp_512x64(d.a_t, d.b_t, epi); break;
-    case T_PP_256x128: BM = 256; BN = 128; fn = gemm::pp_256x128(d.a_t, d.b_t, epi); break;
     case T_128x64: BM = 128; BN = 64; fn = gemm::staged_128x64(d.a_t, d.b_t, epi); resident = false; break;
     case T_RING_64x64: BM = 64; BN = 64; fn = gemm::ring_64x64(d.a_t, d.b_t, epi); resident = false; break;
     case T_RING_64x128: BM = 64; BN = 128; fn = gemm::ring_64x128(d.a_t, d.b_t, epi); resident = false; break;
     case T_RING_128x128: BM = 128; BN = 128; fn = gemm::ring_128x128(d.a_t, d.b_t, epi); resident = false; break;
     case T_DMA_256x256: BM = 256; BN = 256; fn = gemm::dma_256x256(d.a_t, d.b_t, epi); resident = false; break;
     case T_DMA_256x128: BM = 256; BN = 128; fn = gemm::dma_256x128(d.a_t, d.b_t, epi); resident = false; break;
-    case T_PP_256x192: BM = 256; BN = 192; fn = gemm::pp_256x192(d.a_t, d.b_t, epi); break;
-    case T_PP_256x256: BM = 256; BN = 256; fn = gemm::pp_256x256(d.a_t, d.b_t, epi); break;
+    case T_DIRECT_256x256: BM = 256; BN = 256; fn = gemm::direct_256x256(d.a_t, d.b_t, epi); break;
+    case T_DIRECT_192x256: BM = 192; BN = 256; fn = gemm::direct_192x256(d.a_t, d.b_t, epi); break;
+    case T_DIRECT_128x256: BM = 128; BN = 256; fn = gemm::direct_128x256(d.a_t, d.b_t, epi); break;
     default: BM = 128; BN = 128; fn = gemm::staged_128x128(d.a_t, d.b_t, epi); resident = false; break;
   }
   if (!fn) return hipErrorInvalidValue;  // this (layout, epilogue) pair is not part of the training step

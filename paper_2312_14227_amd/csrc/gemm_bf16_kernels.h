@@ -17,14 +17,15 @@
 //     [k-rows][tile rows] and the lanes fetch their 2 x 4 k values with ds_read_b64_tr_b16, the
 //     LDS transpose read of gfx950: in every group of 16 lanes, lane 4c+a supplies the address of
 //     4 consecutive elements of k-row c, and lane i receives element i of k-rows 0..3.
-// Four main loops share this (the fourth, the ring of small tiles, is in gemm_bf16_ring.h):
+// Five main loops share this (the ring of small tiles is in gemm_bf16_ring.h, the two-group kernel whose operands go straight to
+// LDS, for the large plain products, in gemm_bf16_direct.h):
 //   gemm_staged_kernel: K slices of 64 through two LDS buffers, the global loads of slice t+1 are
 //     issued into registers before the MFMAs of slice t (many short tiles, several workgroups per CU;
 //     any K, with a predicated last slice);
 //   gemm_dma_kernel: K slices of 32 loaded with global_load_lds_dwordx4 straight into a ring of
 //     LDS stages, several slices in flight (large tiles; K a multiple of 32);
 //   gemm_pp_kernel: K slices of 64 through registers into two LDS stages, the eight waves in two
-//     groups that alternate between MFMAs and memory work (256x256 tile; K a multiple of 64).
+//     groups that alternate between MFMAs and memory work (implicit convolutions; K a multiple of 64).
 // Rows beyond the matrix edge are clamped to valid addresses (their products are never stored).
 // Epilogue: every wave passes its accumulators through a private LDS area, 32 rows at a time, so
 // that each lane ends up with 4 consecutive columns of one row: bias, residual, GELU and the
@@ -734,6 +735,9 @@ __device__ __forceinline__ void dma16(const void* gptr, unsigned lds_base) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds_base), "v"(gptr) : "memory");
 }
 
+// what a lane reads instead of a piece beyond the end of its operand
+__device__ __attribute__((aligned(64))) static const unsigned int kZeroBlock[16] = {0};
+
 template <int BM, int BN, int WGM, int WGN, int RING, bool AT, bool BT, int EPI>
 __global__ __launch_bounds__(WGM* WGN * 64) void gemm_dma_kernel(Params g) {
   constexpr int NW = WGM * WGN;
@@ -1396,9 +1400,9 @@ LaunchFn staged_128x128(bool a_t, bool b_t, int epi);
 LaunchFn staged_128x64(bool a_t, bool b_t, int epi);
 LaunchFn dma_256x256(bool a_t, bool b_t, int epi);
 LaunchFn dma_256x128(bool a_t, bool b_t, int epi);
-LaunchFn pp_256x256(bool a_t, bool b_t, int epi);
-LaunchFn pp_256x192(bool a_t, bool b_t, int epi);
-LaunchFn pp_256x128(bool a_t, bool b_t, int epi);
+LaunchFn direct_256x256(bool a_t, bool b_t, int epi);
+LaunchFn direct_192x256(bool a_t, bool b_t, int epi);
+LaunchFn direct_128x256(bool a_t, bool b_t, int epi);
 LaunchFn pp_512x64(bool a_t, bool b_t, int epi);
 // implicit 3x3 convolution (A gathered from the activation), row-major operands
 LaunchFn pp_conv_256x256(int epi, bool general);

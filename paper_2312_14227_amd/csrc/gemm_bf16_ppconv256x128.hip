@@ -14,24 +14,6 @@ hipError_t launch(const Params& p, dim3 grid, hipStream_t s) {
 
 }  // namespace
 
-LaunchFn pp_256x128(bool a_t, bool b_t, int epi) {
-#define ET_PICK(AT, BT, E) \
-  if (a_t == AT && b_t == BT && epi == E) return launch<AT, BT, E, 0>;
-  ET_PICK(false, false, E_F32)
-  ET_PICK(false, false, E_F32_RES)
-  ET_PICK(false, false, E_BF16)
-  ET_PICK(false, false, E_BIAS_RELU)
-  ET_PICK(false, false, E_AFFINE)
-  ET_PICK(false, false, E_AFFINE_ADD)
-  ET_PICK(false, true, E_F32)
-  ET_PICK(false, true, E_BF16)
-  ET_PICK(true, true, E_F32)
-  ET_PICK(true, true, E_BF16)
-  ET_PICK(true, true, E_PARTIAL)
-#undef ET_PICK
-  return nullptr;
-}
-
 LaunchFn pp_conv_256x128(int epi, bool general) {
   // (general: stride 2, 1x1 taps or the stem form, geometry from the launch arguments; the epilogues those layers use)
   if (general) {

@@ -27,8 +27,6 @@
 namespace et {
 namespace gemm {
 
-__device__ __attribute__((aligned(64))) static const unsigned int kZeroBlock[16] = {0};
-
 template <int BM, int BN, int WGM, int WGN, int RING, bool AT, bool BT, int EPI, int CONV = 0>
 __global__ __launch_bounds__(WGM* WGN * 64) void gemm_ring_kernel(Params g) {
   constexpr int NW = WGM * WGN;
