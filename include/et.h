@@ -280,7 +280,8 @@ int et_last_launch_counts(const et_ctx* ctx, int32_t* forward, int32_t* backward
  * pair of HIP events on the context's stream, so that a benchmark can report the average
  * duration of a kernel inside real training steps.  Classes:
  *   0 forward GEMM (X W^T), 1 gradient-passing GEMM (dY W), 2 weight-gradient GEMM (dY^T X,
- *   including its split-K reduction), 3 importance reduction, 4 masked optimizer update,
+ *   including its split-K reduction; while timing is enabled each runs by itself, otherwise most run together at
+ *   the end of the backward pass), 3 importance reduction, 4 masked optimizer update,
  *   5 fused attention forward, 6 fused attention backward (but not that of the last block, where only one query has a
  *   gradient and another kernel runs), 7 the data-movement kernels of the
  *   convolutional workload (im2col and its adjoint, affine, pooling, per-channel reductions).

@@ -76,6 +76,13 @@ size_t et_debug_stem_ws_bytes(int batch, int H, int W, int C, int N);
 int et_debug_stem(int op, const void* x, const void* w_or_d, float* out, void* ws, int batch, int H, int W, int C, int N,
                   void* stream);
 
+/* Weight gradients in a group, as at the end of a backward pass: C[i] fp32 [M][N] = sum over K rows of A[i][k][m] B[i][k][n], bf16, rows padded to
+ * multiples of 8.  shape: per job M, N, K, split (chunks of the reduction) and, for a convolution's gradient with B[i] the NHWC activation, H, W, C,
+ * taps, stride (C = 0: plain).  partials: device, split * M * N floats of every split job, in all at most partial_elems.  Host arrays of
+ * device pointers, 16-byte aligned; n <= 120.  Returns 0, -1, -3 as above. */
+int et_debug_dw_group(int n, const void* const* A, const void* const* B, float* const* C, const int* shape, float* partials, size_t partial_elems,
+                      void* stream);
+
 /* 3x3 depthwise convolution kernels (zero padding 1, stride 1 or 2; NHWC bf16, C a multiple of 8; weights bf16
  * [C][9]; Ho = (H - 1) / stride + 1, Wo likewise).  op selects the kernel:
  *   0 forward: a = x [batch][H][W][C], b = weights, gain, shift [C]; out0 (nullable) = z, the convolution rounded to

@@ -117,6 +117,13 @@ struct et_ctx {
   size_t sum_arena_elems = 0, sum_used = 0;
   std::vector<et::SumJob> sum_jobs;
   std::vector<int> sum_tensors;
+  // weight gradients that run together at the end of a backward pass, and the arena (bump allocated) for the gradients they read: what
+  // each layer's gradient is stored in if its weight is selected, instead of the scratch buffer that the next layer overwrites
+  bf16* keep_arena = nullptr;
+  size_t keep_elems = 0, keep_used = 0;
+  std::vector<et::DwJob> dw_jobs;
+  std::vector<int> dw_tensors;
+  std::vector<et::DwGroupPlan> dw_plans;   // one per group (a group ends where the scratch of split reductions does)
   // transformer: share of a launch's time that the column sums riding on it take, measured by et_profile ([the last block's few rows][kernel])
   double sum_cost[2][3] = {};
 
@@ -322,6 +329,31 @@ inline et::GemmDesc linear_dw(et_ctx* c, const bf16* dY, int ldy, const bf16* X,
   return g;
 }
 
+// ---- weight gradients at the end of the pass (see et_ctx::keep_arena)
+// `total`: elements of all the gradients that weight gradients are taken from; beyond 24 GB those that find no room run at once
+inline void reserve_keep(et_ctx* c, size_t total) {
+  c->keep_elems = std::min(total, (size_t)12 << 30);
+  reserve(c, &c->keep_arena, sizeof(bf16) * std::max<size_t>(c->keep_elems, 8));
+}
+inline size_t keep_size(size_t elems) { return (elems + 127) / 128 * 128; }
+// where the gradient in front of a weight is to be stored: kept for the end of the pass if the weight is selected
+inline bf16* keep(et_ctx* c, bool selected, size_t elems, bf16* scratch) {
+  if (!selected || c->keep_used + keep_size(elems) > c->keep_elems) return scratch;
+  bf16* p = c->keep_arena + c->keep_used;
+  c->keep_used += keep_size(elems);
+  return p;
+}
+inline bool kept(const et_ctx* c, const bf16* d) { return d == c->dl16 || (d >= c->keep_arena && d < c->keep_arena + c->keep_elems); }
+inline void dw_defer(et_ctx* c, int tensor, const et::DwJob& j) {
+  c->dw_jobs.push_back(j);
+  c->dw_tensors.push_back(tensor);
+}
+// partial sums of split products: room for the largest single one (`elems`), and for all weight gradients of a pass (`all`) up to 1.5 GB
+inline void reserve_partials(et_ctx* c, size_t elems, size_t all) {
+  c->gemm_partial_elems = std::max(elems, std::min((size_t)384 << 20, all));
+  reserve(c, &c->gemm_partials, sizeof(float) * std::max<size_t>(c->gemm_partial_elems, 64));
+}
+
 // bracket a launch with events while per-kernel timing is on
 struct KernelTimer {
   et_ctx* c;
@@ -364,6 +396,52 @@ inline int launch_gemm(et_ctx* c, const et::GemmDesc& g) {
     int r__ = launch_gemm(c, (g));         \
     if (r__ != ET_OK) return r__;          \
   } while (0)
+
+// weight gradient of `tensor`, dW[N][K] = dY[M][N]^T X[M][K]: with the others at the end of the pass if dY stays, else at once (and while
+// kernels are timed, each with a record of its own)
+inline int weight_grad(et_ctx* c, int tensor, const bf16* dY, int ldy, const bf16* X, int ldx, int M, int N, int K) {
+  et::DwJob j;
+  j.A = dY; j.lda = ldy; j.B = X; j.ldb = ldx; j.C = c->grad[tensor]; j.M = N; j.N = K; j.K = M;
+  const et::GemmDesc g = linear_dw(c, dY, ldy, X, ldx, c->grad[tensor], M, N, K);
+  j.split = g.split_k;
+  if (!c->ktiming && kept(c, dY) && et::dw_group_takes(j)) {
+    dw_defer(c, tensor, j);
+    return ET_OK;
+  }
+  Region r(c, PH_DW, tensor);
+  ET_G(g);
+  return ET_OK;
+}
+
+// runs what has been deferred, in groups whose split reductions find room in the scratch
+inline int dw_finish(et_ctx* c) {
+  hipError_t e = hipSuccess;
+  const int n = (int)c->dw_jobs.size();
+  for (int at = 0, group = 0; at < n && e == hipSuccess; group++) {
+    int end = at;
+    for (size_t used = 0; end < n && end - at < et::DW_GROUP_MAX; end++) {
+      used += et::dw_group_elems(c->dw_jobs[end]);
+      if (used > c->gemm_partial_elems && end > at) break;
+    }
+    // the plan depends on the shapes alone and is kept while they stay the same
+    et::DwGroupPlan& plan = c->dw_plans[group];
+    e = et::dw_group_plan(c->dw_jobs.data() + at, end - at, plan);
+    if (e == hipSuccess) {
+      std::vector<Share> shares;
+      if (c->profiling)
+        for (int i = at; i < end; i++) shares.push_back({PH_DW, c->dw_tensors[i], plan.cost[i - at]});
+      Region r(c, PH_DW, shares.data(), shares.size());
+      int launches = 0;
+      e = et::dw_group(c->dw_jobs.data() + at, end - at, plan, c->gemm_partials, c->stream, &launches);
+      c->launches[PH_DW] += launches;
+    }
+    at = end;
+  }
+  c->dw_jobs.clear();
+  c->dw_tensors.clear();
+  if (e != hipSuccess) { c->hip_err = e; return ET_EHIP; }
+  return ET_OK;
+}
 
 }  // namespace et_exec
 

@@ -153,23 +153,31 @@ inline int conv_forward(et_ctx* c, const ConvUnit& u, const bf16* in, const bf16
   return ET_OK;
 }
 
-inline int conv_dw(et_ctx* c, const ConvUnit& u, const bf16* in, const bf16* d, float* dW) {
+// weight gradient of a unit, from the gradient d of its convolution's output: with the others at the end of the pass if d stays, else at once
+inline int conv_dw(et_ctx* c, const ConvUnit& u, const bf16* in, const bf16* d) {
+  const int t = u.t;
   if (implicit_dw(c, u)) {   // B operand: the activation standing for its im2col matrix
     et::GemmDesc g;
     const int kk = u.k * u.k * u.Cin;
     g.A = d; g.a_t = true; g.lda = u.Cout; g.B = in; g.b_t = true; g.ldb = kk;
     g.M = u.Cout; g.N = kk; g.K = (int)rows_of(c, u);
-    g.C = dW; g.ldc = kk; g.c_f32 = true;
+    g.C = c->grad[t]; g.ldc = kk; g.c_f32 = true;
     g.conv_h = u.H; g.conv_w = u.W; g.conv_c = u.Cin; g.conv_taps = u.k; g.conv_stride = u.stride;
     et::gemm_bf16_plan_conv_dw(g.M, g.N, g.K, &g.tile, &g.split_k);
     g.partials = c->gemm_partials;
     if (et::gemm_bf16_partial_elems(g.M, g.N, g.split_k) > c->gemm_partial_elems) g.split_k = 1;
+    et::DwJob j;
+    j.A = d; j.lda = u.Cout; j.B = in; j.ldb = kk; j.C = c->grad[t]; j.M = g.M; j.N = g.N; j.K = g.K;
+    j.conv_h = u.H; j.conv_w = u.W; j.conv_c = u.Cin; j.conv_taps = u.k; j.conv_stride = u.stride; j.split = g.split_k;
+    if (!c->ktiming && kept(c, d) && et::dw_group_takes(j)) {
+      dw_defer(c, t, j);
+      return ET_OK;
+    }
+    Region r(c, PH_DW, t);
     ET_G(g);
     return ET_OK;
   }
-  const bf16* A = needs_cols(u) ? u.cols : in;
-  ET_G(linear_dw(c, d, u.Cout, A, u.Kc, dW, (int)rows_of(c, u), u.Cout, u.Kc));
-  return ET_OK;
+  return weight_grad(c, t, d, u.Cout, needs_cols(u) ? u.cols : in, u.Kc, (int)rows_of(c, u), u.Cout, u.Kc);
 }
 
 // Gradient of the column matrix: dcols[M][Kc] = d[M][Cout] * Wm[Cout][Kc].  For a 1x1 convolution this is the

@@ -95,13 +95,21 @@ int build_vit(et_ctx* c) {
   if (!fused) reserve(c, &c->ds, b16 * B * H * T * ldT);
   reserve(c, &c->de, b16 * B * (T - 1) * D);
   // split-K partials: the largest weight gradient
-  size_t pe = 0;
-  auto wg = [&](size_t Mo, size_t No, size_t K) {
-    pe = std::max(pe, et::gemm_bf16_partial_elems((int)Mo, (int)No, split_for((int)Mo, (int)No, (int)K)));
+  size_t pe = 0, all = 0;
+  auto wg = [&](size_t Mo, size_t No, size_t K, int times = 1) {
+    const size_t n = et::gemm_bf16_partial_elems((int)Mo, (int)No, split_for((int)Mo, (int)No, (int)K));
+    pe = std::max(pe, n);
+    all += times * n;
   };
-  wg(3 * D, D, M); wg(D, D, M); wg(F, D, M); wg(D, F, M); wg(D, P, B * (T - 1)); wg(C, D, B);
-  c->gemm_partial_elems = pe;
-  reserve(c, &c->gemm_partials, f32 * std::max<size_t>(pe, 64));
+  // (the last block's projection and MLP have B rows)
+  for (size_t K : {M, B}) {
+    const int times = K == M ? d.blocks : 1;
+    wg(3 * D, D, M, K == M ? times : 0); wg(D, D, K, times); wg(F, D, K, times); wg(D, F, K, times);
+  }
+  wg(D, P, B * (T - 1)); wg(C, D, B);
+  reserve_partials(c, pe, all);
+  // gradients that weight gradients read: per block behind both residual sums, inside the MLP, of q, k and v; of the patches
+  reserve_keep(c, (size_t)d.blocks * (2 * keep_size(M * D) + keep_size(M * F) + keep_size(M * 3 * D)) + keep_size(B * (T - 1) * D));
   {
     // per block: gain, shift and bias sums of both LayerNorms, the fc1 and qkv biases; largest group: three sums of one LayerNorm
     const size_t ln = std::max(sum_elems(et::layernorm_bwd_parts((int)M), D), sum_elems(et::colsum_parts((int)M, (int)D), D));
@@ -286,14 +294,14 @@ int vit_forward(et_ctx* c, const void* x, const int32_t* y, const uint8_t* mask)
 
 // part: where the fused core leaves the partial column sums of dqkv (the bias of the product in front of it), or null
 // few: the gradient is zero but for the first token of a sequence (fused core only)
-int vit_attention_backward(et_ctx* c, const VitDims& v, VitBlockBufs& b, bool few, float* part) {
+int vit_attention_backward(et_ctx* c, const VitDims& v, VitBlockBufs& b, bf16* dqkv, bool few, float* part) {
   if (few) {   // (not among the attention's timed launches: vector work bound by memory)
-    ET_K(1, et::attention_bwd_cls(b.qkv, b.o, b.o_rest, c->dattn, b.lse, c->dqkv, v.B, v.T, v.H, v.dh, v.scale, c->stream, part));
+    ET_K(1, et::attention_bwd_cls(b.qkv, b.o, b.o_rest, c->dattn, b.lse, dqkv, v.B, v.T, v.H, v.dh, v.scale, c->stream, part));
     return ET_OK;
   }
   if (et::attention_fused_supported(v.T, v.dh)) {
     KernelTimer kt(c, 6, 8.0 * v.B * v.H * (double)v.T * v.T * v.dh);
-    ET_K(1, et::attention_bwd(b.qkv, b.o, b.o_rest, c->dattn, b.lse, c->dqkv, v.B, v.T, v.H, v.dh, v.scale, c->stream, part));
+    ET_K(1, et::attention_bwd(b.qkv, b.o, b.o_rest, c->dattn, b.lse, dqkv, v.B, v.T, v.H, v.dh, v.scale, c->stream, part));
     return ET_OK;
   }
   const long long sQo = (long long)v.T * 3 * v.D, sPo = (long long)v.H * v.T * v.ldT, sPi = (long long)v.T * v.ldT;
@@ -304,7 +312,7 @@ int vit_attention_backward(et_ctx* c, const VitDims& v, VitBlockBufs& b, bool fe
     g.A = b.p; g.a_t = true; g.lda = v.ldT; g.sAo = sPo; g.sAi = sPi;
     g.B = c->dattn; g.b_t = true; g.ldb = v.D; g.sBo = sOo; g.sBi = v.dh;
     g.M = v.T; g.N = v.dh; g.K = v.T; batched(g);
-    g.C = c->dqkv + 2 * v.D; g.ldc = 3 * v.D; g.sCo = sQo; g.sCi = v.dh;
+    g.C = dqkv + 2 * v.D; g.ldc = 3 * v.D; g.sCo = sQo; g.sCi = v.dh;
     ET_G(g);
   }
   {  // dP = dO V^T
@@ -321,7 +329,7 @@ int vit_attention_backward(et_ctx* c, const VitDims& v, VitBlockBufs& b, bool fe
     g.A = c->ds; g.lda = v.ldT; g.sAo = sPo; g.sAi = sPi;
     g.B = b.qkv + v.D; g.b_t = true; g.ldb = 3 * v.D; g.sBo = sQo; g.sBi = v.dh;
     g.M = v.T; g.N = v.dh; g.K = v.T; batched(g);
-    g.C = c->dqkv; g.ldc = 3 * v.D; g.sCo = sQo; g.sCi = v.dh;
+    g.C = dqkv; g.ldc = 3 * v.D; g.sCo = sQo; g.sCi = v.dh;
     ET_G(g);
   }
   {  // dK[s][d] = sum_t dS[t][s] Q[t][d]
@@ -329,7 +337,7 @@ int vit_attention_backward(et_ctx* c, const VitDims& v, VitBlockBufs& b, bool fe
     g.A = c->ds; g.a_t = true; g.lda = v.ldT; g.sAo = sPo; g.sAi = sPi;
     g.B = b.qkv; g.b_t = true; g.ldb = 3 * v.D; g.sBo = sQo; g.sBi = v.dh;
     g.M = v.T; g.N = v.dh; g.K = v.T; batched(g);
-    g.C = c->dqkv + v.D; g.ldc = 3 * v.D; g.sCo = sQo; g.sCi = v.dh;
+    g.C = dqkv + v.D; g.ldc = 3 * v.D; g.sCo = sQo; g.sCi = v.dh;
     ET_G(g);
   }
   return ET_OK;
@@ -340,17 +348,17 @@ struct VitRows { bool few; int R, step, ldD, ldF; };
 VitRows vit_rows(const VitDims& v, bool few) { return {few, few ? v.B : v.M, few ? v.T : 1, (few ? v.T : 1) * v.D, (few ? v.T : 1) * v.F}; }
 
 // through fc2.W, then through the GELU (b.u holds gelu'(pre-activation)); fc1.b's column sums on the way
-et::GemmDesc vit_fc2_dx(et_ctx* c, const VitDims& v, const VitRows& q, const VitBlockBufs& b, int t0, float* colsum) {
-  et::GemmDesc g = linear_dx(c->dh16, (const bf16*)c->w[t0 + 10], q.R, v.D, v.F);
+et::GemmDesc vit_fc2_dx(et_ctx* c, const VitDims& v, const VitRows& q, const VitBlockBufs& b, int t0, const bf16* dh16, bf16* du, float* colsum) {
+  et::GemmDesc g = linear_dx(dh16, (const bf16*)c->w[t0 + 10], q.R, v.D, v.F);
   g.lda = q.ldD; g.ldc = q.ldF;
-  g.mode = et::EPI_GELU_BWD; g.U = b.u; g.C = c->du; g.colsum = colsum;
+  g.mode = et::EPI_GELU_BWD; g.U = b.u; g.C = du; g.colsum = colsum;
   return g;
 }
 // second LayerNorm of a block: input gradient joined by the residual branch
-et::LayerNormBwd vit_ln2_back(et_ctx* c, const VitDims& v, const VitRows& q, const VitBlockBufs& b, int t0) {
+et::LayerNormBwd vit_ln2_back(et_ctx* c, const VitDims& v, const VitRows& q, const VitBlockBufs& b, int t0, bf16* dh16) {
   et::LayerNormBwd a;
   a.d = c->da; a.d_stride = q.ldD; a.h = b.h_mid; a.h_stride = q.ldD; a.mean = b.mean2; a.rstd = b.rstd2; a.stat_stride = q.step;
-  a.gain = (const bf16*)c->w[t0 + 6]; a.skip = c->dh; a.dh = c->dh; a.dh16 = c->dh16; a.out_stride = q.ldD; a.rows = q.R; a.D = v.D;
+  a.gain = (const bf16*)c->w[t0 + 6]; a.skip = c->dh; a.dh = c->dh; a.dh16 = dh16; a.out_stride = q.ldD; a.rows = q.R; a.D = v.D;
   return a;
 }
 
@@ -371,11 +379,11 @@ int vit_time_sums(et_ctx* c) {
       c->sum_cost[few][kernel] = 0.0;
       if ((kernel == SUM_ATTENTION && !cls) || (kernel == SUM_LAYERNORM && v.D > et::LAYERNORM_SUMS_MAX_D)) continue;
       auto launch = [&](float* part) -> int {
-        if (kernel == SUM_ATTENTION) return vit_attention_backward(c, v, b, few != 0, part);
+        if (kernel == SUM_ATTENTION) return vit_attention_backward(c, v, b, c->dqkv, few != 0, part);
         if (kernel == SUM_GELU) {
-          ET_G(vit_fc2_dx(c, v, q, b, t0, part));
+          ET_G(vit_fc2_dx(c, v, q, b, t0, c->dh16, c->du, part));
         } else {
-          et::LayerNormBwd a = vit_ln2_back(c, v, q, b, t0);
+          et::LayerNormBwd a = vit_ln2_back(c, v, q, b, t0, c->dh16);
           const size_t one = sum_elems(et::layernorm_bwd_parts(q.R), v.D);
           if (part) { a.part_gain = part; a.part_shift = part + one; a.part_bias = part + 2 * one; }
           ET_K(1, et::layernorm_bwd(a, c->stream));
@@ -462,25 +470,25 @@ int vit_backward(et_ctx* c, const void* x, const uint8_t* mask) {
 
   // ---- head and final LayerNorm (CLS rows)
   if (sel(N - 1) && (rc = colsum_dw(c, N - 1, nullptr, c->dlogits, v.C, v.B, v.C)) != ET_OK) return rc;
-  if (sel(N - 2)) {
-    Region r(c, PH_DW, N - 2);
-    ET_G(linear_dw(c, c->dl16, v.C8, c->zc, v.D, c->grad[N - 2], v.B, v.C, v.D));
-  }
+  if (sel(N - 2) && (rc = weight_grad(c, N - 2, c->dl16, v.C8, c->zc, v.D, v.B, v.C, v.D)) != ET_OK) return rc;
   if (pass(N - 2)) {
     Region r(c, PH_DY, N - 2);
     et::GemmDesc g = linear_dx(c->dl16, W(N - 2), v.B, v.C, v.D);
     g.lda = v.C8; g.C = c->dz;
     ET_G(g);
   }
+  // (the gradient of the residual stream in bf16, wherever it is kept)
+  const size_t MD = (size_t)v.M * v.D;
+  bf16* dh16 = keep(c, pass(N - 4) && sel(N - 6), MD, c->dh16);
   if (pass(N - 4) && !cls) {
     Region r(c, PH_DY, N - 4);
     ET_K(1, et::fill_zero(c->dh, sizeof(float) * (size_t)v.M * v.D, s));
-    ET_K(1, et::fill_zero(c->dh16, sizeof(bf16) * (size_t)v.M * v.D, s));
+    ET_K(1, et::fill_zero(dh16, sizeof(bf16) * (size_t)v.M * v.D, s));
   }
   {
     et::LayerNormBwd a;
     a.d = c->dz; a.d_stride = v.D; a.h = c->h_out; a.h_stride = sD; a.mean = c->meanf; a.rstd = c->rstdf; a.gain = W(N - 4);
-    a.dh = c->dh; a.dh16 = c->dh16; a.out_stride = sD; a.rows = v.B; a.D = v.D;
+    a.dh = c->dh; a.dh16 = dh16; a.out_stride = sD; a.rows = v.B; a.D = v.D;
     if ((rc = layernorm_back(c, mask, jstar, N - 4, N - 5, a)) != ET_OK) return rc;
   }
 
@@ -491,10 +499,8 @@ int vit_backward(et_ctx* c, const void* x, const uint8_t* mask) {
     if (jstar > t0 + 11) break;
     const VitRows q = vit_rows(v, cls && l + 1 == v.L);
     const int R = q.R, ldD = q.ldD, ldF = q.ldF;
-    if (sel(t0 + 10)) {
-      Region r(c, PH_DW, t0 + 10);
-      ET_G(linear_dw(c, c->dh16, ldD, b.ga, ldF, c->grad[t0 + 10], R, v.D, v.F));
-    }
+    if (sel(t0 + 10) && (rc = weight_grad(c, t0 + 10, dh16, ldD, b.ga, ldF, R, v.D, v.F)) != ET_OK) return rc;
+    bf16* du = keep(c, pass(t0 + 10) && sel(t0 + 8), (size_t)v.M * v.F, c->du);
     if (pass(t0 + 10)) {
       float* part = nullptr;
       if (sel(t0 + 9)) {
@@ -505,24 +511,20 @@ int vit_backward(et_ctx* c, const void* x, const uint8_t* mask) {
       const double cost = c->sum_cost[q.few][SUM_GELU];
       const Share shares[2] = {{PH_DY, t0 + 10, 1.0 - cost}, {PH_DW, t0 + 9, cost}};
       Region r(c, PH_DY, shares, part ? 2 : 1);
-      ET_G(vit_fc2_dx(c, v, q, b, t0, part));
+      ET_G(vit_fc2_dx(c, v, q, b, t0, dh16, du, part));
     }
-    if (sel(t0 + 8)) {
-      Region r(c, PH_DW, t0 + 8);
-      ET_G(linear_dw(c, c->du, ldF, b.a2, ldD, c->grad[t0 + 8], R, v.F, v.D));
-    }
+    if (sel(t0 + 8) && (rc = weight_grad(c, t0 + 8, du, ldF, b.a2, ldD, R, v.F, v.D)) != ET_OK) return rc;
     if (pass(t0 + 8)) {
       Region r(c, PH_DY, t0 + 8);
-      et::GemmDesc g = linear_dx(c->du, W(t0 + 8), R, v.F, v.D);
+      et::GemmDesc g = linear_dx(du, W(t0 + 8), R, v.F, v.D);
       g.lda = ldF; g.ldc = ldD;
       g.C = c->da;
       ET_G(g);
     }
-    if ((rc = layernorm_back(c, mask, jstar, t0 + 6, t0 + 5, vit_ln2_back(c, v, q, b, t0))) != ET_OK) return rc;
-    if (sel(t0 + 4)) {
-      Region r(c, PH_DW, t0 + 4);
-      ET_G(linear_dw(c, c->dh16, ldD, b.o, ldD, c->grad[t0 + 4], R, v.D, v.D));
-    }
+    dh16 = keep(c, pass(t0 + 6) && sel(t0 + 4), MD, c->dh16);
+    if ((rc = layernorm_back(c, mask, jstar, t0 + 6, t0 + 5, vit_ln2_back(c, v, q, b, t0, dh16))) != ET_OK) return rc;
+    if (sel(t0 + 4) && (rc = weight_grad(c, t0 + 4, dh16, ldD, b.o, ldD, R, v.D, v.D)) != ET_OK) return rc;
+    bf16* dqkv = keep(c, pass(t0 + 4) && sel(t0 + 2), 3 * MD, c->dqkv);
     if (pass(t0 + 4)) {  // through proj.W, then through the attention core, which leaves the column sums of qkv.b
       float* part = nullptr;
       if (sel(t0 + 3) && cls) {
@@ -532,7 +534,7 @@ int vit_backward(et_ctx* c, const void* x, const uint8_t* mask) {
       }
       {
         Region r(c, PH_DY, t0 + 4);
-        et::GemmDesc g = linear_dx(c->dh16, W(t0 + 4), R, v.D, v.D);
+        et::GemmDesc g = linear_dx(dh16, W(t0 + 4), R, v.D, v.D);
         g.lda = ldD; g.ldc = ldD;
         g.C = c->dattn;
         ET_G(g);
@@ -540,23 +542,21 @@ int vit_backward(et_ctx* c, const void* x, const uint8_t* mask) {
       const double cost = c->sum_cost[q.few][SUM_ATTENTION];
       const Share shares[2] = {{PH_DY, t0 + 4, 1.0 - cost}, {PH_DW, t0 + 3, cost}};
       Region r(c, PH_DY, shares, part ? 2 : 1);
-      if ((rc = vit_attention_backward(c, v, b, q.few, part)) != ET_OK) return rc;
+      if ((rc = vit_attention_backward(c, v, b, dqkv, q.few, part)) != ET_OK) return rc;
     }
-    if (sel(t0 + 3) && !cls && (rc = colsum_dw(c, t0 + 3, c->dqkv, nullptr, 3 * v.D, v.M, 3 * v.D)) != ET_OK) return rc;
-    if (sel(t0 + 2)) {
-      Region r(c, PH_DW, t0 + 2);
-      ET_G(linear_dw(c, c->dqkv, 3 * v.D, b.a1, v.D, c->grad[t0 + 2], v.M, 3 * v.D, v.D));
-    }
+    if (sel(t0 + 3) && !cls && (rc = colsum_dw(c, t0 + 3, dqkv, nullptr, 3 * v.D, v.M, 3 * v.D)) != ET_OK) return rc;
+    if (sel(t0 + 2) && (rc = weight_grad(c, t0 + 2, dqkv, 3 * v.D, b.a1, v.D, v.M, 3 * v.D, v.D)) != ET_OK) return rc;
     if (pass(t0 + 2)) {
       Region r(c, PH_DY, t0 + 2);
-      et::GemmDesc g = linear_dx(c->dqkv, W(t0 + 2), v.M, 3 * v.D, v.D);
+      et::GemmDesc g = linear_dx(dqkv, W(t0 + 2), v.M, 3 * v.D, v.D);
       g.C = c->da;
       ET_G(g);
     }
+    dh16 = keep(c, pass(t0) && l > 0 && sel(t0 - 2), MD, c->dh16);
     {
       et::LayerNormBwd a;
       a.d = c->da; a.d_stride = v.D; a.h = b.h_in; a.h_stride = v.D; a.mean = b.mean1; a.rstd = b.rstd1; a.gain = W(t0 + 0);
-      a.skip = c->dh; a.skip_period = q.step; a.dh = c->dh; a.dh16 = c->dh16; a.out_stride = v.D; a.rows = v.M; a.D = v.D;
+      a.skip = c->dh; a.skip_period = q.step; a.dh = c->dh; a.dh16 = dh16; a.out_stride = v.D; a.rows = v.M; a.D = v.D;
       if ((rc = layernorm_back(c, mask, jstar, t0 + 0, l > 0 ? t0 - 1 : -1, a)) != ET_OK) return rc;   // (fc2.b of the block before)
     }
   }
@@ -571,15 +571,13 @@ int vit_backward(et_ctx* c, const void* x, const uint8_t* mask) {
       Region r(c, PH_DW, 2);
       ET_K(1, et::batchsum(c->dh, c->grad[2], v.B, (long long)v.T * v.D, v.D, s));
     }
+    bf16* de = keep(c, pass(2) && sel(0), (size_t)v.B * (v.T - 1) * v.D, c->de);
     if (pass(2)) {  // past the CLS token: keep the patch rows
       Region r(c, PH_DY, 2);
-      ET_K(1, et::gather_patch_rows(c->dh, c->de, v.B, v.T, v.D, s));
+      ET_K(1, et::gather_patch_rows(c->dh, de, v.B, v.T, v.D, s));
     }
-    if (sel(1) && (rc = colsum_dw(c, 1, c->de, nullptr, v.D, v.B * (v.T - 1), v.D)) != ET_OK) return rc;
-    if (sel(0)) {
-      Region r(c, PH_DW, 0);
-      ET_G(linear_dw(c, c->de, v.D, (const bf16*)x, v.P, c->grad[0], v.B * (v.T - 1), v.D, v.P));
-    }
+    if (sel(1) && (rc = colsum_dw(c, 1, de, nullptr, v.D, v.B * (v.T - 1), v.D)) != ET_OK) return rc;
+    if (sel(0) && (rc = weight_grad(c, 0, de, v.D, (const bf16*)x, v.P, v.B * (v.T - 1), v.D, v.P)) != ET_OK) return rc;
   }
   return ET_OK;
 }
@@ -598,11 +596,15 @@ int run_backward(et_ctx* c, const void* x, const uint8_t* mask) {
   c->sum_jobs.clear();      // (a pass that ended early leaves nothing behind)
   c->sum_tensors.clear();
   c->sum_used = 0;
+  c->dw_jobs.clear();
+  c->dw_tensors.clear();
+  c->keep_used = 0;
   int rc;
   if (c->desc.kind == ET_RESNET) rc = resnet_backward(c, x, mask);
   else if (c->desc.kind == ET_VGG) rc = vgg_backward(c, x, mask);
   else if (c->desc.kind == ET_MOBILENET) rc = mobilenet_backward(c, x, mask);
   else rc = c->desc.kind == ET_MLP ? mlp_backward(c, x, mask) : vit_backward(c, x, mask);
+  if (rc == ET_OK) rc = dw_finish(c);
   return rc == ET_OK ? sums_finish(c) : rc;
 }
 
@@ -686,6 +688,9 @@ int et_create(const et_model_desc* desc, void* hip_stream, et_ctx** out) {
     if (rc == ET_OK) {
       c->state_slots = c->bf16_model ? 3 : 2;
       build_tables_plan(c);
+      c->dw_jobs.reserve(c->tensors.size());
+      c->dw_tensors.reserve(c->tensors.size());
+      c->dw_plans.resize(c->tensors.size());
     }
   } catch (const std::bad_alloc&) {
     rc = ET_ENOMEM;

@@ -1,5 +1,7 @@
 // Kernel-level entry points for tests and tuning.
 #include "et_debug.h"
+#include <new>
+#include <vector>
 
 #include "et.h"
 #include "kernels.h"
@@ -370,4 +372,30 @@ extern "C" int et_debug_copy(void* dst, const void* src, size_t bytes, void* str
   hipLaunchKernelGGL(et_copy_kernel, dim3(256 * 8), dim3(256), 0, (hipStream_t)stream, (const uint4*)src, (uint4*)dst,
                      bytes / 16);
   return hipGetLastError() == hipSuccess ? ET_OK : ET_EHIP;
+}
+
+extern "C" int et_debug_dw_group(int n, const void* const* A, const void* const* B, float* const* C, const int* shape, float* partials, size_t partial_elems,
+                                 void* stream) {
+  if (n < 1 || n > et::DW_GROUP_MAX || !A || !B || !C || !shape || !partials) return ET_EINVAL;
+  try {
+    std::vector<et::DwJob> jobs(n);
+    size_t elems = 0;
+    for (int i = 0; i < n; i++) {
+      const int* q = shape + 9 * i;
+      et::DwJob& j = jobs[i];
+      j.A = (const et::bf16*)A[i]; j.B = (const et::bf16*)B[i]; j.C = C[i];
+      j.M = q[0]; j.N = q[1]; j.K = q[2]; j.split = q[3];
+      j.lda = (j.M + 7) & ~7; j.ldb = (j.N + 7) & ~7;
+      j.conv_h = q[4]; j.conv_w = q[5]; j.conv_c = q[6]; j.conv_taps = q[7]; j.conv_stride = q[8];
+      if (!et::dw_group_takes(j)) return ET_EINVAL;
+      elems += et::dw_group_elems(j);
+    }
+    if (elems > partial_elems) return ET_EINVAL;
+    et::DwGroupPlan plan;
+    int launches = 0;
+    if (et::dw_group_plan(jobs.data(), n, plan) != hipSuccess) return ET_EINVAL;
+    return et::dw_group(jobs.data(), n, plan, partials, (hipStream_t)stream, &launches) == hipSuccess ? ET_OK : ET_EHIP;
+  } catch (const std::bad_alloc&) {
+    return ET_ENOMEM;
+  }
 }

@@ -261,10 +261,13 @@ int choose_large_tile(const GemmDesc& d, int K) {
   return best;
 }
 
-// Weight gradients [M][N] over K rows of 4 GFLOP and more: tile and split with the least estimated time (us).  As above, with the partials' traffic and
-// the second launch of a split; the time per slice of a ring tile grows with the length of its chunk (its operand re-reads).  Fitted to
-// 85 shapes of [384 .. 4096] x [384 .. 1024] over 1576 .. 17000 rows with up to a dozen plans each: the chosen plans take 3053 us in sum, the best 3007.
-// [3072 x 768] over 12608 rows 77 -> 70 us, [2304 x 768] 63 -> 58, [768 x 768] 38 -> 28, [4096 x 1024] over 6304 71 -> 65.
+// Weight gradients [M][N] over K rows of 4 GFLOP and more.  The split is a function of the shape alone, so that a gradient has the same bits
+// whichever others are computed: chunks of about 66 slices.  Most gradients run in a group (dw_group), which fills the chip without a split;
+// what the chunks are for is a gradient on its own, or in a small group, and rounds of even length there.  [3072 x 768] over 12608 rows
+// alone: unsplit 127 us, 2 chunks 107, 3 chunks 84, 5 chunks 70; all 48 gradients of such a transformer write 1.0 GB of partial sums with 3.
+// Tile: the least estimated time (us) with that split.  As above, with the partials' traffic and the second launch; the time per slice of a ring
+// tile grows with the length of its chunk (its operand re-reads).  Fitted to 85 shapes of [384 .. 4096] x [384 .. 1024] over 1576 .. 17000 rows
+// with up to a dozen plans each (relative error 5 - 8 %).
 Plan plan_dw(int M, int N, int K) {
   struct Cand { int tile, bm, bn; double slice, slice2, load, solo, fixed, once, part, elem, split, rounds2; };
   static const Cand cand[5] = {{T_DIRECT_256x256, 256, 256, 0.833, 0.0, 0.696, 0.0, 5.38, 5.92, 0.880e-6, 0.0, 0.0, 0.0},
@@ -273,20 +276,15 @@ Plan plan_dw(int M, int N, int K) {
                                {T_RING_64x128, 64, 128, 0.179, 0.00069, 0.0, 0.0, 0.0, 5.61, 1.377e-6, 0.750e-6, 2.53, 0.0228},
                                {T_RING_64x64, 64, 64, 0.116, 0.00047, 0.0, 0.0179, 0.0, 5.95, 1.581e-6, 0.189e-6, 1.00, 0.0122}};
   const int slices = (K + gemm::PBK - 1) / gemm::PBK;
-  const int max_split = (N & 3) == 0 ? std::max(1, std::min(256, slices / 4)) : 1;
-  Plan best = {T_RING_64x128, 1, 1e30};
+  const int wanted = (N & 3) == 0 ? std::max(1, std::min(256, (slices + 33) / 66)) : 1;
+  const int per = (slices + wanted - 1) / wanted, split = (slices + per - 1) / per;   // (no empty chunks)
+  Plan best = {T_RING_64x128, split, 1e30};
   for (const Cand& c : cand) {
-    const double tiles = (double)((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn), elems = (double)M * N;
-    for (int s = 1; s <= max_split; s++) {
-      if (s > 1 && tiles * s > 1280) break;
-      const int per = (slices + s - 1) / s;
-      if ((slices + per - 1) / per != s) continue;   // this split leaves empty chunks
-      const double rounds = std::ceil(tiles * s / 256.0);
-      double t = rounds * (per * (c.slice + c.slice2 * per + c.load * tiles * s / rounds / 256.0 + c.rounds2 * rounds) + c.fixed) + c.once + c.elem * elems;
-      if (rounds == 1.0) t += c.solo * per;
-      if (s > 1) t += c.part * s * elems + c.split;
-      if (t < best.cost) best = {c.tile, s, t};
-    }
+    const double units = (double)((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn) * split, elems = (double)M * N, rounds = std::ceil(units / 256.0);
+    double t = rounds * (per * (c.slice + c.slice2 * per + c.load * units / rounds / 256.0 + c.rounds2 * rounds) + c.fixed) + c.once + c.elem * elems;
+    if (rounds == 1.0) t += c.solo * per;
+    if (split > 1) t += c.part * split * elems + c.split;
+    if (t < best.cost) best = {c.tile, split, t};
   }
   return best;
 }

@@ -275,8 +275,10 @@ __device__ __forceinline__ void direct_epilogue(const Params& g, f32x16 (&acc)[M
   }
 }
 
-template <int MI, bool AT, bool BT, int EPI>
-__global__ __launch_bounds__(512) void gemm_direct_kernel(Params g) {
+// GROUP: the units are those of a group of weight gradients (AT, BT, E_PARTIAL)
+template <int MI, bool AT, bool BT, int EPI, bool GROUP = false>
+__global__ __launch_bounds__(512) void gemm_direct_kernel(std::conditional_t<GROUP, GroupParams<false>, Params> g) {
+  static_assert(!GROUP || (AT && BT && EPI == E_PARTIAL), "groups of weight gradients");
   constexpr int BM = 64 * MI, BN = 256, NW = 8, NI = 2, TM = 32 * MI, TN = 64;
   constexpr int A_BYTES = BM * PBK * 2, B_BYTES = BN * PBK * 2;
   constexpr int A_LOADS = MI, B_LOADS = 4, LOADS = A_LOADS + B_LOADS;   // wave-wide 1 KiB pieces per wave and slice
@@ -292,18 +294,28 @@ __global__ __launch_bounds__(512) void gemm_direct_kernel(Params g) {
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wave_m = wave >> 2, wave_n = wave & 3, group = wave_m;
   const unsigned lds0 = (unsigned)(unsigned long long)(__attribute__((address_space(3))) unsigned char*)smem;
-  const long long a_step = (AT ? (long long)PBK * g.lda : PBK) * 2, b_step = (BT ? (long long)PBK * g.ldb : PBK) * 2;
-
   // where unit w lies: tile corner, operands, offset of the result, number of slices and k values of the last one, all uniform
-  struct Unit { int m0, n0, k_begin, nk, rem; const bf16 *A, *B; long long c_off; };
+  struct Unit { int m0, n0, k_begin, nk, rem, M, N, lda, ldb; const bf16 *A, *B; long long c_off; void* C; };
   auto unit = [&](int w) {
     Unit u;
     int z, k_end;
-    unit_coords<BM, BN>(g, w, u.m0, u.n0, z);
+    if constexpr (GROUP) {
+      const int at = __builtin_amdgcn_readfirstlane(group_unit(w, (int)gridDim.x, g.units));
+      const GroupJob& j = g.job[__builtin_amdgcn_readfirstlane(group_job<false>(g, at))];
+      u.M = j.M; u.N = j.N; u.lda = j.lda; u.ldb = j.ldb; u.A = j.A; u.B = j.B; u.C = j.C;
+      group_tile<BM, BN>(u.M, u.N, at - j.unit0, u.m0, u.n0, z);
+      z = __builtin_amdgcn_readfirstlane(z);
+      u.k_begin = z * j.k_chunk;
+      k_end = min(j.K, u.k_begin + j.k_chunk);
+      u.c_off = (long long)z * u.M * u.N;
+    } else {
+      u.M = g.M; u.N = g.N; u.lda = g.lda; u.ldb = g.ldb; u.C = g.C;
+      unit_coords<BM, BN>(g, w, u.m0, u.n0, z);
+      z = __builtin_amdgcn_readfirstlane(z);
+      batch_offsets(g, z, u.A, u.B, u.c_off, u.k_begin, k_end);
+    }
     u.m0 = __builtin_amdgcn_readfirstlane(u.m0);
     u.n0 = __builtin_amdgcn_readfirstlane(u.n0);
-    z = __builtin_amdgcn_readfirstlane(z);
-    batch_offsets(g, z, u.A, u.B, u.c_off, u.k_begin, k_end);
     u.nk = (k_end - u.k_begin + PBK - 1) / PBK;
     u.rem = k_end - u.k_begin - (u.nk - 1) * PBK;
     return u;
@@ -313,12 +325,14 @@ __global__ __launch_bounds__(512) void gemm_direct_kernel(Params g) {
   // are recomputed per unit instead of kept in registers.)
   int a_w = blockIdx.x, b_w = blockIdx.x, a_left, b_left, a_rem, b_rem;
   const char *pa, *pb;
+  long long a_step, b_step;
   unsigned oa[A_LOADS], ob[B_LOADS];
   auto setup_a = [&]() {
     const Unit u = unit(a_w);
     a_left = u.nk;
     a_rem = u.rem;
-    pa = uniform_ptr(AT ? u.A + (long long)u.k_begin * g.lda : u.A + (long long)u.m0 * g.lda + u.k_begin);
+    pa = uniform_ptr(AT ? u.A + (long long)u.k_begin * u.lda : u.A + (long long)u.m0 * u.lda + u.k_begin);
+    a_step = (AT ? (long long)PBK * u.lda : PBK) * 2;
     int s_tid = tid;
     asm volatile("" : "+v"(s_tid));
     const int lane = s_tid & 63;
@@ -327,12 +341,12 @@ __global__ __launch_bounds__(512) void gemm_direct_kernel(Params g) {
       const int q = wave * A_LOADS + i;
       if (!AT) {   // 8 rows x 128 B; 16-byte chunk c of row r lands at chunk position c ^ ((r >> 1) & 7)
         const int row = q * 8 + (lane >> 3), chunk = (lane & 7) ^ ((row >> 1) & 7);
-        oa[i] = (unsigned)(min(row, g.M - 1 - u.m0) * g.lda + chunk * 8) * 2u;
+        oa[i] = (unsigned)(min(row, u.M - 1 - u.m0) * u.lda + chunk * 8) * 2u;
       } else {
         const int pos = q * 64 + lane, k = pos / (BM / 8), j = (pos % (BM / 8)) ^ ((k & 3) << TSH_A);
         int gi = u.m0 + j * 8;
-        if (gi + 8 > ((g.M + 7) & ~7)) gi = 0;
-        oa[i] = (unsigned)(k * g.lda + gi) * 2u;
+        if (gi + 8 > ((u.M + 7) & ~7)) gi = 0;
+        oa[i] = (unsigned)(k * u.lda + gi) * 2u;
       }
     }
   };
@@ -340,7 +354,8 @@ __global__ __launch_bounds__(512) void gemm_direct_kernel(Params g) {
     const Unit u = unit(b_w);
     b_left = u.nk;
     b_rem = u.rem;
-    pb = uniform_ptr(BT ? u.B + (long long)u.k_begin * g.ldb : u.B + (long long)u.n0 * g.ldb + u.k_begin);
+    pb = uniform_ptr(BT ? u.B + (long long)u.k_begin * u.ldb : u.B + (long long)u.n0 * u.ldb + u.k_begin);
+    b_step = (BT ? (long long)PBK * u.ldb : PBK) * 2;
     int s_tid = tid;
     asm volatile("" : "+v"(s_tid));
     const int lane = s_tid & 63;
@@ -349,12 +364,12 @@ __global__ __launch_bounds__(512) void gemm_direct_kernel(Params g) {
       const int q = wave * B_LOADS + i;
       if (!BT) {
         const int row = q * 8 + (lane >> 3), chunk = (lane & 7) ^ ((row >> 1) & 7);
-        ob[i] = (unsigned)(min(row, g.N - 1 - u.n0) * g.ldb + chunk * 8) * 2u;
+        ob[i] = (unsigned)(min(row, u.N - 1 - u.n0) * u.ldb + chunk * 8) * 2u;
       } else {
         const int pos = q * 64 + lane, k = pos / (BN / 8), j = (pos % (BN / 8)) ^ ((k & 3) << TSH_B);
         int gj = u.n0 + j * 8;
-        if (gj + 8 > ((g.N + 7) & ~7)) gj = 0;
-        ob[i] = (unsigned)(k * g.ldb + gj) * 2u;
+        if (gj + 8 > ((u.N + 7) & ~7)) gj = 0;
+        ob[i] = (unsigned)(k * u.ldb + gj) * 2u;
       }
     }
   };
@@ -523,12 +538,18 @@ __global__ __launch_bounds__(512) void gemm_direct_kernel(Params g) {
     const int last = sa == 0 ? 2 : sa - 1;
     unsigned char* area = smem + (wave < IN_STAGE ? last * A_BYTES + wave * kEpiStage : REST_AT + (wave - IN_STAGE) * kEpiStage);
     const int row0 = u.m0 + wave_m * TM, col0 = u.n0 + wave_n * TN;
-    const int ld = EPI == E_PARTIAL ? g.N : g.ldc;
-    bool full = row0 + TM <= g.M && col0 + TN <= g.N;
-    if (EPI != E_F32 && EPI != E_F32_RES && EPI != E_PARTIAL)
-      full = full && (ld & 7) == 0 && (u.c_off & 7) == 0 && (((uintptr_t)g.C | (uintptr_t)g.C2 | (uintptr_t)g.U) & 15) == 0;
-    if (full) direct_epilogue<EPI, MI, true>(g, acc, area, row0, col0, u.c_off, e_lane);
-    else direct_epilogue<EPI, MI, false>(g, acc, area, row0, col0, u.c_off, e_lane);
+    bool full = row0 + TM <= u.M && col0 + TN <= u.N;
+    if constexpr (GROUP) {
+      Params e;
+      e.M = u.M; e.N = u.N; e.C = u.C;
+      if (full) direct_epilogue<EPI, MI, true>(e, acc, area, row0, col0, u.c_off, e_lane);
+      else direct_epilogue<EPI, MI, false>(e, acc, area, row0, col0, u.c_off, e_lane);
+    } else {
+      if (EPI != E_F32 && EPI != E_F32_RES && EPI != E_PARTIAL)
+        full = full && (g.ldc & 7) == 0 && (u.c_off & 7) == 0 && (((uintptr_t)g.C | (uintptr_t)g.C2 | (uintptr_t)g.U) & 15) == 0;
+      if (full) direct_epilogue<EPI, MI, true>(g, acc, area, row0, col0, u.c_off, e_lane);
+      else direct_epilogue<EPI, MI, false>(g, acc, area, row0, col0, u.c_off, e_lane);
+    }
     w += (int)gridDim.x;
     if (w >= g.units) break;
   }

@@ -186,6 +186,60 @@ __device__ __forceinline__ void unit_coords(const Params& g, int w, int& m0, int
   n0 = qn * BN;
 }
 
+// A group: products of one kind (weight gradients [M][N] over K rows) in one launch.  Their units of work, (chunk of the reduction, tile) pairs,
+// are numbered through all jobs; a chunk of a split job goes to C + chunk * M * N.  CONV: the second operand is gathered (see gemm_pp_kernel).
+struct GroupJob {
+  const bf16* A;
+  const bf16* B;
+  float* C;
+  int M, N, K, lda, ldb;
+  int k_chunk, split;    // chunk z covers [z * k_chunk, min(K, (z + 1) * k_chunk))
+  int unit0;             // number of the first unit
+};
+struct GroupConvJob : GroupJob {
+  int cH, cW, cC, cT, cS, cHo, cWo;
+};
+template <bool CONV>
+struct GroupParams {   // (kernel arguments: 4 KB)
+  typedef std::conditional_t<CONV, GroupConvJob, GroupJob> Job;
+  static constexpr int MAX = CONV ? 42 : 62;
+  int n, units;
+  Job job[MAX];
+};
+
+// Unit that position p of a launch (or of a round of `window` resident workgroups) works on: positions are dealt to the XCDs round-robin,
+// and within every window each XCD gets consecutive units, which share operands.
+__device__ __forceinline__ int group_unit(int p, int window, int units) {
+  const int base = p / window * window, q = p - base, size = min(window, units - base);
+  const int xcd = q % NUM_XCD, idx = q / NUM_XCD, per = size / NUM_XCD, rem = size % NUM_XCD;
+  return base + xcd * per + min(xcd, rem) + idx;
+}
+
+// job of unit u: the last with unit0 <= u
+template <bool CONV>
+__device__ __forceinline__ int group_job(const GroupParams<CONV>& p, int u) {
+  int lo = 0, hi = p.n - 1;
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if (p.job[mid].unit0 <= u) lo = mid;
+    else hi = mid - 1;
+  }
+  return lo;
+}
+
+// tile corner and chunk of unit v of a job
+template <int BM, int BN>
+__device__ __forceinline__ void group_tile(int M, int N, int v, int& m0, int& n0, int& z) {
+  const int tiles_n = (N + BN - 1) / BN, tiles_m = (M + BM - 1) / BM, nt = tiles_m * tiles_n;
+  z = v / nt;
+  const int t = v - z * nt;
+  constexpr int GROUP = 8;                                   // 8 tile rows, walked column by column
+  const int gsz = GROUP * tiles_n, grp = t / gsz, in = t - grp * gsz, first = grp * GROUP;
+  const int gm = min(tiles_m - first, GROUP);
+  m0 = (first + in % gm) * BM;
+  n0 = (in / gm) * BN;
+}
+
 // batch / split-K bookkeeping
 __device__ __forceinline__ void batch_offsets(const Params& g, int z, const bf16*& A, const bf16*& B, long long& c_off,
                                               int& k_begin, int& k_end) {
@@ -1393,6 +1447,13 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_pp_kernel(Params g) {
     lds_barrier();    // and done with the epilogue's staging area before the next unit's first slice is stored
   }
 }
+
+// grouped weight gradients: fp32 results, plain and gathered
+hipError_t direct_group(int rows, const GroupParams<false>& p, int grid, hipStream_t s);   // tiles of 256, 192 or 128 rows by 256 columns
+hipError_t ring_group_64x64(const GroupParams<false>& p, hipStream_t s);
+hipError_t ring_group_64x128(const GroupParams<false>& p, hipStream_t s);
+hipError_t ring_group_conv_64x64(const GroupParams<true>& p, hipStream_t s);
+hipError_t ring_group_conv_64x128(const GroupParams<true>& p, hipStream_t s);
 
 // host side: pick the instantiation for (layout, epilogue); returns false if that pair is not built
 typedef hipError_t (*LaunchFn)(const Params&, dim3 grid, hipStream_t);

@@ -27,8 +27,9 @@
 namespace et {
 namespace gemm {
 
-template <int BM, int BN, int WGM, int WGN, int RING, bool AT, bool BT, int EPI, int CONV = 0>
-__global__ __launch_bounds__(WGM* WGN * 64) void gemm_ring_kernel(Params g) {
+// one tile with the corner (m0, n0), of batch entry or reduction chunk z
+template <int BM, int BN, int WGM, int WGN, int RING, bool AT, bool BT, int EPI, int CONV>
+__device__ __forceinline__ void ring_tile(const Params& g, int m0, int n0, int z) {
   constexpr int NW = WGM * WGN;
   constexpr int TM = BM / WGM, TN = BN / WGN;
   constexpr int MI = TM / 32, NI = TN / 32;
@@ -44,8 +45,6 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_ring_kernel(Params g) {
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wave_m = wave / WGN, wave_n = wave % WGN;
-  int m0, n0, z;
-  tile_coords<BM, BN>(g, m0, n0, z);
   const bf16* A;
   const bf16* B;
   long long c_off;
@@ -310,6 +309,31 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_ring_kernel(Params g) {
   }
   __syncthreads();   // every wave is done with the stages before they are reused for the epilogue
   wave_epilogue<EPI, MI, NI>(g, acc, smem + wave * epi_wave_bytes<TN>(), m0 + wave_m * TM, n0 + wave_n * TN, c_off, lane);
+}
+
+template <int BM, int BN, int WGM, int WGN, int RING, bool AT, bool BT, int EPI, int CONV = 0>
+__global__ __launch_bounds__(WGM* WGN * 64) void gemm_ring_kernel(Params g) {
+  int m0, n0, z;
+  tile_coords<BM, BN>(g, m0, n0, z);
+  ring_tile<BM, BN, WGM, WGN, RING, AT, BT, EPI, CONV>(g, m0, n0, z);
+}
+
+// The weight gradients of a whole backward pass in one launch: one workgroup per unit, the units with the longest chunks first.  What it is for: a
+// gradient of its own is a launch of 4 - 15 us that fills the chip once with chunks of the reduction, and a second launch adds them up;
+// together the gradients have tiles enough without a split, or with a few chunks for the longest.
+template <int BM, int BN, int WGM, int WGN, bool GATHERED>
+__global__ __launch_bounds__(WGM* WGN * 64) void gemm_ring_group_kernel(GroupParams<GATHERED> p) {
+  const int u = group_unit((int)blockIdx.x, 1024, p.units);
+  const auto& j = p.job[group_job<GATHERED>(p, u)];
+  Params g;
+  g.A = j.A; g.B = j.B; g.M = j.M; g.N = j.N; g.K = j.K; g.lda = j.lda; g.ldb = j.ldb;
+  g.split_k = j.split; g.k_chunk = j.k_chunk; g.z_inner = 1;
+  g.sAo = g.sAi = g.sBo = g.sBi = g.sCo = g.sCi = 0;
+  g.C = j.C;
+  if constexpr (GATHERED) { g.cH = j.cH; g.cW = j.cW; g.cC = j.cC; g.cT = j.cT; g.cS = j.cS; g.cHo = j.cHo; g.cWo = j.cWo; }
+  int m0, n0, z;
+  group_tile<BM, BN>(j.M, j.N, u - j.unit0, m0, n0, z);
+  ring_tile<BM, BN, WGM, WGN, 3, true, true, E_PARTIAL, GATHERED ? 2 : 0>(g, m0, n0, z);
 }
 
 LaunchFn ring_64x64(bool a_t, bool b_t, int epi);

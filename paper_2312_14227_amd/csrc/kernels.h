@@ -4,6 +4,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <vector>
+
 namespace et {
 
 typedef __bf16 bf16;
@@ -88,6 +90,41 @@ void gemm_bf16_plan_conv(int M, int N, int K, int* tile, int* split_k, bool fixe
 // the same for the implicit weight gradient of a 3x3 convolution (M output channels, N = 9 input channels, K pixels); taps = 7: of a
 // 7x7 stem (N = 256)
 void gemm_bf16_plan_conv_dw(int M, int N, int K, int* tile, int* split_k, int taps = 3);
+
+// The weight gradients of a backward pass together: C[M][N] (fp32, rows without padding) = sum over K rows of A[k][m] B[k][n], plain or, with
+// conv_c > 0, with B gathered from the NHWC activation [.., conv_h, conv_w, conv_c] (M output channels, N = taps^2 conv_c, K output pixels).
+struct DwJob {
+  const bf16* A = nullptr;
+  const bf16* B = nullptr;
+  float* C = nullptr;
+  int M = 0, N = 0, K = 0, lda = 0, ldb = 0;
+  int conv_h = 0, conv_w = 0, conv_c = 0, conv_taps = 3, conv_stride = 1;
+  int split = 1;   // chunks of the reduction: the plan of the product on its own (a gradient has the same bits whatever runs beside it)
+};
+// One launch of a group: tile, and the jobs in the order of their units
+struct DwGroupLaunch {
+  struct Part { int job, split, per; long long tiles; };   // chunks of the reduction, of `per` slices of 64 rows; tiles of each
+  bool direct = false, gathered = false;
+  int bm = 64, bn = 64;
+  double cost = 0.0;     // estimate, us
+  std::vector<Part> parts;
+};
+// Which kernels run a group, in which order; a function of the jobs' shapes alone
+struct DwGroupPlan {
+  std::vector<long long> shapes;
+  std::vector<DwGroupLaunch> launches;
+  std::vector<double> cost;   // per job: estimated share of the time, in arbitrary units
+};
+// whether a gradient can take part (an implicit one of 14 GFLOP and more is better off on its own)
+bool dw_group_takes(const DwJob& j);
+// floats of scratch that its chunks take
+inline size_t dw_group_elems(const DwJob& j) { return j.split > 1 ? (size_t)j.split * j.M * j.N : 0; }
+constexpr int DW_GROUP_MAX = 120;   // jobs of a group
+// makes `plan` that of the jobs, unless it is
+hipError_t dw_group_plan(const DwJob* jobs, int n, DwGroupPlan& plan);
+inline double dw_group_cost(const DwGroupPlan& plan, int job) { return plan.cost[job]; }
+// Runs them, in few launches; the gradients are bit-reproducible.  partials: scratch for dw_group_elems of all jobs, 16-byte aligned
+hipError_t dw_group(const DwJob* jobs, int n, const DwGroupPlan& plan, float* partials, hipStream_t s, int* launches);
 
 // ------------------------------------------------------------------------------------------
 // fp32 GEMM (true fp32 FMA), same operand convention, for the fp32 MLP workload

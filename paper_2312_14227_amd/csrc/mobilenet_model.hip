@@ -132,8 +132,21 @@ int build_mobilenet(et_ctx* c) {
   wgrad(C, d.last, B);
   for (int i = 0; i < 3; i++) reserve(c, &c->rd[i], b16 * max_act);
   reserve(c, &c->rdsum, b16 * max_act);
-  c->gemm_partial_elems = pe;
-  reserve(c, &c->gemm_partials, f32 * std::max<size_t>(pe, 64));
+  {
+    size_t all = 0, keeps = 0;
+    auto weight = [&](size_t rows, int out, int in) {
+      all += et::gemm_bf16_partial_elems(out, in, split_for(out, in, (int)rows));
+      keeps += keep_size(rows * out);
+    };
+    for (const MbBlockBufs& b : c->mblk) {
+      if (b.expand) weight(rows_in(c, b), b.hid, b.Cin);
+      weight(rows_out(c, b), b.Cout, b.hid);
+    }
+    weight(rows_of(c, c->mlast), c->mlast.Cout, c->mlast.Cin);
+    weight(B, d.classes, d.last);
+    reserve_partials(c, pe, all);
+    reserve_keep(c, keeps);
+  }
   reserve_sums(c, all_cs + hb, std::max(max_cs, hb));
   // every matrix dimension and element count below is handled as int by the GEMM
   if (max_act > 0x7fffffffull || rows_of(c, c->stem) * c->stem.Kc > 0x7fffffffull || max_dwp > 0x7fffffffull) return ET_EINVAL;
@@ -223,10 +236,7 @@ int mobilenet_backward(et_ctx* c, const void* x, const uint8_t* mask) {
   const int tl = ul.t, Cl = ul.Cout, C = md.classes, HWl = ul.Ho * ul.Wo;
   const long long Ml = (long long)rows_of(c, ul);
   if (sel(tl + 4) && (rc = colsum_dw(c, tl + 4, nullptr, c->dlogits, C, B, C)) != ET_OK) return rc;
-  if (sel(tl + 3)) {
-    Region r(c, PH_DW, tl + 3);
-    ET_G(linear_dw(c, c->dl16, C, c->zc, Cl, c->grad[tl + 3], B, C, Cl));
-  }
+  if (sel(tl + 3) && (rc = weight_grad(c, tl + 3, c->dl16, C, c->zc, Cl, B, C, Cl)) != ET_OK) return rc;
   if (!pass(tl + 3)) return ET_OK;
   {  // through the head matrix, the average pooling and the ReLU6 of the last convolution
     Region r(c, PH_DY, tl + 3);
@@ -235,17 +245,15 @@ int mobilenet_backward(et_ctx* c, const void* x, const uint8_t* mask) {
     ET_G(g);
     ET_KB(1, 4.0 * Ml * Cl, et::avgpool_bwd_relu(c->dz, ul.y, c->rd[1], B, HWl, Cl, s, 6.f));
   }
-  if ((rc = affine_back(tl + 1, plain(c->rd[1]), ul.z, c->rd[0], Ml, Cl)) != ET_OK) return rc;
+  bf16* d = keep(c, pass(tl + 1) && sel(tl), (size_t)Ml * Cl, c->rd[0]);   // gradient of a convolution's output, wherever it is kept
+  if ((rc = affine_back(tl + 1, plain(c->rd[1]), ul.z, d, Ml, Cl)) != ET_OK) return rc;
   if (jstar > tl) return ET_OK;
   const bf16* last_in = c->mblk.back().y;
-  if (sel(tl)) {
-    Region r(c, PH_DW, tl);
-    ET_G(linear_dw(c, c->rd[0], Cl, last_in, ul.Cin, c->grad[tl], (int)Ml, Cl, ul.Cin));
-  }
+  if (sel(tl) && (rc = weight_grad(c, tl, d, Cl, last_in, ul.Cin, (int)Ml, Cl, ul.Cin)) != ET_OK) return rc;
   if (!pass(tl)) return ET_OK;
   {  // the block output in front of it has no activation
     Region r(c, PH_DY, tl);
-    et::GemmDesc g = linear_dx(c->rd[0], Wt(tl), (int)Ml, Cl, ul.Cin);
+    et::GemmDesc g = linear_dx(d, Wt(tl), (int)Ml, Cl, ul.Cin);
     g.C = c->rdsum;
     ET_G(g);
   }
@@ -261,16 +269,14 @@ int mobilenet_backward(et_ctx* c, const void* x, const uint8_t* mask) {
     const bf16* stem_y = bi == 0 ? c->stem.y : nullptr;   // ReLU6 of the stem sits in front of the first block
     // projection (a shortcut hands the block output's gradient on: it is kept in rdsum)
     if (b.shortcut && out.d != c->rdsum) out.dmid = c->rdsum;
-    if ((rc = affine_back(td + 4, out, b.z_proj, c->rd[0], Mo, b.Cout)) != ET_OK) return rc;
+    d = keep(c, pass(td + 4) && sel(td + 3), (size_t)Mo * b.Cout, c->rd[0]);
+    if ((rc = affine_back(td + 4, out, b.z_proj, d, Mo, b.Cout)) != ET_OK) return rc;
     if (jstar > td + 3) return ET_OK;
-    if (sel(td + 3)) {
-      Region r(c, PH_DW, td + 3);
-      ET_G(linear_dw(c, c->rd[0], b.Cout, b.y_dw, b.hid, c->grad[td + 3], (int)Mo, b.Cout, b.hid));
-    }
+    if (sel(td + 3) && (rc = weight_grad(c, td + 3, d, b.Cout, b.y_dw, b.hid, (int)Mo, b.Cout, b.hid)) != ET_OK) return rc;
     if (!pass(td + 3)) return ET_OK;
     {  // through the projection matrix and the ReLU6 after the depthwise convolution
       Region r(c, PH_DY, td + 3);
-      et::GemmDesc g = linear_dx(c->rd[0], Wt(td + 3), (int)Mo, b.Cout, b.hid);
+      et::GemmDesc g = linear_dx(d, Wt(td + 3), (int)Mo, b.Cout, b.hid);
       g.C = c->rd[1];
       ET_G(g);
     }
@@ -299,16 +305,14 @@ int mobilenet_backward(et_ctx* c, const void* x, const uint8_t* mask) {
       ET_KB(1, 2.0 * (Mo + Mi) * b.hid, et::depthwise3x3_dx(c->rd[0], Wt(td), nullptr, nullptr, c->rd[1], B, b.H, b.W, b.hid, b.stride, s));
     }
     // expansion
-    if ((rc = affine_back(t + 1, behind(c->rd[1], b.y_exp, td), b.z_exp, c->rd[0], Mi, b.hid)) != ET_OK) return rc;
+    d = keep(c, pass(t + 1) && sel(t), (size_t)Mi * b.hid, c->rd[0]);
+    if ((rc = affine_back(t + 1, behind(c->rd[1], b.y_exp, td), b.z_exp, d, Mi, b.hid)) != ET_OK) return rc;
     if (jstar > t) return ET_OK;
-    if (sel(t)) {
-      Region r(c, PH_DW, t);
-      ET_G(linear_dw(c, c->rd[0], b.hid, b.x, b.Cin, c->grad[t], (int)Mi, b.hid, b.Cin));
-    }
+    if (sel(t) && (rc = weight_grad(c, t, d, b.hid, b.x, b.Cin, (int)Mi, b.hid, b.Cin)) != ET_OK) return rc;
     if (!pass(t)) return ET_OK;
     {  // through the expansion matrix to the block input, where the shortcut's gradient joins (in front of the first block, the stem's ReLU6)
       Region r(c, PH_DY, t);
-      et::GemmDesc g = linear_dx(c->rd[0], Wt(t), (int)Mi, b.hid, b.Cin);
+      et::GemmDesc g = linear_dx(d, Wt(t), (int)Mi, b.hid, b.Cin);
       out = stem_y ? behind(c->rd[2], stem_y, t) : plain(c->rd[2]);
       out.tensor = t;
       if (b.shortcut) out.add = c->rdsum;

@@ -141,8 +141,17 @@ int build_resnet(et_ctx* c) {
   reserve(c, &c->rdsum, b16 * max_act);
   reserve(c, &c->rdsc, b16 * max_act);
   reserve(c, &c->rdcols, std::max(b16 * std::max<size_t>(max_cols, 8), dcols_b));
-  c->gemm_partial_elems = pe;
-  reserve(c, &c->gemm_partials, f32 * std::max<size_t>(pe, 64));
+  {
+    size_t all = et::gemm_bf16_partial_elems(C, Cf, split_for(C, Cf, (int)B)), keeps = 0;
+    for (const ResBlockBufs& b : c->rblk)
+      for (const ConvUnit* u : {&b.c1, &b.c2, &b.c3, &b.sc})
+        if (u != &b.sc || b.proj) {
+          all += conv_dw_partials(c, *u);
+          keeps += keep_size(rows_of(c, *u) * u->Cout);
+        }
+    reserve_partials(c, pe, all);
+    reserve_keep(c, keeps);
+  }
   const size_t hb = sum_elems(et::colsum_parts((int)B, C), C);
   reserve_sums(c, all_cs + hb, std::max(max_cs, hb));
   // every matrix dimension and element count below is handled as int by the GEMM
@@ -230,10 +239,7 @@ int resnet_backward(et_ctx* c, const void* x, const uint8_t* mask) {
   const ResBlockBufs& last = c->rblk.back();
   const int Cf = last.c3.Cout, C = md.classes, C8 = round8(md.classes), HWf = last.c3.Ho * last.c3.Wo;
   if (sel(N - 1) && (rc = colsum_dw(c, N - 1, nullptr, c->dlogits, C, B, C)) != ET_OK) return rc;
-  if (sel(N - 2)) {
-    Region r(c, PH_DW, N - 2);
-    ET_G(linear_dw(c, c->dl16, C8, c->zc, Cf, c->grad[N - 2], B, C, Cf));
-  }
+  if (sel(N - 2) && (rc = weight_grad(c, N - 2, c->dl16, C8, c->zc, Cf, B, C, Cf)) != ET_OK) return rc;
   if (pass(N - 2)) {  // through the head matrix, the average pooling and the ReLU closing the last block
     Region r(c, PH_DY, N - 2);
     et::GemmDesc g = linear_dx(c->dl16, Wt(N - 2), B, C, Cf);
@@ -262,58 +268,51 @@ int resnet_backward(et_ctx* c, const void* x, const uint8_t* mask) {
     const int t = b.t;
     if (jstar > t + (b.proj ? 11 : 8)) break;
     const long long M3 = (long long)rows_of(c, b.c3), M2 = (long long)rows_of(c, b.c2), M1 = (long long)rows_of(c, b.c1);
+    bf16* dsc = nullptr;
     if (b.proj) {
       bool done;
-      if ((rc = affine_back(c, mask, jstar, t + 10, out, b.sc.z, nullptr, c->rdsc, M3, b.sc.Cout, sel(t + 9) || pass(t), &done)) != ET_OK)
+      dsc = keep(c, pass(t + 10) && sel(t + 9), (size_t)M3 * b.sc.Cout, c->rdsc);
+      if ((rc = affine_back(c, mask, jstar, t + 10, out, b.sc.z, nullptr, dsc, M3, b.sc.Cout, sel(t + 9) || pass(t), &done)) != ET_OK)
         return rc;
       if (done) out = plain(c->rdsum);
-      if (sel(t + 9)) {
-        Region r(c, PH_DW, t + 9);
-        if ((rc = conv_dw(c, b.sc, b.x, c->rdsc, c->grad[t + 9])) != ET_OK) return rc;
-      }
+      if (sel(t + 9) && (rc = conv_dw(c, b.sc, b.x, dsc)) != ET_OK) return rc;
     }
     // main branch: c3
-    if ((rc = affine_back(c, mask, jstar, t + 7, out, b.c3.z, nullptr, c->rd[0], M3, b.c3.Cout)) != ET_OK) return rc;
-    if (sel(t + 6)) {
-      Region r(c, PH_DW, t + 6);
-      if ((rc = conv_dw(c, b.c3, b.c2.y, c->rd[0], c->grad[t + 6])) != ET_OK) return rc;
-    }
+    const bf16* d = keep(c, pass(t + 7) && sel(t + 6), (size_t)M3 * b.c3.Cout, c->rd[0]);
+    if ((rc = affine_back(c, mask, jstar, t + 7, out, b.c3.z, nullptr, const_cast<bf16*>(d), M3, b.c3.Cout)) != ET_OK) return rc;
+    if (sel(t + 6) && (rc = conv_dw(c, b.c3, b.c2.y, d)) != ET_OK) return rc;
     if (pass(t + 6)) {  // through the 1x1 convolution (the ReLU after c2 with c2's affine)
       Region r(c, PH_DY, t + 6);
-      if ((rc = conv_dcols(c, b.c3, c->rd[0], Wt(t + 6), c->rd[1])) != ET_OK) return rc;
+      if ((rc = conv_dcols(c, b.c3, d, Wt(t + 6), c->rd[1])) != ET_OK) return rc;
     }
     // c2
-    if ((rc = affine_back(c, mask, jstar, t + 4, behind(c->rd[1], b.c2.y, t + 6), b.c2.z, nullptr, c->rd[0], M2, b.c2.Cout)) != ET_OK) return rc;
-    if (sel(t + 3)) {
-      Region r(c, PH_DW, t + 3);
-      if ((rc = conv_dw(c, b.c2, b.c1.y, c->rd[0], c->grad[t + 3])) != ET_OK) return rc;
-    }
+    d = keep(c, pass(t + 4) && sel(t + 3), (size_t)M2 * b.c2.Cout, c->rd[0]);
+    if ((rc = affine_back(c, mask, jstar, t + 4, behind(c->rd[1], b.c2.y, t + 6), b.c2.z, nullptr, const_cast<bf16*>(d), M2, b.c2.Cout)) != ET_OK) return rc;
+    if (sel(t + 3) && (rc = conv_dw(c, b.c2, b.c1.y, d)) != ET_OK) return rc;
     // through the 3x3 convolution and the ReLU after c1; where c1's z is stored, c1's affine applies the mask without reading y
     const bool late = implicit_dy(b.c2) && sel(t + 1);
     if (pass(t + 3)) {
       Region r(c, PH_DY, t + 3);
       if (implicit_dy(b.c2)) {
-        if ((rc = conv_dy_implicit(c, b.c2, c->rd[0], late ? nullptr : b.c1.y, c->rd[1])) != ET_OK) return rc;
+        if ((rc = conv_dy_implicit(c, b.c2, d, late ? nullptr : b.c1.y, c->rd[1])) != ET_OK) return rc;
       } else {
-        if ((rc = conv_dcols(c, b.c2, c->rd[0], Wt(t + 3), c->rdcols)) != ET_OK) return rc;
+        if ((rc = conv_dcols(c, b.c2, d, Wt(t + 3), c->rdcols)) != ET_OK) return rc;
         ET_KB(1, (dcols_f32(b.c2) ? 4.0 : 2.0) * M2 * b.c2.Kc + 4.0 * M1 * b.c1.Cout, et::col2im(c->rdcols, dcols_f32(b.c2), nullptr, b.c1.y, c->rd[1], geom(c, b.c2), s));
       }
     }
     // c1
-    if ((rc = affine_back(c, mask, jstar, t + 1, late ? behind(c->rd[1], b.c1.y, t + 3) : plain(c->rd[1]), b.c1.z, nullptr, c->rd[0], M1, b.c1.Cout)) != ET_OK) return rc;
-    if (sel(t)) {
-      Region r(c, PH_DW, t);
-      if ((rc = conv_dw(c, b.c1, b.x, c->rd[0], c->grad[t])) != ET_OK) return rc;
-    }
+    d = keep(c, pass(t + 1) && sel(t), (size_t)M1 * b.c1.Cout, c->rd[0]);
+    if ((rc = affine_back(c, mask, jstar, t + 1, late ? behind(c->rd[1], b.c1.y, t + 3) : plain(c->rd[1]), b.c1.z, nullptr, const_cast<bf16*>(d), M1, b.c1.Cout)) != ET_OK) return rc;
+    if (sel(t) && (rc = conv_dw(c, b.c1, b.x, d)) != ET_OK) return rc;
     if (pass(t)) {
       // through c1, joined by the shortcut branch (through the shortcut convolution, or the
       // identity), then through the ReLU closing the previous block -- or, for the first block,
       // the max pooling and the stem's ReLU
       Region r(c, PH_DY, t);
-      if ((rc = conv_dcols(c, b.c1, c->rd[0], Wt(t), c->rd[1])) != ET_OK) return rc;
+      if ((rc = conv_dcols(c, b.c1, d, Wt(t), c->rd[1])) != ET_OK) return rc;
       const bf16* prev_y = bi > 0 ? c->rblk[bi - 1].y : nullptr;
       if (b.proj) {
-        if ((rc = conv_dcols(c, b.sc, c->rdsc, Wt(t + 9), c->rdcols)) != ET_OK) return rc;
+        if ((rc = conv_dcols(c, b.sc, dsc, Wt(t + 9), c->rdcols)) != ET_OK) return rc;
         ET_KB(1, 2.0 * M3 * b.sc.Kc + (prev_y ? 6.0 : 4.0) * M1 * b.c1.Cin,
               et::col2im(c->rdcols, dcols_f32(b.sc), c->rd[1], prev_y, prev_y ? c->rdsum : c->rd[0], geom(c, b.sc), s));
         out = plain(c->rdsum);

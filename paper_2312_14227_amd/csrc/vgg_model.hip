@@ -249,16 +249,14 @@ int vgg_backward(et_ctx* c, const void* x, const uint8_t* mask) {
       KernelTimer kt(c, 7, 2.0 * M * u.Cout);
       if ((rc = colsum_dw(c, t + 1, dcur, nullptr, u.Cout, (int)M, u.Cout)) != ET_OK) return rc;
     }
-    if (sel(t)) {
+    if (sel(t) && u.Kc == 9 * u.Cin) {
+      if ((rc = conv_dw(c, u, u.in, dcur)) != ET_OK) return rc;
+    } else if (sel(t)) {   // few input channels: from the column matrix, whose padding is stripped
       Region r(c, PH_DW, t);
       if (et::conv_first_supported(u.k, u.Cin))
         ET_KB(1, 2.0 * ((double)M * u.Cin + (double)M * u.Kc), et::im2col((const bf16*)x, u.cols, geom(c, u), s));
-      if (u.Kc == 9 * u.Cin) {
-        if ((rc = conv_dw(c, u, u.in, dcur, c->grad[t])) != ET_OK) return rc;
-      } else {
-        if ((rc = conv_dw(c, u, u.in, dcur, c->stem_dw8)) != ET_OK) return rc;
-        ET_K(1, et::strip_rows(c->stem_dw8, c->grad[t], u.Cout, 9 * u.Cin, u.Kc, s));
-      }
+      ET_G(linear_dw(c, dcur, u.Cout, u.cols, u.Kc, c->stem_dw8, (int)M, u.Cout, u.Kc));
+      ET_K(1, et::strip_rows(c->stem_dw8, c->grad[t], u.Cout, 9 * u.Cin, u.Kc, s));
     }
     if (pass(t)) {   // i > 0 here: tensor 0 is never passed
       Region r(c, PH_DY, t);
