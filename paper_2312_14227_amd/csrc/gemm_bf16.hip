@@ -523,6 +523,13 @@ hipError_t gemm_bf16(const GemmDesc& d, hipStream_t s, int* launches) {
     case T_DIRECT_128x256: BM = 128; BN = 256; fn = gemm::direct_128x256(d.a_t, d.b_t, epi); break;
     default: BM = 128; BN = 128; fn = gemm::staged_128x128(d.a_t, d.b_t, epi); resident = false; break;
   }
+  // a lone 64x64 tile per CU with a long reduction waits for memory, the more so where its operands are read for the first time: five slices in
+  // flight instead of three.  Weights from memory, [788 x 768 x 3072] 19.2 -> 14.2 us, x 2304 12.4 -> 10.8, x 1536 equal, x 768 6.1 -> 6.4;
+  // with two or more tiles per CU the LDS that it takes costs more than it gives ([788 x 3072 x 768] 12.4 -> 13.7)
+  if (fn && !conv && BM == 64 && BN == 64 && !resident && k_per_block >= 32 * gemm::PBK && (long long)((d.M + 63) / 64) * ((d.N + 63) / 64) * zdim <= 256) {
+    const gemm::LaunchFn deep = gemm::ring_64x64_deep(d.a_t, d.b_t, epi);
+    if (deep) fn = deep;
+  }
   if (!fn) return hipErrorInvalidValue;  // this (layout, epilogue) pair is not part of the training step
   const int tiles = ((d.M + BM - 1) / BM) * ((d.N + BN - 1) / BN);
   if ((long long)tiles * zdim >= (1ll << 23)) return hipErrorInvalidValue;   // (the resident kernels' unit arithmetic)

@@ -18,7 +18,7 @@ hipError_t launch(const GroupParams<false>& p, int grid, hipStream_t s) {
 }
 template <int BM, int BN, int WGM, int WGN, bool GATHERED>
 hipError_t launch_ring(const GroupParams<GATHERED>& p, hipStream_t s) {
-  hipLaunchKernelGGL((gemm_ring_group_kernel<BM, BN, WGM, WGN, GATHERED>), dim3(p.units), dim3(WGM * WGN * 64), 0, s, p);
+  hipLaunchKernelGGL((gemm_ring_kernel<BM, BN, WGM, WGN, 3, true, true, E_PARTIAL, GATHERED ? 2 : 0, true>), dim3(p.units), dim3(WGM * WGN * 64), 0, s, p);
   return hipGetLastError();
 }
 

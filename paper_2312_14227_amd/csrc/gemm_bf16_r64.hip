@@ -5,9 +5,9 @@ namespace et {
 namespace gemm {
 namespace {
 
-template <bool AT, bool BT, int E, int CONV = 0>
+template <bool AT, bool BT, int E, int CONV = 0, int RING = 3>
 hipError_t launch(const Params& p, dim3 grid, hipStream_t s) {
-  hipLaunchKernelGGL((gemm_ring_kernel<64, 64, 2, 2, 3, AT, BT, E, CONV>), grid, dim3(256), 0, s, p);
+  hipLaunchKernelGGL((gemm_ring_kernel<64, 64, 2, 2, RING, AT, BT, E, CONV>), grid, dim3(256), 0, s, p);
   return hipGetLastError();
 }
 
@@ -31,6 +31,19 @@ LaunchFn ring_64x64(bool a_t, bool b_t, int epi) {
   ET_PICK(true, true, E_F32)
   ET_PICK(true, true, E_BF16)
   ET_PICK(true, true, E_PARTIAL)
+#undef ET_PICK
+  return nullptr;
+}
+
+LaunchFn ring_64x64_deep(bool a_t, bool b_t, int epi) {
+#define ET_PICK(AT, BT, E) \
+  if (a_t == AT && b_t == BT && epi == E) return launch<AT, BT, E, 0, 5>;
+  ET_PICK(false, false, E_F32)
+  ET_PICK(false, false, E_F32_RES)
+  ET_PICK(false, false, E_BF16)
+  ET_PICK(false, false, E_AFFINE)
+  ET_PICK(false, false, E_AFFINE_ADD)
+  ET_PICK(false, true, E_BF16)
 #undef ET_PICK
   return nullptr;
 }

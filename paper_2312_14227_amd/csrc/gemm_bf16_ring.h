@@ -27,9 +27,26 @@
 namespace et {
 namespace gemm {
 
-// one tile with the corner (m0, n0), of batch entry or reduction chunk z
-template <int BM, int BN, int WGM, int WGN, int RING, bool AT, bool BT, int EPI, int CONV>
-__device__ __forceinline__ void ring_tile(const Params& g, int m0, int n0, int z) {
+// the product of a launch: its arguments, or a job of a group as such
+template <bool CONV>
+__device__ __forceinline__ const Params& ring_product(const Params& p, const Params&, int) { return p; }
+template <bool CONV>
+__device__ __forceinline__ const Params& ring_product(const GroupParams<CONV>& p, Params& g, int job) {
+  const auto& j = p.job[job];
+  g.A = j.A; g.B = j.B; g.M = j.M; g.N = j.N; g.K = j.K; g.lda = j.lda; g.ldb = j.ldb;
+  g.split_k = j.split; g.k_chunk = j.k_chunk; g.z_inner = 1;
+  g.sAo = g.sAi = g.sBo = g.sBi = g.sCo = g.sCi = 0;
+  g.C = j.C;
+  if constexpr (CONV) { g.cH = j.cH; g.cW = j.cW; g.cC = j.cC; g.cT = j.cT; g.cS = j.cS; g.cHo = j.cHo; g.cWo = j.cWo; }
+  return g;
+}
+
+// GROUP: the weight gradients of a whole backward pass in one launch: one workgroup per unit, the units with the longest chunks first.  What it is
+// for: a gradient of its own is a launch of 4 - 15 us that fills the chip once with chunks of the reduction, and a second launch adds them up;
+// together the gradients have tiles enough with few chunks or none.
+template <int BM, int BN, int WGM, int WGN, int RING, bool AT, bool BT, int EPI, int CONV = 0, bool GROUP = false>
+__global__ __launch_bounds__(WGM* WGN * 64) void gemm_ring_kernel(std::conditional_t<GROUP, GroupParams<CONV == 2>, Params> args) {
+  static_assert(!GROUP || (AT && BT && EPI == E_PARTIAL && CONV != 1), "groups of weight gradients");
   constexpr int NW = WGM * WGN;
   constexpr int TM = BM / WGM, TN = BN / WGN;
   constexpr int MI = TM / 32, NI = TN / 32;
@@ -40,11 +57,20 @@ __device__ __forceinline__ void ring_tile(const Params& g, int m0, int n0, int z
   static_assert(CONV != 2 || (AT && BT), "implicit convolution, weight gradient: both operands reduce over rows");
   constexpr int EPI_BYTES = NW * epi_wave_bytes<TN>();
   constexpr int SMEM = RING * STAGE > EPI_BYTES ? RING * STAGE : EPI_BYTES;
-  static_assert((RING == 2 || RING == 3) && SMEM <= 160 * 1024, "LDS ring");
+  static_assert(RING >= 2 && RING <= 8 && SMEM <= 160 * 1024, "LDS ring");
   __shared__ __attribute__((aligned(1024))) unsigned char smem[SMEM];
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wave_m = wave / WGN, wave_n = wave % WGN;
+  int m0, n0, z, job = 0, unit = 0;
+  if constexpr (GROUP) {
+    unit = group_unit((int)blockIdx.x, 1024, args.units);
+    job = group_job<CONV == 2>(args, unit);
+  }
+  Params from_job;
+  const Params& g = ring_product<CONV == 2>(args, from_job, job);
+  if constexpr (GROUP) group_tile<BM, BN>(g.M, g.N, unit - args.job[job].unit0, m0, n0, z);
+  else tile_coords<BM, BN>(g, m0, n0, z);
   const bf16* A;
   const bf16* B;
   long long c_off;
@@ -233,9 +259,14 @@ __device__ __forceinline__ void ring_tile(const Params& g, int m0, int n0, int z
   // wait until slice `sl` has landed: up to `most` younger slices stay in flight
   auto wait_slice = [&](int sl, auto most_tag) {
     constexpr int MOST = decltype(most_tag)::value;
-    static_assert(MOST <= 2 && MOST * LOADS <= 63, "vmcnt");
+    static_assert(MOST <= 7 && MOST * LOADS <= 63, "vmcnt");
     const int younger = min(MOST, nk - 1 - sl);
-    if (younger == MOST) wait_vmcnt<MOST * LOADS>();
+    if (younger == MOST) { wait_vmcnt<MOST * LOADS>(); return; }
+    if (MOST > 6 && younger == 6) wait_vmcnt<6 * LOADS>();
+    else if (MOST > 5 && younger == 5) wait_vmcnt<5 * LOADS>();
+    else if (MOST > 4 && younger == 4) wait_vmcnt<4 * LOADS>();
+    else if (MOST > 3 && younger == 3) wait_vmcnt<3 * LOADS>();
+    else if (MOST > 2 && younger == 2) wait_vmcnt<2 * LOADS>();
     else if (MOST > 1 && younger == 1) wait_vmcnt<LOADS>();
     else wait_vmcnt<0>();
   };
@@ -311,32 +342,8 @@ __device__ __forceinline__ void ring_tile(const Params& g, int m0, int n0, int z
   wave_epilogue<EPI, MI, NI>(g, acc, smem + wave * epi_wave_bytes<TN>(), m0 + wave_m * TM, n0 + wave_n * TN, c_off, lane);
 }
 
-template <int BM, int BN, int WGM, int WGN, int RING, bool AT, bool BT, int EPI, int CONV = 0>
-__global__ __launch_bounds__(WGM* WGN * 64) void gemm_ring_kernel(Params g) {
-  int m0, n0, z;
-  tile_coords<BM, BN>(g, m0, n0, z);
-  ring_tile<BM, BN, WGM, WGN, RING, AT, BT, EPI, CONV>(g, m0, n0, z);
-}
-
-// The weight gradients of a whole backward pass in one launch: one workgroup per unit, the units with the longest chunks first.  What it is for: a
-// gradient of its own is a launch of 4 - 15 us that fills the chip once with chunks of the reduction, and a second launch adds them up;
-// together the gradients have tiles enough without a split, or with a few chunks for the longest.
-template <int BM, int BN, int WGM, int WGN, bool GATHERED>
-__global__ __launch_bounds__(WGM* WGN * 64) void gemm_ring_group_kernel(GroupParams<GATHERED> p) {
-  const int u = group_unit((int)blockIdx.x, 1024, p.units);
-  const auto& j = p.job[group_job<GATHERED>(p, u)];
-  Params g;
-  g.A = j.A; g.B = j.B; g.M = j.M; g.N = j.N; g.K = j.K; g.lda = j.lda; g.ldb = j.ldb;
-  g.split_k = j.split; g.k_chunk = j.k_chunk; g.z_inner = 1;
-  g.sAo = g.sAi = g.sBo = g.sBi = g.sCo = g.sCi = 0;
-  g.C = j.C;
-  if constexpr (GATHERED) { g.cH = j.cH; g.cW = j.cW; g.cC = j.cC; g.cT = j.cT; g.cS = j.cS; g.cHo = j.cHo; g.cWo = j.cWo; }
-  int m0, n0, z;
-  group_tile<BM, BN>(j.M, j.N, u - j.unit0, m0, n0, z);
-  ring_tile<BM, BN, WGM, WGN, 3, true, true, E_PARTIAL, GATHERED ? 2 : 0>(g, m0, n0, z);
-}
-
 LaunchFn ring_64x64(bool a_t, bool b_t, int epi);
+LaunchFn ring_64x64_deep(bool a_t, bool b_t, int epi);   // five slices in flight, or null
 LaunchFn ring_64x128(bool a_t, bool b_t, int epi);
 LaunchFn ring_128x128(bool a_t, bool b_t, int epi);
 LaunchFn ring_conv_64x64(int epi);
