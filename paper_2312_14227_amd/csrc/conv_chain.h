@@ -103,6 +103,7 @@ inline void plan_implicit(et_ctx* c, et::GemmDesc& g, bool fixed_sums = false) {
   et::gemm_bf16_plan_conv(g.M, g.N, g.K, &g.tile, &g.split_k, fixed_sums);
   g.partials = c->gemm_partials;
   if (et::gemm_bf16_partial_elems(g.M, g.N, g.split_k) > c->gemm_partial_elems) g.split_k = 1;
+  if (et::conv_halo_pays(g)) g.tile = et::CONV_TILE_HALO;   // (not a split one; the sums are in the same order)
 }
 inline size_t conv_split_partials(const et_ctx* c, const ConvUnit& u, bool fixed_sums = false) {
   size_t n = 0;

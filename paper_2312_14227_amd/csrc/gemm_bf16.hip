@@ -410,6 +410,12 @@ hipError_t gemm_bf16(const GemmDesc& d, hipStream_t s, int* launches) {
                           (d.mode == EPI_RELU_MASK && (!d.U || !aligned(d.U, 8))) || (d.mode == EPI_BIAS_RELU && !d.bias)))
       return hipErrorInvalidValue;
   }
+  if (d.tile == CONV_TILE_HALO) {
+    if (!conv || conv_dw || stem || !conv_halo_takes(d)) return hipErrorInvalidValue;
+    const hipError_t e = conv_halo(d, s);
+    if (e == hipSuccess && launches) *launches = 1;
+    return e;
+  }
   const bool conv_split = conv && !conv_dw && d.split_k > 1;
   if (d.residual && (d.ldr < d.N || (d.ldr & 3) || !aligned(d.residual, 16))) return hipErrorInvalidValue;
 

@@ -75,6 +75,12 @@ struct GemmDesc {
   int tile = 0;                    // 0 = choose by shape; else a TileId (tuning/tests)
 };
 
+// 3x3 / stride 1 convolution of 64 channels from tiles of the input with their border (conv_halo.hip); tile id of that kernel in GemmDesc::tile
+constexpr int CONV_TILE_HALO = 31;
+bool conv_halo_takes(const GemmDesc& d);
+bool conv_halo_pays(const GemmDesc& d);
+hipError_t conv_halo(const GemmDesc& d, hipStream_t s);
+
 // returns hipSuccess, or hipErrorInvalidValue when a requirement above is violated
 // *launches (nullable) receives the number of kernels launched (1, or 2 with split-K)
 hipError_t gemm_bf16(const GemmDesc& d, hipStream_t s, int* launches = nullptr);
