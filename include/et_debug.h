@@ -36,7 +36,8 @@ int et_debug_gemm_bf16_colsum(const void* A, const void* B, void* C, const void*
  * [N][3][3][C]; out bf16 [batch*H*W][N], N a multiple of 4.  mode 0: plain; 1: out = max(v + bias[n], 0);
  * 2: out = U > 0 ? v : 0 with U bf16 shaped like out.  tile: 0 = automatic, or 11, 13, 15, 17 for the
  * 256x256, 256x192, 256x128, 512x64 tiles, 23, 25, 27, 29 for the ring tiles, or 31 for tiles of the input with their border (C = 64, N a multiple
- * of 64, at least two thirds of the 8 x 32 pixel tiles inside the image).  Device pointers, 16-byte aligned.  Returns 0, -1, -3 as above. */
+ * of 64, at least two thirds of the 8 x 32 pixel tiles inside the image) or 33, 35 for those of
+ * small images (N a multiple of 64, W at most 62, 30).  Device pointers, 16-byte aligned.  Returns 0, -1, -3 as above. */
 int et_debug_conv3x3(const void* x, const void* w, void* out, int batch, int H, int W, int C, int N,
                      const void* bias, const void* U, int mode, int tile, void* stream);
 

@@ -100,6 +100,11 @@ inline bool implicit_dw(const et_ctx*, const ConvUnit& u) {
 // and with another order of the sums another tap wins here and there, which moves gradients by some per cent; so the order
 // stays that of one plan while the tile is free)
 inline void plan_implicit(et_ctx* c, et::GemmDesc& g, bool fixed_sums = false) {
+  if (const int tile = fixed_sums ? 0 : et::conv_raster_tile(g)) {   // (sums over chunks of channels, then taps)
+    g.tile = tile;
+    g.split_k = 1;
+    return;
+  }
   et::gemm_bf16_plan_conv(g.M, g.N, g.K, &g.tile, &g.split_k, fixed_sums);
   g.partials = c->gemm_partials;
   if (et::gemm_bf16_partial_elems(g.M, g.N, g.split_k) > c->gemm_partial_elems) g.split_k = 1;

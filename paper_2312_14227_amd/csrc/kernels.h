@@ -80,6 +80,11 @@ constexpr int CONV_TILE_HALO = 31;
 bool conv_halo_takes(const GemmDesc& d);
 bool conv_halo_pays(const GemmDesc& d);
 hipError_t conv_halo(const GemmDesc& d, hipStream_t s);
+// the same with many channels on small images (conv_raster.hip)
+constexpr int CONV_TILE_RASTER = 33, CONV_TILE_RASTER_256 = 35;   // 128 or 256 positions per workgroup
+bool conv_raster_takes(const GemmDesc& d);
+int conv_raster_tile(GemmDesc d);   // the tile id where this kernel is to be used, without a split; else 0
+hipError_t conv_raster(const GemmDesc& d, hipStream_t s);
 
 // returns hipSuccess, or hipErrorInvalidValue when a requirement above is violated
 // *launches (nullable) receives the number of kernels launched (1, or 2 with split-K)
