@@ -11,6 +11,7 @@ the roofline of the dominant kernel (bf16 MFMA GEMM) measured with HIP events in
 and the fp64 CPU oracle timed on a bounded sample of the same workload.
 """
 import argparse
+import gc
 import json
 import os
 import sys
@@ -29,6 +30,7 @@ GEMM_CLASS_NAMES = {0: "gemm_bf16_kernel<forward X*W^T>", 1: "gemm_bf16_kernel<p
 
 def timed_steps(s, xt, yt, mask, make_opt_fn, n, first_step):
     import torch
+    gc.collect()   # what has piled up, in front of the timed region: one collection of 25 - 45 ms would fall into some step of a long loop
     torch.cuda.synchronize()
     t0 = time.perf_counter()
     for i in range(n):
