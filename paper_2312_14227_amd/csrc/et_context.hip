@@ -4,10 +4,11 @@
 //
 // The backward pass is the loop of the tensor-level time model:
 //     for j = N-1 .. j*:   if M[j]: dw(j);    if j > j*: dy(j)
-// with j* the input-most selected tensor.  dw(j) and dy(j) are separate kernel launches, so the
+// with j* the input-most selected tensor.  dw(j) and dy(j) are separate pieces of work, so the
 // time of a masked step is the sum of the times of the launched pieces, which is what the
 // selector's time model assumes; where one launch produces several pieces (the column sums of biases, gains and shifts ride
-// on the kernels that read or write the gradient anyway), the profile divides its time by what each adds to it.  Backward kernels of operations without weights (ReLU, GELU, the
+// on the kernels that read or write the gradient anyway; the weight gradients of a transformer, of ResNet and of MobileNet run in groups at the end
+// of the pass), the profile divides its time by what each adds to it.  Backward kernels of operations without weights (ReLU, GELU, the
 // attention core, residual additions) sit in the dy() of the tensor that has to be passed for them
 // to be needed; a LayerNorm's input-gradient kernel sits in dy(gain).
 #include "context.h"
