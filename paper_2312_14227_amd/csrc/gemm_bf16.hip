@@ -410,8 +410,7 @@ hipError_t gemm_bf16(const GemmDesc& d, hipStream_t s, int* launches) {
                           (d.mode == EPI_RELU_MASK && (!d.U || !aligned(d.U, 8))) || (d.mode == EPI_BIAS_RELU && !d.bias)))
       return hipErrorInvalidValue;
   }
-  if (d.tile == CONV_TILE_HALO || d.tile == CONV_TILE_RASTER || d.tile == CONV_TILE_RASTER_256) {
-    if (!conv || conv_dw || stem) return hipErrorInvalidValue;
+  if (conv && !conv_dw && !stem && (d.tile == CONV_TILE_HALO || d.tile == CONV_TILE_RASTER || d.tile == CONV_TILE_RASTER_256)) {
     const hipError_t e = d.tile == CONV_TILE_HALO ? conv_halo(d, s) : conv_raster(d, s);   // (each checks its own requirements)
     if (e == hipSuccess && launches) *launches = 1;
     return e;
