@@ -181,87 +181,87 @@ __global__ __launch_bounds__(512) void conv_raster_kernel(RasterParams g) {
   // add the quarters: first with quarter kq ^ 2, halves of the positions exchanged, then with kq ^ 1, halves of the channels
   block_barrier();
   {
-  constexpr int HALF = MI / 2;
-  const int mq = kq >> 1, ni = kq & 1;   // this wave is left with the positions' half mq, the channels' half ni
-  int e_tid = tid;   // (lane-dependent values below are not kept in registers through the loop)
-  asm volatile("" : "+v"(e_tid));
-  const int lane = e_tid & 63, l32 = lane & 31, khalf = lane >> 5;
-  const auto put = [&](unsigned char* at, const f32x16& v) {
+    constexpr int HALF = MI / 2;
+    const int mq = kq >> 1, ni = kq & 1;   // this wave is left with the positions' half mq, the channels' half ni
+    int e_tid = tid;   // (lane-dependent values below are not kept in registers through the loop)
+    asm volatile("" : "+v"(e_tid));
+    const int lane = e_tid & 63, l32 = lane & 31, khalf = lane >> 5;
+    const auto put = [&](unsigned char* at, const f32x16& v) {
 #pragma unroll
-    for (int q = 0; q < 4; q++) *(float4*)(at + q * 1024 + lane * 16) = make_float4(v[q * 4], v[q * 4 + 1], v[q * 4 + 2], v[q * 4 + 3]);
-  };
-  const auto add = [&](const unsigned char* at, f32x16& v) {
+      for (int q = 0; q < 4; q++) *(float4*)(at + q * 1024 + lane * 16) = make_float4(v[q * 4], v[q * 4 + 1], v[q * 4 + 2], v[q * 4 + 3]);
+    };
+    const auto add = [&](const unsigned char* at, f32x16& v) {
 #pragma unroll
-    for (int q = 0; q < 4; q++) {
-      const float4 t = *(const float4*)(at + q * 1024 + lane * 16);
-      v[q * 4] += t.x; v[q * 4 + 1] += t.y; v[q * 4 + 2] += t.z; v[q * 4 + 3] += t.w;
-    }
-  };
-  f32x16 keep[HALF][2], sum[HALF];
-#pragma unroll
-  for (int m = 0; m < HALF; m++)
-#pragma unroll
-    for (int n = 0; n < 2; n++) {
-      put(smem + ((wave * HALF + m) * 2 + n) * 4096, mq ? acc[m][n] : acc[HALF + m][n]);
-      keep[m][n] = mq ? acc[HALF + m][n] : acc[m][n];
-    }
-  __builtin_amdgcn_s_waitcnt(0xc07f);
-  block_barrier();
-  unsigned char* mine = smem + (wave ^ 2) * HALF * 8192;   // read by this wave alone from here on
-#pragma unroll
-  for (int m = 0; m < HALF; m++) {
-#pragma unroll
-    for (int n = 0; n < 2; n++) add(mine + (m * 2 + n) * 4096, keep[m][n]);
-    put(mine + m * 8192, ni ? keep[m][0] : keep[m][1]);
-    sum[m] = ni ? keep[m][1] : keep[m][0];
-  }
-  __builtin_amdgcn_s_waitcnt(0xc07f);
-  block_barrier();
-#pragma unroll
-  for (int m = 0; m < HALF; m++) add(smem + ((wave ^ 1) ^ 2) * HALF * 8192 + m * 8192, sum[m]);
-
-  // 32 positions x 32 channels at a time: lane l32 holds a position's channels q * 8 + khalf * 4 + 0..3; through LDS (rows of 64 bytes, chunk c at
-  // c ^ ((row >> 2) & 3)) to rows of channels
-  unsigned char* area = mine + 4096;
-  const int col = n0 + ni * 32, c8 = (lane & 3) * 8;
-#pragma unroll
-  for (int m = 0; m < HALF; m++) {
-#pragma unroll
-  for (int q = 0; q < 4; q++) {
-    bf16x4 o, b = {};
-    if (EPI == E_BIAS_RELU) b = *(const bf16x4*)(g.bias + col + q * 8 + khalf * 4);
-#pragma unroll
-    for (int j = 0; j < 4; j++) {
-      const float v = sum[m][q * 4 + j];
-      o[j] = (bf16)(EPI == E_BIAS_RELU ? fmaxf(v + (float)b[j], 0.f) : v);
-    }
-    *(bf16x4*)(area + l32 * 64 + ((q ^ ((l32 >> 2) & 3)) << 4) + khalf * 8) = o;
-  }
-#pragma unroll
-  for (int it = 0; it < 2; it++) {
-    const int row = it * 16 + (lane >> 2);
-    bf16x8 v = *(const bf16x8*)(area + row * 64 + (((lane & 3) ^ ((row >> 2) & 3)) << 4));
-    int img, y, x;
-    locate(s0 + mh * (BM / 2) + (mq * HALF + m) * 32 + row, img, y, x);
-    if (y >= g.H || x >= g.W || img0 + img >= g.images) continue;
-    const long long at = (((long long)(img0 + img) * g.H + y) * g.W + x) * g.N + col + c8;
-    if (EPI == E_AFFINE) {
-      const bf16x8 gain = *(const bf16x8*)(g.gain + col + c8), shift = *(const bf16x8*)(g.bias + col + c8);
-      bf16x8 yv;
-#pragma unroll
-      for (int j = 0; j < 8; j++) yv[j] = (bf16)fminf(fmaxf((float)v[j] * (float)gain[j] + (float)shift[j], g.lo), g.hi);
-      if (g.out) *(bf16x8*)(g.out + at) = v;
-      *(bf16x8*)(g.out2 + at) = yv;
-    } else {
-      if (EPI == E_RELU_MASK) {
-        const bf16x8 u = *(const bf16x8*)(g.U + at);
-#pragma unroll
-        for (int j = 0; j < 8; j++) v[j] = ((float)u[j] > 0.f && (float)u[j] < g.mask_hi) ? v[j] : (bf16)0.f;
+      for (int q = 0; q < 4; q++) {
+        const float4 t = *(const float4*)(at + q * 1024 + lane * 16);
+        v[q * 4] += t.x; v[q * 4 + 1] += t.y; v[q * 4 + 2] += t.z; v[q * 4 + 3] += t.w;
       }
-      *(bf16x8*)(g.out + at) = v;
+    };
+    f32x16 keep[HALF][2], sum[HALF];
+#pragma unroll
+    for (int m = 0; m < HALF; m++)
+#pragma unroll
+      for (int n = 0; n < 2; n++) {
+        put(smem + ((wave * HALF + m) * 2 + n) * 4096, mq ? acc[m][n] : acc[HALF + m][n]);
+        keep[m][n] = mq ? acc[HALF + m][n] : acc[m][n];
+      }
+    __builtin_amdgcn_s_waitcnt(0xc07f);
+    block_barrier();
+    unsigned char* mine = smem + (wave ^ 2) * HALF * 8192;   // read by this wave alone from here on
+#pragma unroll
+    for (int m = 0; m < HALF; m++) {
+#pragma unroll
+      for (int n = 0; n < 2; n++) add(mine + (m * 2 + n) * 4096, keep[m][n]);
+      put(mine + m * 8192, ni ? keep[m][0] : keep[m][1]);
+      sum[m] = ni ? keep[m][1] : keep[m][0];
     }
-  }
-  }
+    __builtin_amdgcn_s_waitcnt(0xc07f);
+    block_barrier();
+#pragma unroll
+    for (int m = 0; m < HALF; m++) add(smem + ((wave ^ 1) ^ 2) * HALF * 8192 + m * 8192, sum[m]);
+
+    // 32 positions x 32 channels at a time: lane l32 holds a position's channels q * 8 + khalf * 4 + 0..3; through LDS (rows of 64 bytes, chunk c at
+    // c ^ ((row >> 2) & 3)) to rows of channels
+    unsigned char* area = mine + 4096;
+    const int col = n0 + ni * 32, c8 = (lane & 3) * 8;
+#pragma unroll
+    for (int m = 0; m < HALF; m++) {
+#pragma unroll
+      for (int q = 0; q < 4; q++) {
+        bf16x4 o, b = {};
+        if (EPI == E_BIAS_RELU) b = *(const bf16x4*)(g.bias + col + q * 8 + khalf * 4);
+#pragma unroll
+        for (int j = 0; j < 4; j++) {
+          const float v = sum[m][q * 4 + j];
+          o[j] = (bf16)(EPI == E_BIAS_RELU ? fmaxf(v + (float)b[j], 0.f) : v);
+        }
+        *(bf16x4*)(area + l32 * 64 + ((q ^ ((l32 >> 2) & 3)) << 4) + khalf * 8) = o;
+      }
+#pragma unroll
+      for (int it = 0; it < 2; it++) {
+        const int row = it * 16 + (lane >> 2);
+        bf16x8 v = *(const bf16x8*)(area + row * 64 + (((lane & 3) ^ ((row >> 2) & 3)) << 4));
+        int img, y, x;
+        locate(s0 + mh * (BM / 2) + (mq * HALF + m) * 32 + row, img, y, x);
+        if (y >= g.H || x >= g.W || img0 + img >= g.images) continue;
+        const long long at = (((long long)(img0 + img) * g.H + y) * g.W + x) * g.N + col + c8;
+        if (EPI == E_AFFINE) {
+          const bf16x8 gain = *(const bf16x8*)(g.gain + col + c8), shift = *(const bf16x8*)(g.bias + col + c8);
+          bf16x8 yv;
+#pragma unroll
+          for (int j = 0; j < 8; j++) yv[j] = (bf16)fminf(fmaxf((float)v[j] * (float)gain[j] + (float)shift[j], g.lo), g.hi);
+          if (g.out) *(bf16x8*)(g.out + at) = v;
+          *(bf16x8*)(g.out2 + at) = yv;
+        } else {
+          if (EPI == E_RELU_MASK) {
+            const bf16x8 u = *(const bf16x8*)(g.U + at);
+#pragma unroll
+            for (int j = 0; j < 8; j++) v[j] = ((float)u[j] > 0.f && (float)u[j] < g.mask_hi) ? v[j] : (bf16)0.f;
+          }
+          *(bf16x8*)(g.out + at) = v;
+        }
+      }
+    }
   }
 }
 
