@@ -78,6 +78,9 @@ size_t et_debug_stem_ws_bytes(int batch, int H, int W, int C, int N);
 int et_debug_stem(int op, const void* x, const void* w_or_d, float* out, void* ws, int batch, int H, int W, int C, int N,
                   void* stream);
 
+/* Chunks that the reduction of a weight gradient [M][N] over K rows is cut into (no device needed); 0 for a rejected argument. */
+int et_debug_dw_chunks(int M, int N, int K);
+
 /* Weight gradients in a group, as at the end of a backward pass: C[i] fp32 [M][N] = sum over K rows of A[i][k][m] B[i][k][n], bf16, rows padded to
  * multiples of 8.  shape: per job M, N, K, split (chunks of the reduction) and, for a convolution's gradient with B[i] the NHWC activation, H, W, C,
  * taps, stride (C = 0: plain).  partials: device, split * M * N floats of every split job, in all at most partial_elems.  Host arrays of

@@ -374,6 +374,13 @@ extern "C" int et_debug_copy(void* dst, const void* src, size_t bytes, void* str
   return hipGetLastError() == hipSuccess ? ET_OK : ET_EHIP;
 }
 
+extern "C" int et_debug_dw_chunks(int M, int N, int K) {
+  if (M < 1 || N < 1 || K < 1) return 0;
+  int tile, split;
+  et::gemm_bf16_plan_split(M, N, K, &tile, &split);
+  return split;
+}
+
 extern "C" int et_debug_dw_group(int n, const void* const* A, const void* const* B, float* const* C, const int* shape, float* partials, size_t partial_elems,
                                  void* stream) {
   if (n < 1 || n > et::DW_GROUP_MAX || !A || !B || !C || !shape || !partials) return ET_EINVAL;

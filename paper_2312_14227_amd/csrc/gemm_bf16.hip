@@ -116,10 +116,10 @@ int compute_units() {
 
 inline bool aligned(const void* p, uintptr_t a) { return (reinterpret_cast<uintptr_t>(p) & (a - 1)) == 0; }
 
-// Cost model behind the tile and split choice for large problems (seconds, one launch):
+// Cost model behind the tile and split choice of the gathered convolutions and the chunks of large weight gradients (seconds, one launch):
 //   rounds of workgroups over the 256 CUs x time of one workgroup at the rate a CU sustains with
-//   that tile (measured on the ViT shapes: about 3.3 TFLOP/s per CU with the 256x256 two-group
-//   tile, 3.0 with 256x192), plus, for a split reduction, writing and re-reading the fp32 partials.
+//   that tile (about 3.3 TFLOP/s per CU with 256x256 through registers, 3.0 with 256x192), plus, for a split
+//   reduction, writing and re-reading the fp32 partials.
 struct Plan { int tile, split; double cost; };
 
 struct TileRate { int tile, bm, bn; double rate; };
@@ -261,30 +261,44 @@ int choose_large_tile(const GemmDesc& d, int K) {
   return best;
 }
 
-// Weight gradients [M][N] over K rows of 4 GFLOP and more.  The split is a function of the shape alone, so that a gradient has the same bits
-// whichever others are computed: chunks of about 66 slices.  Most gradients run in a group (dw_group), which fills the chip without a split;
-// what the chunks are for is a gradient on its own, or in a small group, and rounds of even length there.  [3072 x 768] over 12608 rows
-// alone: unsplit 127 us, 2 chunks 107, 3 chunks 84, 5 chunks 70; all 48 gradients of such a transformer write 1.0 GB of partial sums with 3.
-// Tile: the least estimated time (us) with that split.  As above, with the partials' traffic and the second launch; the time per slice of a ring
-// tile grows with the length of its chunk (its operand re-reads).  Fitted to 85 shapes of [384 .. 4096] x [384 .. 1024] over 1576 .. 17000 rows
-// with up to a dozen plans each (relative error 5 - 8 %).
-Plan plan_dw(int M, int N, int K) {
+// Chunks of a weight gradient's reduction [M][N] over K rows, from the shape alone: they fix the order of the sums, and so a gradient's bits, whichever
+// kernel runs it, alone or in a group.  The error of an fp32 sum grows with the length of its chunk: against 64 bits (2-norms), [2304 x 768] over
+// 12608 rows 2.6e-7 with these 7 chunks and 4.0e-7 with 3, [2304 x 768] over 6304 1.7e-7 with 8 and 3.4e-7 with 2, twice to three times as much
+// where the activations have a mean.  3 chunks would write less: a full step of 12 such blocks takes 10.24 ms with 3, 10.53 ms with these.
+// 16 GFLOP and more: over a multiple of 64 rows the least of rounds of 256 x 256 or 256 x 192 tiles and the partials' traffic; over a multiple of
+// 32, about 256 tiles in all and at most 8 chunks.  Else the plan of the ring tiles.
+int split_of_dw(int M, int N, int K) {
+  if (M >= 256 && N >= 256 && 2.0 * M * N * (double)K >= 1.6e10) {
+    static const TileRate cand[2] = {{T_AUTO, 256, 256, 3.3e12}, {T_AUTO, 256, 192, 3.0e12}};
+    if ((K % gemm::PBK) == 0) return plan_tiles(M, N, K, (N & 3) == 0, cand, 2).split;
+    if ((K % gemm::DBK) == 0 && K >= 128 * gemm::DBK) {
+      const int slices = (K + gemm::PBK - 1) / gemm::PBK, tiles = ((M + 255) / 256) * ((N + 255) / 256);
+      const int wanted = (N & 3) == 0 ? std::max(1, std::min(8, 256 / tiles)) : 1, per = (slices + wanted - 1) / wanted;
+      return (slices + per - 1) / per;   // (no empty chunks)
+    }
+  }
+  return plan_ring(M, N, K, true, ((double)M + N) * K, kRingDw).split;
+}
+
+// Tile of a weight gradient of 4 GFLOP and more that runs by itself, in those chunks: the least estimated time (us).  As above, with the
+// partials' traffic and the second launch; the time per slice of a ring tile grows with the length of its chunk (its operand re-reads).  Fitted to
+// 85 shapes of [384 .. 4096] x [384 .. 1024] over 1576 .. 17000 rows with up to a dozen plans each (relative error 5 - 8 %).
+int tile_of_dw(int M, int N, int K, int split) {
   struct Cand { int tile, bm, bn; double slice, slice2, load, solo, fixed, once, part, elem, split, rounds2; };
   static const Cand cand[5] = {{T_DIRECT_256x256, 256, 256, 0.833, 0.0, 0.696, 0.0, 5.38, 5.92, 0.880e-6, 0.0, 0.0, 0.0},
                                {T_DIRECT_192x256, 192, 256, 0.841, 0.0, 0.419, 0.0, 3.84, 4.65, 0.890e-6, 0.0, 1.80, 0.0},
                                {T_DIRECT_128x256, 128, 256, 0.765, 0.0, 0.304, 0.0, 2.35, 5.45, 0.744e-6, 0.0, 2.41, 0.0},
                                {T_RING_64x128, 64, 128, 0.179, 0.00069, 0.0, 0.0, 0.0, 5.61, 1.377e-6, 0.750e-6, 2.53, 0.0228},
                                {T_RING_64x64, 64, 64, 0.116, 0.00047, 0.0, 0.0179, 0.0, 5.95, 1.581e-6, 0.189e-6, 1.00, 0.0122}};
-  const int slices = (K + gemm::PBK - 1) / gemm::PBK;
-  const int wanted = (N & 3) == 0 ? std::max(1, std::min(256, (slices + 33) / 66)) : 1;
-  const int per = (slices + wanted - 1) / wanted, split = (slices + per - 1) / per;   // (no empty chunks)
-  Plan best = {T_RING_64x128, split, 1e30};
+  const int slices = (K + gemm::PBK - 1) / gemm::PBK, per = (slices + split - 1) / split;
+  int best = T_RING_64x128;
+  double least = 1e30;
   for (const Cand& c : cand) {
     const double units = (double)((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn) * split, elems = (double)M * N, rounds = std::ceil(units / 256.0);
     double t = rounds * (per * (c.slice + c.slice2 * per + c.load * units / rounds / 256.0 + c.rounds2 * rounds) + c.fixed) + c.once + c.elem * elems;
     if (rounds == 1.0) t += c.solo * per;
     if (split > 1) t += c.part * split * elems + c.split;
-    if (t < best.cost) best = {c.tile, split, t};
+    if (t < least) { least = t; best = c.tile; }
   }
   return best;
 }
@@ -346,15 +360,9 @@ void gemm_bf16_plan_conv_dw(int M, int N, int K, int* tile, int* split_k, int ta
 void gemm_bf16_plan_split(int M, int N, int K, int* tile, int* split_k) {
   *tile = T_AUTO;
   *split_k = 1;
-  if (2.0 * M * N * (double)K >= 4e9 && M >= 256 && N >= 256 && K >= 4 * gemm::PBK) {
-    const Plan pl = plan_dw(M, N, K);
-    *tile = pl.tile;
-    *split_k = pl.split;
-  } else {   // everything else runs on the ring tile, any K
-    const Plan pl = plan_ring(M, N, K, true, ((double)M + N) * K, kRingDw);
-    *split_k = pl.split;
-    if (pl.split > 1) *tile = pl.tile;   // (unsplit: whichever tile choose_tile prefers)
-  }
+  *split_k = split_of_dw(M, N, K);
+  if (2.0 * M * N * (double)K >= 4e9 && M >= 256 && N >= 256 && K >= 4 * gemm::PBK) *tile = tile_of_dw(M, N, K, *split_k);
+  else if (*split_k > 1) *tile = plan_ring(M, N, K, true, ((double)M + N) * K, kRingDw).tile;   // (unsplit: whichever tile choose_tile prefers)
 }
 
 hipError_t gemm_bf16(const GemmDesc& d, hipStream_t s, int* launches) {
