@@ -30,6 +30,10 @@ int et_debug_gemm_bf16(const void* A, const void* B, void* C, int M, int N, int 
 int et_debug_gemm_bf16_colsum(const void* A, const void* B, void* C, const void* aux, float* colsum, int M, int N, int K, int lda, int ldb, int ldc,
                               int tile, void* stream);
 
+/* Tile id that et_debug_gemm_bf16 takes for tile 0 without a split (no device needed); epilogue, a_t, b_t, c_f32 as there, residual: whether there is
+ * one.  0 for a rejected argument. */
+int et_debug_gemm_tile(int M, int N, int K, int a_t, int b_t, int c_f32, int residual, int epilogue);
+
 /* 3x3 / stride 1 / zero padding 1 convolution as an implicit GEMM (the im2col matrix of Section 5.1's
  * convolution kernels is never written): out[b][h][w][n] = sum over (ky, kx, c) of
  * x[b][h+ky-1][w+kx-1][c] * w[n][ky][kx][c].  x bf16 NHWC [batch][H][W][C], C a multiple of 64; w bf16

@@ -36,6 +36,17 @@ extern "C" int et_debug_gemm_bf16_colsum(const void* A, const void* B, void* C, 
   return e == hipSuccess ? ET_OK : ET_EHIP;
 }
 
+extern "C" int et_debug_gemm_tile(int M, int N, int K, int a_t, int b_t, int c_f32, int residual, int epilogue) {
+  if (M < 1 || N < 1 || K < 1 || epilogue < 0 || epilogue > 3) return 0;
+  et::GemmDesc g;
+  float there;
+  g.M = M; g.N = N; g.K = K; g.a_t = a_t != 0; g.b_t = b_t != 0; g.c_f32 = c_f32 != 0;
+  g.lda = ((g.a_t ? M : K) + 7) & ~7; g.ldb = ((g.b_t ? N : K) + 7) & ~7; g.ldc = N;
+  g.residual = residual ? &there : nullptr;
+  g.mode = epilogue == 1 ? et::EPI_GELU_FWD : epilogue == 2 ? et::EPI_GELU_BWD : epilogue == 3 ? et::EPI_GELU_ONLY : et::EPI_PLAIN;
+  return et::gemm_bf16_tile(g);
+}
+
 extern "C" int et_debug_conv3x3(const void* x, const void* w, void* out, int batch, int H, int W, int C, int N,
                                 const void* bias, const void* U, int mode, int tile, void* stream) {
   et::GemmDesc g;

@@ -233,15 +233,17 @@ const RingTile kRingConvDw[3] = {{T_RING_64x64, 64, 64, 0.365e-6, 0.24e-6, 0.5e-
 
 // Large products with K in slices of 64: rounds of workgroups over the 256 CUs x (slices x time per slice + fixed part), us.  A slice takes longer the more
 // CUs are at work (`load` more with all of them: the clock follows the load); an epilogue with more arithmetic or with an fp32 residual adds per
-// round, a residual its memory traffic.  Fitted (relative error 3 - 5 %) to 161 products of [1576 .. 17000 rows] x [384 .. 4096] x [512 .. 4096]: those of 8 GFLOP
-// and more take 8656 us with this choice, the best tile of each 8641, and took 9877 with the tiles through registers (256x256, 256x192,
-// 256x128) that the direct ones replace: [12608 x 3072 x 768] 78 -> 68 us, with GELU 106 -> 94, [12608 x 768 x 3072] 73 -> 62, with
-// residual 92 -> 73, [9000 x 4096 x 1024] 92 -> 76.  Between 6 and 8 GFLOP 444 -> 431, below nothing.
+// round, a residual its memory traffic.  Fitted (relative error 3 - 5 %) to 161 products of [1576 .. 17000 rows] x [384 .. 4096] x [512 .. 4096]; the
+// epilogues' terms of the direct tiles corrected by 140 others with six epilogues each, [724 .. 12600 rows] x [256 .. 4096] x [256 .. 4096], 8 GFLOP
+// and more: 26.4 ms with this choice, 26.4 the best tile of each, 28.7 with the tiles through registers (256x256, 256x192, 256x128) that the
+// direct ones replace, no product more than 3 % behind what it took with those: [12608 x 3072 x 768] 78 -> 68 us, with GELU 106 -> 94,
+// [12608 x 768 x 3072] 73 -> 62, with residual 92 -> 73.  Between 6 and 8 GFLOP it would be 0.99x in the sum and 0.8x for tall reductions
+// ([1377 x 640 x 4032] 18.1 -> 22.5): those stay with plan_small.
 int choose_large_tile(const GemmDesc& d, int K) {
   struct Cand { int tile, bm, bn; double slice, load, rounds2, fixed, once, gelu, gelu_back, res, res_elem, elem; };
-  static const Cand cand[5] = {{T_DIRECT_256x256, 256, 256, 0.870, 0.525, 0.0, 2.79, 3.68, 8.31, 2.56, 3.39, 0.632e-6, 0.238e-6},
-                               {T_DIRECT_192x256, 192, 256, 0.686, 0.536, 0.0, 3.48, 2.62, 6.68, 2.15, 2.20, 0.679e-6, 0.110e-6},
-                               {T_DIRECT_128x256, 128, 256, 0.644, 0.345, 0.0, 2.92, 2.41, 4.66, 1.74, 1.39, 0.785e-6, 0.041e-6},
+  static const Cand cand[5] = {{T_DIRECT_256x256, 256, 256, 0.870, 0.525, 0.0, 2.79, 3.68, 9.81, 3.56, 3.99, 0.632e-6, 0.238e-6},
+                               {T_DIRECT_192x256, 192, 256, 0.686, 0.536, 0.0, 3.48, 2.62, 8.18, 3.15, 2.80, 0.679e-6, 0.110e-6},
+                               {T_DIRECT_128x256, 128, 256, 0.644, 0.345, 0.0, 2.92, 2.41, 6.16, 2.74, 1.99, 0.785e-6, 0.041e-6},
                                {T_RING_64x128, 64, 128, 0.227, 0.092, 0.00065, 1.00, 3.90, 1.38, 0.02, 0.0, 0.640e-6, 0.0},
                                {T_RING_128x128, 128, 128, 0.431, 0.147, 0.0, 2.11, 2.14, 3.31, 0.0, 0.0, 0.715e-6, 0.317e-6}};
   const bool gelu = d.mode == EPI_GELU_FWD || d.mode == EPI_GELU_ONLY, gelu_back = d.mode == EPI_GELU_BWD;
@@ -316,11 +318,10 @@ int choose_tile(const GemmDesc& d, int k_per_block) {
   if (d.tile == T_PP_512x64 || d.tile == T_PP_128x256 || d.tile == T_PP_64x512) return slices_ok ? d.tile : T_128x128;
   if (d.tile == T_DMA_256x256 || d.tile == T_DMA_256x128) return dma_ok ? d.tile : T_128x128;
   if (d.tile != T_AUTO) return d.tile;
-  // large problems (6 GFLOP and more, with the epilogues of a folded BatchNorm 8; a ViT-L layer at batch 32 has 13): the tile with the least
-  // estimated time where K comes in slices of 64, else the direct-to-LDS tile with slices of 32.
+  // large problems (8 GFLOP and more; a ViT-L layer at batch 32 has 13): the tile with the least estimated time where K comes in
+  // slices of 64, else the direct-to-LDS tile with slices of 32.
   const int batch = d.z_outer * d.z_inner;
-  const bool affine = d.mode == EPI_AFFINE_RELU || d.mode == EPI_AFFINE_ADD_RELU;
-  if (d.M >= 512 && d.N >= 256 && 2.0 * d.M * d.N * (double)k_per_block * batch >= (affine ? 8e9 : 6e9)) {
+  if (d.M >= 512 && d.N >= 256 && 2.0 * d.M * d.N * (double)k_per_block * batch >= 8e9) {
     const long long big_tiles = (long long)((d.M + 255) / 256) * ((d.N + 255) / 256) * batch;
     if (direct_ok && k_per_block >= 4 * gemm::PBK) return choose_large_tile(d, k_per_block);
     if (dma_ok && k_per_block >= 4 * gemm::DBK && big_tiles >= 128) return d.N >= 2560 ? T_DMA_256x128 : T_DMA_256x256;
@@ -329,6 +330,8 @@ int choose_tile(const GemmDesc& d, int k_per_block) {
 }
 
 }  // namespace
+
+int gemm_bf16_tile(const GemmDesc& d) { return choose_tile(d, d.K); }
 
 size_t gemm_bf16_partial_elems(int M, int N, int split_k) { return split_k > 1 ? (size_t)M * N * split_k : 0; }
 

@@ -89,6 +89,8 @@ hipError_t conv_raster(const GemmDesc& d, hipStream_t s);
 // returns hipSuccess, or hipErrorInvalidValue when a requirement above is violated
 // *launches (nullable) receives the number of kernels launched (1, or 2 with split-K)
 hipError_t gemm_bf16(const GemmDesc& d, hipStream_t s, int* launches = nullptr);
+// tile id that a plain product without a split runs with
+int gemm_bf16_tile(const GemmDesc& d);
 // fp32 partial elements needed for a split-K call
 size_t gemm_bf16_partial_elems(int M, int N, int split_k);
 // tile and split for a weight gradient [M][N] reduced over K rows (a cost model over tile shapes
