@@ -539,10 +539,13 @@ hipError_t gemm_bf16(const GemmDesc& d, hipStream_t s, int* launches) {
     case T_DIRECT_128x256: BM = 128; BN = 256; fn = gemm::direct_128x256(d.a_t, d.b_t, epi); break;
     default: BM = 128; BN = 128; fn = gemm::staged_128x128(d.a_t, d.b_t, epi); resident = false; break;
   }
-  // a lone 64x64 tile per CU with a long reduction waits for memory, the more so where its operands are read for the first time: five slices in
-  // flight instead of three.  Weights from memory, [788 x 768 x 3072] 19.2 -> 14.2 us, x 2304 12.4 -> 10.8, x 1536 equal, x 768 6.1 -> 6.4;
-  // with two or more tiles per CU the LDS that it takes costs more than it gives ([788 x 3072 x 768] 12.4 -> 13.7)
-  if (fn && !conv && BM == 64 && BN == 64 && !resident && k_per_block >= 32 * gemm::PBK && (long long)((d.M + 63) / 64) * ((d.N + 63) / 64) * zdim <= 256) {
+  // a lone 64x64 tile per CU with a long reduction waits for memory: five slices in flight instead of three.  [788 x 768 x 3072] with weights
+  // from memory 14.3 -> 13.3 us, with both operands from memory 14.4 -> 13.3; the same times a transposed weight 13.6 -> 13.4 and 13.9 -> 13.3.
+  // At 32 slices 10.2 -> 10.2 and 10.6 -> 10.3, transposed 10.1 -> 10.3 and 10.4 -> 10.4, hence the later start there.  With both operands in
+  // the L2, which no pass over a model leaves, it costs 4 - 6 %; so does the LDS that it takes with two or more tiles per CU
+  // ([788 x 3072 x 768] 12.4 -> 13.7)
+  if (fn && !conv && BM == 64 && BN == 64 && !resident && k_per_block >= (d.b_t ? 48 : 32) * gemm::PBK &&
+      (long long)((d.M + 63) / 64) * ((d.N + 63) / 64) * zdim <= 256) {
     const gemm::LaunchFn deep = gemm::ring_64x64_deep(d.a_t, d.b_t, epi);
     if (deep) fn = deep;
   }
