@@ -33,6 +33,8 @@ int et_debug_gemm_bf16_colsum(const void* A, const void* B, void* C, const void*
 /* Tile id that et_debug_gemm_bf16 takes for tile 0 without a split (no device needed); epilogue, a_t, b_t, c_f32 as there, residual: whether there is
  * one.  0 for a rejected argument. */
 int et_debug_gemm_tile(int M, int N, int K, int a_t, int b_t, int c_f32, int residual, int epilogue);
+/* Tile id that the models take for the 3x3 / stride 1 convolution below, and the split of its reduction in *split (no device needed). */
+int et_debug_conv3x3_plan(int batch, int H, int W, int C, int N, int* split);
 
 /* 3x3 / stride 1 / zero padding 1 convolution as an implicit GEMM (the im2col matrix of Section 5.1's
  * convolution kernels is never written): out[b][h][w][n] = sum over (ky, kx, c) of

@@ -76,6 +76,7 @@ def _load():
         "et_debug_gemm_bf16_colsum": (C.c_int, [vp] * 5 + [C.c_int] * 7 + [vp]),
         "et_debug_conv_first": (C.c_int, [vp] * 6 + [C.c_int] * 6 + [C.c_float] * 2 + [vp]),
         "et_debug_gemm_tile": (C.c_int, [C.c_int] * 8),
+        "et_debug_conv3x3_plan": (C.c_int, [C.c_int] * 5 + [C.POINTER(C.c_int)]),
         "et_debug_dw_chunks": (C.c_int, [C.c_int] * 3),
         "et_debug_dw_group": (C.c_int, [C.c_int, C.POINTER(vp), C.POINTER(vp), C.POINTER(vp), C.POINTER(C.c_int), vp, C.c_size_t, vp]),
         "et_debug_flip3x3": (C.c_int, [C.POINTER(vp), C.POINTER(vp), C.POINTER(C.c_int), C.POINTER(C.c_int), C.c_int, vp]),
@@ -102,7 +103,7 @@ _lib = _load()
 EXPORTS = ["et_create", "et_destroy", "et_num_tensors", "et_tensor_info", "et_workspace_bytes", "et_state_slots",
            "et_bind", "et_profile", "et_importance", "et_importance_master", "et_importance_reduce_static", "et_select", "et_select_stats", "et_tensor_metric", "et_train_step", "et_last_launch_counts",
            "et_kernel_timing", "et_kernel_timing_read", "et_kernel_timing_overhead", "et_last_hip_error", "et_strerror", "et_debug_gemm_bf16", "et_debug_copy", "et_debug_mfma_peak", "et_debug_conv3x3",
-           "et_debug_conv3x3_dw", "et_debug_depthwise3x3", "et_debug_depthwise3x3_ws_floats", "et_debug_affine_back", "et_debug_affine_back_ws_floats", "et_debug_flip3x3", "et_debug_dw_chunks", "et_debug_gemm_tile", "et_debug_dw_group", "et_debug_conv_first",
+           "et_debug_conv3x3_dw", "et_debug_depthwise3x3", "et_debug_depthwise3x3_ws_floats", "et_debug_affine_back", "et_debug_affine_back_ws_floats", "et_debug_flip3x3", "et_debug_dw_chunks", "et_debug_gemm_tile", "et_debug_conv3x3_plan", "et_debug_dw_group", "et_debug_conv_first",
            "et_debug_activation", "et_debug_conv3x3_split", "et_debug_attention", "et_debug_attention_long", "et_debug_attention_long_rest", "et_debug_gemm_bf16_colsum",
            "et_debug_conv_gathered", "et_debug_stem", "et_debug_stem_ws_bytes"]
 
@@ -366,6 +367,12 @@ def et_debug_conv_first(x, w, gain, shift, z, y, batch, H, W, Cin, N, stride, lo
 
 def et_debug_gemm_tile(M, N, K, a_t=0, b_t=0, c_f32=0, residual=0, epilogue=0):
     return _lib.et_debug_gemm_tile(M, N, K, a_t, b_t, c_f32, residual, epilogue)
+
+
+def et_debug_conv3x3_plan(batch, H, W, Cin, N):
+    """(tile id, split)"""
+    split = C.c_int(0)
+    return _lib.et_debug_conv3x3_plan(batch, H, W, Cin, N, C.byref(split)), split.value
 
 
 def et_debug_dw_chunks(M, N, K):

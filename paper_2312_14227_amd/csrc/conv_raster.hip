@@ -304,14 +304,18 @@ bool conv_raster_takes(const GemmDesc& d) {
 }
 
 // Where this kernel is the faster one: its tiles fill the chip once.  Every further round costs the latency of its first window and the addition of the
-// quarters again, and a single tile per CU has to make up for both.  Measured against the gathered products, us: 128-position tiles, 52 tiles of
-// [13 x 13 x 256] 12.2 / 12.1, 64 of [7 x 7 x 512] 19.6 / 17.0, 122 of [50 x 50 x 64] 7.7 / 7.8, 128 of [7 x 7 x 512] 19.7 / 24.2, 153 of
-// [56 x 56 x 64] 8.1 / 9.7, 228 of [14 x 14 x 256] 13.7 / 20.1, but 284 24.4 / 20.1; 256-position tiles: 211 of [28 x 28 x 128] 16.1 / 19.0, 228 of
-// [14 x 14 x 512] 37.2 / 42.8, but 142 of [14 x 14 x 256] 20.5 / 20.1.
+// quarters again, and a single tile per CU has to make up for both: 128-position tiles, 52 tiles of [13 x 13 x 256] 12.2 us against 12.1 of the
+// gathered products, 64 of [7 x 7 x 512] 19.6 / 17.0, but 128 of [7 x 7 x 512] 19.7 / 24.2, 228 of [14 x 14 x 256] 13.7 / 20.1, and 284 again
+// 24.4 / 20.1; 256-position tiles: 211 of [28 x 28 x 128] 16.1 / 19.0, 228 of [14 x 14 x 512] 37.2 / 42.8, but 142 of [14 x 14 x 256] 20.5 / 20.1.
+// At most 512 channels: the gathered products split longer reductions, and are then the faster ones up to 190 tiles (128 tiles of [7 x 7 x 1024] 32.9 /
+// 29.7, [4 x 4 x 1024] 33.3 / 25.9) and the more precise ones (chains of 144 products of 16 against 96: a tenth more roundings to the wrong
+// neighbour of a bf16 result; at 512 channels a fifth fewer).  Over 370 shapes of 4 x 4 .. 60 x 60 pixels, 64 .. 512 channels and 1 .. 128 images that
+// this rule takes, time against the gathered products' by reduction and tiles: 1 chunk of 64 channels 0.83 - 0.93, 2 chunks 0.75 - 0.86, 4 and 8
+// chunks 0.66 - 0.86 in the mean; the worst 1.03.
 int conv_raster_tile(GemmDesc d) {
   d.split_k = 1;
   d.tile = CONV_TILE_RASTER;
-  if (!conv_raster_takes(d)) return 0;
+  if (d.conv_c > 512 || !conv_raster_takes(d)) return 0;
   const long long small = raster_units(d, 2), large = raster_units(d, 4);
   if (small <= 256) return small >= 128 ? CONV_TILE_RASTER : 0;
   d.tile = CONV_TILE_RASTER_256;

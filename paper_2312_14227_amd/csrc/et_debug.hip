@@ -47,6 +47,22 @@ extern "C" int et_debug_gemm_tile(int M, int N, int K, int a_t, int b_t, int c_f
   return et::gemm_bf16_tile(g);
 }
 
+extern "C" int et_debug_conv3x3_plan(int batch, int H, int W, int C, int N, int* split) {
+  if (!split || batch < 1 || H < 1 || W < 1 || C < 1 || N < 1 || (long long)batch * H * W > 0x7fffffffll) return 0;
+  alignas(16) static et::bf16 there[8];   // (the rules look at alignment, not at what is there)
+  et::GemmDesc g;
+  g.A = g.B = there; g.C = there;
+  g.M = batch * H * W; g.N = N; g.K = 9 * C; g.lda = g.ldb = 9 * C; g.ldc = N;
+  g.conv_h = H; g.conv_w = W; g.conv_c = C;
+  g.tile = et::conv_raster_tile(g);
+  if (!g.tile) {
+    et::gemm_bf16_plan_conv(g.M, g.N, g.K, &g.tile, &g.split_k);
+    if (et::conv_halo_pays(g)) g.tile = et::CONV_TILE_HALO;
+  }
+  *split = g.split_k;
+  return g.tile;
+}
+
 extern "C" int et_debug_conv3x3(const void* x, const void* w, void* out, int batch, int H, int W, int C, int N,
                                 const void* bias, const void* U, int mode, int tile, void* stream) {
   et::GemmDesc g;

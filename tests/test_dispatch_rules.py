@@ -1,10 +1,11 @@
-"""Which kernel a product takes, at sizes on either side of the rules' lines where the other choice was measured to be the slower one.
-Host code only."""
+"""Which kernel a product or convolution takes, at sizes on either side of the rules' lines where the other choice was measured to be the slower one
+(or, for long reductions of convolutions, the less precise one).  Host code only."""
 import pytest
 
 from paper_2312_14227_amd import binding as et
 
 DIRECT, RING = {11, 13, 15}, {23, 25, 29}
+RASTER = {33, 35}
 
 
 @pytest.mark.parametrize("M,N,K,kw,allowed", [
@@ -20,3 +21,12 @@ DIRECT, RING = {11, 13, 15}, {23, 25, 29}
 ])
 def test_products(M, N, K, kw, allowed):
     assert et.et_debug_gemm_tile(M, N, K, **kw) in allowed
+
+
+@pytest.mark.parametrize("batch,side,C,raster", [
+    (16, 7, 1024, False), (36, 4, 1024, False), (48, 7, 1024, False), (28, 7, 1024, False), (8, 14, 576, False),
+    (32, 7, 512, True), (32, 14, 256, True), (32, 28, 128, True), (64, 7, 512, True), (16, 7, 512, False), (40, 14, 256, False),
+])
+def test_convolutions(batch, side, C, raster):
+    tile, split = et.et_debug_conv3x3_plan(batch, side, side, C, C)
+    assert (tile in RASTER) == raster and (split == 1 or not raster)
