@@ -61,9 +61,9 @@ __device__ __forceinline__ void stage_rows(unsigned char* const (&dst)[NM], cons
 // (base in M0) + 16 * lane: the bank swizzle is therefore applied on the global side (the lane at chunk position p
 // of row r fetches chunk p ^ swz(r)).  Rows beyond the sequence repeat the last row: their keys are masked with
 // -inf, and a probability of zero times a finite V row adds nothing.
-// Few items (at most half the CUs, more than 4 query tiles): two workgroups share one, the second with the query tiles from 4 on, so that a wave has
-// a SIMD to itself.
-template <int KT>
+// SHARED, for few items (at most half the CUs, more than 4 query tiles): two workgroups share one, the second with the query tiles from 4 on, so that a
+// wave has a SIMD to itself.  (A template argument: the load of the grid's height alone cost every launch 0.3 us.)
+template <int KT, bool SHARED>
 __global__ __launch_bounds__(NTHREADS) void attention_fwd_kernel(const bf16* __restrict__ qkv, bf16* __restrict__ out,
                                                                  float* __restrict__ lse, int T, int H, float scale, int items) {
   constexpr int TP = KT * 32;
@@ -98,7 +98,7 @@ __global__ __launch_bounds__(NTHREADS) void attention_fwd_kernel(const bf16* __r
   auto load_q = [&](int item, bf16x8 (&qf)[4]) {
     int t_ = tid;
     asm volatile("" : "+v"(t_));
-    const int l32 = t_ & 31, khalf = (t_ >> 5) & 1, tile = (t_ >> 6) + 4 * (int)blockIdx.y;
+    const int l32 = t_ & 31, khalf = (t_ >> 5) & 1, tile = (t_ >> 6) + (SHARED ? 4 * (int)blockIdx.y : 0);
     const int b = item / H, h = item % H;
     const bf16* q = qkv + (long long)b * T * ld + h * DH;
     const int qrow = min(tile * 32 + l32, T - 1);
@@ -108,8 +108,8 @@ __global__ __launch_bounds__(NTHREADS) void attention_fwd_kernel(const bf16* __r
 
   int item = blockIdx.x;
   if (item >= items) return;
-  const int qt = wave + 4 * (int)blockIdx.y;
-  const bool mine = qt < KT && (gridDim.y == 1 || wave < 4);   // this wave has a query tile
+  const int qt = wave + (SHARED ? 4 * (int)blockIdx.y : 0);
+  const bool mine = qt < KT && (!SHARED || wave < 4);   // this wave has a query tile
   bf16x8 qf[4];
   load_q(item, qf);
   issue(item, 0);
@@ -188,7 +188,7 @@ __global__ __launch_bounds__(NTHREADS) void attention_fwd_kernel(const bf16* __r
 // -------------------------------------------------------------------------------------------------
 // backward: dS = P * (dP - rowsum(P*dP)) / sqrt(d);  dQ = dS K,  dK = dS^T Q,  dV = P^T dO
 // -------------------------------------------------------------------------------------------------
-template <int KT>
+template <int KT, bool SHARED>
 __global__ __launch_bounds__(NTHREADS) void attention_bwd_kernel(const bf16* __restrict__ qkv, const bf16* __restrict__ out,
                                                             const bf16* __restrict__ dout, const float* __restrict__ lse,
                                                             bf16* __restrict__ dqkv, float* __restrict__ part, int T, int H, float scale) {
@@ -237,8 +237,8 @@ __global__ __launch_bounds__(NTHREADS) void attention_bwd_kernel(const bf16* __r
     if (khalf == 0) s_dot[qt * 32 + l32] = dot;
     return dot;
   };
-  // few items (at most half the CUs): two workgroups share one, the first takes pass A, the second pass B
-  const bool pass_a = gridDim.y == 1 || blockIdx.y == 0, pass_b = gridDim.y == 1 || blockIdx.y == 1;
+  // SHARED, for few items (at most half the CUs): two workgroups share one, the first takes pass A, the second pass B
+  const bool pass_a = !SHARED || blockIdx.y == 0, pass_b = !SHARED || blockIdx.y == 1;
   if (!pass_a && wave < KT) {
     bf16x8 dof[4];
 #pragma unroll
@@ -451,14 +451,23 @@ hipError_t launch_fwd(const bf16* qkv, bf16* out, float* lse, int B, int T, int 
   if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
     cus = 256;
   const int items = B * H;
-  const bool shared = KT > 4 && items <= SHARED_ITEMS && 2 * items <= cus;
-  hipLaunchKernelGGL((attention_fwd_kernel<KT>), dim3(items < cus ? items : cus, shared ? 2 : 1), dim3(NTHREADS), 0, s, qkv, out, lse, T, H, scale, items);
+  const dim3 grid(items < cus ? items : cus), block(NTHREADS);
+  if constexpr (KT > 4)
+    if (items <= SHARED_ITEMS && 2 * items <= cus) {
+      hipLaunchKernelGGL((attention_fwd_kernel<KT, true>), dim3(items, 2), block, 0, s, qkv, out, lse, T, H, scale, items);
+      return hipGetLastError();
+    }
+  hipLaunchKernelGGL((attention_fwd_kernel<KT, false>), grid, block, 0, s, qkv, out, lse, T, H, scale, items);
   return hipGetLastError();
 }
 template <int KT>
 hipError_t launch_bwd(const bf16* qkv, const bf16* out, const bf16* dout, const float* lse, bf16* dqkv, int B, int T, int H,
                       float scale, hipStream_t s, float* part) {
-  hipLaunchKernelGGL((attention_bwd_kernel<KT>), dim3(B * H, B * H <= SHARED_ITEMS ? 2 : 1), dim3(NTHREADS), 0, s, qkv, out, dout, lse, dqkv, part, T, H, scale);
+  const int items = B * H;
+  if (items <= SHARED_ITEMS)
+    hipLaunchKernelGGL((attention_bwd_kernel<KT, true>), dim3(items, 2), dim3(NTHREADS), 0, s, qkv, out, dout, lse, dqkv, part, T, H, scale);
+  else
+    hipLaunchKernelGGL((attention_bwd_kernel<KT, false>), dim3(items), dim3(NTHREADS), 0, s, qkv, out, dout, lse, dqkv, part, T, H, scale);
   return hipGetLastError();
 }
 
