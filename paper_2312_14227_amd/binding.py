@@ -54,6 +54,7 @@ def _load():
         "et_num_tensors": (C.c_int, [vp, C.POINTER(i32)]),
         "et_tensor_info": (C.c_int, [vp, i32, C.POINTER(C.c_size_t), C.POINTER(i32), C.POINTER(C.c_char_p)]),
         "et_workspace_bytes": (C.c_size_t, [vp]),
+        "et_workspace_min_bytes": (C.c_size_t, [vp]),
         "et_state_slots": (C.c_int, [vp, C.POINTER(i32)]),
         "et_bind": (C.c_int, [vp, C.POINTER(vp), C.POINTER(vp), C.POINTER(vp), vp, C.c_size_t]),
         "et_profile": (C.c_int, [vp, vp, vp, i32, i32, C.POINTER(u64), C.POINTER(u64), C.POINTER(u64)]),
@@ -100,7 +101,7 @@ def _load():
 
 
 _lib = _load()
-EXPORTS = ["et_create", "et_destroy", "et_num_tensors", "et_tensor_info", "et_workspace_bytes", "et_state_slots",
+EXPORTS = ["et_create", "et_destroy", "et_num_tensors", "et_tensor_info", "et_workspace_bytes", "et_workspace_min_bytes", "et_state_slots",
            "et_bind", "et_profile", "et_importance", "et_importance_master", "et_importance_reduce_static", "et_select", "et_select_stats", "et_tensor_metric", "et_train_step", "et_last_launch_counts",
            "et_kernel_timing", "et_kernel_timing_read", "et_kernel_timing_overhead", "et_last_hip_error", "et_strerror", "et_debug_gemm_bf16", "et_debug_copy", "et_debug_mfma_peak", "et_debug_conv3x3",
            "et_debug_conv3x3_dw", "et_debug_depthwise3x3", "et_debug_depthwise3x3_ws_floats", "et_debug_affine_back", "et_debug_affine_back_ws_floats", "et_debug_flip3x3", "et_debug_dw_chunks", "et_debug_gemm_tile", "et_debug_conv3x3_plan", "et_debug_dw_group", "et_debug_conv_first",
@@ -173,6 +174,10 @@ def et_tensor_info(ctx, i):
 
 def et_workspace_bytes(ctx):
     return _lib.et_workspace_bytes(ctx)
+
+
+def et_workspace_min_bytes(ctx):
+    return _lib.et_workspace_min_bytes(ctx)
 
 
 def et_state_slots(ctx):

@@ -90,6 +90,9 @@ struct et_ctx {
 
   // workspace plan (offsets in bytes)
   size_t ws_bytes = 0;
+  // At its end lie two parts that work with less room than they can use (see place_tail): the scratch of split reductions, of which the largest single
+  // product has to find its part, and the gradients that are kept
+  size_t ws_min = 0, tail_at = 0, group_most = 0, keep_most = 0;
   std::vector<std::pair<void**, size_t>> plan;  // (where to store the pointer, offset)
 
   // bound buffers
@@ -109,7 +112,7 @@ struct et_ctx {
   bf16 *zc = nullptr, *dl16 = nullptr, *dz = nullptr, *dh16 = nullptr, *da = nullptr, *du = nullptr, *dattn = nullptr,
        *dqkv = nullptr, *ds = nullptr, *de = nullptr;
   float* gemm_partials = nullptr;
-  size_t gemm_partial_elems = 0;
+  size_t gemm_partial_elems = 0;   // what one product may take (fixed by the shapes, so that a split is)
 
   // column sums of the backward pass that wait for their second step: partial rows in sum_arena (bump allocated), finished
   // together by one launch at the end of the pass, or earlier when the arena is full
@@ -120,7 +123,7 @@ struct et_ctx {
   // weight gradients that run together at the end of a backward pass, and the arena (bump allocated) for the gradients they read: what
   // each layer's gradient is stored in if its weight is selected, instead of the scratch buffer that the next layer overwrites
   bf16* keep_arena = nullptr;
-  size_t keep_elems = 0, keep_used = 0;
+  size_t keep_elems = 0, keep_used = 0, group_elems = 0;   // group_elems: what the products of a group may take of gemm_partials
   std::vector<et::DwJob> dw_jobs;
   std::vector<int> dw_tensors;
   std::vector<et::DwGroupPlan> dw_plans;   // one per group (a group ends where the scratch of split reductions does)
@@ -330,11 +333,8 @@ inline et::GemmDesc linear_dw(et_ctx* c, const bf16* dY, int ldy, const bf16* X,
 }
 
 // ---- weight gradients at the end of the pass (see et_ctx::keep_arena)
-// `total`: elements of all the gradients that weight gradients are taken from; beyond 24 GB those that find no room run at once
-inline void reserve_keep(et_ctx* c, size_t total) {
-  c->keep_elems = std::min(total, (size_t)12 << 30);
-  reserve(c, &c->keep_arena, sizeof(bf16) * std::max<size_t>(c->keep_elems, 8));
-}
+// `total`: elements of all the gradients that weight gradients are taken from; beyond 24 GB, or the room that is given, weight gradients run at once
+inline void reserve_keep(et_ctx* c, size_t total) { c->keep_most = std::min(total, (size_t)12 << 30); }
 inline size_t keep_size(size_t elems) { return (elems + 127) / 128 * 128; }
 // where the gradient in front of a weight is to be stored: kept for the end of the pass if the weight is selected
 inline bf16* keep(et_ctx* c, bool selected, size_t elems, bf16* scratch) {
@@ -350,8 +350,28 @@ inline void dw_defer(et_ctx* c, int tensor, const et::DwJob& j) {
 }
 // partial sums of split products: room for the largest single one (`elems`), and for all weight gradients of a pass (`all`) up to 1.5 GB
 inline void reserve_partials(et_ctx* c, size_t elems, size_t all) {
-  c->gemm_partial_elems = std::max(elems, std::min((size_t)384 << 20, all));
-  reserve(c, &c->gemm_partials, sizeof(float) * std::max<size_t>(c->gemm_partial_elems, 64));
+  c->gemm_partial_elems = elems;
+  c->group_most = std::max(std::max<size_t>(elems, 64), std::min((size_t)384 << 20, all));
+}
+// behind everything else: the sizes of a workspace
+inline void reserve_tail(et_ctx* c) {
+  c->tail_at = c->ws_min = c->ws_bytes;
+  if (c->group_most == 0) return;   // (a model that keeps no gradients)
+  c->ws_min += align_up(sizeof(float) * std::max<size_t>(c->gemm_partial_elems, 64), 256);
+  c->ws_bytes += align_up(sizeof(float) * c->group_most, 256) + align_up(sizeof(bf16) * c->keep_most, 256);
+}
+// divides what is there beyond the least between both parts as they could use it; returns the bytes in use
+inline size_t place_tail(et_ctx* c, size_t bytes) {
+  bytes = std::min(bytes, c->ws_bytes) / 256 * 256;
+  if (c->group_most == 0) return bytes;
+  const size_t least = c->ws_min - c->tail_at, most = align_up(sizeof(float) * c->group_most, 256);
+  const size_t extra = bytes - c->ws_min, extra_most = c->ws_bytes - c->ws_min;
+  const size_t scratch = extra == extra_most ? most : least + (size_t)((double)(most - least) * ((double)extra / (double)extra_most)) / 256 * 256;
+  c->gemm_partials = (float*)(c->ws + c->tail_at);
+  c->group_elems = scratch / sizeof(float);
+  c->keep_arena = (bf16*)(c->ws + c->tail_at + scratch);
+  c->keep_elems = (bytes - c->tail_at - scratch) / sizeof(bf16);
+  return bytes;
 }
 
 // bracket a launch with events while per-kernel timing is on
@@ -421,7 +441,7 @@ inline int dw_finish(et_ctx* c) {
     int end = at;
     for (size_t used = 0; end < n && end - at < et::DW_GROUP_MAX; end++) {
       used += et::dw_group_elems(c->dw_jobs[end]);
-      if (used > c->gemm_partial_elems && end > at) break;
+      if (used > c->group_elems && end > at) break;
     }
     // the plan depends on the shapes alone and is kept while they stay the same
     et::DwGroupPlan& plan = c->dw_plans[group];

@@ -97,17 +97,13 @@ int build_vit(et_ctx* c) {
   reserve(c, &c->de, b16 * B * (T - 1) * D);
   // split-K partials: the largest weight gradient
   size_t pe = 0, all = 0;
-  auto wg = [&](size_t Mo, size_t No, size_t K, int times = 1) {
+  auto wg = [&](size_t Mo, size_t No, size_t K, int times) {
     const size_t n = et::gemm_bf16_partial_elems((int)Mo, (int)No, split_for((int)Mo, (int)No, (int)K));
     pe = std::max(pe, n);
     all += times * n;
   };
-  // (the last block's projection and MLP have B rows)
-  for (size_t K : {M, B}) {
-    const int times = K == M ? d.blocks : 1;
-    wg(3 * D, D, M, K == M ? times : 0); wg(D, D, K, times); wg(F, D, K, times); wg(D, F, K, times);
-  }
-  wg(D, P, B * (T - 1)); wg(C, D, B);
+  wg(3 * D, D, M, d.blocks); wg(D, D, M, d.blocks); wg(F, D, M, d.blocks); wg(D, F, M, d.blocks);
+  wg(D, P, B * (T - 1), 1); wg(C, D, B, 1);
   reserve_partials(c, pe, all);
   // gradients that weight gradients read: per block behind both residual sums, inside the MLP, of q, k and v; of the patches
   reserve_keep(c, (size_t)d.blocks * (2 * keep_size(M * D) + keep_size(M * F) + keep_size(M * 3 * D)) + keep_size(B * (T - 1) * D));
@@ -689,6 +685,7 @@ int et_create(const et_model_desc* desc, void* hip_stream, et_ctx** out) {
     if (rc == ET_OK) {
       c->state_slots = c->bf16_model ? 3 : 2;
       build_tables_plan(c);
+      reserve_tail(c);
       c->dw_jobs.reserve(c->tensors.size());
       c->dw_tensors.reserve(c->tensors.size());
       c->dw_plans.resize(c->tensors.size());
@@ -727,6 +724,7 @@ int et_tensor_info(const et_ctx* c, int32_t i, size_t* numel, int32_t* dtype, co
 }
 
 size_t et_workspace_bytes(const et_ctx* c) { return c ? c->ws_bytes : 0; }
+size_t et_workspace_min_bytes(const et_ctx* c) { return c ? c->ws_min : 0; }
 
 int et_state_slots(const et_ctx* c, int32_t* k) {
   if (!c || !k) return ET_EINVAL;
@@ -737,9 +735,10 @@ int et_state_slots(const et_ctx* c, int32_t* k) {
 int et_bind(et_ctx* c, void* const* w_dev, void* const* opt_state_dev, void* const* grad_dev, void* workspace_dev,
             size_t workspace_bytes) {
   if (!c || !w_dev || !grad_dev || !workspace_dev) return ET_EINVAL;
-  if (workspace_bytes < c->ws_bytes) return ET_ENOMEM;
+  if (workspace_bytes < c->ws_min) return ET_ENOMEM;
   if (reinterpret_cast<uintptr_t>(workspace_dev) & 255) return ET_EINVAL;
   const size_t N = c->tensors.size();
+  size_t used = 0;
   const int k = c->state_slots;
   for (size_t i = 0; i < N; i++) {
     if (!w_dev[i] || !grad_dev[i]) return ET_EINVAL;
@@ -762,6 +761,7 @@ int et_bind(et_ctx* c, void* const* w_dev, void* const* opt_state_dev, void* con
     }
     c->ws = (unsigned char*)workspace_dev;
     for (auto& pr : c->plan) *pr.first = c->ws + pr.second;
+    used = place_tail(c, workspace_bytes);
     // static tables
     c->upd_segs_host.assign(c->n_segs, et::UpdateSeg());
     c->imp_segs_host.assign(c->n_segs, et::TensorSeg());
@@ -790,7 +790,7 @@ int et_bind(et_ctx* c, void* const* w_dev, void* const* opt_state_dev, void* con
   } catch (const std::bad_alloc&) {
     return ET_ENOMEM;
   }
-  ET_HIP(et::fill_zero(c->ws, c->ws_bytes, c->stream));
+  ET_HIP(et::fill_zero(c->ws, used, c->stream));
   ET_HIP(hipMemcpyAsync(c->upd_segs_dev, c->upd_segs_host.data(), sizeof(et::UpdateSeg) * c->n_segs,
                         hipMemcpyHostToDevice, c->stream));
   ET_HIP(hipMemcpyAsync(c->seg_begin_dev, c->seg_begin.data(), sizeof(uint32_t) * (N + 1), hipMemcpyHostToDevice,

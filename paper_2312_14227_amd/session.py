@@ -36,7 +36,8 @@ class Session:
     """One model on one GPU.  `weights` are float32 numpy arrays in chain order (already
     representable in the model's storage type)."""
 
-    def __init__(self, cfg, weights, batch=None, device="cuda:0", with_state=True):
+    def __init__(self, cfg, weights, batch=None, device="cuda:0", with_state=True, workspace_bytes=None):
+        """workspace_bytes: None: all the library can use, or what it cannot do without if the GPU has no room for that."""
         if not torch.cuda.is_available():
             raise RuntimeError("no GPU: the HIP path has no CPU fallback")
         self.cfg, self.dev = cfg, torch.device(device)
@@ -61,8 +62,14 @@ class Session:
                     else:
                         slots.append(torch.zeros(numel, dtype=torch.float32, device=self.dev))
                 self.state.append(slots)
-        self.ws_bytes = et.et_workspace_bytes(self.ctx)
-        self.ws = torch.empty(self.ws_bytes + 256, dtype=torch.uint8, device=self.dev)
+        self.ws_bytes = et.et_workspace_bytes(self.ctx) if workspace_bytes is None else workspace_bytes
+        try:
+            self.ws = torch.empty(self.ws_bytes + 256, dtype=torch.uint8, device=self.dev)
+        except torch.cuda.OutOfMemoryError:
+            if workspace_bytes is not None:
+                raise
+            self.ws_bytes = et.et_workspace_min_bytes(self.ctx)
+            self.ws = torch.empty(self.ws_bytes + 256, dtype=torch.uint8, device=self.dev)
         off = (-self.ws.data_ptr()) % 256
         self.ws_ptr = self.ws.data_ptr() + off
         st = [s.data_ptr() for slots in self.state for s in slots] if with_state else None
