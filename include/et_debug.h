@@ -30,6 +30,13 @@ int et_debug_gemm_bf16(const void* A, const void* B, void* C, int M, int N, int 
 int et_debug_gemm_bf16_colsum(const void* A, const void* B, void* C, const void* aux, float* colsum, int M, int N, int K, int lda, int ldb, int ldc,
                               int tile, void* stream);
 
+/* The epilogues of a layer's activation on a plain product v = A B^T (row-major operands, bf16 outputs [M][ldc]):
+ *   gain = NULL: y = max(v + bias, 0), z unused;
+ *   else z = v (nullable: not stored), y = clamp(z * gain + bias [+ U * gain2 + bias2], lo, hi) from z as rounded; U nullable, [M][ldc]; gain2 = NULL: + U.
+ * Returns 0, -1, -3 as above. */
+int et_debug_gemm_bf16_act(const void* A, const void* B, void* z, void* y, int M, int N, int K, int lda, int ldb, int ldc, const void* bias,
+                           const void* gain, const void* U, const void* gain2, const void* bias2, float lo, float hi, int tile, void* stream);
+
 /* Tile id that et_debug_gemm_bf16 takes for tile 0 without a split (no device needed); epilogue, a_t, b_t, c_f32 as there, residual: whether there is
  * one.  0 for a rejected argument. */
 int et_debug_gemm_tile(int M, int N, int K, int a_t, int b_t, int c_f32, int residual, int epilogue);

@@ -76,6 +76,7 @@ def _load():
         "et_debug_depthwise3x3": (C.c_int, [C.c_int] + [vp] * 7 + [C.c_int] * 5 + [vp]),
         "et_debug_gemm_bf16_colsum": (C.c_int, [vp] * 5 + [C.c_int] * 7 + [vp]),
         "et_debug_conv_first": (C.c_int, [vp] * 6 + [C.c_int] * 6 + [C.c_float] * 2 + [vp]),
+        "et_debug_gemm_bf16_act": (C.c_int, [vp] * 4 + [C.c_int] * 6 + [vp] * 5 + [C.c_float] * 2 + [C.c_int, vp]),
         "et_debug_gemm_tile": (C.c_int, [C.c_int] * 8),
         "et_debug_conv3x3_plan": (C.c_int, [C.c_int] * 5 + [C.POINTER(C.c_int)]),
         "et_debug_dw_chunks": (C.c_int, [C.c_int] * 3),
@@ -104,7 +105,7 @@ _lib = _load()
 EXPORTS = ["et_create", "et_destroy", "et_num_tensors", "et_tensor_info", "et_workspace_bytes", "et_workspace_min_bytes", "et_state_slots",
            "et_bind", "et_profile", "et_importance", "et_importance_master", "et_importance_reduce_static", "et_select", "et_select_stats", "et_tensor_metric", "et_train_step", "et_last_launch_counts",
            "et_kernel_timing", "et_kernel_timing_read", "et_kernel_timing_overhead", "et_last_hip_error", "et_strerror", "et_debug_gemm_bf16", "et_debug_copy", "et_debug_mfma_peak", "et_debug_conv3x3",
-           "et_debug_conv3x3_dw", "et_debug_depthwise3x3", "et_debug_depthwise3x3_ws_floats", "et_debug_affine_back", "et_debug_affine_back_ws_floats", "et_debug_flip3x3", "et_debug_dw_chunks", "et_debug_gemm_tile", "et_debug_conv3x3_plan", "et_debug_dw_group", "et_debug_conv_first",
+           "et_debug_conv3x3_dw", "et_debug_depthwise3x3", "et_debug_depthwise3x3_ws_floats", "et_debug_affine_back", "et_debug_affine_back_ws_floats", "et_debug_flip3x3", "et_debug_dw_chunks", "et_debug_gemm_tile", "et_debug_gemm_bf16_act", "et_debug_conv3x3_plan", "et_debug_dw_group", "et_debug_conv_first",
            "et_debug_activation", "et_debug_conv3x3_split", "et_debug_attention", "et_debug_attention_long", "et_debug_attention_long_rest", "et_debug_gemm_bf16_colsum",
            "et_debug_conv_gathered", "et_debug_stem", "et_debug_stem_ws_bytes"]
 
@@ -368,6 +369,11 @@ def et_debug_gemm_bf16_colsum(A, B, Cp, aux, colsum, M, N, K, lda, ldb, ldc, til
 def et_debug_conv_first(x, w, gain, shift, z, y, batch, H, W, Cin, N, stride, lo, hi, stream=0):
     return _lib.et_debug_conv_first(C.c_void_p(x), C.c_void_p(w), C.c_void_p(gain), C.c_void_p(shift), C.c_void_p(z), C.c_void_p(y), batch, H, W,
                                     Cin, N, stride, lo, hi, C.c_void_p(stream))
+
+
+def et_debug_gemm_bf16_act(A, B, z, y, M, N, K, lda, ldb, ldc, bias, gain=0, U=0, gain2=0, bias2=0, lo=0.0, hi=float("inf"), tile=0, stream=0):
+    p = C.c_void_p
+    return _lib.et_debug_gemm_bf16_act(p(A), p(B), p(z), p(y), M, N, K, lda, ldb, ldc, p(bias), p(gain), p(U), p(gain2), p(bias2), lo, hi, tile, p(stream))
 
 
 def et_debug_gemm_tile(M, N, K, a_t=0, b_t=0, c_f32=0, residual=0, epilogue=0):

@@ -36,6 +36,25 @@ extern "C" int et_debug_gemm_bf16_colsum(const void* A, const void* B, void* C, 
   return e == hipSuccess ? ET_OK : ET_EHIP;
 }
 
+extern "C" int et_debug_gemm_bf16_act(const void* A, const void* B, void* z, void* y, int M, int N, int K, int lda, int ldb, int ldc, const void* bias,
+                                      const void* gain, const void* U, const void* gain2, const void* bias2, float lo, float hi, int tile,
+                                      void* stream) {
+  if (!y || !bias) return ET_EINVAL;
+  et::GemmDesc g;
+  g.A = (const et::bf16*)A; g.B = (const et::bf16*)B; g.M = M; g.N = N; g.K = K; g.lda = lda; g.ldb = ldb; g.ldc = ldc; g.tile = tile;
+  g.bias = (const et::bf16*)bias;
+  if (gain) {
+    g.mode = U ? et::EPI_AFFINE_ADD_RELU : et::EPI_AFFINE_RELU;
+    g.C = z; g.C2 = (et::bf16*)y; g.gain = (const et::bf16*)gain; g.act_lo = lo; g.act_hi = hi;
+    g.U = (const et::bf16*)U; g.gain2 = (const et::bf16*)gain2; g.bias2 = (const et::bf16*)bias2;
+  } else {
+    g.mode = et::EPI_BIAS_RELU; g.C = y;
+  }
+  const hipError_t e = et::gemm_bf16(g, (hipStream_t)stream);
+  if (e == hipErrorInvalidValue) return ET_EINVAL;
+  return e == hipSuccess ? ET_OK : ET_EHIP;
+}
+
 extern "C" int et_debug_gemm_tile(int M, int N, int K, int a_t, int b_t, int c_f32, int residual, int epilogue) {
   if (M < 1 || N < 1 || K < 1 || epilogue < 0 || epilogue > 3) return 0;
   et::GemmDesc g;

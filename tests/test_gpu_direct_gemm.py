@@ -1,6 +1,6 @@
 """The two-group tiles that load their operands straight to LDS (256 x 256, 192 x 256, 128 x 256): one to many slices of 64, so that the requests run ahead
 into the same tile, the workgroup's next one and the one after that; ragged rows and columns; more tiles than CUs; split reductions with a shorter
-last chunk; every epilogue.  References and bounds are those of the other tiles' tests."""
+last chunk; every epilogue (those with an activation that is no GELU in test_gpu_act_epilogues.py).  References and bounds are those of the other tiles' tests."""
 import pytest
 
 from test_gpu_gemm import _run
