@@ -100,20 +100,6 @@ enum TileId : int { T_AUTO = 0, T_128x128 = 1, T_128x64 = 3, T_DMA_256x256 = 5, 
               T_DIRECT_128x256 = 15, T_PP_256x256 = 11, T_PP_256x192 = 13, T_PP_256x128 = 15, T_PP_512x64 = 17, T_PP_128x256 = 19, T_PP_64x512 = 21,
               T_RING_64x64 = 23, T_RING_64x128 = 25, T_RING_128x64 = 27, T_RING_128x128 = 29 };
 
-// number of compute units of the current device (256 on an MI355X), looked up once per device; a multiple of 8
-// (one share per XCD) as the resident kernels' unit order assumes whenever a workgroup takes a second unit
-int compute_units() {
-  static int cus[64] = {0};
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;
-  if (cus[dev] == 0) {
-    int n = 0;
-    if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n < 8) n = 256;
-    cus[dev] = n & ~7;
-  }
-  return cus[dev];
-}
-
 inline bool aligned(const void* p, uintptr_t a) { return (reinterpret_cast<uintptr_t>(p) & (a - 1)) == 0; }
 
 // Cost model behind the tile and split choice of the gathered convolutions and the chunks of large weight gradients (seconds, one launch):
@@ -308,14 +294,14 @@ int tile_of_dw(int M, int N, int K, int split) {
 int choose_tile(const GemmDesc& d, int k_per_block) {
   const bool dma_ok = (d.K % gemm::DBK) == 0 && (k_per_block % gemm::DBK) == 0;
   const bool slices_ok = (d.K % gemm::PBK) == 0 && (k_per_block % gemm::PBK) == 0;
-  // the direct tiles take any number of rows of a weight gradient; their lanes' offsets within a slice are 32 bits wide
-  const bool direct_ok = (slices_ok || (d.a_t && d.b_t)) && d.lda < (1 << 22) && d.ldb < (1 << 22);
+  // the direct tiles take any number of rows of a weight gradient, and split no other product; their lanes' offsets within a slice are 32 bits wide
+  const bool direct_ok = ((d.a_t && d.b_t) || (slices_ok && d.split_k <= 1)) && d.lda < (1 << 22) && d.ldb < (1 << 22);
   if (d.tile == T_DIRECT_256x256 || d.tile == T_DIRECT_192x256 || d.tile == T_DIRECT_128x256) {
     if (!direct_ok) return dma_ok ? T_DMA_256x256 : T_128x128;
     if (d.mode == EPI_AFFINE_ADD_RELU) return T_DIRECT_128x256;
     return d.mode == EPI_AFFINE_RELU && d.tile == T_DIRECT_256x256 ? T_DIRECT_192x256 : d.tile;
   }
-  if (d.tile == T_PP_512x64 || d.tile == T_PP_128x256 || d.tile == T_PP_64x512) return slices_ok ? d.tile : T_128x128;
+  if (d.tile == T_PP_512x64 || d.tile == T_PP_128x256 || d.tile == T_PP_64x512) return slices_ok ? d.tile : T_128x128;   // (by id only: tests, tuning)
   if (d.tile == T_DMA_256x256 || d.tile == T_DMA_256x128) return dma_ok ? d.tile : T_128x128;
   if (d.tile != T_AUTO) return d.tile;
   // large problems (8 GFLOP and more; a ViT-L layer at batch 32 has 13): the tile with the least estimated time where K comes in
@@ -332,6 +318,20 @@ int choose_tile(const GemmDesc& d, int k_per_block) {
 }  // namespace
 
 int gemm_bf16_tile(const GemmDesc& d) { return choose_tile(d, d.K); }
+
+// number of compute units of the current device (256 on an MI355X), looked up once per device; a multiple of 8
+// (one share per XCD) as the resident kernels' unit order assumes whenever a workgroup takes a second unit
+int compute_units() {
+  static int cus[64] = {0};
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;
+  if (cus[dev] == 0) {
+    int n = 0;
+    if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n < 8) n = 256;
+    cus[dev] = n & ~7;
+  }
+  return cus[dev];
+}
 
 size_t gemm_bf16_partial_elems(int M, int N, int split_k) { return split_k > 1 ? (size_t)M * N * split_k : 0; }
 

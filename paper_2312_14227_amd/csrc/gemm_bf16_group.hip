@@ -198,7 +198,7 @@ hipError_t run(const Launch& l, const DwJob* jobs, float* partials, size_t& used
     }
     hipError_t e;
     if constexpr (CONV) e = l.bn == 128 ? gemm::ring_group_conv_64x128(g, s) : gemm::ring_group_conv_64x64(g, s);
-    else if (l.direct) e = gemm::direct_group(l.bm, g, std::min(g.units, 256), s);
+    else if (l.direct) e = gemm::direct_group(l.bm, g, std::min(g.units, compute_units()), s);
     else e = l.bn == 128 ? gemm::ring_group_64x128(g, s) : gemm::ring_group_64x64(g, s);
     if (e != hipSuccess) return e;
     (*launches)++;

@@ -25,7 +25,7 @@
 //   gemm_dma_kernel: K slices of 32 loaded with global_load_lds_dwordx4 straight into a ring of
 //     LDS stages, several slices in flight (large tiles; K a multiple of 32);
 //   gemm_pp_kernel: K slices of 64 through registers into two LDS stages, the eight waves in two
-//     groups that alternate between MFMAs and memory work (implicit convolutions; K a multiple of 64).
+//     groups that alternate between MFMAs and memory work (implicit convolutions; plain products by tile id only; K a multiple of 64).
 // Rows beyond the matrix edge are clamped to valid addresses (their products are never stored).
 // Epilogue: every wave passes its accumulators through a private LDS area, 32 rows at a time, so
 // that each lane ends up with 4 consecutive columns of one row: bias, residual, GELU and the

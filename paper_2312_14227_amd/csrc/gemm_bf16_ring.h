@@ -57,7 +57,7 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_ring_kernel(std::condition
   static_assert(CONV != 2 || (AT && BT), "implicit convolution, weight gradient: both operands reduce over rows");
   constexpr int EPI_BYTES = NW * epi_wave_bytes<TN>();
   constexpr int SMEM = RING * STAGE > EPI_BYTES ? RING * STAGE : EPI_BYTES;
-  static_assert(RING >= 2 && RING <= 8 && SMEM <= 160 * 1024, "LDS ring");
+  static_assert(RING >= 2 && RING <= 5 && SMEM <= 160 * 1024, "LDS ring");
   __shared__ __attribute__((aligned(1024))) unsigned char smem[SMEM];
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -259,13 +259,10 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_ring_kernel(std::condition
   // wait until slice `sl` has landed: up to `most` younger slices stay in flight
   auto wait_slice = [&](int sl, auto most_tag) {
     constexpr int MOST = decltype(most_tag)::value;
-    static_assert(MOST <= 7 && MOST * LOADS <= 63, "vmcnt");
+    static_assert(MOST <= 4 && MOST * LOADS <= 63, "vmcnt");
     const int younger = min(MOST, nk - 1 - sl);
     if (younger == MOST) { wait_vmcnt<MOST * LOADS>(); return; }
-    if (MOST > 6 && younger == 6) wait_vmcnt<6 * LOADS>();
-    else if (MOST > 5 && younger == 5) wait_vmcnt<5 * LOADS>();
-    else if (MOST > 4 && younger == 4) wait_vmcnt<4 * LOADS>();
-    else if (MOST > 3 && younger == 3) wait_vmcnt<3 * LOADS>();
+    if (MOST > 3 && younger == 3) wait_vmcnt<3 * LOADS>();
     else if (MOST > 2 && younger == 2) wait_vmcnt<2 * LOADS>();
     else if (MOST > 1 && younger == 1) wait_vmcnt<LOADS>();
     else wait_vmcnt<0>();

@@ -32,6 +32,9 @@ enum EpiMode : int {
   EPI_AFFINE_ADD_RELU = 4,  // C = z, C2 = max(z * gain + bias + U * gain2 + bias2, 0); gain2 null: + U
 };
 
+// compute units of the current device (a multiple of 8): what a resident kernel's grid is
+int compute_units();
+
 struct GemmDesc {
   const bf16* A = nullptr;
   const bf16* B = nullptr;
@@ -135,7 +138,6 @@ inline size_t dw_group_elems(const DwJob& j) { return j.split > 1 ? (size_t)j.sp
 constexpr int DW_GROUP_MAX = 120;   // jobs of a group
 // makes `plan` that of the jobs, unless it is
 hipError_t dw_group_plan(const DwJob* jobs, int n, DwGroupPlan& plan);
-inline double dw_group_cost(const DwGroupPlan& plan, int job) { return plan.cost[job]; }
 // Runs them, in few launches; the gradients are bit-reproducible.  partials: scratch for dw_group_elems of all jobs, 16-byte aligned
 hipError_t dw_group(const DwJob* jobs, int n, const DwGroupPlan& plan, float* partials, hipStream_t s, int* launches);
 
