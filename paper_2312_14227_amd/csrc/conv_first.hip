@@ -1,7 +1,7 @@
 // First 3x3 convolution of a chain, at most three input channels: all 9 C <= 27 products of an output are two matrix
 // instructions, so no column matrix is written (for 32 images of 224x224, 1.6 million rows of 64 bytes: 93 us to write and 77 us for
-// the product with 64 channels; 66 - 83 us here, bound by the output's 205 MB: with the window in four wide loads and the next tile's requested
-// ahead of the stores it took 78; 48 and 24 us for 32 channels at stride 2).  A wave owns 32 output pixels at a time; a lane gathers the 8 + 8
+// the product with 64 channels; 66 - 83 us here, 2.5 - 3.1 TB/s of output where a launch that only writes reaches 5.2.  It is not the gather that is in
+// the way: with the window in four wide loads and the next tile's requested ahead of the stores it took 78.  48 and 24 us for 32 channels at stride 2).  A wave owns 32 output pixels at a time; a lane gathers the 8 + 8
 // window values of its pixel that the fragments ask for, the weights stay in registers.  The instructions, their order and the
 // epilogue are those of the product over the column matrix, and so are the results.
 #include "gemm_bf16_kernels.h"

@@ -1,7 +1,7 @@
 // 3x3 / stride 1 / zero padding 1 convolution of small images with many channels (forward, or gradient passing with the mirrored weight).
 //
 // What bounds the gathered products on these layers ([32 x 14 x 14 x 256] -> 256: 7.4 GFLOP in 21.5 us) is bringing operands to a CU: a 64 x 64
-// tile takes 16 KB per slice of 64 k values, 9/10 of it pixels that the eight other taps bring again, at 10 ns per KB.  Here the pixels of
+// tile takes 16 KB per slice of 64 k values, half of it pixels, of which the eight other taps bring 8/9 again, at 10 ns per KB.  Here the pixels of
 // 64 input channels lie in LDS once for all nine taps.  The images are laid out as one raster with a column of zeros in front of every row and a
 // row of zeros in front of every image, which also serve as the borders behind: position s = (image * (H + 1) + Y) * (W + 1) + X holds pixel
 // (Y - 1, X - 1), and the output at raster position p reads p + dy (W + 1) + dx for tap (dy, dx), whatever the width.  A workgroup owns
