@@ -540,11 +540,11 @@ hipError_t gemm_bf16(const GemmDesc& d, hipStream_t s, int* launches) {
     default: BM = 128; BN = 128; fn = gemm::staged_128x128(d.a_t, d.b_t, epi); resident = false; break;
   }
   // a lone 64x64 tile per CU with a long reduction waits for memory: five slices in flight instead of three.  [788 x 768 x 3072] with weights
-  // from memory 14.3 -> 13.3 us, with both operands from memory 14.4 -> 13.3; the same times a transposed weight 13.6 -> 13.4 and 13.9 -> 13.3.
-  // At 32 slices 10.2 -> 10.2 and 10.6 -> 10.3, transposed 10.1 -> 10.3 and 10.4 -> 10.4, hence the later start there.  With both operands in
-  // the L2, which no pass over a model leaves, it costs 4 - 6 %; so does the LDS that it takes with two or more tiles per CU
-  // ([788 x 3072 x 768] 12.4 -> 13.7)
-  if (fn && !conv && BM == 64 && BN == 64 && !resident && k_per_block >= (d.b_t ? 48 : 32) * gemm::PBK &&
+  // from memory 14.3 -> 13.3 us, with both operands from memory 14.4 -> 13.3; the same times a transposed weight 13.6 -> 13.4 and 13.9 -> 13.3,
+  // x 2304 10.9 -> 11.0 and 11.3 -> 11.1, in a training pass 11.9 -> 11.1.  At 32 slices 10.2 -> 10.2 and 10.6 -> 10.3, transposed 10.1 -> 10.3
+  // and 10.4 -> 10.4, hence the later start there.  With both operands in the L2, which no pass over a model leaves, it costs 4 - 6 %; so does
+  // the LDS that it takes with two or more tiles per CU ([788 x 3072 x 768] 12.4 -> 13.7)
+  if (fn && !conv && BM == 64 && BN == 64 && !resident && k_per_block >= (d.b_t ? 36 : 32) * gemm::PBK &&
       (long long)((d.M + 63) / 64) * ((d.N + 63) / 64) * zdim <= 256) {
     const gemm::LaunchFn deep = gemm::ring_64x64_deep(d.a_t, d.b_t, epi);
     if (deep) fn = deep;

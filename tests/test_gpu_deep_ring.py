@@ -1,4 +1,4 @@
-"""The 64 x 64 ring tile with five slices in flight, taken by products of at most one tile per CU and 32 slices or more (48 where the second operand is
+"""The 64 x 64 ring tile with five slices in flight, taken by products of at most one tile per CU and 32 slices or more (36 where the second operand is
 transposed): reductions of these lengths and around them, with whole and ragged ends, in every layout and epilogue that has it (the affine ones in
 test_gpu_act_epilogues.py).  References and bounds are those of the other tiles' tests."""
 import pytest
