@@ -156,7 +156,7 @@ int et_state_slots(const et_ctx* ctx, int32_t* k);
  * grad_dev[i]: float32 [numel_i]; opt_state_dev[i*k + s]: float32 [numel_i] (k from
  * et_state_slots; may be NULL as a whole if et_train_step is only called with opt == NULL);
  * workspace_dev: at least et_workspace_min_bytes() bytes (more than et_workspace_bytes() are not used), 256-byte aligned.  The arrays of
- * pointers are host arrays and are copied.  The workspace is cleared on the stream. */
+ * pointers are host arrays and are copied.  The first et_workspace_min_bytes() bytes are cleared on the stream. */
 int et_bind(et_ctx* ctx, void* const* w_dev, void* const* opt_state_dev, void* const* grad_dev,
             void* workspace_dev, size_t workspace_bytes);
 

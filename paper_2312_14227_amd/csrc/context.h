@@ -360,10 +360,10 @@ inline void reserve_tail(et_ctx* c) {
   c->ws_min += align_up(sizeof(float) * std::max<size_t>(c->gemm_partial_elems, 64), 256);
   c->ws_bytes += align_up(sizeof(float) * c->group_most, 256) + align_up(sizeof(bf16) * c->keep_most, 256);
 }
-// divides what is there beyond the least between both parts as they could use it; returns the bytes in use
-inline size_t place_tail(et_ctx* c, size_t bytes) {
+// divides what is there beyond the least between both parts as they could use it
+inline void place_tail(et_ctx* c, size_t bytes) {
+  if (c->group_most == 0) return;
   bytes = std::min(bytes, c->ws_bytes) / 256 * 256;
-  if (c->group_most == 0) return bytes;
   const size_t least = c->ws_min - c->tail_at, most = align_up(sizeof(float) * c->group_most, 256);
   const size_t extra = bytes - c->ws_min, extra_most = c->ws_bytes - c->ws_min;
   const size_t scratch = extra == extra_most ? most : least + (size_t)((double)(most - least) * ((double)extra / (double)extra_most)) / 256 * 256;
@@ -371,7 +371,6 @@ inline size_t place_tail(et_ctx* c, size_t bytes) {
   c->group_elems = scratch / sizeof(float);
   c->keep_arena = (bf16*)(c->ws + c->tail_at + scratch);
   c->keep_elems = (bytes - c->tail_at - scratch) / sizeof(bf16);
-  return bytes;
 }
 
 // bracket a launch with events while per-kernel timing is on

@@ -738,7 +738,6 @@ int et_bind(et_ctx* c, void* const* w_dev, void* const* opt_state_dev, void* con
   if (workspace_bytes < c->ws_min) return ET_ENOMEM;
   if (reinterpret_cast<uintptr_t>(workspace_dev) & 255) return ET_EINVAL;
   const size_t N = c->tensors.size();
-  size_t used = 0;
   const int k = c->state_slots;
   for (size_t i = 0; i < N; i++) {
     if (!w_dev[i] || !grad_dev[i]) return ET_EINVAL;
@@ -761,7 +760,7 @@ int et_bind(et_ctx* c, void* const* w_dev, void* const* opt_state_dev, void* con
     }
     c->ws = (unsigned char*)workspace_dev;
     for (auto& pr : c->plan) *pr.first = c->ws + pr.second;
-    used = place_tail(c, workspace_bytes);
+    place_tail(c, workspace_bytes);
     // static tables
     c->upd_segs_host.assign(c->n_segs, et::UpdateSeg());
     c->imp_segs_host.assign(c->n_segs, et::TensorSeg());
@@ -790,7 +789,7 @@ int et_bind(et_ctx* c, void* const* w_dev, void* const* opt_state_dev, void* con
   } catch (const std::bad_alloc&) {
     return ET_ENOMEM;
   }
-  ET_HIP(et::fill_zero(c->ws, used, c->stream));
+  ET_HIP(et::fill_zero(c->ws, c->ws_min, c->stream));   // (what lies behind is written before it is read)
   ET_HIP(hipMemcpyAsync(c->upd_segs_dev, c->upd_segs_host.data(), sizeof(et::UpdateSeg) * c->n_segs,
                         hipMemcpyHostToDevice, c->stream));
   ET_HIP(hipMemcpyAsync(c->seg_begin_dev, c->seg_begin.data(), sizeof(uint32_t) * (N + 1), hipMemcpyHostToDevice,
